@@ -1,8 +1,10 @@
-"""Thin ctypes binding of libspdl's C ABI: argument marshalling only.
+"""Thin binding of libspdl's C ABI: argument marshalling only.
 
 Every function has the name and argument order of its C entry point (include/spdl.h).  Device
 arrays are torch tensors on the GPU (PyTorch supplies memory and streams, nothing else); host
-arrays are numpy.  There is no fallback: if libspdl.so is missing, loading raises.
+arrays are numpy.  The calls that launch work go through _native.so (csrc/native_binding.cpp): a
+small kernel is done in 5 us, about what checking ten arguments costs in Python.  Everything else
+goes through ctypes.  There is no fallback: if libspdl.so or _native.so is missing, loading raises.
 """
 from __future__ import annotations
 
@@ -13,6 +15,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libspdl.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
 
 EXPORTS = (
@@ -68,213 +71,147 @@ def _check(status, where):
         raise SpdlError(status, where)
 
 
-def _dev(t, dtype, name, allow_none=False):
-    """Device pointer of a contiguous GPU tensor of the given torch dtype."""
-    import torch
-    if t is None:
-        if allow_none:
-            return ctypes.c_void_p(0)
-        raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise ValueError(f"{name} must be a GPU tensor")
-    if t.dtype != dtype:
-        raise ValueError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+def _raise_status(status, where):
+    raise SpdlError(status, where)
 
 
-def _stream(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+# Arguments of the entry points that take device arrays, in order, up to the stream (the letters
+# are explained in csrc/native_binding.cpp).
+_DIMS = "i:m i:k i:n i:nnz I:row_offsets "
+_CI = "I:column_indices "
+_SIGNATURES = {
+    "spdl_spmm": _DIMS + _CI + "F:values ?I:row_order F:B F:C",
+    "spdl_spmm_f16": _DIMS + _CI + "H:values ?I:row_order H:B H:C",
+    "spdl_spmm_f16_i16": _DIMS + "S:column_indices H:values ?I:row_order H:B H:C",
+    "spdl_spmm_banded": _DIMS + _CI + "F:values F:B F:C",
+    "spdl_spmm_skewed": _DIMS + _CI + "F:values F:B F:C",
+    "spdl_spmm_bias_relu": _DIMS + _CI + "F:values ?I:row_order F:B ?F:bias i:relu F:C",
+    "spdl_spmm_bias_relu_f16": _DIMS + _CI + "H:values ?I:row_order H:B ?H:bias i:relu H:C",
+    "spdl_sddmm": _DIMS + _CI + "F:L F:R F:out_values",
+    "spdl_sddmm_f16": _DIMS + _CI + "H:L H:R H:out_values",
+    "spdl_sddmm_banded": _DIMS + _CI + "F:L F:R F:out_values",
+    "spdl_sddmm_skewed": _DIMS + _CI + "F:L F:R F:out_values",
+    "spdl_sddmm_ordered": _DIMS + _CI + "?I:row_order F:L F:R F:out_values",
+    "spdl_sddmm_scaled": _DIMS + _CI + "F:values F:L F:R F:out_values",
+    "spdl_sddmm_scaled_f16": _DIMS + _CI + "H:values H:L H:R H:out_values",
+    "spdl_sddmm_nt": _DIMS + _CI + "?F:values F:L F:Rn F:out_values",
+    "spdl_sddmm_nt_f16": _DIMS + _CI + "?H:values H:L H:Rn H:out_values",
+    "spdl_csr_softmax": "i:m i:nnz I:row_offsets F:logits f:scale F:probabilities",
+    ("spdl_permute_values", 4): "i:nnz i:elem_bytes I:perm F:values F:out",
+    ("spdl_permute_values", 2): "i:nnz i:elem_bytes I:perm H:values H:out",
+}
+
+
+class _Calls(dict):
+    """The bound entry points; each is bound at its first use."""
+
+    def __missing__(self, key):
+        name = key if isinstance(key, str) else key[0]
+        address = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2006_10901_amd.build`")
+        from . import _native
+        self[key] = fn = _native.bind(address, name, _SIGNATURES[key], _raise_status)
+        return fn
+
+
+_call = _Calls()
 
 
 def spdl_spmm(m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream=None):
-    import torch
-    _check(lib().spdl_spmm(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float32, "values"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(B, torch.float32, "B"),
-        _dev(C, torch.float32, "C"), _stream(stream)), "spdl_spmm")
+    _call["spdl_spmm"](m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream)
     return C
 
 
 def spdl_sddmm(m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(L, torch.float32, "L"),
-        _dev(R, torch.float32, "R"), _dev(out_values, torch.float32, "out_values"), _stream(stream)),
-        "spdl_sddmm")
+    _call["spdl_sddmm"](m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream)
     return out_values
 
 
 def spdl_spmm_banded(m, k, n, nnz, row_offsets, column_indices, values, B, C, stream=None):
-    import torch
-    _check(lib().spdl_spmm_banded(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float32, "values"),
-        _dev(B, torch.float32, "B"), _dev(C, torch.float32, "C"), _stream(stream)), "spdl_spmm_banded")
+    _call["spdl_spmm_banded"](m, k, n, nnz, row_offsets, column_indices, values, B, C, stream)
     return C
 
 
 def spdl_sddmm_banded(m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_banded(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(L, torch.float32, "L"),
-        _dev(R, torch.float32, "R"), _dev(out_values, torch.float32, "out_values"), _stream(stream)),
-        "spdl_sddmm_banded")
+    _call["spdl_sddmm_banded"](m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream)
     return out_values
 
 
 def spdl_spmm_skewed(m, k, n, nnz, row_offsets, column_indices, values, B, C, stream=None):
-    import torch
-    _check(lib().spdl_spmm_skewed(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float32, "values"),
-        _dev(B, torch.float32, "B"), _dev(C, torch.float32, "C"), _stream(stream)), "spdl_spmm_skewed")
+    _call["spdl_spmm_skewed"](m, k, n, nnz, row_offsets, column_indices, values, B, C, stream)
     return C
 
 
 def spdl_sddmm_skewed(m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_skewed(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(L, torch.float32, "L"),
-        _dev(R, torch.float32, "R"), _dev(out_values, torch.float32, "out_values"), _stream(stream)),
-        "spdl_sddmm_skewed")
+    _call["spdl_sddmm_skewed"](m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream)
     return out_values
 
 
 def spdl_sddmm_ordered(m, k, n, nnz, row_offsets, column_indices, row_order, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_ordered(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(L, torch.float32, "L"),
-        _dev(R, torch.float32, "R"), _dev(out_values, torch.float32, "out_values"), _stream(stream)),
-        "spdl_sddmm_ordered")
+    _call["spdl_sddmm_ordered"](m, k, n, nnz, row_offsets, column_indices, row_order, L, R, out_values, stream)
     return out_values
 
 
 def spdl_sddmm_scaled(m, k, n, nnz, row_offsets, column_indices, values, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_scaled(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float32, "values"),
-        _dev(L, torch.float32, "L"), _dev(R, torch.float32, "R"),
-        _dev(out_values, torch.float32, "out_values"), _stream(stream)), "spdl_sddmm_scaled")
+    _call["spdl_sddmm_scaled"](m, k, n, nnz, row_offsets, column_indices, values, L, R, out_values, stream)
     return out_values
 
 
 def spdl_sddmm_scaled_f16(m, k, n, nnz, row_offsets, column_indices, values, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_scaled_f16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float16, "values"),
-        _dev(L, torch.float16, "L"), _dev(R, torch.float16, "R"),
-        _dev(out_values, torch.float16, "out_values"), _stream(stream)), "spdl_sddmm_scaled_f16")
+    _call["spdl_sddmm_scaled_f16"](m, k, n, nnz, row_offsets, column_indices, values, L, R, out_values, stream)
     return out_values
 
 
 def spdl_sddmm_nt(m, k, n, nnz, row_offsets, column_indices, values, L, Rn, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_nt(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"),
-        _dev(values, torch.float32, "values", allow_none=True), _dev(L, torch.float32, "L"),
-        _dev(Rn, torch.float32, "Rn"), _dev(out_values, torch.float32, "out_values"), _stream(stream)),
-        "spdl_sddmm_nt")
+    _call["spdl_sddmm_nt"](m, k, n, nnz, row_offsets, column_indices, values, L, Rn, out_values, stream)
     return out_values
 
 
 def spdl_sddmm_nt_f16(m, k, n, nnz, row_offsets, column_indices, values, L, Rn, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_nt_f16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"),
-        _dev(values, torch.float16, "values", allow_none=True), _dev(L, torch.float16, "L"),
-        _dev(Rn, torch.float16, "Rn"), _dev(out_values, torch.float16, "out_values"), _stream(stream)),
-        "spdl_sddmm_nt_f16")
+    _call["spdl_sddmm_nt_f16"](m, k, n, nnz, row_offsets, column_indices, values, L, Rn, out_values, stream)
     return out_values
 
 
 def spdl_spmm_f16_i16(m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream=None):
-    import torch
-    _check(lib().spdl_spmm_f16_i16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int16, "column_indices"), _dev(values, torch.float16, "values"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(B, torch.float16, "B"),
-        _dev(C, torch.float16, "C"), _stream(stream)), "spdl_spmm_f16_i16")
+    _call["spdl_spmm_f16_i16"](m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream)
     return C
 
 
 def spdl_spmm_f16(m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream=None):
-    import torch
-    _check(lib().spdl_spmm_f16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float16, "values"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(B, torch.float16, "B"),
-        _dev(C, torch.float16, "C"), _stream(stream)), "spdl_spmm_f16")
+    _call["spdl_spmm_f16"](m, k, n, nnz, row_offsets, column_indices, values, row_order, B, C, stream)
     return C
 
 
 def spdl_sddmm_f16(m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream=None):
-    import torch
-    _check(lib().spdl_sddmm_f16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(L, torch.float16, "L"),
-        _dev(R, torch.float16, "R"), _dev(out_values, torch.float16, "out_values"), _stream(stream)),
-        "spdl_sddmm_f16")
+    _call["spdl_sddmm_f16"](m, k, n, nnz, row_offsets, column_indices, L, R, out_values, stream)
     return out_values
 
 
 def spdl_spmm_bias_relu(m, k, n, nnz, row_offsets, column_indices, values, row_order, B, bias, relu, C,
                         stream=None):
-    import torch
-    _check(lib().spdl_spmm_bias_relu(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float32, "values"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(B, torch.float32, "B"),
-        _dev(bias, torch.float32, "bias", allow_none=True), int(bool(relu)),
-        _dev(C, torch.float32, "C"), _stream(stream)), "spdl_spmm_bias_relu")
+    _call["spdl_spmm_bias_relu"](m, k, n, nnz, row_offsets, column_indices, values, row_order, B, bias,
+                                 bool(relu), C, stream)
     return C
 
 
 def spdl_spmm_bias_relu_f16(m, k, n, nnz, row_offsets, column_indices, values, row_order, B, bias, relu, C,
                             stream=None):
-    import torch
-    _check(lib().spdl_spmm_bias_relu_f16(
-        int(m), int(k), int(n), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(column_indices, torch.int32, "column_indices"), _dev(values, torch.float16, "values"),
-        _dev(row_order, torch.int32, "row_order", allow_none=True), _dev(B, torch.float16, "B"),
-        _dev(bias, torch.float16, "bias", allow_none=True), int(bool(relu)),
-        _dev(C, torch.float16, "C"), _stream(stream)), "spdl_spmm_bias_relu_f16")
+    _call["spdl_spmm_bias_relu_f16"](m, k, n, nnz, row_offsets, column_indices, values, row_order, B, bias,
+                                     bool(relu), C, stream)
     return C
 
 
 def spdl_csr_softmax(m, nnz, row_offsets, logits, scale, probabilities, stream=None):
-    import torch
-    _check(lib().spdl_csr_softmax(
-        int(m), int(nnz), _dev(row_offsets, torch.int32, "row_offsets"),
-        _dev(logits, torch.float32, "logits"), ctypes.c_float(float(scale)),
-        _dev(probabilities, torch.float32, "probabilities"), _stream(stream)), "spdl_csr_softmax")
+    _call["spdl_csr_softmax"](m, nnz, row_offsets, logits, scale, probabilities, stream)
     return probabilities
 
 
 def spdl_permute_values(nnz, elem_bytes, perm, values, out, stream=None):
-    import torch
-    dtype = {2: torch.float16, 4: torch.float32}.get(int(elem_bytes))
-    if dtype is None:
+    elem_bytes = int(elem_bytes)
+    if elem_bytes not in (2, 4):
         raise ValueError("elem_bytes must be 2 or 4")
-    _check(lib().spdl_permute_values(
-        int(nnz), int(elem_bytes), _dev(perm, torch.int32, "perm"), _dev(values, dtype, "values"),
-        _dev(out, dtype, "out"), _stream(stream)), "spdl_permute_values")
+    _call["spdl_permute_values", elem_bytes](nnz, elem_bytes, perm, values, out, stream)
     return out
 
 

@@ -1,4 +1,4 @@
-"""Builds libspdl.so (HIP, gfx950 only) next to this file with hipcc."""
+"""Builds libspdl.so (HIP, gfx950 only) next to this file with hipcc, and the binding's native half."""
 from __future__ import annotations
 
 import glob
@@ -50,6 +50,26 @@ def build_phase_clocks(verbose: bool = False) -> str:
     return CLOCKS_LIB_PATH
 
 
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """The binding's native half (csrc/native_binding.cpp): host code only, against torch's headers."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *(f"-I{d}" for d in cpp_extension.include_paths()), "-I/opt/rocm/include",
+           "-I" + sysconfig.get_paths()["include"], "-o", NATIVE_PATH, os.path.join(CSRC, "native_binding.cpp"),
+           *(f"-L{d}" for d in cpp_extension.library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + proc.stdout)
+    return NATIVE_PATH
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
@@ -61,6 +81,7 @@ def build(verbose: bool = False) -> str:
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + proc.stdout)
+    build_native(verbose)
     return LIB_PATH
 
 
