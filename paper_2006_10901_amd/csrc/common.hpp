@@ -14,8 +14,21 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// VEC consecutive elements of T, moved with one memory instruction and widened to fp32.
+// VEC consecutive elements of T, moved with one memory instruction and widened to fp32.  Element
+// alignment is enough: the vector types below promise no more (the memory path takes any, at the same
+// rate but for the extra cache line that a piece may touch).
 template <typename T, int VEC> struct Pack;
+typedef f32x2 f32x2_any __attribute__((aligned(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef f16x2 f16x2_any __attribute__((aligned(2)));
+typedef f16x4 f16x4_any __attribute__((aligned(2)));
+typedef f16x8 f16x8_any __attribute__((aligned(2)));
+
+// First of the V columns that a lane works on, of a row of n: `col`, except that the lane that would
+// reach past the row's end takes the row's last V columns, some of them its neighbour's.  What both
+// compute is the same, so both may store it; a sum over columns leaves the shared ones to the
+// neighbour.  (n >= V; columns from n on belong to nobody.)
+__host__ __device__ __forceinline__ int piece_start(int col, int n, int V) { return col < n && col > n - V ? n - V : col; }
 
 template <> struct Pack<float, 1> {
   static __device__ __forceinline__ void load(const float* p, float (&x)[1]) { x[0] = *p; }
@@ -23,18 +36,18 @@ template <> struct Pack<float, 1> {
 };
 template <> struct Pack<float, 2> {
   static __device__ __forceinline__ void load(const float* p, float (&x)[2]) {
-    f32x2 v = *reinterpret_cast<const f32x2*>(p); x[0] = v.x; x[1] = v.y;
+    f32x2 v = *reinterpret_cast<const f32x2_any*>(p); x[0] = v.x; x[1] = v.y;
   }
   static __device__ __forceinline__ void store(float* p, const float (&x)[2]) {
-    f32x2 v = {x[0], x[1]}; *reinterpret_cast<f32x2*>(p) = v;
+    f32x2 v = {x[0], x[1]}; *reinterpret_cast<f32x2_any*>(p) = v;
   }
 };
 template <> struct Pack<float, 4> {
   static __device__ __forceinline__ void load(const float* p, float (&x)[4]) {
-    f32x4 v = *reinterpret_cast<const f32x4*>(p); x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    f32x4 v = *reinterpret_cast<const f32x4_any*>(p); x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
   }
   static __device__ __forceinline__ void store(float* p, const float (&x)[4]) {
-    f32x4 v = {x[0], x[1], x[2], x[3]}; *reinterpret_cast<f32x4*>(p) = v;
+    f32x4 v = {x[0], x[1], x[2], x[3]}; *reinterpret_cast<f32x4_any*>(p) = v;
   }
 };
 template <> struct Pack<_Float16, 1> {
@@ -43,15 +56,15 @@ template <> struct Pack<_Float16, 1> {
 };
 template <> struct Pack<_Float16, 2> {
   static __device__ __forceinline__ void load(const _Float16* p, float (&x)[2]) {
-    f16x2 v = *reinterpret_cast<const f16x2*>(p); x[0] = (float)v.x; x[1] = (float)v.y;
+    f16x2 v = *reinterpret_cast<const f16x2_any*>(p); x[0] = (float)v.x; x[1] = (float)v.y;
   }
   static __device__ __forceinline__ void store(_Float16* p, const float (&x)[2]) {
-    f16x2 v = {(_Float16)x[0], (_Float16)x[1]}; *reinterpret_cast<f16x2*>(p) = v;
+    f16x2 v = {(_Float16)x[0], (_Float16)x[1]}; *reinterpret_cast<f16x2_any*>(p) = v;
   }
 };
 template <> struct Pack<_Float16, 4> {
   static __device__ __forceinline__ void load(const _Float16* p, float (&x)[4]) {
-    f16x4 v = *reinterpret_cast<const f16x4*>(p);
+    f16x4 v = *reinterpret_cast<const f16x4_any*>(p);
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[i] = (float)v[i];
   }
@@ -59,12 +72,12 @@ template <> struct Pack<_Float16, 4> {
     f16x4 v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = (_Float16)x[i];
-    *reinterpret_cast<f16x4*>(p) = v;
+    *reinterpret_cast<f16x4_any*>(p) = v;
   }
 };
 template <> struct Pack<_Float16, 8> {
   static __device__ __forceinline__ void load(const _Float16* p, float (&x)[8]) {
-    f16x8 v = *reinterpret_cast<const f16x8*>(p);
+    f16x8 v = *reinterpret_cast<const f16x8_any*>(p);
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = (float)v[i];
   }
@@ -72,7 +85,7 @@ template <> struct Pack<_Float16, 8> {
     f16x8 v;
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = (_Float16)x[i];
-    *reinterpret_cast<f16x8*>(p) = v;
+    *reinterpret_cast<f16x8_any*>(p) = v;
   }
 };
 

@@ -79,7 +79,12 @@ int pick_segments(int m, int nnz, int vec, int g) {
 
 template <typename T>
 void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C, spdl_launch_info* info) {
-  const int vec = pick_vec<T>(n, B, C, 16 / (int)sizeof(T));
+  constexpr int kWide = 16 / (int)sizeof(T);
+  int vec = pick_vec<T>(n, B, C, kWide);
+  // (Rows of B at any alignment: 16 bytes per lane all the same, the lane at the row's end taking the
+  // row's last ones.  Not for small problems, where more lanes per row count for more: 512 x 512
+  // at 10 %, n = 127: 5.1 us against 6.3.)
+  if (vec < kWide && n >= kWide && (int64_t)nnz * n >= (1 << 24)) vec = kWide;
   const int g = pick_group(n, vec);
   const int seg = pick_segments<T>(m, nnz, vec, g);
   info->variant = kSpmmRowsplit;
@@ -96,6 +101,10 @@ bool slab_usable(int n, int nnz, const void* B, const void* C) {
   // 32-bit byte offsets: into the pair arrays, and from a slab's start to any of its elements
   return n % 4 == 0 && n < (1 << 21) && nnz < (1 << 29) && aligned(B, 4 * sizeof(T)) && aligned(C, 4 * sizeof(T));
 }
+// The copy-based slab kernels take any n from 4 on and element-aligned operands: a copy of 16 bytes
+// into LDS may start at any float, at the same rate.  (LSTM shape at 90 % sparsity, n = 127: 95 us
+// against 256 for row splitting with one column per lane; 4096 x 1024 at 10 %, n = 1001: 38 against 93.)
+inline bool slab_dma_usable(int n, int nnz) { return n >= 4 && n < (1 << 21) && nnz < (1 << 29); }
 
 // A slab kernel's workgroup fills a compute unit (LDS), so a grid of more than `slots` workgroups
 // runs in rounds.  `total` units of work per panel (tiles of C, slabs of A's columns), walked back
@@ -290,7 +299,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     const int64_t min_tiles = (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
                               : (n > 32 && n <= 2 * kSlabTile && reuse >= 16.0) ? 3 * kComputeUnits / 8
                                                                                  : kComputeUnits / 2;
-    variant = (sizeof(T) == 4 && slab_usable<T>(n, nnz, B, C) && reuse >= min_reuse && out_tiles >= min_tiles)
+    variant = (sizeof(T) == 4 && slab_dma_usable(n, nnz) && reuse >= min_reuse && out_tiles >= min_tiles)
                   ? kSpmmSlabDma : kSpmmRowsplit;
     // Thousands of rows of a few hundred entries or more, one or two 64-column tiles, and a shape the
     // slab kernel does not take: the shape of an attention head (paper Sec. "Application: Sparse
@@ -344,7 +353,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     info->block_threads = 64 * kWinWaves;
     info->grid_x = (m + info->rows_per_block - 1) / info->rows_per_block;
     info->grid_y = (n + kWinTile - 1) / kWinTile;
-  } else if ((variant == kSpmmSlab || variant == kSpmmSlabDma) && sizeof(T) == 4 && slab_usable<T>(n, nnz, B, C)) {
+  } else if (sizeof(T) == 4 && ((variant == kSpmmSlabDma && slab_dma_usable(n, nnz)) ||
+                                (variant == kSpmmSlab && slab_usable<T>(n, nnz, B, C)))) {
     fill_spmm_slab_info(m, k, n, nnz, variant, info);
   } else {
     fill_spmm_rowsplit_info<T>(m, n, nnz, B, C, info);

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
   if (slot >= m) return;
   int row = row_order ? row_order[slot] : slot;          // row swizzle: one extra load
   if (G * SEG == kWave) row = uniform(row);              // whole wave on one row: scalar loads
-  const int col = (blockIdx.y * G + lane) * VEC;
+  const int col = piece_start((blockIdx.y * G + lane) * VEC, n, VEC);
   const bool active = col < n;
   const int start = row_offsets[row];
   const int end = row_offsets[row + 1];

@@ -63,7 +63,8 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
   // The address is a scalar base (start of the slab in B, moved from stage to stage with scalar
   // arithmetic) plus a per-lane byte offset that is the same in every stage except a ragged
   // last slab, whose rows past k are clamped to row k-1, and a ragged last tile, whose columns
-  // past n are clamped to the tile's first column: nothing valid ever reads those.
+  // past n are clamped to the first ones (nothing valid ever reads those) and whose last piece
+  // of four starts at n - 4 (piece_start): no address is past B, whatever n and its alignment.
   // (S * n * 4 < 2^31 is checked on the host.)
   unsigned row_off[kCopies], row_off_last[kCopies];
   const int last_rows = k - (nslabs - 1) * S;               // rows of the last slab, 1..S
@@ -82,9 +83,9 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
     const int t = q / nslabs;
     const int slab = q - t * nslabs;
     const int tile = tile_begin + t;
-    const bool ragged_tile = tile * kSlabTile + l16 * 4 >= n;
-    const unsigned col_off = ragged_tile ? 0u : (unsigned)(l16 * 16);
-    const char* base = reinterpret_cast<const char*>(B + (size_t)slab * S * n + tile * kSlabTile);
+    const int piece = piece_start(tile * kSlabTile + l16 * 4, n, 4);
+    const unsigned col_off = piece < n ? (unsigned)piece * 4u : 0u;
+    const char* base = reinterpret_cast<const char*>(B + (size_t)slab * S * n);
     const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)(lds_raw + (q & 1) * kBufBytes) +
                          (unsigned)wave * (4 * kSlabTile * 4);
     const bool last = slab == nslabs - 1;
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
   clocks.lap(kPhaseSetup);
   int q = 0;
   for (int tile = tile_begin; tile < tile_end; ++tile) {
-    const int col = tile * kSlabTile + l16 * 4;
+    const int col = piece_start(tile * kSlabTile + l16 * 4, n, 4);
     const bool col_ok = col < n;
 #pragma unroll
     for (int j = 0; j < RPG; ++j) {

@@ -60,15 +60,15 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
   // wait that ends every stage); the stages are copied in order, so source and destination are
   // running scalar state.
   const size_t slab_bytes = (size_t)S * (size_t)n * 4;
-  const char* slab_base = reinterpret_cast<const char*>(B + (size_t)tile_begin * kSlabTile);
+  const char* slab_base = reinterpret_cast<const char*>(B);
   int cp_slab = 0, cp_t = 0;
   unsigned cp_dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_raw +
                     (unsigned)wave * (4 * kSlabTile * 4);
   unsigned cp_flip = (unsigned)kBufBytes;
   auto copy_stage = [&]() {
-    const bool ragged_tile = (tile_begin + cp_t) * kSlabTile + l16 * 4 >= n;
-    const unsigned col_off = ragged_tile ? 0u : (unsigned)(l16 * 16);
-    const char* base = slab_base + (size_t)cp_t * (kSlabTile * 4);
+    const int piece = piece_start((tile_begin + cp_t) * kSlabTile + l16 * 4, n, 4);
+    const unsigned col_off = piece < n ? (unsigned)piece * 4u : 0u;
+    const char* base = slab_base;
     const bool last = cp_slab == nslabs - 1;
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     if (t < ntiles) {
-      const int col = (tile_begin + t) * kSlabTile + l16 * 4;
+      const int col = piece_start((tile_begin + t) * kSlabTile + l16 * 4, n, 4);
       const bool col_ok = col < n;
 #pragma unroll
       for (int j = 0; j < RPG; ++j) {
