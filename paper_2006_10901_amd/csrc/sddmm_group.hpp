@@ -55,6 +55,17 @@ __device__ __forceinline__ int sddmm_strip_offset(int n, int q, int end, int l16
   return column_indices[min(q + l16, end - 1)] * n;
 }
 
+// One dot product by one lane, for the rare paths.
+template <typename T>
+__device__ __forceinline__ float sddmm_plain_dot(int n, const T* l, const T* r) {
+  float s = 0.f;
+  for (int j = 0; j < n; ++j) s = __builtin_fmaf((float)l[j], (float)r[j], s);
+  return s;
+}
+
+// n >= 4.  With n % 4 != 0 the lane at the row's end takes the row's last four columns (piece_start)
+// and leaves out of its sum, with zeros for L, those that the lane before it has; an Inf there would
+// still make the result NaN, so a NaN is looked at again.
 template <typename T>
 __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int l16, int roff,
                                                       const T* __restrict__ Lrow, const T* __restrict__ R,
@@ -66,7 +77,7 @@ __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int
   for (int col0 = 0; col0 < n; col0 += 64) {
     const int col = col0 + 4 * l16;
     const bool ok = col < n;
-    const int colc = ok ? col : 0;
+    const int colc = ok ? piece_start(col, n, 4) : 0;
     const int lane_off = colc;
     // All sixteen gathers are issued before the first multiply-add (the scheduling barrier keeps
     // the compiler from interleaving them with the arithmetic, which it otherwise does whenever
@@ -81,13 +92,14 @@ __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int
     Pack<T, 4>::load(Lrow + colc, l);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) l[v] = ok ? l[v] : 0.f;
+    for (int v = 0; v < 4; ++v) l[v] = ok && colc + v >= col ? l[v] : 0.f;
 #pragma unroll
     for (int t = 0; t < 16; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) partial[t] = __builtin_fmaf(l[v], r[t][v], partial[t]);
   }
-  const float total = reduce16x16(partial, l16);
+  float total = reduce16x16(partial, l16);
+  if ((n & 3) != 0 && cidx < end && total != total) total = sddmm_plain_dot<T>(n, Lrow, R + roff);
   if (cidx < end) sddmm_store<T>(out, scale, cidx, total);
 }
 

@@ -54,6 +54,7 @@
 // and a 16-byte aligned Rn as well.
 #pragma once
 #include "common.hpp"
+#include "sddmm_group.hpp"
 #include "sddmm_slab.hpp"
 
 namespace spdl {
@@ -142,8 +143,9 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
   // row L/16, and the hardware places lane L's bytes at M0 + 16 L.  The address is a scalar
   // base (start of the slab in R) plus a per-lane byte offset that is the same in every stage
   // except the last slab, whose rows past k are clamped to row k-1; columns past n are clamped
-  // to the row's first columns (the matching values of L are zero).  S * n * 4 < 2^31 is
-  // checked on the host.
+  // to the row's first columns (the matching values of L are zero), and the row's last piece of
+  // four starts at n - 4 (piece_start; L is zero where the piece before has the column).
+  // S * n * 4 < 2^31 is checked on the host.
   unsigned src_off[kCopies], src_off_last[kCopies];
   int dst_off[kCopies];
   const int last_rows = k - (k0 + (nslabs - 1) * S);          // rows of R from the last slab's start
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
     const int reg = idx & 1, rblock = idx >> 1;
     const int lrow = rblock * 4 + sub;
     const int col = reg * 64 + l16 * 4;
-    const unsigned colb = col < n ? (unsigned)col * 4u : 0u;
+    const unsigned colb = col < n ? (unsigned)piece_start(col, n, 4) * 4u : 0u;
     src_off[i] = (unsigned)lrow * (unsigned)ld * 4u + colb;
     src_off_last[i] = (unsigned)min(lrow, last_rows - 1) * (unsigned)ld * 4u + colb;
     dst_off[i] = reg * kLaneRegion + rblock * 1024;
@@ -272,7 +274,7 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int c = 32 * h4 + 8 * t4 + 4 * u;
-        lraw[j][u] = *reinterpret_cast<const f32x4*>(lrow + (c < n ? c : 0));
+        lraw[j][u] = *reinterpret_cast<const f32x4_any*>(lrow + (c < n ? piece_start(c, n, 4) : 0));
       }
     }
   }
@@ -342,9 +344,11 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
   for (int j = 0; j < RPG; ++j)
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const bool in = lok[j] && 32 * h4 + 8 * t4 + 4 * u < n;
+      const int c = 32 * h4 + 8 * t4 + 4 * u;
+      const bool in = lok[j] && c < n;
+      const int skip = c - piece_start(c, n, 4);   // columns that the piece before has
       const f32x4 vv = lraw[j][u];
-      const float own[4] = {in ? vv.x : 0.f, in ? vv.y : 0.f, in ? vv.z : 0.f, in ? vv.w : 0.f};
+      const float own[4] = {in && skip <= 0 ? vv.x : 0.f, in && skip <= 1 ? vv.y : 0.f, in && skip <= 2 ? vv.z : 0.f, in ? vv.w : 0.f};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int bits = __builtin_bit_cast(int, own[e]);
@@ -551,6 +555,26 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
                                       SCALED ? scale : nullptr);
       }
     }
+
+  // n % 4 != 0: where a row of R holds an Inf in a column that two pieces have, a zero of L has met it
+  // and made NaN of what may be an Inf.
+  if constexpr (!NT) {
+    if ((n & 3) != 0) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's results are read by other lanes
+#pragma unroll
+      for (int j = 0; j < RPG; ++j)
+        if (p[j] == p_end[j] && row[j] >= 0) {
+          const int rb = row_offsets[row[j]], re = row_offsets[row[j] + 1];
+          int lo2[1] = {rb}, hi2[1] = {k0 <= 0 ? rb : re};
+          const int key2[1] = {k0};
+          sd_lower_bound16_batch<1>(column_indices, lo2, hi2, key2, sub, l16, last_nz, k);
+          for (int t = lo2[0] + l16; t < p_end[j]; t += 16)
+            if (out[t] != out[t])
+              sddmm_store<float>(out, SCALED ? scale : nullptr, t,
+                                 sddmm_plain_dot<float>(c0 + n, L - c0 + (size_t)row[j] * ld, R - c0 + (size_t)column_indices[t] * ld));
+        }
+    }
+  }
 }
 
 }  // namespace spdl

@@ -9,7 +9,9 @@
 
 namespace spdl {
 
-template <int U, int S, bool DEFERRED>
+// ANY: n % 4 != 0 (a form of its own: the few instructions per stage that it takes cost the aligned form
+// 2 % on the Transformer shape).
+template <int U, int S, bool DEFERRED, bool ANY>
 __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
     int m, int k, int n, int nnz, int ksplit, int slabs_per_part, int panels,
     const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
@@ -50,7 +52,8 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
   // scalar base (start of the slab and column chunk in R, moved from stage to stage with scalar
   // arithmetic) plus a per-lane byte offset that is the same in every stage except a ragged
   // last slab, whose rows past k are clamped to row k-1, and a ragged last column chunk, whose
-  // columns past n are clamped to the chunk's first column: nothing valid ever reads those.
+  // columns past n are clamped to the first ones (nothing valid ever reads those) and whose last piece of
+  // four starts at n - 4 (piece_start; L is zero where the piece before has the column).
   // (S * n * 4 < 2^31 is checked on the host.)
   unsigned row_off[kCopies], row_off_last[kCopies];
   const int last_rows = k - (k0 + (nslabs - 1) * S);        // rows of the last slab, 1..S
@@ -70,8 +73,9 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
     const int slab = q / ncc;
     const int cc = q - slab * ncc;
     const int lcol = (lane % kLanesPerRow) * 4;
-    const unsigned col_off = cc * CW + lcol < n ? (unsigned)(lcol * 4) : 0u;
-    const char* base = reinterpret_cast<const char*>(R + (size_t)(k0 + slab * S) * n + cc * CW);
+    const int piece = ANY ? piece_start(cc * CW + lcol, n, 4) : cc * CW + lcol;
+    const unsigned col_off = piece < n ? (unsigned)(ANY ? piece : lcol) * 4u : 0u;
+    const char* base = reinterpret_cast<const char*>(R + (size_t)(k0 + slab * S) * n + (ANY ? 0 : cc * CW));
     const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)(lds_raw + (q & 1) * kBufBytes) +
                          (unsigned)wave * 1024u;
     const bool last = slab == nslabs - 1;
@@ -111,13 +115,29 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
     for (int u = 0; u < U; ++u) {
       const int col = cc * CW + u * 64 + 4 * l16;
       const bool ok = col < n && r.row >= 0;
-      Pack<T, 4>::load(Lrow + (ok ? col : 0), dst[u]);
+      Pack<T, 4>::load(Lrow + (ok ? (ANY ? piece_start(col, n, 4) : col) : 0), dst[u]);
       if (!ok) dst[u][0] = dst[u][1] = dst[u][2] = dst[u][3] = 0.f;
     }
   };
+  // the columns of a row's last piece that the piece before has (not while they are loaded: that would
+  // wait for them)
+  auto drop_shared = [&](int cc, float (&dst)[U][4]) {
+    if (ANY && (cc + 1) * CW >= n) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int col = cc * CW + u * 64 + 4 * l16;
+#pragma unroll
+        for (int v = 0; v < 3; ++v) dst[u][v] = piece_start(col, n, 4) + v >= col ? dst[u][v] : 0.f;
+      }
+    }
+  };
   float l_next[U][4];
-  if (DEFERRED) load_l(0, l_next);
-  else load_l(0, l);
+  if (DEFERRED) {
+    load_l(0, l_next);
+  } else {
+    load_l(0, l);
+    drop_shared(0, l);
+  }
 
   copy_stage(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -171,6 +191,7 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int v = 0; v < 4; ++v) l[u][v] = l_next[u][v];
+        drop_shared(cc, l);
         load_l(cc + 1 < ncc ? cc + 1 : 0, l_next);
         const char* buf = lds_raw + (q & 1) * kBufBytes;
 #pragma unroll
@@ -202,6 +223,15 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
   if (r.p != r.p_end && r.row >= 0)
     for (int t = r.p_start; t < r.p_end; t += 16)
       sd_strip_direct_call<T>(n, t, r.p_end, l16, Lrow, column_indices, R, out, scale);
+
+  // n % 4 != 0: where a row of R holds an Inf in a column that two pieces have, a zero of L has met it
+  // and made NaN of what may be an Inf.
+  if (ANY && r.p == r.p_end && r.row >= 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's results are read by other lanes
+    for (int t = r.p_start + l16; t < r.p_end; t += 16)
+      if ((float)out[t] != (float)out[t])
+        sddmm_store<T>(out, scale, t, sddmm_plain_dot<T>(n, Lrow, R + (size_t)column_indices[t] * n));
+  }
 }
 
 }  // namespace spdl

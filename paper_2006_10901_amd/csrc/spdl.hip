@@ -576,10 +576,21 @@ bool sddmm_lane_usable(int n, int nnz, const void* L, const void* R) {
   return sizeof(T) == 4 && sddmm_group_usable<T>(n, L, R) && n < (1 << 21) && nnz < (1 << 29);
 }
 
+// Dot products of any width from 4 columns on, operands at any element: the kernels that move 16 bytes
+// per lane take them, the lane at a row's end working on the row's last piece (piece_start).  (LSTM
+// shape at 90 % sparsity, n = 127: 92 us against 1782 for one column per lane.)  Not 129 .. 191 columns,
+// which are two passes of the lane kernel or two chunks of the slab kernel, the second mostly empty:
+// there the nonzero-split kernel serves as the general one.  (A pass of the lane kernel is at least
+// four columns wide.)
+inline bool sddmm_any_width(int n) { return n >= 4; }
+inline bool sddmm_wide_any(int n) { return n >= 4 && (n <= 128 || n >= 192); }
+inline bool sddmm_lane_pass_ok(int n) { return n % 128 == 0 || n % 128 >= 4; }
+
 template <typename T>
 void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R, spdl_launch_info* info,
                      int hint = 0) {
-  const bool fast_ok = sddmm_group_usable<T>(n, L, R);
+  const bool vec_ok = sddmm_group_usable<T>(n, L, R);          // whole pieces at aligned addresses
+  const bool fast_ok = vec_ok || sddmm_wide_any(n);
   int variant = g_forced[1].load();
   const bool free_choice = variant < 0;
   const bool mfma_ok = sizeof(T) == 2 && n > 0 && n % 8 == 0 && aligned(L, 16) && aligned(R, 16) &&
@@ -664,7 +675,7 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       const SddmmSlabShape ssh = sddmm_slab_shape(m, k, n);
       const double lane_fill = std::min(1.0, (double)lsh.panels * lsh.ksplit / kComputeUnits);
       const double slab_fill = std::min(1.0, (double)ssh.panels * ssh.ksplit / kComputeUnits);
-      const double t_lane = passes * 9.5 + flops / (rate(lane_rate) * 1e6 * lane_fill);   // microseconds
+      const double t_lane = !sddmm_lane_pass_ok(n) ? 1.0e30 : passes * 9.5 + flops / (rate(lane_rate) * 1e6 * lane_fill);   // microseconds
       // (every panel of 64 rows streams all of R through its compute unit: 8 TB/s over the chip at best)
       const double panels64 = (double)((m + kSdRows - 1) / kSdRows);
       const double t_slab = 8.0 + std::max(flops / (rate(slab_rate) * 1e6 * slab_fill), panels64 * (double)k * (double)n * 4.0 / 8.0e6);
@@ -679,8 +690,10 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   if ((variant == kSddmmSlab || variant == kSddmmSlabDma) &&
       !(fast_ok && sizeof(T) == 4 && nnz < (1 << 29) && n < (1 << 21)))   // 32-bit byte offsets
     variant = kSddmmGroup;
-  if (variant == kSddmmLane && !sddmm_lane_usable<T>(n, nnz, L, R)) variant = kSddmmGroup;
-  const bool window_ok = sizeof(T) == 4 && fast_ok && aligned(L, 16) && aligned(R, 16) && n <= 2 * kWinTile && nnz > 0 &&
+  if ((variant == kSddmmSlab && !vec_ok) ||
+      (variant == kSddmmLane && !(fast_ok && sddmm_lane_pass_ok(n) && sizeof(T) == 4 && nnz < (1 << 29) && n < (1 << 21))))
+    variant = kSddmmGroup;
+  const bool window_ok = sizeof(T) == 4 && vec_ok && aligned(L, 16) && aligned(R, 16) && n <= 2 * kWinTile && nnz > 0 &&
                          (int64_t)k * n < ((int64_t)1 << 29);
   // the caller says that the entries form a band (a problem the window kernel cannot take keeps the
   // choice made above)
@@ -726,7 +739,8 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_y = sh.ksplit;               // column ranges of A (the grid is 1-D)
     return;
   }
-  if (variant == kSddmmGroup) {
+  // (the general kernel of widths that the choice above leaves to it: the nonzero-split one again)
+  if (variant == kSddmmGroup || (free_choice && variant == kSddmmRowstrip && sddmm_any_width(n))) {
     // entries per wave: four strips of 16 while the machine (32 waves on each CU) is not
     // full, then as many as keep the grid at about one wave per slot
     const int64_t slots = (int64_t)kComputeUnits * 32;
@@ -755,11 +769,12 @@ int launch_sddmm_slab(const SddmmSlabShape& sh, int grid, int m, int k, int n, i
   static std::atomic<bool> configured{false};
   static std::atomic<bool> configured_dma{false};
   if (dma) {
-    auto kernel = sddmm_slab_dma_kernel<U, S, DEFERRED>;
+    auto kernel = n % 4 == 0 ? sddmm_slab_dma_kernel<U, S, DEFERRED, false> : sddmm_slab_dma_kernel<U, S, DEFERRED, true>;
     if (!configured_dma.load()) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              sh.lds_bytes) != hipSuccess)
-        return SPDL_ERR_LAUNCH;
+      for (auto f : {sddmm_slab_dma_kernel<U, S, DEFERRED, false>, sddmm_slab_dma_kernel<U, S, DEFERRED, true>})
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                sh.lds_bytes) != hipSuccess)
+          return SPDL_ERR_LAUNCH;
       configured_dma.store(true);
     }
     kernel<<<dim3(grid), dim3(kSdThreads), sh.lds_bytes, st>>>(m, k, n, nnz, sh.ksplit, sh.spp, sh.panels, ro, ci,
@@ -869,7 +884,7 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
       return SPDL_ERR_UNSUPPORTED;
     }
   }
-  if (li.variant == kSddmmGroup) {
+  if (li.lanes_per_row == 16 && (li.variant == kSddmmGroup || li.variant == kSddmmRowstrip)) {
     sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
     return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
   }

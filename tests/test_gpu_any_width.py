@@ -86,3 +86,78 @@ def test_spmm_row_splitting_with_wide_loads_at_any_width(g, oracle_lib, n, dtype
         spdl.spdl_force_variant(0, -1)
     g.assert_close(dC.cpu().numpy(), C, S, g.TOL_F16 if dtype == np.float16 else g.TOL_F32, f"row splitting n={n}")
     assert frame_intact(cbuf, at, m * n)
+
+
+def sddmm_any(g, oracle_lib, A, n, dtype, forced, shift, scaled=False, poke=None):
+    import torch
+    import paper_2006_10901_amd as spdl
+    L, R = wl.dense(A.m, n, 7201 + n, dtype), wl.dense(A.k, n, 7202 + n, dtype)
+    if poke:
+        poke(L, R)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, S = oracle_lib.sddmm(A.m, A.k, n, A.row_offsets, A.column_indices, L, R)
+    d = g.DevCsr(A)
+    _, dL, _ = framed(L, shift)
+    _, dR, _ = framed(R, shift)
+    obuf, out, at = framed(np.full(A.nnz, np.nan, dtype), shift, 777.0)
+    spdl.spdl_force_variant(1, forced)
+    try:
+        chosen = spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, L.itemsize, dL, dR)["variant"])
+        if scaled:
+            spdl.spdl_sddmm_scaled(A.m, A.k, n, A.nnz, d.ro, d.ci, d.val, dL, dR, out)
+        elif dtype == np.float16:
+            spdl.spdl_sddmm_f16(A.m, A.k, n, A.nnz, d.ro, d.ci, dL, dR, out)
+        else:
+            spdl.spdl_sddmm(A.m, A.k, n, A.nnz, d.ro, d.ci, dL, dR, out)
+        torch.cuda.synchronize()
+    finally:
+        spdl.spdl_force_variant(1, -1)
+    assert frame_intact(obuf, at, A.nnz)
+    v = A.values.astype(np.float64) if scaled else np.ones(A.nnz)
+    return chosen, out.cpu().numpy(), v * ref, np.abs(v) * S
+
+
+@pytest.mark.parametrize("n", [4, 5, 31, 63, 65, 67, 97, 127, 129, 195, 254, 261, 387, 1001])
+@pytest.mark.parametrize("kernel", ["group", "slabdma", "lane", None])
+def test_sddmm_any_width(g, oracle_lib, n, kernel):
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(1, v): v for v in range(16) if spdl.spdl_variant_name(1, v)}
+    A = wl.uniform_mask_csr(700, 1111, 0.12, 7200 + n)
+    for shift, scaled in ((0, False), (1, True)):
+        chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float32, -1 if kernel is None else ids[kernel], shift, scaled)
+        if kernel and (n <= 128 or n >= 192) and not (kernel == "lane" and 0 < n % 128 < 4):
+            assert chosen == kernel
+        g.assert_close(got, ref, S, g.TOL_F32, f"sddmm {chosen} n={n} shift={shift}")
+    U = wl.adversarial_csr(203, 700, 7203 + n, sorted_cols=False)
+    chosen, got, ref, S = sddmm_any(g, oracle_lib, U, n, np.float32, -1 if kernel is None else ids[kernel], 1)
+    g.assert_close(got, ref, S, g.TOL_F32, f"sddmm {chosen} n={n}, rows that are not ascending")
+
+
+@pytest.mark.parametrize("n", [5, 63, 98, 131, 1001])
+def test_sddmm_f16_any_width(g, oracle_lib, n):
+    A = wl.uniform_mask_csr(300, 500, 0.1, 7300 + n)
+    A.values = A.values.astype(np.float16)
+    chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float16, -1, 1)
+    g.assert_close(got, ref, S, g.TOL_F16, f"sddmm f16 {chosen} n={n}")
+
+
+@pytest.mark.parametrize("n", [63, 127, 261])
+@pytest.mark.parametrize("kernel", ["group", "slabdma", "lane"])
+def test_sddmm_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib, n, kernel):
+    """An Inf in a column that the last two pieces of a row share, and a NaN in the row after it."""
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(1, v): v for v in range(16) if spdl.spdl_variant_name(1, v)}
+    A = wl.uniform_mask_csr(600, 640, 0.1, 7400 + n)
+
+    def poke(L, R):
+        L[L == 0] = 1
+        R[77, n - 4] = np.inf
+        R[78, n - 1] = np.nan
+        R[79, 0] = -np.inf
+        R[639, n - 2] = np.inf
+    chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float32, ids[kernel], 1, poke=poke)
+    assert chosen == kernel
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+    assert np.all(np.abs(got[fin] - ref[fin]) <= g.TOL_F32 * S[fin])
