@@ -233,6 +233,7 @@ template <typename T>
 void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, spdl_launch_info* info,
                     int hint = 0) {
   int variant = g_forced[0].load();
+  const bool free_choice = variant < 0;
   const bool mfma_ok = sizeof(T) == 2 && n % 8 == 0 && n < (1 << 24) && k >= 16 && aligned(B, 16) && aligned(C, 16);
   // nnz == 0: column_indices, values and B may be null, and the slab and matrix-core kernels
   // fetch from them unconditionally; the row-splitting kernel only writes the zeros of C
@@ -318,7 +319,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // applies it stays the choice from the shape alone: on uniform masks it is up to 1.9 times faster
     // than the window kernel (16384 x 4096 at 10 %), on banded ones 2.2 .. 2.6 times slower, and only
     // the caller knows which it is (spdl_spmm_banded).
-    if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_usable<T>(n, nnz, B, C) &&
+    if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_dma_usable(n, nnz) &&
         (int64_t)k * n < ((int64_t)1 << 29) &&
         n > 32 && n <= 2 * kWinTile &&
         ((m >= 4096 && (double)nnz >= 100.0 * (double)m) ||
@@ -330,7 +331,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // flight per wave hide the longer latency better (15796 x 11092 at 1.2 %, n = 256: 116 us against
     // 175; 19428 x 9075 at 2.1 %, n = 1024: 636 against 1108; 13651 x 3925 at 3.1 %, n = 256: 98
     // against 69, not taken).
-    if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_usable<T>(n, nnz, B, C) &&
+    if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_dma_usable(n, nnz) &&
         (int64_t)k * n < ((int64_t)1 << 29) && n > 2 * kWinTile && m >= 4096 && k >= 7000 &&
         (double)nnz >= 120.0 * (double)m)
       variant = kSpmmWindow;
@@ -344,8 +345,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // slab kernels wait for their longest row)
     if (hint == kHintSkewed && n > 2 * kWinTile && k < 4000) variant = kSpmmRowsplit;
   }
-  if (variant == kSpmmWindow && sizeof(T) == 4 && nnz > 0 && slab_usable<T>(n, nnz, B, C) &&
-      (int64_t)k * n < ((int64_t)1 << 29)) {
+  if (variant == kSpmmWindow && sizeof(T) == 4 && nnz > 0 && slab_dma_usable(n, nnz) &&
+      (free_choice || slab_usable<T>(n, nnz, B, C)) && (int64_t)k * n < ((int64_t)1 << 29)) {
     info->variant = kSpmmWindow;
     info->vec = 4;
     info->lanes_per_row = 16;

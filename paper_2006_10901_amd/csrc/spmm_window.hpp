@@ -29,7 +29,7 @@
 // wave and round, gathers only), whose partial sums meet in LDS and are added by the row's owner,
 // so a few very long rows among short ones do not leave one wave working while the others have
 // finished.  Workgroups without such a row do not synchronise again once the window is in place.
-// Needs n % 4 == 0, 16-byte aligned B and C, k * n * 4 < 2^31.
+// Any n from 4 on, any element alignment (the lane at a row's end takes its last four columns); k * n * 4 < 2^31.
 #pragma once
 #include "common.hpp"
 #include "spmm_slab.hpp"
@@ -67,7 +67,7 @@ __device__ __forceinline__ f32x4 win_tail_gather(const int* __restrict__ column_
   const int o##T = __builtin_amdgcn_update_dpp(0, goff, 0x150 + (T), 0xf, 0xf, false);                          \
   const float av##T = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x150 + (T), 0xf, 0xf, false)); \
   f32x4 b##T = {0.f, 0.f, 0.f, 0.f};                                                                            \
-  if (o##T >= 0) b##T = *reinterpret_cast<const f32x4*>(gbase + (unsigned)o##T);
+  if (o##T >= 0) b##T = *reinterpret_cast<const f32x4_any*>(gbase + (unsigned)o##T);
 #define SPDL_TAILF(T)                                                                                          \
   if (o##T >= 0) {                                                                                              \
     acc.x = __builtin_fmaf(av##T, b##T.x, acc.x);                                                               \
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * NW, 4) void spmm_window_kernel(
   const int lane_b = l16 * 16;
   const int panel = blockIdx.x;
   const int tile = blockIdx.y;
-  const int col = tile * kWinTile + l16 * 4;
+  const int col = piece_start(tile * kWinTile + l16 * 4, n, 4);
   const bool col_ok = col < n;
   const int last_nz = nnz - 1;
 
@@ -162,10 +162,10 @@ __global__ __launch_bounds__(64 * NW, 4) void spmm_window_kernel(
 
   // The window copy: copy i of wave w fills window rows (i*NW + w)*4 .. +3, lane L row L/16 of
   // those and columns 4*(L%16) .. +3 of the tile; rows past k are clamped to row k-1 and
-  // columns past n to the tile's first column (nothing valid reads those).
+  // columns past n to the first ones (nothing valid reads those).
   if (c0 < k) {
-    const unsigned col_off = col_ok ? (unsigned)(l16 * 16) : 0u;
-    const char* base = reinterpret_cast<const char*>(B + tile * kWinTile);
+    const unsigned col_off = col_ok ? (unsigned)col * 4u : 0u;
+    const char* base = reinterpret_cast<const char*>(B);
     const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_raw +
                          (unsigned)wave * (4 * kWinTile * 4);
 #pragma unroll
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(64 * NW, 4) void spmm_window_kernel(
 #define SPDL_WIN_GATHER(G, T)                                                                    \
   {                                                                                              \
     const int o = __builtin_amdgcn_update_dpp(0, goff, 0x150 + (T), 0xf, 0xf, false);            \
-    if (o >= 0) G[(T) & 3] = *reinterpret_cast<const f32x4*>(gbase + (unsigned)o);               \
+    if (o >= 0) G[(T) & 3] = *reinterpret_cast<const f32x4_any*>(gbase + (unsigned)o);               \
   }
       // all the loads of the chunk first (blocks of four positions that no group needs are
       // skipped), then the multiply-adds

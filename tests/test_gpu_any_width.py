@@ -63,6 +63,24 @@ def test_spmm_slab_kernels_any_width(g, oracle_lib, m, k, n, density, shift):
     assert frame_intact(cbuf, at, m * n)
 
 
+@pytest.mark.parametrize("n", [33, 63, 127])
+@pytest.mark.parametrize("banded", [False, True])
+def test_spmm_window_kernel_any_width(g, oracle_lib, n, banded):
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = wl.banded_attention_csr(4099, 256, 0.075, 7050 + n) if banded else wl.uniform_mask_csr(4099, 4300, 0.047, 7050 + n)
+    B = wl.dense(A.k, n, 7051 + n)
+    C, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
+    d = g.DevCsr(A)
+    _, dB, _ = framed(B, 1)
+    cbuf, dC, at = framed(np.full((A.m, n), np.nan, np.float32), 1, 777.0)
+    assert spdl.spdl_variant_name(0, spdl.spdl_select_spmm(A.m, A.k, n, A.nnz, 4, dB, dC)["variant"]) == "window"
+    spdl.spdl_spmm(A.m, A.k, n, A.nnz, d.ro, d.ci, d.val, None, dB, dC)
+    torch.cuda.synchronize()
+    g.assert_close(dC.cpu().numpy(), C, S, g.TOL_F32, f"window n={n}")
+    assert frame_intact(cbuf, at, A.m * n)
+
+
 @pytest.mark.parametrize("n", [5, 19, 63, 130])
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 def test_spmm_row_splitting_with_wide_loads_at_any_width(g, oracle_lib, n, dtype):
