@@ -153,16 +153,24 @@ __device__ __forceinline__ int leading16(unsigned piece) { return __builtin_ctz(
 // Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: all
 // groups of a panel get ids that are equal modulo 8, so the panel's part of A is fetched into
 // one L2 only.  (The opposite choice, one slice of the dense operand per XCD, was measured: same
-// run time, 60 % more HBM reads.)  slab_grid_size() is the matching grid.
-__host__ __device__ __forceinline__ bool slab_wg_map(int bid, int panels, int groups, int& panel, int& group) {
-  const int per_block = 8 * groups;
-  const int blk = bid / per_block, rem = bid - blk * per_block;
-  panel = blk * 8 + (rem & 7);
-  group = rem >> 3;
-  return panel < panels;
+// run time, 60 % more HBM reads.)  The panels beyond the last multiple of eight would leave some
+// XCDs a whole panel more than others (9 panels of 25 tiles: 50 workgroups on one XCD, 25 on each of
+// the others): their (panel, group) pairs are dealt to all eight in equal runs.
+// slab_grid_size() is the matching grid, slab_xcd_load() the workgroups of one XCD.
+__host__ __device__ __forceinline__ int slab_xcd_load(int panels, int groups) {
+  return panels / 8 * groups + (panels % 8 * groups + 7) / 8;
 }
 __host__ __device__ __forceinline__ int slab_grid_size(int panels, int groups) {
-  return ((panels + 7) / 8) * 8 * groups;
+  return 8 * slab_xcd_load(panels, groups);
+}
+__host__ __device__ __forceinline__ bool slab_wg_map(int bid, int panels, int groups, int& panel, int& group) {
+  const int xcd = bid & 7, i = bid >> 3, eighths = panels >> 3, whole = eighths * groups;
+  const bool rest = i >= whole;
+  const int at = rest ? xcd * (((panels & 7) * groups + 7) >> 3) + i - whole : i;
+  const int p = at / groups;
+  panel = rest ? eighths * 8 + p : p * 8 + xcd;
+  group = at - p * groups;
+  return panel < panels;
 }
 
 // Store of one SDDMM result: as it is, or times the sparse matrix's value at that position (the

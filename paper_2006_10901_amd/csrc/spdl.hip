@@ -109,8 +109,8 @@ inline bool slab_dma_usable(int n, int nnz) { return n >= 4 && n < (1 << 21) && 
 // A slab kernel's workgroup fills a compute unit (LDS), so a grid of more than `slots` workgroups
 // runs in rounds.  `total` units of work per panel (tiles of C, slabs of A's columns), walked back
 // to back by one workgroup, are dealt to the number of workgroups per panel that gives the shortest
-// chain: rounds x (units per workgroup + two units' worth of set-up).  All workgroups of a panel
-// run on the same XCD (slab_wg_map), so the rounds are those of the XCD with the most panels.
+// chain: rounds x (units per workgroup + two units' worth of set-up).  slab_wg_map ties the
+// workgroups to XCDs, so the rounds are those of the XCD with the most of them.
 // (3072 rows, 48 panels, six per XCD: six workgroups per panel would be 36 on each XCD's 32 compute
 // units, a second round for four of them; five make 30 in one round.)  Returns the units per
 // workgroup.
@@ -119,7 +119,7 @@ int split_for_machine(int panels, int total, int slots = kComputeUnits) {
   double best = 1e300;
   for (int parts = 1; parts <= std::min(total, slots); ++parts) {
     const int units = (total + parts - 1) / parts;
-    const int64_t wgs = (int64_t)((panels + 7) / 8) * ((total + units - 1) / units);    // on the fullest XCD
+    const int64_t wgs = slab_xcd_load(panels, (total + units - 1) / units);
     const double cost = (double)((wgs + slots / 8 - 1) / (slots / 8)) * (units + 2.0);
     if (cost < best - 1e-9) {
       best = cost;
