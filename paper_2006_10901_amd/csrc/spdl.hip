@@ -139,7 +139,12 @@ int slab_rows_per_group(int m, int n) {
 }
 
 // Workgroups of 8 waves (panels of 32 rows, slabs of 128 rows of B, two workgroups per CU) for the
-// copy-based kernel when panels of 64 rows would leave compute units without a workgroup.
+// copy-based kernel when panels of 64 rows would leave half of the compute units or more without a
+// workgroup.  With 130 tiles of 64 x 64 and more the full form is faster although some compute units
+// stay idle, because every slab of B is copied for 64 rows instead of 32 (130 tiles, 4104 x 5093 at
+// 11 %, n = 112: 61 us in halves, 50 whole; 188 tiles, 12000 x 4000, n = 64: 51 and 39; 240 tiles,
+// 7640 x 4322 at 5 %, n = 104: 48 and 30); at 128 and fewer the halves are (128 tiles: 83 us and 90;
+// 82 tiles, 2592 x 4240 at 15 %, n = 120: 42 and 51).
 constexpr int kSlabHalfS = 128;
 constexpr int kSlabHalfLdsBytes = 2 * (kSlabHalfS + 1) * kSlabTile * 4;
 
@@ -155,7 +160,7 @@ constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators th
 
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
-  const bool half = variant == kSpmmSlabDma && (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles < kComputeUnits;
+  const bool half = variant == kSpmmSlabDma && (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles <= kComputeUnits / 2;
   const int rpg = (variant == kSpmmSlabDma && !half) ? slab_rows_per_group(m, n) : 1;
   const int rows = (half ? kSlabRows / 2 : kSlabRows) * rpg;
   const int panels = (m + rows - 1) / rows;
@@ -284,21 +289,33 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     const double narrow_reuse = (m != k && narrow_fill >= 0.95)                        ? 2.0
                                 : (m != k && narrow_fill >= 0.75 && narrow_rounds >= 2) ? 3.0
                                                                                         : 5.0;
+    // (One round that is more than half full: the slab kernel's time does not depend on how many compute
+    // units work, the gathers' grows with the rows, so the densities where the two meet lie on a
+    // hyperbola in the number of tiles.  n = 80 and 128, 2048 .. 9000 columns: 64 * density = 3.1 at 138
+    // tiles, 2.5 at 170, 2.0 at 200, 1.7 at 250 (8000 x 5000 at 6 %, n = 128: 34 us against 52); n = 40 and
+    // 64 some 15 % later (15800 x 5000 at 5 %, n = 64: 33 us against 47).)
+    const double one_round_reuse = (m != k && 2 * out_tiles > kComputeUnits && out_tiles <= kComputeUnits)
+                                       ? (n <= kSlabTile ? 500.0 : 430.0) / (double)out_tiles : 5.0;
     // (fewer than 16 columns use a quarter of a tile's lanes or less: 9957 x 8063 at 28 %, n = 8: 182 us
     // against 135 for row-splitting)
     const double min_reuse = n < 16                                           ? 1.0e9
                              : n <= 32                                        ? 12.0
-                             : n <= 64                                        ? narrow_reuse
-                             : out_tiles < kComputeUnits                      ? 5.0
+                             : n <= 64                                        ? std::min(narrow_reuse, one_round_reuse)
+                             : out_tiles < kComputeUnits                      ? one_round_reuse
                              : (n <= 4 * kSlabTile && k < 8192) || k < 4000   ? 3.0
                              : n >= 16 * kSlabTile                            ? 1.3
                              : n >= 8 * kSlabTile                             ? 1.8
                                                                               : 2.0;
     // (Dense matrices gain so much from the slab kernel that it pays with most compute units idle:
     // 6144 x 2048 at 35 %, n = 64, 96 workgroups: 36 us against 54 for row-splitting; 4096 x 4096 at
-    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.)
+    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  From 9 % on
+    // 80 tiles are enough where the output is wider than one: 2592 x 4240 at 15 %, n = 120, 82 tiles: 42 us
+    // against 50; 746 x 2984 at 12 %, n = 531, 108 tiles: 29 against 38; 977 x 3908 at 12 %, n = 268, 80
+    // tiles: level.  One tile wide, 97: 6900 x 2366 at 14 %, n = 40: 26 us against 34.  Not square matrices.)
     const int64_t min_tiles = (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
                               : (n > 32 && n <= 2 * kSlabTile && reuse >= 16.0) ? 3 * kComputeUnits / 8
+                              : (m != k && n > kSlabTile && reuse >= 5.5)       ? 5 * kComputeUnits / 16
+                              : (m != k && n > 32 && reuse >= 5.5)              ? 3 * kComputeUnits / 8 + 1
                                                                                  : kComputeUnits / 2;
     variant = (sizeof(T) == 4 && slab_dma_usable(n, nnz) && reuse >= min_reuse && out_tiles >= min_tiles)
                   ? kSpmmSlabDma : kSpmmRowsplit;
@@ -315,13 +332,15 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // what a row holds beyond 512 pairs is dealt to all waves of its workgroup, so strongly skewed
     // row lengths (log-normal, a few rows of thousands of entries among rows of hundreds) are no
     // reason to hold back: 4096 x 4096 at 6 %, n = 64: 27 us against 40 for row-splitting, n = 128:
-    // 46 against 82.  Where the slab kernel
+    // 46 against 82.  A second tile that is not full costs it as much as a full one: 6404 x 5399 at 2 %,
+    // n = 72: 27 us against 23 for row-splitting, 2924 x 3724 at 6 %, n = 123: 28 against 24; at n = 126
+    // it is level again.  Where the slab kernel
     // applies it stays the choice from the shape alone: on uniform masks it is up to 1.9 times faster
     // than the window kernel (16384 x 4096 at 10 %), on banded ones 2.2 .. 2.6 times slower, and only
     // the caller knows which it is (spdl_spmm_banded).
     if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_dma_usable(n, nnz) &&
         (int64_t)k * n < ((int64_t)1 << 29) &&
-        n > 32 && n <= 2 * kWinTile &&
+        n > 32 && n <= 2 * kWinTile && (n <= kWinTile || n >= 2 * kWinTile - 4) &&
         ((m >= 4096 && (double)nnz >= 100.0 * (double)m) ||
          (m >= 2048 && (double)nnz >= (n > kWinTile ? 192.0 : 400.0) * (double)m)))
       variant = kSpmmWindow;

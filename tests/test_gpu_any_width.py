@@ -68,7 +68,7 @@ def test_spmm_slab_kernels_any_width(g, oracle_lib, m, k, n, density, shift):
 def test_spmm_window_kernel_any_width(g, oracle_lib, n, banded):
     import torch
     import paper_2006_10901_amd as spdl
-    A = wl.banded_attention_csr(4099, 256, 0.075, 7050 + n) if banded else wl.uniform_mask_csr(4099, 4300, 0.047, 7050 + n)
+    A = wl.banded_attention_csr(4099, 256, 0.075, 7050 + n) if banded else wl.uniform_mask_csr(4099, 4300, 0.04, 7050 + n)
     B = wl.dense(A.k, n, 7051 + n)
     C, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
     d = g.DevCsr(A)
