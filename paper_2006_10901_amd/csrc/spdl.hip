@@ -195,13 +195,13 @@ constexpr int kSpmmMfmaKParts = 2;                // waves per tile, splitting t
 // measured rates on shapes from 1024 x 1024 x 3136 to 8192 x 10240 x 128).  The matrix-core kernels
 // do work proportional to m*k whatever the density, in rounds of one workgroup per CU: a panel of
 // 32 rows x 512 columns costs about 8.4 us plus 13.8 ns per column of A (SpMM), a 64 x 64 block
-// 3.5 us plus 0.5 us per 128 columns of the dot product (SDDMM); filling a panel adds 1 ns per entry
-// of its 32 rows (a workgroup walks its rows about twice: once whole, once in pieces per chunk of
-// 1024 columns), sampling the blocks 8 us per million entries.  The direct kernels run at the rate
+// 3.3 us plus 0.44 us per 128 columns of the dot product and 0.75 us for columns that fill no piece of eight
+// (SDDMM); filling a panel adds 1 ns per entry of its 32 rows (a workgroup walks its rows about twice: once
+// whole, once in pieces per chunk of 1024 columns), sampling the blocks 10.5 us per million entries.  The direct kernels run at the rate
 // of their gathers: 19.5 TFLOP/s (SpMM); 14 TFLOP/s for short dot products, 12 beyond 128 columns,
-// after a latency floor of 2 us per 64 columns of the dot product (SDDMM).  (Rates refitted on 120
-// random shapes, 512 .. 12000 rows and columns, 1 .. 50 % density, n = 48 .. 3136, both families
-// forced: the choice then takes 1.006 times the faster one's time on average.)
+// after a latency floor of 1.5 us per 64 columns of the dot product (SDDMM).  (SpMM's rates were fitted on
+// 120 random shapes, 512 .. 12000 rows and columns, 1 .. 50 % density, n = 48 .. 3136, SDDMM's on 60,
+// 256 .. 8192 rows and columns, 1 .. 40 %, n = 24 .. 3136, half of them odd; both families forced.)
 inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
   const double wgs = (double)((m + 31) / 32) * (double)(((n + 255) / 256 + kSpmmMfmaWaves - 1) / kSpmmMfmaWaves);
   const double per_panel = m > 0 ? 32.0 * (double)nnz / (double)m : 0.0;
@@ -211,8 +211,9 @@ inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
 }
 inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
   const double blocks = (double)((m + 63) / 64) * (double)((k + 63) / 64);
-  const double t_mfma = std::ceil(blocks / kComputeUnits) * (3.5 + 0.5 * (double)((n + 127) / 128)) + 8e-6 * (double)nnz;
-  const double t_direct = 5.0 + 2.0 * (double)(n / 64) + 2.0 * (double)nnz * (double)n / ((n <= 128 ? 14.0 : 12.0) * 1e6);
+  const double t_mfma = 1.0 + std::ceil(blocks / kComputeUnits) *
+                                  (3.3 + 0.44 * (double)((n + 127) / 128) + (n % 8 != 0 ? 0.75 : 0.0)) + 10.5e-6 * (double)nnz;
+  const double t_direct = 5.0 + 1.5 * (double)(n / 64) + 2.0 * (double)nnz * (double)n / ((n <= 128 ? 14.0 : 12.0) * 1e6);
   return t_mfma <= t_direct;
 }
 
@@ -610,10 +611,10 @@ template <typename T>
 void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R, spdl_launch_info* info,
                      int hint = 0) {
   const bool vec_ok = sddmm_group_usable<T>(n, L, R);          // whole pieces at aligned addresses
-  const bool fast_ok = vec_ok || sddmm_wide_any(n);
+  const bool fast_ok = vec_ok || (sizeof(T) == 2 ? sddmm_any_width(n) : sddmm_wide_any(n));
   int variant = g_forced[1].load();
   const bool free_choice = variant < 0;
-  const bool mfma_ok = sizeof(T) == 2 && n > 0 && n % 8 == 0 && aligned(L, 16) && aligned(R, 16) &&
+  const bool mfma_ok = sizeof(T) == 2 && n >= 8 &&
                        (int64_t)((m + 63) / 64) * ((k + 63) / 64) < ((int64_t)1 << 31);
   if (variant == kSddmmMfma && !mfma_ok) variant = kSddmmGroup;
   if (variant < 0 && mfma_ok && sddmm_mfma_pays(m, k, n, nnz)) variant = kSddmmMfma;
@@ -623,9 +624,8 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->vec = 8;
     info->lanes_per_row = kWave;
     info->rows_per_block = 64;
-    info->block_threads = 256;
-    // 8 XCDs x (half the row tiles, rounded up) x (a quarter of the column tiles, rounded up)
-    info->grid_x = 8 * (((m + 63) / 64 + 1) / 2) * (((k + 63) / 64 + 3) / 4);
+    info->block_threads = kSmThreads;
+    info->grid_x = sddmm_mfma_grid((m + 63) / 64, (k + 63) / 64);
     info->grid_y = (k + 63) / 64;               // 64-column blocks per panel (the grid is 1-D)
     return;
   }
@@ -827,15 +827,17 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
   (void)hipGetLastError();
   if (li.variant == kSddmmMfma) {
     if constexpr (sizeof(T) == 2) {
-      static std::atomic<bool> configured{false};
-      if (!configured.load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(sddmm_mfma_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSddmmMfmaLdsBytes) != hipSuccess)
+      // copies start at multiples of four bytes: every row's first element, or every other row's
+      const bool odd = n % 2 != 0 || !aligned(L, 4) || !aligned(R, 4);
+      const auto kernel = odd ? sddmm_mfma_kernel<true> : sddmm_mfma_kernel<false>;
+      static std::atomic<bool> configured[2];
+      if (!configured[odd].load()) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kSddmmMfmaLdsBytes) != hipSuccess)
           return SPDL_ERR_LAUNCH;
-        configured.store(true);
+        configured[odd].store(true);
       }
-      sddmm_mfma_kernel<<<dim3(li.grid_x), dim3(256), kSddmmMfmaLdsBytes, st>>>(m, k, n, li.grid_y, ro, ci, L, R, out,
-                                                                                scale);
+      kernel<<<dim3(li.grid_x), dim3(kSmThreads), kSddmmMfmaLdsBytes, st>>>(m, k, n, li.grid_y, ro, ci, L, R, out, scale);
       return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
     } else {
       return SPDL_ERR_UNSUPPORTED;

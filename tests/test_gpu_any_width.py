@@ -159,6 +159,21 @@ def test_sddmm_f16_any_width(g, oracle_lib, n):
     g.assert_close(got, ref, S, g.TOL_F16, f"sddmm f16 {chosen} n={n}")
 
 
+@pytest.mark.parametrize("m,k", [(300, 500), (65, 63), (2600, 320)])
+@pytest.mark.parametrize("n", [8, 9, 15, 16, 17, 119, 120, 122, 127, 128, 129, 137, 514, 1001])
+def test_sddmm_matrix_core_kernel_any_width(g, oracle_lib, m, k, n):
+    """Stages of 16 pieces of 8 columns, of 15 where rows start at odd elements, and the columns left over;
+    blocks dealt to the XCDs as regions and (41 x 5 of them) as runs; rows that are not ascending."""
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(1, v): v for v in range(16) if spdl.spdl_variant_name(1, v)}
+    for A in (wl.uniform_mask_csr(m, k, 0.15, 7350 + n), wl.adversarial_csr(m, k, 7351 + n, sorted_cols=False)):
+        A.values = A.values.astype(np.float16)
+        for shift in (0, 1):
+            chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float16, ids["mfma"], shift)
+            assert chosen == "mfma"
+            g.assert_close(got, ref, S, g.TOL_F16, f"sddmm mfma {m}x{k} n={n} shift={shift}")
+
+
 @pytest.mark.parametrize("n", [63, 127, 261])
 @pytest.mark.parametrize("kernel", ["group", "slabdma", "lane"])
 def test_sddmm_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib, n, kernel):
