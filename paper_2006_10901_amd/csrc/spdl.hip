@@ -187,26 +187,35 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
 // workgroup per compute unit, and keeps 16 waves.
 constexpr int kWinWaves = 8;                      // waves per workgroup of the window kernels, one sparse row each
 constexpr int kWinWavesWide = 16;                 // ... of the SDDMM window kernel with two column chunks
-constexpr int kSpmmMfmaWaves = 2;                 // 256-column tiles per workgroup of the MFMA kernel
-constexpr int kSpmmMfmaKParts = 2;                // waves per tile, splitting the contraction
+// Workgroups of the MFMA kernel, four waves: two tiles of 256 columns, each with the contraction split over
+// two waves; one tile and four parts where the machine has room for twice as many workgroups.
+inline int spmm_mfma_tiles(int m, int n) {
+  const int64_t wgs = (int64_t)((m + 31) / 32) * (((n + 255) / 256 + 1) / 2);
+  return wgs <= kComputeUnits / 2 ? 1 : 2;
+}
 
 // The matrix-core kernels (fp16 only) do dense work on 32-row panels / 64x64 blocks: selected
 // when an estimate of their run time is below that of the direct kernel (microseconds, from
 // measured rates on shapes from 1024 x 1024 x 3136 to 8192 x 10240 x 128).  The matrix-core kernels
 // do work proportional to m*k whatever the density, in rounds of one workgroup per CU: a panel of
-// 32 rows x 512 columns costs about 8.4 us plus 13.8 ns per column of A (SpMM), a 64 x 64 block
+// 32 rows x 512 columns costs about 5.2 us plus 13 ns per column of A, x 256 columns 8.3 ns per column, 4 ns more
+// where half of B's rows start at odd addresses (SpMM), a 64 x 64 block
 // 3.3 us plus 0.44 us per 128 columns of the dot product and 0.75 us for columns that fill no piece of eight
-// (SDDMM); filling a panel adds 1 ns per entry of its 32 rows (a workgroup walks its rows about twice: once
-// whole, once in pieces per chunk of 1024 columns), sampling the blocks 10.5 us per million entries.  The direct kernels run at the rate
-// of their gathers: 19.5 TFLOP/s (SpMM); 14 TFLOP/s for short dot products, 12 beyond 128 columns,
+// (SDDMM); filling a panel adds 0.5 ns per entry of its 32 rows, sampling the blocks 10.5 us per million
+// entries.  The direct kernels run at the rate of their gathers: 21 TFLOP/s, 10 for rows at odd addresses,
+// plus 8 ns per entry of a row and 512 columns (SpMM); 14 TFLOP/s for short dot products, 12 beyond 128 columns,
 // after a latency floor of 1.5 us per 64 columns of the dot product (SDDMM).  (SpMM's rates were fitted on
-// 120 random shapes, 512 .. 12000 rows and columns, 1 .. 50 % density, n = 48 .. 3136, SDDMM's on 60,
+// 160 random shapes, two thirds of them 256 .. 1024 rows and columns, n = 49 .. 3584, the others up to 8192 rows
+// and columns, 1 .. 40 % density: the choice then takes 1.017 times the faster one's time on average; SDDMM's on 60,
 // 256 .. 8192 rows and columns, 1 .. 40 %, n = 24 .. 3136, half of them odd; both families forced.)
 inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
-  const double wgs = (double)((m + 31) / 32) * (double)(((n + 255) / 256 + kSpmmMfmaWaves - 1) / kSpmmMfmaWaves);
-  const double per_panel = m > 0 ? 32.0 * (double)nnz / (double)m : 0.0;
-  const double t_mfma = std::ceil(wgs / kComputeUnits) * (8.4 + 0.0138 * (double)k + 1.0e-3 * per_panel);
-  const double t_direct = 7.0 + 2.0 * (double)nnz * (double)n / 19.5e6;
+  const int tiles = spmm_mfma_tiles(m, n);
+  const double wgs = (double)((m + 31) / 32) * (double)(((n + 255) / 256 + tiles - 1) / tiles);
+  const double row = m > 0 ? (double)nnz / (double)m : 0.0;
+  const double t_mfma = std::ceil(wgs / kComputeUnits) *
+                        (5.2 + ((tiles == 2 ? 13.0 : 8.3) + (n % 2 != 0 ? 4.1 : 0.0)) * 1e-3 * (double)k + 0.49e-3 * 32.0 * row);
+  const double t_direct = 4.5 + 2.0 * (double)nnz * (double)n / ((n % 2 != 0 ? 10.1 : 21.4) * 1e6) +
+                          8.1e-3 * row * (double)((n + 511) / 512);
   return t_mfma <= t_direct;
 }
 inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
@@ -226,8 +235,14 @@ bool spmm_mfma_runnable() {
   static const bool ok = [] {
     hipFuncAttributes attr;
     bool fine = true;
-    for (const void* f : {reinterpret_cast<const void*>(spmm_mfma_kernel<kSpmmMfmaWaves, kSpmmMfmaKParts, int, 1>),
-                          reinterpret_cast<const void*>(spmm_mfma_kernel<kSpmmMfmaWaves, kSpmmMfmaKParts, int16_t, 1>)})
+    for (const void* f : {reinterpret_cast<const void*>(spmm_mfma_kernel<2, 2, false, int>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<2, 2, true, int>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<1, 4, false, int>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<1, 4, true, int>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<2, 2, false, int16_t>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<2, 2, true, int16_t>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<1, 4, false, int16_t>),
+                          reinterpret_cast<const void*>(spmm_mfma_kernel<1, 4, true, int16_t>)})
       if (hipFuncGetAttributes(&attr, f) == hipSuccess && attr.localSizeBytes != 0) fine = false;
     (void)hipGetLastError();
     return fine;
@@ -240,7 +255,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
                     int hint = 0) {
   int variant = g_forced[0].load();
   const bool free_choice = variant < 0;
-  const bool mfma_ok = sizeof(T) == 2 && n % 8 == 0 && n < (1 << 24) && k >= 16 && aligned(B, 16) && aligned(C, 16);
+  // (n % 8 == 4: rows of whole 8-byte pieces stay with row splitting)
+  const bool mfma_ok = sizeof(T) == 2 && n >= 8 && n % 8 != 4 && n < (1 << 24) && k >= 16;
   // nnz == 0: column_indices, values and B may be null, and the slab and matrix-core kernels
   // fetch from them unconditionally; the row-splitting kernel only writes the zeros of C
   if (nnz == 0 && (variant == kSpmmMfma || variant == kSpmmSlab || variant == kSpmmSlabDma)) variant = kSpmmRowsplit;
@@ -248,7 +264,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
   if (variant < 0 && mfma_ok && nnz > 0 && spmm_mfma_pays(m, k, n, nnz) && spmm_mfma_runnable())
     variant = kSpmmMfma;
   if (variant == kSpmmMfma) {
-    // 32-row panels, kSpmmMfmaWaves tiles per workgroup.  (64-row panels, which would halve the
+    // 32-row panels, one or two tiles per workgroup.  (64-row panels, which would halve the
     // reads of B, need 256 accumulator registers per lane; the compiler then spills in the main
     // loop and the kernel is twice as slow.)
     const int tiles_n = (n + 255) / 256;
@@ -256,8 +272,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     info->vec = 8;
     info->lanes_per_row = kWave;
     info->rows_per_block = 32;
-    info->block_threads = 64 * kSpmmMfmaWaves * kSpmmMfmaKParts;
-    info->grid_x = ((m + 31) / 32) * ((tiles_n + kSpmmMfmaWaves - 1) / kSpmmMfmaWaves);
+    info->block_threads = 256;
+    info->grid_x = ((m + 31) / 32) * ((tiles_n + spmm_mfma_tiles(m, n) - 1) / spmm_mfma_tiles(m, n));
     info->grid_y = tiles_n;                     // 256-column tiles (the grid is 1-D)
     return;
   }
@@ -441,16 +457,18 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
   constexpr bool kInt32 = sizeof(I) == 4;        // the slab kernels read 32-bit indices only
   if (li.variant == kSpmmMfma) {
     if constexpr (sizeof(T) == 2) {
-      static std::atomic<bool> configured{false};
-      auto kernel = spmm_mfma_kernel<kSpmmMfmaWaves, kSpmmMfmaKParts, I, 1>;
-      if (!configured.load()) {
+      const bool chunks = k > kMfmaChunk, one = spmm_mfma_tiles(m, n) == 1;
+      static std::atomic<bool> configured[4];
+      const auto kernel = one ? (chunks ? spmm_mfma_kernel<1, 4, true, I> : spmm_mfma_kernel<1, 4, false, I>)
+                              : (chunks ? spmm_mfma_kernel<2, 2, true, I> : spmm_mfma_kernel<2, 2, false, I>);
+      const int lds = one ? spmm_mfma_lds_bytes(k, 1, 4) : spmm_mfma_lds_bytes(k, 2, 2);
+      if (!configured[2 * one + chunks].load()) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                spmm_mfma_lds_bytes(kMfmaChunk, kSpmmMfmaWaves, 1)) != hipSuccess)
+                                spmm_mfma_lds_bytes(kMfmaChunk, 1, 4)) != hipSuccess)
           return SPDL_ERR_LAUNCH;
-        configured.store(true);
+        configured[2 * one + chunks].store(true);
       }
-      kernel<<<dim3(li.grid_x), dim3(li.block_threads), spmm_mfma_lds_bytes(k, kSpmmMfmaWaves, 1), st>>>(
-          m, k, n, li.grid_y, ro, ci, val, B, C, bias, relu);
+      kernel<<<dim3(li.grid_x), dim3(li.block_threads), lds, st>>>(m, k, n, li.grid_y, ro, ci, val, B, C, bias, relu);
     } else {
       return SPDL_ERR_UNSUPPORTED;
     }

@@ -5,7 +5,7 @@
 // learning the multiplications by zero cost less than gathering one row of B per stored entry.
 // Sparsity still saves the memory and the traffic of A.
 //
-// A workgroup owns one panel (32 or 64 rows) and WAVES tiles of 256 output columns.  The panel
+// A workgroup owns one panel and WAVES tiles of 256 output columns.  The panel
 // is expanded once per chunk of up to kMfmaChunk columns of A and shared by the waves.  For a
 // step of 16 columns of A, lane (c, h) of a wave loads rows k0+8h .. k0+8h+7 of B, columns
 // n0+8c .. n0+8c+7 (eight 16-byte loads; the 32 lanes of a half read 512 contiguous bytes of each
@@ -16,17 +16,21 @@
 //
 // Rows whose indices are not strictly ascending (duplicates included) cannot be expanded by
 // plain stores; they are found while the panel is filled and computed by direct gathers.
-// Needs n % 8 == 0, k >= 16 and 16-byte aligned B and C.  The row order is not used: dense work
-// is the same for every row.
+// Any n from 8 on and any alignment (the lane at a row's end takes the row's last eight columns), k >= 16.
+// The row order is not used: dense work is the same for every row.
 //
-// What bounds it: every MFMA of a 32-row panel needs a fresh 1 KB fragment of B, and a CU's
-// vector memory path delivers about 64 bytes per clock (some 100-120 GB/s measured for
-// L2-resident data with copy-only kernels) against the 32 clocks of an MFMA: the main loop runs
-// at the rate at which B arrives (1 MB per workgroup), not at the matrix cores' rate.  Timed
-// inside the kernel on the 1x1 convolution (k = 1024, n = 3136; 20 us in all): 2.4 us until the
-// first loads are out, 4 us to clear and fill the panel (mostly waiting for loads), 10.6 us main
-// loop, 1.1 us to add the two k-parts, 1.9 us to convert and store.
+// What bounds it: every MFMA of a panel needs a fresh 1 KB fragment of B, and a CU's
+// vector memory path takes 16 clocks for that against the 32 clocks of the MFMA on one of four SIMDs: the
+// kernel runs at the rate at which B arrives (1 MB per workgroup), at 1024 x 1024, n = 3136 some 40 bytes per clock
+// and compute unit out of L2.  So the memory path has to be kept busy and free of anything else: the
+// first loads of B go out before the offsets of the rows are there, ahead of the entries of the panel; steps
+// past the end load nothing (with no lane active) instead of something unused; workgroups that share a
+// tile's columns of B run on one XCD; and the waves that share a tile each finish their part of its rows.  
+// (1024 x 1024 at 10 %, n = 3136: 23.4 us before all of this, 18.7 with it; with B in memory rather than
+// in a cache, a third more in both.  Of some 17 us in the kernel: 2 until the entries are here and the panel is clear, 2.5 to fill it, 10 main
+// loop, 2 to exchange, convert and store.)
 #pragma once
+#include <type_traits>
 #include "common.hpp"
 #include "sddmm_mfma.hpp"
 
@@ -36,30 +40,32 @@ constexpr int kMfmaChunk = 1024;         // columns of A expanded at a time
 constexpr int kMfmaSets = 6;             // steps of B rows held in registers per wave
 constexpr int kMfmaPad = 8;              // halves of padding per panel row: row stride = 16 mod 128 bytes
 
-// LDS: the panel of 32*rb rows (reused at the end to add up the k-parts' accumulators, rb * 32 KB
-// per tile), the flags of rows that cannot be expanded.
-__host__ __device__ __forceinline__ int spmm_mfma_lds_bytes(int k, int waves, int rb) {
+// LDS: the panel (reused at the end to exchange the k-parts' sums), the flags of rows that cannot be expanded.
+__host__ __device__ __forceinline__ int spmm_mfma_lds_bytes(int k, int waves, int kparts) {
   const int kc = ((k + 15) & ~15) < kMfmaChunk ? ((k + 15) & ~15) : kMfmaChunk;
-  const int panel = 32 * rb * (kc + kMfmaPad) * 2, sums = waves * rb * 128 * 64 * 4;
-  return (panel > sums ? panel : sums) + 32 * rb * 4;
+  const int panel = 32 * (kc + kMfmaPad) * 2, sums = waves * (kparts - 1) * 32 * 64 * 16;
+  return (panel > sums ? panel : sums) + 32 * 4;
 }
 
 // WAVES tiles of 256 columns per workgroup, and KP waves per tile that split the steps of the
-// contraction between them (more loads in flight per CU; their accumulators are added up
-// through LDS at the end).  RB blocks of 32 rows per panel: with two, every fragment of B feeds
-// two MFMAs and B is read from L2 half as often.
-template <int WAVES, int KP, typename I = int, int RB = 1>
+// contraction between them (more loads in flight per CU).  At the end each of the KP waves collects,
+// through LDS, the others' sums of 32 / KP of the rows and stores those.
+template <int WAVES, int KP, bool CHUNKS, typename I = int>
 __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     int m, int k, int n, int tiles_n, const int* __restrict__ row_offsets,
     const I* __restrict__ column_indices, const _Float16* __restrict__ values,
     const _Float16* __restrict__ B, _Float16* __restrict__ C, const _Float16* __restrict__ bias, int relu) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  constexpr int THREADS = 64 * WAVES * KP;
+  constexpr int NW = WAVES * KP;
+  constexpr int NS = kMfmaSets;
+  constexpr int RW = 32 / NW;                           // rows of the panel that a wave expands
+  constexpr int PRE = 2;                                // sixty-fours of a row fetched ahead
+  constexpr int FLAT = 64 / NW;                         // sixty-fours of the panel's entries fetched ahead by a wave
+  static_assert(KP == 2 || KP == 4, "a part of the rows for each wave of a tile");
   const int kc_max = min((k + 15) & ~15, kMfmaChunk);
   const int stride = kc_max + kMfmaPad;                 // halves per panel row
   _Float16* panel = reinterpret_cast<_Float16*>(lds_raw);
-  constexpr int PR = 32 * RB;                           // rows of the panel
-  int* bad = reinterpret_cast<int*>(lds_raw + spmm_mfma_lds_bytes(k, WAVES, RB) - PR * 4);   // rows that cannot be expanded
+  int* bad = reinterpret_cast<int*>(lds_raw + spmm_mfma_lds_bytes(k, WAVES, KP) - 32 * 4);   // rows that cannot be expanded
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -68,31 +74,37 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
   const int kpart = wave / WAVES;                       // which share of the steps
   const int c = lane & 31;
   const int h = lane >> 5;
-  const int groups = (tiles_n + WAVES - 1) / WAVES;
-  const int panel_id = blockIdx.x / groups;
-  const int tile = (blockIdx.x - panel_id * groups) * WAVES + tile_w;
+  // Consecutive workgroup ids go round-robin to the 8 XCDs; each gets a run of the workgroups, tile after
+  // tile, all panels of a tile before the next: an XCD's L2 then holds the columns of B that its
+  // workgroups read, where with the panels one after the other every L2 fetched all of B.
+  const int panels = (m + 31) >> 5;
+  const int eighth = gridDim.x >> 3, xcd = blockIdx.x & 7;
+  const int pos = xcd * eighth + min(xcd, (int)(gridDim.x & 7)) + (int)(blockIdx.x >> 3);
+  const int tile_group = pos / panels;
+  const int i0 = (pos - tile_group * panels) * 32;
+  const int tile = tile_group * WAVES + tile_w;
   const bool active = tile < tiles_n;                   // idle waves still take part in the barriers
-  const int i0 = panel_id * PR;
   const int n0 = tile * 256;
-  const int col = n0 + 8 * c;                           // this lane's eight output columns
-  const bool col_ok = active && col < n;
-  const _Float16* bp = B + (col_ok ? col : 0);
+  const bool col_ok = active && n0 + 8 * c < n;
+  const int col = col_ok ? piece_start(n0 + 8 * c, n, 8) : 0;      // this lane's eight output columns
+  const _Float16* bp = B + col;
 
-  if (tid < PR) bad[tid] = 0;
+  if (CHUNKS && lane < RW) bad[wave + NW * lane] = 0;
 
-  f32x16 acc[RB][8];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  f32x16 acc[8];
+  auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int t = 0; t < 16; ++t) acc[rb][j][t] = 0.f;
+      for (int t = 0; t < 16; ++t) acc[j][t] = 0.f;
+  };
+  if (CHUNKS) clear_sums();
 
   // Where each of this wave's rows continues in the next chunk of columns (rows in ascending order:
   // the entries of a chunk follow those of the chunk before).  The first chunk walks whole rows,
   // which is also what finds the rows that are not ascending; later chunks start at the cursor and
   // stop at the first 64 entries that reach past the chunk.
-  int cursor[(32 * RB) / (THREADS / 64)];
+  int cursor[RW];
   for (int kc0 = 0; kc0 < k; kc0 += kMfmaChunk) {
     const int kc = min(k - kc0, kMfmaChunk);
     const int all_steps = (kc + 15) >> 4;
@@ -100,8 +112,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     const int s_begin = min(all_steps, kpart * per_part);
     const int steps = min(all_steps, s_begin + per_part) - s_begin;      // this wave's steps: s_begin ..
     // Second operand source: rows kc0 + 16*(s_begin + s) + 8h + r of B, r < 8: a scalar base that
-    // moves with the step and the row plus this lane's fixed 32-bit byte offset (8h rows down,
-    // `col` columns in), so a load needs no vector arithmetic at all.  The loads are issued from
+    // moves with the step, and four rows down for r >= 4, plus this lane's fixed 32-bit byte offset (8h + r%4 rows
+    // down, `col` columns in), so a load needs no vector arithmetic and a step little on the scalar unit.  The loads are issued from
     // inline assembly and waited for with explicit counts (they complete in the order issued, and
     // inside the main loop they are the only vector-memory operations): the compiler's own
     // placement of waits made every step wait for all loads in flight, which left one step's
@@ -110,147 +122,257 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     // row of B (k % 16 != 0) is kept out of this pipeline and done at the end with clamped rows
     // (the panel holds zeros there).
     // (rows of B are kept as four 32-bit words each: the byte permutes work on those)
-    constexpr int NS = RB == 1 ? kMfmaSets : 4;        // register sets: loads run NS-1 steps ahead
     u32x4 w[NS][8];
-    const unsigned lane_off = (unsigned)((8 * h * n + (col_ok ? col : 0)) * 2);
+    unsigned lane_off[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lane_off[r] = (unsigned)(((8 * h + r) * n + col) * 2);
     const bool ragged_last = kc0 + 16 * (s_begin + steps) > k && steps > 0;   // this wave's last step is the ragged one
     const int full_steps = steps - (ragged_last ? 1 : 0);
-    // A step past this wave's last full one loads nothing useful: it re-reads the start of rows 0
-    // and 8 of B (cache hits; k >= 16 is required), so that the number of loads behind any set is
-    // the same at every step and one wait count serves them all.  The vector offset is the same
-    // register for every load of the kernel.
-    auto load_rows = [&](int s, u32x4 (&ws)[8]) {
-      const bool real = s < full_steps;
-      const char* base = reinterpret_cast<const char*>(B + (real ? (size_t)(kc0 + 16 * (s_begin + s)) * n : (size_t)0));
-      const size_t row_bytes = real ? (size_t)n * 2 : (size_t)0;
-      const unsigned voff = lane_off;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const char* row_base = base + (size_t)r * row_bytes;
-        asm volatile("global_load_dwordx4 %0, %1, %2" : "=&v"(ws[r]) : "v"(voff), "s"(row_base) : "memory");
-      }
+    // The panels of a tile run on one XCD and want the same rows of B: each starts an eighth of its steps after
+    // the one before, so that eight times as much of B is on its way from memory at a time.
+    const int turn = ((i0 >> 5) & 7) * full_steps >> 3;
+    const char* step_rows = reinterpret_cast<const char*>(B + (size_t)(kc0 + 16 * s_begin) * n);
+    // A step past this wave's last full one loads with no lane active: nothing is fetched, but the
+    // number of loads behind any set is the same at every step and one wait count serves them all.
+    auto load_rows = [&](int s, u32x4 (&ws)[8]) __attribute__((always_inline)) {
+      const int t = s + turn - (s + turn >= full_steps ? full_steps : 0);
+      const char* b0 = step_rows + (size_t)t * ((size_t)n * 32);
+      const char* b1 = b0 + (size_t)n * 8;
+      const int lanes = uniform((s - full_steps) >> 31);               // all ones while s < full_steps
+      asm volatile(
+          "s_mov_b32 exec_lo, %14\n\t"
+          "s_mov_b32 exec_hi, %14\n\t"
+          "global_load_dwordx4 %0, %8, %12\n\t"
+          "global_load_dwordx4 %1, %9, %12\n\t"
+          "global_load_dwordx4 %2, %10, %12\n\t"
+          "global_load_dwordx4 %3, %11, %12\n\t"
+          "global_load_dwordx4 %4, %8, %13\n\t"
+          "global_load_dwordx4 %5, %9, %13\n\t"
+          "global_load_dwordx4 %6, %10, %13\n\t"
+          "global_load_dwordx4 %7, %11, %13\n\t"
+          "s_mov_b64 exec, -1"
+          : "=&v"(ws[0]), "=&v"(ws[1]), "=&v"(ws[2]), "=&v"(ws[3]), "=&v"(ws[4]), "=&v"(ws[5]), "=&v"(ws[6]), "=&v"(ws[7])
+          : "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]), "s"(b0), "s"(b1), "s"(lanes)
+          : "memory");
     };
     // the set is complete once only the NS - 1 later sets (8 loads each) are outstanding
-    auto await_rows = [&](u32x4 (&ws)[8]) {
-      static_assert(NS == 6 || NS == 4, "wait counts below");
-      if constexpr (NS == 6)
-        asm volatile("s_waitcnt vmcnt(40)"
-                     : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]), "+v"(ws[4]), "+v"(ws[5]), "+v"(ws[6]),
-                       "+v"(ws[7])::"memory");
-      else
-        asm volatile("s_waitcnt vmcnt(24)"
-                     : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]), "+v"(ws[4]), "+v"(ws[5]), "+v"(ws[6]),
-                       "+v"(ws[7])::"memory");
+    auto await_rows = [&](u32x4 (&ws)[8]) __attribute__((always_inline)) {
+      static_assert(NS == 6, "wait count below");
+      asm volatile("s_waitcnt vmcnt(40)"
+                   : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]), "+v"(ws[4]), "+v"(ws[5]), "+v"(ws[6]),
+                     "+v"(ws[7])::"memory");
     };
     // keeps a set's registers allocated up to this point (a load into them may still be in flight)
-    auto hold_rows = [&](u32x4 (&ws)[8]) {
+    auto hold_rows = [&](u32x4 (&ws)[8]) __attribute__((always_inline)) {
       asm volatile("" : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]), "+v"(ws[4]), "+v"(ws[5]), "+v"(ws[6]),
                    "+v"(ws[7])::"memory");
     };
-    if (active) {
-      // the first loads go out before the panel is built: they do not depend on it
+    if constexpr (!CHUNKS) {
+      // Expansion, all columns of A at once: the panel's entries lie one after the other in memory, and
+      // each wave takes an equal run of them, 64 at a time, whatever rows they belong to.  The rows of 64
+      // entries follow from the row starts among them (lane l holds the offset of row l), one step of
+      // scalar work for each.  Nothing but these loads is ahead of the first sets of B.
+      // (A wave is alone on its SIMD and issues an instruction every five clocks: all of this is written for
+      // few of them.)
+      const int first = uniform(row_offsets[i0]), last = uniform(row_offsets[min(i0 + 32, m)]);
+      int row_start = row_offsets[min(i0 + min(lane, 32), m)];
+      if (row_start >= last) row_start = 0x7fffffff;                     // (also rows without entries at the end)
+      const int final_entry = max(last - 1, 0);
+      const int share = (last - first + 64 * NW - 1) / (64 * NW);        // sixty-fours of this wave
+      const int mine = min(first + wave * share * 64, final_entry);
+      const I* my_columns = column_indices + mine;
+      const _Float16* my_values = values + mine;
+      // lanes past the last entry take it again (to the same place in the panel)
+      auto entry = [&](int e) __attribute__((always_inline)) { return (unsigned)min(64 * e + lane, final_entry - mine); };
+      int ecol[FLAT];
+      _Float16 eval[FLAT];
 #pragma unroll
-      for (int u = 0; u < NS - 1; ++u) load_rows(u, w[u]);
-    }
-    // Expansion.  A wave takes every fourth row of the panel (or so: one in THREADS/64) and its
-    // lanes take the row's entries 64 at a time: coalesced loads, no search for the row of an
-    // entry, and the loads of each row's first 128 entries are all issued before the panel is
-    // even cleared.  Longer rows finish in a loop.  An entry whose column is not above its
-    // predecessor's marks the row as not expandable (the predecessor is the lane below, or lane
-    // 63 of the previous 64).
-    constexpr int NW = THREADS / 64, RW = PR / NW;       // waves, rows per wave
-    constexpr int PRE = RB == 1 ? 2 : 1;                // sixty-fours of a row fetched ahead
-    int row_begin[RW], row_end[RW];
-    int cfirst[RW][PRE];
-    _Float16 afirst[RW][PRE];
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      const int rr = wave + NW * i;
-      row_begin[i] = uniform(row_offsets[min(i0 + rr, m)]);
-      row_end[i] = uniform(row_offsets[min(i0 + rr + 1, m)]);
-      if (kc0 > 0) row_begin[i] = cursor[i];
-    }
-    const int kend = kc0 + kc;
-#pragma unroll
-    for (int i = 0; i < RW; ++i)
-#pragma unroll
-      for (int e = 0; e < PRE; ++e) {
-        const int p = row_begin[i] + 64 * e + lane;
-        cfirst[i][e] = 0;
-        afirst[i][e] = (_Float16)0.f;
-        if (p < row_end[i]) {
-          cfirst[i][e] = (int)column_indices[p];
-          afirst[i][e] = values[p];
-        }
+      for (int e = 0; e < FLAT; ++e) {
+        ecol[e] = (int)my_columns[entry(e)];
+        eval[e] = my_values[entry(e)];
       }
-    __syncthreads();                                     // the previous chunk's reads are done
-    for (int o = tid * 16; o < PR * stride * 2; o += THREADS * 16)
-      *reinterpret_cast<f32x4*>(lds_raw + o) = f32x4{0.f, 0.f, 0.f, 0.f};
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      const int rr = wave + NW * i;
-      _Float16* prow = panel + rr * stride;
-      int below = 0;                                     // column of the previous 64's lane 63
-      bool unordered = false;
-      int before_end = 0;                                // entries seen whose column lies before the chunk's end
-      bool past = false;                                 // some entry seen lies past the chunk
-      auto place = [&](int p, int cidx, _Float16 a, bool head) {
-        const int prev = __shfl_up(cidx, 1);
-        const bool valid = p < row_end[i];
-        if (valid) {
-          if (!head && (lane == 0 ? below : prev) >= cidx) unordered = true;
-          const unsigned rel = (unsigned)(cidx - kc0);
-          if (rel < (unsigned)kc) prow[rel] = a;
+      const int before = mine > first ? (int)column_indices[mine - 1] : -1;
+#pragma unroll 8
+      for (int o = tid * 16; o < 32 * stride * 2; o += 64 * NW * 16)
+        *reinterpret_cast<f32x4*>(lds_raw + o) = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (tid < 32) bad[tid] = 0;
+      __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt 0: the entries; lgkmcnt is left to the barrier
+      if (active) {
+        load_rows(0, w[0]);
+        load_rows(1, w[1]);
+      }
+      clear_sums();
+      __syncthreads();
+      // Ascending rows have ascending places in the panel, across rows too: an entry whose place is not above
+      // its predecessor's shows a row that is not ascending.
+      int row = __builtin_popcountll(__builtin_amdgcn_ballot_w64(row_start <= mine)) - 1;
+      int next = __builtin_amdgcn_readlane(row_start, row + 1);
+      int place_before = -1;                             // (the first of a wave's entries: looked at below)
+      unsigned long long descending = 0;
+      const int row_bytes_lds = stride * 2;
+      auto place = [&](int e, int cidx, _Float16 a) __attribute__((always_inline)) {
+        const int p0 = mine + 64 * e, p = p0 + lane;
+        int at = row * row_bytes_lds;
+        while (next <= p0 + 63) {
+          ++row;
+          at = p >= next ? row * row_bytes_lds : at;
+          next = __builtin_amdgcn_readlane(row_start, row + 1);
         }
-        if (k > kMfmaChunk) {                            // (one chunk: no cursor to keep)
-          const unsigned long long inside = __builtin_amdgcn_ballot_w64(valid && cidx < kend);
-          before_end += __builtin_popcountll(inside);
-          past = past || __builtin_amdgcn_ballot_w64(valid && cidx >= kend) != 0;
-        }
-        below = __builtin_amdgcn_readlane(cidx, 63);
+        at += 2 * (int)min((unsigned)cidx, (unsigned)kc_max);            // a column outside the matrix: padding
+        *reinterpret_cast<_Float16*>(lds_raw + at) = a;
+        const int prev = __builtin_amdgcn_update_dpp(place_before, at, 0x138, 0xf, 0xf, false);   // the lane below's; lane 0's
+        place_before = __builtin_amdgcn_readlane(at, 63);
+        descending |= __builtin_amdgcn_ballot_w64(prev >= at && p < last);
       };
 #pragma unroll
-      for (int e = 0; e < PRE; ++e)
-        if (row_begin[i] + 64 * e < row_end[i])
-          place(row_begin[i] + 64 * e + lane, cfirst[i][e], afirst[i][e], e == 0 && lane == 0);
-      for (int base = row_begin[i] + 64 * PRE; base < row_end[i]; base += 256) {   // long rows: 256 entries per round
-        if (kc0 > 0 && past) break;                      // (ascending rows: nothing further belongs to this chunk)
+      for (int e = 0; e < FLAT; e += 4) {
+        if (e < share) {
+#pragma unroll
+          for (int f = 0; f < 4; ++f) place(e + f, ecol[e + f], eval[e + f]);
+        }
+        // (further sets of B in between: the memory path takes 500 clocks for one of all waves)
+        if (active && 2 + e / 4 < NS - 1) load_rows(2 + e / 4, w[2 + e / 4]);
+      }
+      for (int e0 = FLAT; e0 < share; e0 += 4) {
         int cmore[4];
         _Float16 amore[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int q = min(base + 64 * e + lane, row_end[i] - 1);
-          cmore[e] = (int)column_indices[q];
-          amore[e] = values[q];
+        for (int f = 0; f < 4; ++f) {
+          cmore[f] = (int)my_columns[entry(e0 + f)];
+          amore[f] = my_values[entry(e0 + f)];
         }
+        __builtin_amdgcn_s_waitcnt(0x0F70);              // (no path leaves one of these to be waited for in the main loop)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (base + 64 * e < row_end[i]) place(base + 64 * e + lane, cmore[e], amore[e], false);
+        for (int f = 0; f < 4; ++f) place(e0 + f, cmore[f], amore[f]);
       }
-      if (kc0 == 0 && __builtin_amdgcn_ballot_w64(unordered) != 0 && lane == 0) bad[rr] = 1;
-      cursor[i] = row_begin[i] + before_end;
+      // which rows they are, and the pair across the start of the run: no need to hurry unless there is one
+      const bool head = __builtin_amdgcn_ballot_w64(row_start == mine) != 0;
+      if (descending != 0 || (!head && before >= __builtin_amdgcn_readlane(ecol[0], 0))) {
+        for (int p = mine + lane; p < min(mine + 64 * share, last); p += 64) {
+          int rr = 0, begin = first;
+          for (int r = 1; r < 32; ++r) {
+            const int at = __builtin_amdgcn_readlane(row_start, r);
+            if (p >= at) {
+              rr = r;
+              begin = at;
+            }
+          }
+          if (p > begin && column_indices[p - 1] >= column_indices[p]) bad[rr] = 1;
+        }
+      }
+    } else {
+      // Expansion, a chunk of columns.  A wave takes every fourth row of the panel and its
+      // lanes take the row's entries 64 at a time: coalesced loads, no search for the row of an
+      // entry, and the loads of each row's first 128 entries are all issued before the panel is
+      // even cleared.  Longer rows finish in a loop.  An entry whose column is not above its
+      // predecessor's marks the row as not expandable (the predecessor is the lane below, or lane
+      // 63 of the previous 64).
+      int row_begin[RW], row_end[RW];
+      int cfirst[RW][PRE];
+      _Float16 afirst[RW][PRE];
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+        const int rr = wave + NW * i;
+        row_begin[i] = uniform(row_offsets[min(i0 + rr, m)]);
+        row_end[i] = uniform(row_offsets[min(i0 + rr + 1, m)]);
+        if (kc0 > 0) row_begin[i] = cursor[i];
+      }
+      // half of the sets of B go ahead of the entries: the memory path works on them until the offsets are
+      // there and while the panel is filled (more would hold the entries up, which arrive after everything
+      // issued before them)
+      if (active) {
+#pragma unroll
+        for (int u = 0; u < NS / 2; ++u) load_rows(u, w[u]);
+      }
+      const int kend = kc0 + kc;
+#pragma unroll
+      for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int e = 0; e < PRE; ++e) {
+          const int p = row_begin[i] + 64 * e + lane;
+          cfirst[i][e] = 0;
+          afirst[i][e] = (_Float16)0.f;
+          if (p < row_end[i]) {
+            cfirst[i][e] = (int)column_indices[p];
+            afirst[i][e] = values[p];
+          }
+        }
+      if (kc0 > 0) __syncthreads();                        // the previous chunk's reads are done
+#pragma unroll
+      for (int i = 0; i < RW; ++i)                         // a wave clears the rows that it fills: no barrier in between
+        for (int o = lane * 16; o < stride * 2; o += 64 * 16)
+          *reinterpret_cast<f32x4*>(lds_raw + (wave + NW * i) * stride * 2 + o) = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" ::: "memory");
+      // (vmcnt 0; the other two counters are left alone.)  No load is in flight while the panel is filled: the
+      // compiler, short of registers there, may move some, and does not know which are still to be written.
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      if (active) {
+#pragma unroll
+        for (int u = 0; u < NS / 2; ++u) hold_rows(w[u]);
+      }
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+        const int rr = wave + NW * i;
+        _Float16* prow = panel + rr * stride;
+        int below = -1;                                    // column of the previous 64's lane 63
+        bool unordered = false;
+        int before_end = 0;                                // entries seen whose column lies before the chunk's end
+        bool past = false;                                 // some entry seen lies past the chunk
+        auto place = [&](int p, int cidx, _Float16 a) __attribute__((always_inline)) {
+          const int prev = __builtin_amdgcn_update_dpp(below, cidx, 0x138, 0xf, 0xf, false);   // the lane below's; lane 0: below
+          const bool valid = p < row_end[i];
+          if (valid) {
+            if (prev >= cidx) unordered = true;
+            const unsigned rel = (unsigned)(cidx - kc0);
+            if (rel < (unsigned)kc) prow[rel] = a;
+          }
+          if (k > kMfmaChunk) {                            // (one chunk: no cursor to keep)
+            const unsigned long long inside = __builtin_amdgcn_ballot_w64(valid && cidx < kend);
+            before_end += __builtin_popcountll(inside);
+            past = past || __builtin_amdgcn_ballot_w64(valid && cidx >= kend) != 0;
+          }
+          below = __builtin_amdgcn_readlane(cidx, 63);
+        };
+#pragma unroll
+        for (int e = 0; e < PRE; ++e)
+          if (row_begin[i] + 64 * e < row_end[i]) place(row_begin[i] + 64 * e + lane, cfirst[i][e], afirst[i][e]);
+        for (int base = row_begin[i] + 64 * PRE; base < row_end[i]; base += 256) {   // long rows: 256 entries per round
+          if (kc0 > 0 && past) break;                      // (ascending rows: nothing further belongs to this chunk)
+          int cmore[4];
+          _Float16 amore[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int q = min(base + 64 * e + lane, row_end[i] - 1);
+            cmore[e] = (int)column_indices[q];
+            amore[e] = values[q];
+          }
+          __builtin_amdgcn_s_waitcnt(0x0F70);              // (no path leaves one of these to be waited for in the main loop)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (base + 64 * e < row_end[i]) place(base + 64 * e + lane, cmore[e], amore[e]);
+        }
+        if (kc0 == 0 && __builtin_amdgcn_ballot_w64(unordered) != 0 && lane == 0) bad[rr] = 1;
+        cursor[i] = row_begin[i] + before_end;
+      }
+      if (active) {
+#pragma unroll
+        for (int u = NS / 2; u < NS - 1; ++u) load_rows(u, w[u]);
+      }
     }
-    // Some of the expansion's loads are used on one path only; the compiler would otherwise wait
-    // for them inside the main loop, where its wait also drains the loads of B.  (vmcnt 0; the
-    // other two counters are left alone.)
-    __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     if (active) {
-      // first operands: rows c, 32 + c, .. of the panel, columns 16*s + 8h .. +7 of the chunk
+      // first operands: rows c of the panel, columns 16*s + 8h .. +7 of the chunk
       const _Float16* ap = panel + c * stride + 8 * h + 16 * s_begin;
+      auto fragment = [&](int s) __attribute__((always_inline)) {        // (the ragged step is the last in any order)
+        const int t = s >= full_steps ? s : s + turn - (s + turn >= full_steps ? full_steps : 0);
+        return *reinterpret_cast<const f16x8*>(ap + 16 * t);
+      };
       // (the fragment of a step is read from LDS one step ahead: with one wave per SIMD nothing
       // else would cover the LDS latency)
-      f16x8 a_next[RB];
-      auto read_panel = [&](int s) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) a_next[rb] = *reinterpret_cast<const f16x8*>(ap + 32 * rb * stride + 16 * s);
-      };
-      auto step = [&](int s, const u32x4 (&ws)[8]) {
-        f16x8 a[RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) a[rb] = a_next[rb];
-        if (s + 1 < steps) read_panel(s + 1);
+      f16x8 a_next;
+      auto step = [&](int s, const u32x4 (&ws)[8]) __attribute__((always_inline)) {
+        const f16x8 a = a_next;
+        if (s + 1 < steps) a_next = fragment(s + 1);
         // 8x8 transpose of halves inside the lane: operand j, word q = (ws[2q][j], ws[2q+1][j])
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -260,13 +382,10 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
             const unsigned sel = (j & 1) ? 0x07060302u : 0x05040100u;
             packed[q] = __builtin_amdgcn_perm(ws[2 * q + 1][j / 2], ws[2 * q][j / 2], sel);
           }
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-            acc[rb][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[rb], __builtin_bit_cast(f16x8, packed), acc[rb][j],
-                                                                0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(f16x8, packed), acc[j], 0, 0, 0);
         }
       };
-      if (steps > 0) read_panel(0);
+      if (steps > 0) a_next = fragment(0);
       for (int s0 = 0; s0 < full_steps; s0 += NS) {
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
@@ -276,8 +395,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
           if (s < full_steps) step(s, w[u]);
         }
       }
-      // the loads still in flight fetch nothing that is used; they must land before their
-      // registers serve anything else
+      // (every load has landed before its registers serve anything else)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
       for (int u = 0; u < NS; ++u) hold_rows(w[u]);
@@ -286,88 +404,97 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
         u32x4 tail[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-          tail[r] = *reinterpret_cast<const u32x4*>(bp + (size_t)min(k0 + 8 * h + r, k - 1) * n);
+          tail[r] = __builtin_bit_cast(u32x4, (f16x8)*reinterpret_cast<const f16x8_any*>(bp + (size_t)min(k0 + 8 * h + r, k - 1) * n));
         step(full_steps, tail);
       }
     }
   }
-  // The k-parts' accumulators are added up through LDS (the panel is no longer needed), one
-  // part at a time: elements (rb, j, 4g .. 4g+3) of lane l of tile w are the four floats at index
-  // ((((w*RB + rb)*8 + j)*4 + g)*64 + l)*4, so both sides move 16 bytes per access.  The last
-  // part is not added into the accumulators (which live in the accumulation registers: reading,
-  // adding and writing them back costs three instructions per element) but on the way out, when
-  // they are read for the stores anyway.
-  f32x4* sums = reinterpret_cast<f32x4*>(lds_raw) + tile_w * (RB * 32 * 64) + lane;
-  auto put_sums = [&]() {
+  // Register t of lane (c, h) in accumulator j is row 8*(t/4) + 4h + t%4, column `col` + j.  Wave `kpart`
+  // of a tile finishes the quarters G * kpart .. of t; the others hand it theirs through LDS (the panel
+  // is no longer needed), sixteen bytes per access.
+  constexpr int G = 4 / KP;
+  f32x4* sums = reinterpret_cast<f32x4*>(lds_raw) + (size_t)tile_w * (KP * (KP - 1) * 8 * G * 64) + lane;
+  float row_bias[G * 4];                                 // (zeros without bias: no sum is -0)
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+  for (int t = 0; t < G * 4; ++t) {
+    const int row = i0 + 8 * (G * kpart + t / 4) + 4 * h + t % 4;
+    row_bias[t] = bias && row < m ? (float)bias[row] : 0.f;
+  }
+  auto hand_over = [&](auto part) __attribute__((always_inline)) {
+    constexpr int P = decltype(part)::value;
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          sums[((rb * 8 + j) * 4 + g) * 64] =
-              f32x4{acc[rb][j][4 * g], acc[rb][j][4 * g + 1], acc[rb][j][4 * g + 2], acc[rb][j][4 * g + 3]};
-  };
-  for (int q = 1; q + 1 < KP; ++q) {
-    __syncthreads();
-    if (kpart == q) put_sums();
-    __syncthreads();
-    if (kpart == 0) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+    for (int d = 0; d < KP; ++d)
+      if (d != P) {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 v = sums[((rb * 8 + j) * 4 + g) * 64];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[rb][j][4 * g + t] += v[t];
+          for (int g = 0; g < G; ++g) {
+            const int t = 4 * (G * d + g);
+            sums[(((d * (KP - 1) + (P < d ? P : P - 1)) * 8 + j) * G + g) * 64] =
+                f32x4{acc[j][t], acc[j][t + 1], acc[j][t + 2], acc[j][t + 3]};
           }
-    }
-  }
-  __syncthreads();
-  if constexpr (KP > 1) {
-    if (kpart == KP - 1) put_sums();
-    __syncthreads();
-  }
-  if (!active || kpart != 0) return;
-
-  // which rows could not be expanded, as a mask in scalar registers
-  const unsigned long long bad_mask = __builtin_amdgcn_ballot_w64(lane < PR && bad[lane & (PR - 1)] != 0);
-
-  // Register t of lane (c, h) in accumulator (rb, j) is row 32*rb + 8*(t/4) + 4h + t%4, column
-  // n0 + 8c + j.
+      }
+  };
+  unsigned bad_mask = 0;                                 // which rows could not be expanded
+  auto finish = [&](auto part) __attribute__((always_inline)) {
+    constexpr int P = decltype(part)::value;
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+    for (int g = 0; g < G; ++g) {
+      f32x4 total[8];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      f32x4 last[8];
+      for (int j = 0; j < 8; ++j) {
+        const int t = 4 * (G * P + g);
+        total[j] = f32x4{acc[j][t], acc[j][t + 1], acc[j][t + 2], acc[j][t + 3]};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) last[j] = KP > 1 ? sums[((rb * 8 + j) * 4 + g) * 64] : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int o = 0; o < KP - 1; ++o) total[j] += sums[(((P * (KP - 1) + o) * 8 + j) * G + g) * 64];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) total[j][tt] += row_bias[4 * g + tt];
+      if (relu) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int tt = 0; tt < 4; ++tt) total[j][tt] = fmaxf(total[j][tt], 0.f);
+      }
+      const int rr = 8 * (G * P + g) + 4 * h;
+      _Float16* out = C + (size_t)(i0 + rr) * n + col;
 #pragma unroll
       for (int tt = 0; tt < 4; ++tt) {
-        const int rr = 32 * rb + 8 * g + 4 * h + tt;
-        const int row = i0 + rr;
-        if (row < m && col_ok && !((bad_mask >> rr) & 1)) {
-          float v[8];
+        float v[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = acc[rb][j][4 * g + tt] + last[j][tt];
-          spmm_epilogue<_Float16, 8>(v, bias, row, relu);
-          Pack<_Float16, 8>::store(C + (size_t)row * n + col, v);
-        }
+        for (int j = 0; j < 8; ++j) v[j] = total[j][tt];
+        if (col_ok && i0 + rr + tt < m && !((bad_mask >> (rr + tt)) & 1)) Pack<_Float16, 8>::store(out, v);
+        out += n;
       }
     }
+  };
+  __syncthreads();
+  if (active) {
+    if (kpart == 0) hand_over(std::integral_constant<int, 0>{});
+    else if (kpart == 1) hand_over(std::integral_constant<int, 1>{});
+    else if (KP > 2 && kpart == 2) hand_over(std::integral_constant<int, KP - 2>{});
+    else hand_over(std::integral_constant<int, KP - 1>{});
+  }
+  __syncthreads();
+  if (!active) return;
+  bad_mask = (unsigned)__builtin_amdgcn_ballot_w64(lane < 32 && bad[lane & 31] != 0);
+  if (kpart == 0) finish(std::integral_constant<int, 0>{});
+  else if (kpart == 1) finish(std::integral_constant<int, 1>{});
+  else if (KP > 2 && kpart == 2) finish(std::integral_constant<int, KP - 2>{});
+  else finish(std::integral_constant<int, KP - 1>{});
+  if (kpart != 0) return;
   // rows that could not be expanded: direct gathers, four columns per lane
-  for (unsigned long long left = bad_mask; left != 0; left &= left - 1) {
-    const int rr = __builtin_ctzll(left);
-    const int row = i0 + rr;
-    const int col4 = n0 + 4 * lane;
-    const bool ok = col4 < n;
+  for (unsigned left = bad_mask; left != 0; left &= left - 1) {
+    const int row = i0 + __builtin_ctz(left);
+    const bool ok = n0 + 4 * lane < n;
+    const int col4 = ok ? piece_start(n0 + 4 * lane, n, 4) : 0;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     for (int p = row_offsets[row]; p < row_offsets[row + 1]; ++p) {
       const float a = (float)values[p];
       float b[4];
-      Pack<_Float16, 4>::load(B + (size_t)(int)column_indices[p] * n + (ok ? col4 : 0), b);
+      Pack<_Float16, 4>::load(B + (size_t)(int)column_indices[p] * n + col4, b);
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(a, b[j], v[j]);
     }

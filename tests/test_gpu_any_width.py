@@ -159,6 +159,36 @@ def test_sddmm_f16_any_width(g, oracle_lib, n):
     g.assert_close(got, ref, S, g.TOL_F16, f"sddmm f16 {chosen} n={n}")
 
 
+@pytest.mark.parametrize("m,k,density", [(300, 500, 0.1), (33, 16, 0.6), (65, 1024, 0.3), (4100, 250, 0.05), (70, 1040, 0.5)])
+@pytest.mark.parametrize("n", [8, 9, 15, 34, 255, 257, 263, 519, 1001])
+def test_spmm_matrix_core_kernel_any_width(g, oracle_lib, m, k, density, n):
+    """One and two tiles per workgroup, panels filled at once and by chunks of 1024 columns, rows that end
+    inside a lane's eight columns; empty rows, long rows, rows that are not ascending."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(0, v): v for v in range(16) if spdl.spdl_variant_name(0, v)}
+    for A in (wl.uniform_mask_csr(m, k, density, 7550 + n), wl.adversarial_csr(m, k, 7551 + n, sorted_cols=False),
+              wl.adversarial_csr(m, k, 7552 + n)):
+        A.values = A.values.astype(np.float16)
+        B, bias = wl.dense(k, n, 7553 + n, np.float16), wl.dense(1, m, 7554 + n, np.float16)[0]
+        C, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
+        ref, S = np.maximum(C.astype(np.float64) + bias.astype(np.float64)[:, None], 0), S + np.abs(bias.astype(np.float64))[:, None]
+        d = g.DevCsr(A)
+        for shift in (0, 1):
+            _, dB, _ = framed(B, shift)
+            cbuf, dC, at = framed(np.full((m, n), np.nan, np.float16), shift, 777.0)
+            try:
+                spdl.spdl_force_variant(0, ids["mfma"])
+                assert spdl.spdl_variant_name(0, spdl.spdl_select_spmm(m, k, n, A.nnz, 2, dB, dC)["variant"]) == "mfma"
+                spdl.spdl_spmm_bias_relu_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, None, dB, torch.from_numpy(bias).cuda(), 1, dC)
+                torch.cuda.synchronize()
+            finally:
+                spdl.spdl_force_variant(0, -1)
+            got = dC.cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - ref) <= g.TOL_F16 * S + 2e-3 * np.abs(ref) + 1e-6), (m, k, n, shift)
+            assert frame_intact(cbuf, at, m * n)
+
+
 @pytest.mark.parametrize("m,k", [(300, 500), (65, 63), (2600, 320)])
 @pytest.mark.parametrize("n", [8, 9, 15, 16, 17, 119, 120, 122, 127, 128, 129, 137, 514, 1001])
 def test_sddmm_matrix_core_kernel_any_width(g, oracle_lib, m, k, n):
