@@ -325,13 +325,13 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
                                                                               : 2.0;
     // (Dense matrices gain so much from the slab kernel that it pays with most compute units idle:
     // 6144 x 2048 at 35 %, n = 64, 96 workgroups: 36 us against 54 for row-splitting; 4096 x 4096 at
-    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  From 9 % on
-    // 80 tiles are enough where the output is wider than one: 2592 x 4240 at 15 %, n = 120, 82 tiles: 42 us
-    // against 50; 746 x 2984 at 12 %, n = 531, 108 tiles: 29 against 38; 977 x 3908 at 12 %, n = 268, 80
-    // tiles: level.  One tile wide, 97: 6900 x 2366 at 14 %, n = 40: 26 us against 34.  Not square matrices.)
+    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  97 tiles are
+    // enough from 9 % on (6900 x 2366 at 14 %, n = 40: 26 us against 34; 746 x 2984 at 12 %, n = 531, 108 tiles:
+    // 29 against 38), 80 from 13 % on if the output is wider than one (2592 x 4240 at 15 %, n = 120, 82 tiles: 42 us
+    // against 50; 2636 x 6177 at 11 %, n = 80, 84 tiles: 51 against 46).  Not square matrices.)
     const int64_t min_tiles = (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
                               : (n > 32 && n <= 2 * kSlabTile && reuse >= 16.0) ? 3 * kComputeUnits / 8
-                              : (m != k && n > kSlabTile && reuse >= 5.5)       ? 5 * kComputeUnits / 16
+                              : (m != k && n > kSlabTile && reuse >= 8.0)       ? 5 * kComputeUnits / 16
                               : (m != k && n > 32 && reuse >= 5.5)              ? 3 * kComputeUnits / 8 + 1
                                                                                  : kComputeUnits / 2;
     variant = (sizeof(T) == 4 && slab_dma_usable(n, nnz) && reuse >= min_reuse && out_tiles >= min_tiles)
@@ -350,14 +350,14 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // row lengths (log-normal, a few rows of thousands of entries among rows of hundreds) are no
     // reason to hold back: 4096 x 4096 at 6 %, n = 64: 27 us against 40 for row-splitting, n = 128:
     // 46 against 82.  A second tile that is not full costs it as much as a full one: 6404 x 5399 at 2 %,
-    // n = 72: 27 us against 23 for row-splitting, 2924 x 3724 at 6 %, n = 123: 28 against 24; at n = 126
-    // it is level again.  Where the slab kernel
+    // n = 72: 27 us against 23 for row-splitting, 2924 x 3724 at 6 %, n = 123: 28 against 24; from n = 124 on,
+    // and with rows of 450 entries or more, it is level again (2636 x 6177 at 11 %, n = 80: 46 against 49).  Where the slab kernel
     // applies it stays the choice from the shape alone: on uniform masks it is up to 1.9 times faster
     // than the window kernel (16384 x 4096 at 10 %), on banded ones 2.2 .. 2.6 times slower, and only
     // the caller knows which it is (spdl_spmm_banded).
     if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_dma_usable(n, nnz) &&
         (int64_t)k * n < ((int64_t)1 << 29) &&
-        n > 32 && n <= 2 * kWinTile && (n <= kWinTile || n >= 2 * kWinTile - 4) &&
+        n > 32 && n <= 2 * kWinTile && (n <= kWinTile || n >= 2 * kWinTile - 4 || (double)nnz >= 450.0 * (double)m) &&
         ((m >= 4096 && (double)nnz >= 100.0 * (double)m) ||
          (m >= 2048 && (double)nnz >= (n > kWinTile ? 192.0 : 400.0) * (double)m)))
       variant = kSpmmWindow;
