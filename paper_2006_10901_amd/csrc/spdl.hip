@@ -374,8 +374,9 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // the caller says that the entries form a band, or that the row lengths are strongly unequal: the
     // window kernel gathers what is not in a band and shares long rows among the waves of a workgroup
     // (a problem the window kernel cannot take keeps the choice made above)
+    // (a band and at most 32 columns, half of the window kernel's lanes: gathers, 14.8 us against 18.0 for 4096 rows of 410)
     if (hint != kHintNone && sizeof(T) == 4 && nnz > 0 && slab_usable<T>(n, nnz, B, C) && (int64_t)k * n < ((int64_t)1 << 29))
-      variant = kSpmmWindow;
+      variant = hint == kHintBanded && n <= 32 ? kSpmmRowsplit : kSpmmWindow;
     // (unequal rows, more than two tiles and a B of fewer than 4000 rows, whose share per tile the
     // gathers find in L2: row-splitting, 1.2 .. 2.4 times faster there than the window kernel, while the
     // slab kernels wait for their longest row)
@@ -733,9 +734,17 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     variant = kSddmmGroup;
   const bool window_ok = sizeof(T) == 4 && vec_ok && aligned(L, 16) && aligned(R, 16) && n <= 2 * kWinTile && nnz > 0 &&
                          (int64_t)k * n < ((int64_t)1 << 29);
-  // the caller says that the entries form a band (a problem the window kernel cannot take keeps the
-  // choice made above)
-  if (free_choice && hint == kHintBanded && window_ok) variant = kSddmmWindow;
+  // The caller says that the entries form a band (a problem the window kernel cannot take keeps the
+  // choice made above).  Two of the window kernel's workgroups, 16 rows, are at work on a compute unit: its
+  // time goes in steps of 4096 rows, and below 2048 it is one workgroup's, while the nonzero-split kernel's goes with the
+  // entries and is the shorter one unless the steps come out nearly even (64 columns, 4096 rows of 410: 21 us
+  // against 25; 2994 of 425: 21.5 against 20.3; 1374 of 360: 12.2 against 10.3).  Beyond 64 columns a window fills the
+  // LDS of a compute unit and is no gain (4096 rows of 492, 96 columns: 45 us against 46; 2000 of 340: 22.7
+  // against 20.4; 1129 of 341, 128 columns: 23.3 against 12.8).
+  if (free_choice && hint == kHintBanded && window_ok) {
+    const int64_t stepped = (m + 2047) / 2048 * (int64_t)2048;
+    variant = n <= kWinTile && 5 * stepped <= 6 * (int64_t)m ? kSddmmWindow : kSddmmGroup;
+  }
   // the caller says that the row lengths are strongly unequal: the nonzero-split kernel, which does not
   // care, or for dot products of more than 128 columns the lane kernel in passes where the estimate
   // above gives it less than 0.45 of that kernel's time (dense matrices; the slab kernel, whose
