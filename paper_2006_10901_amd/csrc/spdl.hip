@@ -138,15 +138,14 @@ int slab_rows_per_group(int m, int n) {
   return tiles128 >= 2 * kComputeUnits ? 2 : 1;
 }
 
-// Workgroups of 8 waves (panels of 32 rows, slabs of 128 rows of B, two workgroups per CU) for the
-// copy-based kernel when panels of 64 rows would leave half of the compute units or more without a
-// workgroup.  With 130 tiles of 64 x 64 and more the full form is faster although some compute units
+// Workgroups of 8 waves (panels of 32 rows) for the copy-based kernel when panels of 64 rows would leave half
+// of the compute units or more without a workgroup: one workgroup per CU, as with panels of 64 rows.
+// (With slabs of 128 rows of B, so that two would share a CU, the scan, the waits and the barrier come twice as
+// often: 8192 x 5000 at 5 %, n = 64: 36.7 us against 26.7; 3976 x 4475 at 19 %, n = 76: 53.5 against 45.6.)  With
+// 130 tiles of 64 x 64 and more the full form is faster although some compute units
 // stay idle, because every slab of B is copied for 64 rows instead of 32 (130 tiles, 4104 x 5093 at
 // 11 %, n = 112: 61 us in halves, 50 whole; 188 tiles, 12000 x 4000, n = 64: 51 and 39; 240 tiles,
-// 7640 x 4322 at 5 %, n = 104: 48 and 30); at 128 and fewer the halves are (128 tiles: 83 us and 90;
-// 82 tiles, 2592 x 4240 at 15 %, n = 120: 42 and 51).
-constexpr int kSlabHalfS = 128;
-constexpr int kSlabHalfLdsBytes = 2 * (kSlabHalfS + 1) * kSlabTile * 4;
+// 7640 x 4322 at 5 %, n = 104: 48 and 30).
 
 // The tile-inner slab kernel looks 48 pairs ahead per row: usable where the mean count of a row's
 // pairs in one slab plus three standard deviations fits into that (a row with more takes extra
@@ -164,7 +163,7 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   const int rpg = (variant == kSpmmSlabDma && !half) ? slab_rows_per_group(m, n) : 1;
   const int rows = (half ? kSlabRows / 2 : kSlabRows) * rpg;
   const int panels = (m + rows - 1) / rows;
-  int tpw = slab_tiles_per_wg(panels, tiles, half ? 2 * kComputeUnits : kComputeUnits);
+  int tpw = slab_tiles_per_wg(panels, tiles);
   // wide outputs, two rows per group: the tile-inner kernel, at most kSlabTilesMax tiles per workgroup
   if (rpg == 2 && tpw >= 2 && slab_tiles_fits(m, k, nnz)) tpw = std::min(tpw, kSlabTilesMax);
   const int groups = (tiles + tpw - 1) / tpw;
@@ -311,13 +310,18 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // hyperbola in the number of tiles.  n = 80 and 128, 2048 .. 9000 columns: 64 * density = 3.1 at 138
     // tiles, 2.5 at 170, 2.0 at 200, 1.7 at 250 (8000 x 5000 at 6 %, n = 128: 34 us against 52); n = 40 and
     // 64 some 15 % later (15800 x 5000 at 5 %, n = 64: 33 us against 47).)
-    const double one_round_reuse = (m != k && 2 * out_tiles > kComputeUnits && out_tiles <= kComputeUnits)
-                                       ? (n <= kSlabTile ? 500.0 : 430.0) / (double)out_tiles : 5.0;
+    // (At most half full: workgroups of half the rows, the same hyperbola.  On 110 random shapes of 50 .. 260
+    // tiles the two meet at 64 * density * tiles = 440 .. 480, below 72 tiles at 600: 779 x 3116 at 9 %, n = 392,
+    // 91 tiles: 22.8 us for both; 780 x 3120 at 6 %, n = 576, 117 tiles: 21 against 25; 598 x 2392 at 19 %, n = 296, 50
+    // tiles: 27 against 33.)
+    const double one_round_reuse = m == k || out_tiles > kComputeUnits        ? 5.0
+                                   : 2 * out_tiles <= kComputeUnits           ? (out_tiles < 72 ? 600.0 : 460.0) / (double)std::max<int64_t>(out_tiles, 1)
+                                                                              : (n <= kSlabTile ? 500.0 : 430.0) / (double)out_tiles;
     // (fewer than 16 columns use a quarter of a tile's lanes or less: 9957 x 8063 at 28 %, n = 8: 182 us
     // against 135 for row-splitting)
     const double min_reuse = n < 16                                           ? 1.0e9
                              : n <= 32                                        ? 12.0
-                             : n <= 64                                        ? std::min(narrow_reuse, one_round_reuse)
+                             : n <= 64                                        ? (2 * out_tiles < kComputeUnits ? one_round_reuse : std::min(narrow_reuse, one_round_reuse))
                              : out_tiles < kComputeUnits                      ? one_round_reuse
                              : (n <= 4 * kSlabTile && k < 8192) || k < 4000   ? 3.0
                              : n >= 16 * kSlabTile                            ? 1.3
@@ -325,14 +329,14 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
                                                                               : 2.0;
     // (Dense matrices gain so much from the slab kernel that it pays with most compute units idle:
     // 6144 x 2048 at 35 %, n = 64, 96 workgroups: 36 us against 54 for row-splitting; 4096 x 4096 at
-    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  97 tiles are
-    // enough from 9 % on (6900 x 2366 at 14 %, n = 40: 26 us against 34; 746 x 2984 at 12 %, n = 531, 108 tiles:
-    // 29 against 38), 80 from 13 % on if the output is wider than one (2592 x 4240 at 15 %, n = 120, 82 tiles: 42 us
-    // against 50; 2636 x 6177 at 11 %, n = 80, 84 tiles: 51 against 46).  Not square matrices.)
+    // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  48 tiles
+    // are enough at the densities above if the output is wider than one, 64 if B has more than 2048 rows (6064 x 3050
+    // at 18 %, n = 42, 95 tiles: 31 us against 40; up to there the gathers find B in L2), else 97.  Not square matrices.)
     const int64_t min_tiles = (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
                               : (n > 32 && n <= 2 * kSlabTile && reuse >= 16.0) ? 3 * kComputeUnits / 8
-                              : (m != k && n > kSlabTile && reuse >= 8.0)       ? 5 * kComputeUnits / 16
-                              : (m != k && n > 32 && reuse >= 5.5)              ? 3 * kComputeUnits / 8 + 1
+                              : (m != k && n > kSlabTile)                       ? 3 * kComputeUnits / 16
+                              : (m != k && n > 32 && k > 2048)                  ? kComputeUnits / 4
+                              : (m != k && n > 32)                              ? 3 * kComputeUnits / 8 + 1
                                                                                  : kComputeUnits / 2;
     variant = (sizeof(T) == 4 && slab_dma_usable(n, nnz) && reuse >= min_reuse && out_tiles >= min_tiles)
                   ? kSpmmSlabDma : kSpmmRowsplit;
@@ -496,10 +500,9 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       // on the 70-90 % sparse shapes: the longer scan per round costs more than the waits it saves.
       const bool half = li.block_threads != kSlabThreads;
       const bool two_rows = li.rows_per_block == 2 * kSlabRows;
-      const void* dma_kernel_c = half       ? (const void*)spmm_slab_dma_kernel<kSlabHalfS, 1, 2, 8>
+      const void* dma_kernel_c = half       ? (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2, 8>
                                : two_rows ? (const void*)spmm_slab_dma_kernel<kSlabS, 2, 2>
                                           : (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2>;
-      const int lds = half ? kSlabHalfLdsBytes : kSlabLdsBytes;
       const void* dma_kernel = dma_kernel_c;
       // (two rows per group and 2 .. kSlabTilesMax tiles per workgroup: scanned once per slab for all tiles)
       if (li.variant == kSpmmSlabDma && two_rows && li.grid_y >= 2 && li.grid_y <= kSlabTilesMax &&
@@ -507,13 +510,10 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         dma_kernel = (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>;
       if (!configured.load()) {
         for (const void* f : {(const void*)kernel, (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2>,
-                              (const void*)spmm_slab_dma_kernel<kSlabS, 2, 2>,
+                              (const void*)spmm_slab_dma_kernel<kSlabS, 2, 2>, (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2, 8>,
                               (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>})
           if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes) != hipSuccess)
             return SPDL_ERR_LAUNCH;
-        if (hipFuncSetAttribute((const void*)spmm_slab_dma_kernel<kSlabHalfS, 1, 2, 8>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSlabHalfLdsBytes) != hipSuccess)
-          return SPDL_ERR_LAUNCH;
         configured.store(true);
       }
       const int panels = (m + li.rows_per_block - 1) / li.rows_per_block;
@@ -526,7 +526,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         int tpw = li.grid_y;
         void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, &tpw, (void*)&panels, &ro, &ci, &val, &order, &B, &C,
                         &bias, &relu};
-        if (hipLaunchKernel(dma_kernel, grid, block, args, lds, st) != hipSuccess) return SPDL_ERR_LAUNCH;
+        if (hipLaunchKernel(dma_kernel, grid, block, args, kSlabLdsBytes, st) != hipSuccess) return SPDL_ERR_LAUNCH;
       }
     } else {
       return SPDL_ERR_UNSUPPORTED;

@@ -23,9 +23,8 @@ namespace spdl {
 // enough tiles to fill the machine anyway.
 // NCH = chunks of 16 pairs fetched ahead per row (chosen by the host from the density so that
 // a row's pairs inside one slab usually fit).
-// NW = waves per workgroup: 16 (one workgroup per CU), or 8 with slabs half as large, so that two
-// workgroups share a CU: panels of 32*RPG rows, for outputs with fewer than 256 tiles of 64 x 64,
-// which would otherwise leave compute units without a workgroup.
+// NW = waves per workgroup: 16, or 8 (panels of 32*RPG rows) for outputs with 128 tiles of 64 x 64 or
+// fewer, which would otherwise leave compute units without a workgroup.  One workgroup per CU.
 template <int S, int RPG, int NCH, int NW = 16>
 __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
     int m, int k, int n, int nnz, int tiles_n, int tiles_per_wg, int panels,
