@@ -672,9 +672,16 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       const int64_t panels64 = (m + kSdRows - 1) / kSdRows;
       const int64_t rounds64 = (panels64 + kComputeUnits - 1) / kComputeUnits;
       const bool whole_rounds = m != k && rounds64 > 0 && (double)panels64 >= 0.95 * (double)(rounds64 * kComputeUnits);
+      // (2048 rows and more, not square: from 4.2 on at any number of panels; 4128 x 4212 at 8 %, n = 56: 21.8 us
+      // against 23.3 for gathers and 27.1 for the window kernel; 7500 x 4019 at 11 %, n = 48: 33.5 against 40.4)
       const bool slab = fp32_fast && reuse >= 2.0 &&
-                        (n >= 128 || reuse >= 8.0 || (reuse >= 5.0 && m >= 8192) || (reuse >= 4.0 && whole_rounds));
-      variant = lane ? kSddmmLane : slab ? kSddmmSlabDma : kSddmmGroup;
+                        (n >= 128 || reuse >= 8.0 || (reuse >= 5.0 && m >= 8192) || (reuse >= 4.0 && whole_rounds) ||
+                         (reuse >= 4.2 && m >= 2048 && m != k && n > 16));
+      // (Few entries: the nonzero-split kernel is done before the others have filled their first slabs.  850 x 434
+      // at 25 %, n = 40, 93 thousand: 5.4 us against 10.3; 2792 x 2079 at 2 %, n = 96, 120 thousand: 9.1 against
+      // 10.6; 2124 x 2983 at 4 %, n = 72, 230 thousand: 11.9 against 11.3; 2328 x 1585 at 7 %, n = 43, 270 thousand: 9.4 against
+      // 11.4.)
+      variant = nnz < (n <= 64 ? 300000 : 170000) ? kSddmmGroup : lane ? kSddmmLane : slab ? kSddmmSlabDma : kSddmmGroup;
       // The shape of an attention head (33..64 columns, thousands of rows of a few hundred entries,
       // at most 1/8 dense; paper Sec. "Application: Sparse Transformer"): the window kernel, which is
       // the nonzero-split kernel with the rows of R around a band taken from LDS and the four lane
