@@ -84,7 +84,29 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   // (Rows of B at any alignment: 16 bytes per lane all the same, the lane at the row's end taking the
   // row's last ones.  Not for small problems, where more lanes per row count for more: 512 x 512
   // at 10 %, n = 127: 5.1 us against 6.3.)
-  if (vec < kWide && n >= kWide && (int64_t)nnz * n >= (1 << 24)) vec = kWide;
+  if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2))) vec = kWide;
+  // fp32, few waves: narrower loads, so that a wave has a row to itself (its indices are then scalar loads) and
+  // the row is spread over more waves.  Below 1280 waves (five per compute unit) to a wave per row, two rows per wave
+  // being no gain (3000 x 3000 at 1 %, n = 64: 4.3 us with four rows per wave, 5.2 with two, 4.0 with one), and on
+  // where that pads n less (600 x 2400 at 6 %, n = 300: 13.4 us, 10.4); below 1024 in any case (512 x 512 at
+  // 10 %, n = 128: 5.1 us with 4 columns per lane, two rows per wave; 4.5 with 2, one row; 3.8 with 1, half a row).
+  // (760 x 3000 at 5 %, n = 276, 1520 waves: 14.5 us as it is, 16.5 narrower.)
+  // Widths under 256, where rows share a wave, with short rows only, and not too many: the more nonzeros, the more
+  // the number of load instructions counts, which narrow pieces multiply (n = 128, rows of 150, m = 1000: 6.2 us
+  // as it is, 6.9 narrower; n = 32, rows of 100, m = 2000: 5.1 and 6.3; rows of 40, m = 4000: 4.75 and 4.57,
+  // m = 8000: 5.75 and 6.7).
+  if (sizeof(T) == 4 && vec == kWide && (n >= 256 || (nnz < 3 << 16 && nnz <= 64 * (int64_t)m))) {
+    auto waves = [&](int v) {
+      const int g = pick_group(n, v);
+      return (int64_t)m * g * pick_segments<T>(m, nnz, v, g) / kWave * ((n + g * v - 1) / (g * v));
+    };
+    auto padded = [&](int v) { return (n + pick_group(n, v) * v - 1) / (pick_group(n, v) * v) * (pick_group(n, v) * v); };
+    if (waves(vec) < 5 * kComputeUnits && waves(1) > waves(vec))
+      while (vec > 1 && pick_group(n, vec) < kWave) vec /= 2;
+    while (vec > 1 && waves(vec / 2) > waves(vec) &&
+           waves(vec) < (padded(vec / 2) < padded(vec) ? 5 * kComputeUnits : 4 * kComputeUnits))
+      vec /= 2;
+  }
   const int g = pick_group(n, vec);
   const int seg = pick_segments<T>(m, nnz, vec, g);
   info->variant = kSpmmRowsplit;

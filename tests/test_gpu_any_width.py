@@ -106,6 +106,34 @@ def test_spmm_row_splitting_with_wide_loads_at_any_width(g, oracle_lib, n, dtype
     assert frame_intact(cbuf, at, m * n)
 
 
+@pytest.mark.parametrize("n", [1, 8, 16, 20, 64, 100, 128, 200, 256, 300, 515])
+@pytest.mark.parametrize("longer", [0, 16, 140])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_spmm_row_splitting_remainders_of_rows(g, oracle_lib, n, longer, dtype):
+    """Rows of every length from empty over whole batches of 8 and 16 to one past them, at the widths where the
+    number of columns per lane, of lanes per row and of lane groups sharing a row changes."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    m, k = 517, 400
+    lengths = np.arange(m) % 34 + longer
+    A = wl.row_lengths_csr(m, k, lengths, 7200 + n)
+    A.values = A.values.astype(dtype)
+    B = wl.dense(k, n, 7201 + n, dtype)
+    C, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    d = g.DevCsr(A)
+    _, dB, _ = framed(B, 0)
+    cbuf, dC, at = framed(np.full((m, n), np.nan, dtype), 0, 777.0)
+    spdl.spdl_force_variant(0, 0)
+    try:
+        fn = spdl.spdl_spmm_f16 if dtype == np.float16 else spdl.spdl_spmm
+        fn(m, k, n, A.nnz, d.ro, d.ci, d.val, None, dB, dC)
+        torch.cuda.synchronize()
+    finally:
+        spdl.spdl_force_variant(0, -1)
+    g.assert_close(dC.cpu().numpy(), C, S, g.TOL_F16 if dtype == np.float16 else g.TOL_F32, f"row splitting n={n}")
+    assert frame_intact(cbuf, at, m * n)
+
+
 def sddmm_any(g, oracle_lib, A, n, dtype, forced, shift, scaled=False, poke=None):
     import torch
     import paper_2006_10901_amd as spdl
