@@ -66,7 +66,9 @@ __device__ __forceinline__ float sddmm_plain_dot(int n, const T* l, const T* r) 
 // n >= 4.  With n % 4 != 0 the lane at the row's end takes the row's last four columns (piece_start)
 // and leaves out of its sum, with zeros for L, those that the lane before it has; an Inf there would
 // still make the result NaN, so a NaN is looked at again.
-template <typename T>
+// P: pieces of 64 columns whose gathers are all in flight at once.  Two cost 64 registers more and take
+// a memory latency off every strip of more than 64 columns: for launches that leave the SIMDs nearly empty.
+template <typename T, int P = 1>
 __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int l16, int roff,
                                                       const T* __restrict__ Lrow, const T* __restrict__ R,
                                                       T* __restrict__ out, const T* __restrict__ scale = nullptr) {
@@ -74,29 +76,35 @@ __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int
   float partial[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) partial[t] = 0.f;
-  for (int col0 = 0; col0 < n; col0 += 64) {
-    const int col = col0 + 4 * l16;
-    const bool ok = col < n;
-    const int colc = ok ? piece_start(col, n, 4) : 0;
-    const int lane_off = colc;
-    // All sixteen gathers are issued before the first multiply-add (the scheduling barrier keeps
+  for (int col0 = 0; col0 < n; col0 += 64 * P) {
+    // All gathers are issued before the first multiply-add (the scheduling barrier keeps
     // the compiler from interleaving them with the arithmetic, which it otherwise does whenever
     // the surrounding control flow changes, leaving two loads in flight instead of sixteen).
-    float r[16][4];
+    float r[P][16][4];
+    float l[P][4];
+#pragma unroll
+    for (int h = 0; h < P; ++h) {
+      const int col = col0 + 64 * h + 4 * l16;
+      const int lane_off = col < n ? piece_start(col, n, 4) : 0;
 #define SPDL_R1(T0) \
-    Pack<T, 4>::load(R + (__builtin_amdgcn_update_dpp(0, roff, 0x150 + (T0), 0xf, 0xf, false) + lane_off), r[T0]);
-    SPDL_R1(0) SPDL_R1(1) SPDL_R1(2) SPDL_R1(3) SPDL_R1(4) SPDL_R1(5) SPDL_R1(6) SPDL_R1(7)
-    SPDL_R1(8) SPDL_R1(9) SPDL_R1(10) SPDL_R1(11) SPDL_R1(12) SPDL_R1(13) SPDL_R1(14) SPDL_R1(15)
+    Pack<T, 4>::load(R + (__builtin_amdgcn_update_dpp(0, roff, 0x150 + (T0), 0xf, 0xf, false) + lane_off), r[h][T0]);
+      SPDL_R1(0) SPDL_R1(1) SPDL_R1(2) SPDL_R1(3) SPDL_R1(4) SPDL_R1(5) SPDL_R1(6) SPDL_R1(7)
+      SPDL_R1(8) SPDL_R1(9) SPDL_R1(10) SPDL_R1(11) SPDL_R1(12) SPDL_R1(13) SPDL_R1(14) SPDL_R1(15)
 #undef SPDL_R1
-    float l[4];
-    Pack<T, 4>::load(Lrow + colc, l);
+      Pack<T, 4>::load(Lrow + lane_off, l[h]);
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) l[v] = ok && colc + v >= col ? l[v] : 0.f;
+    for (int h = 0; h < P; ++h) {
+      const int col = col0 + 64 * h + 4 * l16;
+      const int colc = col < n ? piece_start(col, n, 4) : 0;
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+      for (int v = 0; v < 4; ++v) l[h][v] = col < n && colc + v >= col ? l[h][v] : 0.f;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) partial[t] = __builtin_fmaf(l[v], r[t][v], partial[t]);
+      for (int t = 0; t < 16; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) partial[t] = __builtin_fmaf(l[h][v], r[h][t][v], partial[t]);
+    }
   }
   float total = reduce16x16(partial, l16);
   if ((n & 3) != 0 && cidx < end && total != total) total = sddmm_plain_dot<T>(n, Lrow, R + roff);
@@ -120,7 +128,7 @@ __device__ __forceinline__ void sddmm_strip_direct(int n, int q, int end, int l1
 // independent, so rows shared by several waves need no reduction, and the load per wave is
 // the same whatever the row lengths are (the balance the paper gets for SpMM from the row
 // swizzle, Sec. "Row Swizzle Load Balancing", without needing a row order in the interface).
-template <typename T>
+template <typename T, int P = 1>
 __global__ __launch_bounds__(256) void sddmm_group_kernel(
     int m, int n, int nnz, int per_wave, const int* __restrict__ row_offsets,
     const int* __restrict__ column_indices, const T* __restrict__ L, const T* __restrict__ R,
@@ -183,7 +191,7 @@ __global__ __launch_bounds__(256) void sddmm_group_kernel(
     int my_off = 0;
     if (my_q < my_end) my_off = sddmm_strip_offset(n, my_q, my_end, l16, column_indices);
     if (have && cur_q < cur_end)
-      sddmm_strip_direct_at<T>(n, cur_q, cur_end, l16, cur_off, L + (size_t)cur_row * n, R, out, scale);
+      sddmm_strip_direct_at<T, P>(n, cur_q, cur_end, l16, cur_off, L + (size_t)cur_row * n, R, out, scale);
     if (!next) break;
     cur_row = my_row; cur_q = my_q; cur_end = my_end; cur_off = my_off;
     have = true;

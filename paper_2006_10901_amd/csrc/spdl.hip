@@ -963,7 +963,11 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     }
   }
   if (li.lanes_per_row == 16 && (li.variant == kSddmmGroup || li.variant == kSddmmRowstrip)) {
-    sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
+    // (two waves or fewer on each SIMD: registers for both halves of 128 columns)
+    if (n > 64 && (int64_t)grid.x * 4 <= 8 * kComputeUnits)
+      sddmm_group_kernel<T, 2><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
+    else
+      sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
     return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
   }
   switch (li.vec) {
