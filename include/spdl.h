@@ -24,12 +24,14 @@
  *   Non-finite inputs.  With finite inputs every result is the definition's.  An Inf or NaN in
  *   a row of a dense operand reaches the outputs that the definition makes depend on that row
  *   in every kernel; all SDDMM kernels, the fp32 SpMM kernels and the direct fp16 SpMM kernel
- *   keep it away from every other output.  The fp16 matrix-core SpMM (chosen when at least one
- *   position in 32 of A is stored, n % 8 == 0, 16-byte aligned operands) multiplies the zeros of
- *   its expanded sparse panels by whole rows of B: there a non-finite B[k, j] turns C[i, j] into
- *   NaN for every row i (other columns of C are not affected).  Callers whose fp16 activations
- *   can overflow select the direct kernel with spdl_force_variant(0, 0), which follows the
- *   definition exactly.
+ *   keep it away from every other output.  The fp16 matrix-core SpMM multiplies the zeros of its
+ *   expanded sparse panels by whole rows of B.  Where n % 8 != 0, B or C is not 16-byte aligned or
+ *   fewer than one position in 32 of A is stored, it computes again what came out as NaN, and so
+ *   keeps it away as well (rows met by a non-finite value then cost gathers).  Elsewhere a
+ *   non-finite B[k, j] turns the sum behind C[i, j] into NaN for every row i (other columns of C are
+ *   not affected).  Callers whose fp16 activations can overflow select the direct kernel with
+ *   spdl_force_variant(0, 0), which follows the definition exactly.  The ReLU of the fused
+ *   epilogue turns NaN into 0.
  */
 #ifndef SPDL_H_
 #define SPDL_H_

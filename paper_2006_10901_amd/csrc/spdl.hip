@@ -239,6 +239,11 @@ inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
                           8.1e-3 * row * (double)((n + 511) / 512);
   return t_mfma <= t_direct;
 }
+// Whether the matrix-core SpMM keeps an Inf or NaN of B to the rows that store its column (spdl.h states which
+// calls do not: whole 16-byte pieces, one position in 32 stored).
+inline bool spmm_mfma_contains(int m, int k, int n, int nnz, const void* B, const void* C) {
+  return n % 8 != 0 || !aligned(B, 16) || !aligned(C, 16) || 32 * (int64_t)nnz < (int64_t)m * k;
+}
 inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
   const double blocks = (double)((m + 63) / 64) * (double)((k + 63) / 64);
   const double t_mfma = 1.0 + std::ceil(blocks / kComputeUnits) *
@@ -489,13 +494,15 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       const auto kernel = one ? (chunks ? spmm_mfma_kernel<1, 4, true, I> : spmm_mfma_kernel<1, 4, false, I>)
                               : (chunks ? spmm_mfma_kernel<2, 2, true, I> : spmm_mfma_kernel<2, 2, false, I>);
       const int lds = one ? spmm_mfma_lds_bytes(k, 1, 4) : spmm_mfma_lds_bytes(k, 2, 2);
+      const int contain = spmm_mfma_contains(m, k, n, nnz, B, C);
       if (!configured[2 * one + chunks].load()) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 spmm_mfma_lds_bytes(kMfmaChunk, 1, 4)) != hipSuccess)
           return SPDL_ERR_LAUNCH;
         configured[2 * one + chunks].store(true);
       }
-      kernel<<<dim3(li.grid_x), dim3(li.block_threads), lds, st>>>(m, k, n, li.grid_y, ro, ci, val, B, C, bias, relu);
+      kernel<<<dim3(li.grid_x), dim3(li.block_threads), lds, st>>>(m, k, n, li.grid_y, ro, ci, val, B, C, bias, relu,
+                                                                      contain);
     } else {
       return SPDL_ERR_UNSUPPORTED;
     }

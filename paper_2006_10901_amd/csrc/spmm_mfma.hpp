@@ -16,6 +16,11 @@
 //
 // Rows whose indices are not strictly ascending (duplicates included) cannot be expanded by
 // plain stores; they are found while the panel is filled and computed by direct gathers.
+//
+// A row of B meets zeros of the panel in every sparse row that does not store its column, and 0 * Inf
+// is NaN.  With `contain` an output that came out as NaN is looked at again: its row is computed by direct gathers
+// for the tile's columns, so that an Inf or NaN of B reaches the rows that store its column and no other.
+// Two comparisons for four results on finite data, nothing else.
 // Any n from 8 on and any alignment (the lane at a row's end takes the row's last eight columns), k >= 16.
 // The row order is not used: dense work is the same for every row.
 //
@@ -54,7 +59,7 @@ template <int WAVES, int KP, bool CHUNKS, typename I = int>
 __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     int m, int k, int n, int tiles_n, const int* __restrict__ row_offsets,
     const I* __restrict__ column_indices, const _Float16* __restrict__ values,
-    const _Float16* __restrict__ B, _Float16* __restrict__ C, const _Float16* __restrict__ bias, int relu) {
+    const _Float16* __restrict__ B, _Float16* __restrict__ C, const _Float16* __restrict__ bias, int relu, int contain) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int NW = WAVES * KP;
   constexpr int NS = kMfmaSets;
@@ -435,7 +440,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
           }
       }
   };
-  unsigned bad_mask = 0;                                 // which rows could not be expanded
+  unsigned bad_mask = 0;                                 // rows that are computed by gathers
+  unsigned nan_mask = 0;                                 // ... those of them in which this wave has met a NaN
   auto finish = [&](auto part) __attribute__((always_inline)) {
     constexpr int P = decltype(part)::value;
 #pragma unroll
@@ -447,6 +453,18 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
         total[j] = f32x4{acc[j][t], acc[j][t + 1], acc[j][t + 2], acc[j][t + 3]};
 #pragma unroll
         for (int o = 0; o < KP - 1; ++o) total[j] += sums[(((P * (KP - 1) + o) * 8 + j) * G + g) * 64];
+      }
+      if (contain) {                                     // (before the bias and a ReLU that would hide it)
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          bool nan = false;
+#pragma unroll
+          for (int j = 0; j < 8; j += 2) nan |= __builtin_isunordered(total[j][tt], total[j + 1][tt]);
+          const unsigned long long lanes = __builtin_amdgcn_ballot_w64(nan && col_ok);
+          const unsigned both = ((unsigned)lanes != 0 ? 1u : 0u) | ((unsigned)(lanes >> 32) != 0 ? 16u : 0u);   // h = 0, 1
+          nan_mask |= both << (8 * (G * P + g) + tt);
+        }
+        bad_mask |= nan_mask;
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -479,24 +497,37 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
   }
   __syncthreads();
   if (!active) return;
-  bad_mask = (unsigned)__builtin_amdgcn_ballot_w64(lane < 32 && bad[lane & 31] != 0);
+  const unsigned unexpanded = (unsigned)__builtin_amdgcn_ballot_w64(lane < 32 && bad[lane & 31] != 0);
+  bad_mask = unexpanded;
   if (kpart == 0) finish(std::integral_constant<int, 0>{});
   else if (kpart == 1) finish(std::integral_constant<int, 1>{});
   else if (KP > 2 && kpart == 2) finish(std::integral_constant<int, KP - 2>{});
   else finish(std::integral_constant<int, KP - 1>{});
-  if (kpart != 0) return;
-  // rows that could not be expanded: direct gathers, four columns per lane
-  for (unsigned left = bad_mask; left != 0; left &= left - 1) {
+  // Rows that could not be expanded, left to the first wave of the tile, and rows in which a NaN was met: direct
+  // gathers, four columns per lane.  Eight entries at a time; positions past the row's end fetch its last entry
+  // again and multiply nothing (0 * Inf).
+  unsigned left = (kpart == 0 ? unexpanded : 0u) | (nan_mask & ~unexpanded);
+  if (m - i0 < 32) left &= (1u << (m - i0)) - 1u;
+  for (; left != 0; left &= left - 1) {
     const int row = i0 + __builtin_ctz(left);
     const bool ok = n0 + 4 * lane < n;
     const int col4 = ok ? piece_start(n0 + 4 * lane, n, 4) : 0;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int p = row_offsets[row]; p < row_offsets[row + 1]; ++p) {
-      const float a = (float)values[p];
-      float b[4];
-      Pack<_Float16, 4>::load(B + (size_t)(int)column_indices[p] * n + col4, b);
+    const int end = uniform(row_offsets[row + 1]);
+    for (int p = uniform(row_offsets[row]); p < end; p += 8) {
+      float a[8], b[8][4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(a, b[j], v[j]);
+      for (int u = 0; u < 8; ++u) {
+        const int q = min(p + u, end - 1);
+        a[u] = (float)values[q];
+        Pack<_Float16, 4>::load(B + (size_t)(int)column_indices[q] * n + col4, b[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p + u < end) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(a[u], b[u][j], v[j]);
+        }
     }
     spmm_epilogue<_Float16, 4>(v, bias, row, relu);
     if (ok) Pack<_Float16, 4>::store(C + (size_t)row * n + col4, v);

@@ -176,3 +176,44 @@ def test_window_kernels_contain_nonfinite_rows_inside_and_outside_the_window(g, 
     assert spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 4, 0, 0)["variant"] == by1["window"]
     same_where_finite(g.gpu_sddmm(A, L, B, n), out, So, g.TOL_F32, 0.0, "sddmm window")
 
+
+@pytest.mark.parametrize("m,k,n,density,shift_b,shift_c", [
+    (1024, 1024, 3137, 0.10, 0, 0),       # the free choice: one column past whole pieces, one tile past whole tiles
+    (300, 700, 263, 0.10, 1, 0),
+    (300, 700, 264, 0.10, 1, 0),          # whole pieces that start two bytes off
+    (300, 700, 264, 0.10, 0, 1),
+    (70, 2100, 514, 0.10, 0, 0),          # three chunks of A's columns
+    (4100, 320, 600, 0.10, 0, 1),         # two tiles per workgroup
+    (1000, 900, 64, 0.02, 0, 0)])         # aligned, fewer than one position in 32
+@pytest.mark.parametrize("relu", [False, True])
+def test_spmm_matrix_core_kernel_contains_nonfinite_rows_of_B_outside_whole_aligned_pieces(
+        g, oracle_lib, force, m, k, n, density, shift_b, shift_c, relu):
+    """Outside whole 16-byte pieces of moderately sparse matrices the matrix-core SpMM follows the definition: a row
+    of B with Inf and NaN reaches the rows of A that store its column, rows that are not ascending among them."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    from tests.test_gpu_any_width import framed
+    A = wl.uniform_mask_csr(m, k, density, 4400 + n)
+    k0 = k - 3
+    A = place_column(A, k0, set(range(33, 60, 3)) | {m - 1, m - 4})
+    lo, hi = A.row_offsets[36], A.row_offsets[37]
+    A.column_indices[lo:hi] = A.column_indices[lo:hi][::-1]           # stores k0, not ascending
+    lo, hi = A.row_offsets[7], A.row_offsets[8]
+    A.column_indices[lo:hi] = A.column_indices[lo:hi][::-1]           # does not store k0
+    A.values = A.values.astype(np.float16)
+    A.values[A.values == 0] = 1
+    B, bias = wl.dense(k, n, 4401, np.float16), wl.dense(1, m, 4402, np.float16)[0]
+    for j, x in ((0, np.inf), (1, np.nan), (n // 2, -np.inf), (n - 1, np.inf), (n - 2, np.nan)):
+        B[k0, j] = x
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, S = oracle_lib.spmm_bias_relu(m, k, n, A.row_offsets, A.column_indices, A.values, B, bias, relu)
+    d = g.DevCsr(A)
+    _, dB, _ = framed(B, shift_b)
+    _, dC, _ = framed(np.full((m, n), np.nan, np.float16), shift_c)
+    mfma = [v for v, name in variants(0) if name == "mfma"][0]
+    if m != 1024:
+        force(0, mfma)
+    assert spdl.spdl_select_spmm(m, k, n, A.nnz, 2, dB, dC)["variant"] == mfma
+    spdl.spdl_spmm_bias_relu_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, None, dB, g.dev(bias), relu, dC)
+    torch.cuda.synchronize()
+    same_where_finite(dC.cpu().numpy(), ref, S, g.TOL_F16, g.ATOL_F16_STORE, f"mfma {m}x{k} n={n}")
