@@ -5,6 +5,8 @@ import glob
 import os
 import subprocess
 
+from . import loads_in_flight
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libspdl.so")
 CSRC = os.path.join(_HERE, "csrc")
@@ -81,6 +83,7 @@ def build(verbose: bool = False) -> str:
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + proc.stdout)
+    loads_in_flight.check(LIB_PATH, os.path.dirname(os.path.dirname(HIPCC)))
     build_native(verbose)
     return LIB_PATH
 

@@ -253,9 +253,9 @@ inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
 }
 
 // The matrix-core SpMM keeps rows of B in registers whose loads are still in flight (explicit
-// waits); a register spilled inside that window would be copied before its data has arrived.
-// The kernel is built without spills; should a toolchain ever produce one (private memory per
-// lane != 0), the variant is not offered and the row-splitting kernel runs instead.  Queried
+// waits); a register spilled or copied inside that window would be read before its data has arrived.
+// The build reads the machine code for that (loads_in_flight.py).  A library that was built some other way and
+// spills (private memory per lane != 0) is not offered the variant: the row-splitting kernel runs instead.  Queried
 // once; without a device (selection queries on a CPU-only host) the answer is yes.
 bool spmm_mfma_runnable() {
   static const bool ok = [] {

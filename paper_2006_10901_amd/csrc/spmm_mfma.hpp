@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     const int all_steps = (kc + 15) >> 4;
     const int per_part = (all_steps + KP - 1) / KP;
     const int s_begin = min(all_steps, kpart * per_part);
-    const int steps = min(all_steps, s_begin + per_part) - s_begin;      // this wave's steps: s_begin ..
+    const int steps = active ? min(all_steps, s_begin + per_part) - s_begin : 0;     // this wave's steps: s_begin ..
     // Second operand source: rows kc0 + 16*(s_begin + s) + 8h + r of B, r < 8: a scalar base that
     // moves with the step, and four rows down for r >= 4, plus this lane's fixed 32-bit byte offset (8h + r%4 rows
     // down, `col` columns in), so a load needs no vector arithmetic and a step little on the scalar unit.  The loads are issued from
@@ -138,7 +138,10 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     const int turn = ((i0 >> 5) & 7) * full_steps >> 3;
     const char* step_rows = reinterpret_cast<const char*>(B + (size_t)(kc0 + 16 * s_begin) * n);
     // A step past this wave's last full one loads with no lane active: nothing is fetched, but the
-    // number of loads behind any set is the same at every step and one wait count serves them all.
+    // number of loads behind any set is the same at every step and one wait count serves them all.  An idle
+    // wave has no steps and loads like that throughout: no path has a load less than another.  That no instruction
+    // names a register of `w` while a load into it may be in flight is not left to the compiler, which knows nothing of
+    // these loads: the build reads the machine code for it (loads_in_flight.py).
     auto load_rows = [&](int s, u32x4 (&ws)[8]) __attribute__((always_inline)) {
       const int t = s + turn - (s + turn >= full_steps ? full_steps : 0);
       const char* b0 = step_rows + (size_t)t * ((size_t)n * 32);
@@ -202,10 +205,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
         *reinterpret_cast<f32x4*>(lds_raw + o) = f32x4{0.f, 0.f, 0.f, 0.f};
       if (tid < 32) bad[tid] = 0;
       __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt 0: the entries; lgkmcnt is left to the barrier
-      if (active) {
-        load_rows(0, w[0]);
-        load_rows(1, w[1]);
-      }
+      load_rows(0, w[0]);
+      load_rows(1, w[1]);
       clear_sums();
       __syncthreads();
       // Ascending rows have ascending places in the panel, across rows too: an entry whose place is not above
@@ -236,7 +237,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
           for (int f = 0; f < 4; ++f) place(e + f, ecol[e + f], eval[e + f]);
         }
         // (further sets of B in between: the memory path takes 500 clocks for one of all waves)
-        if (active && 2 + e / 4 < NS - 1) load_rows(2 + e / 4, w[2 + e / 4]);
+        if (2 + e / 4 < NS - 1) load_rows(2 + e / 4, w[2 + e / 4]);
       }
       for (int e0 = FLAT; e0 < share; e0 += 4) {
         int cmore[4];
@@ -285,10 +286,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
       // half of the sets of B go ahead of the entries: the memory path works on them until the offsets are
       // there and while the panel is filled (more would hold the entries up, which arrive after everything
       // issued before them)
-      if (active) {
 #pragma unroll
-        for (int u = 0; u < NS / 2; ++u) load_rows(u, w[u]);
-      }
+      for (int u = 0; u < NS / 2; ++u) load_rows(u, w[u]);
       const int kend = kc0 + kc;
 #pragma unroll
       for (int i = 0; i < RW; ++i)
@@ -311,10 +310,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
       // (vmcnt 0; the other two counters are left alone.)  No load is in flight while the panel is filled: the
       // compiler, short of registers there, may move some, and does not know which are still to be written.
       __builtin_amdgcn_s_waitcnt(0x0F70);
-      if (active) {
 #pragma unroll
-        for (int u = 0; u < NS / 2; ++u) hold_rows(w[u]);
-      }
+      for (int u = 0; u < NS / 2; ++u) hold_rows(w[u]);
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
         const int rr = wave + NW * i;
@@ -359,59 +356,55 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
         if (kc0 == 0 && __builtin_amdgcn_ballot_w64(unordered) != 0 && lane == 0) bad[rr] = 1;
         cursor[i] = row_begin[i] + before_end;
       }
-      if (active) {
 #pragma unroll
-        for (int u = NS / 2; u < NS - 1; ++u) load_rows(u, w[u]);
-      }
+      for (int u = NS / 2; u < NS - 1; ++u) load_rows(u, w[u]);
     }
     __syncthreads();
-    if (active) {
-      // first operands: rows c of the panel, columns 16*s + 8h .. +7 of the chunk
-      const _Float16* ap = panel + c * stride + 8 * h + 16 * s_begin;
-      auto fragment = [&](int s) __attribute__((always_inline)) {        // (the ragged step is the last in any order)
-        const int t = s >= full_steps ? s : s + turn - (s + turn >= full_steps ? full_steps : 0);
-        return *reinterpret_cast<const f16x8*>(ap + 16 * t);
-      };
-      // (the fragment of a step is read from LDS one step ahead: with one wave per SIMD nothing
-      // else would cover the LDS latency)
-      f16x8 a_next;
-      auto step = [&](int s, const u32x4 (&ws)[8]) __attribute__((always_inline)) {
-        const f16x8 a = a_next;
-        if (s + 1 < steps) a_next = fragment(s + 1);
-        // 8x8 transpose of halves inside the lane: operand j, word q = (ws[2q][j], ws[2q+1][j])
+    // first operands: rows c of the panel, columns 16*s + 8h .. +7 of the chunk
+    const _Float16* ap = panel + c * stride + 8 * h + 16 * s_begin;
+    auto fragment = [&](int s) __attribute__((always_inline)) {        // (the ragged step is the last in any order)
+      const int t = s >= full_steps ? s : s + turn - (s + turn >= full_steps ? full_steps : 0);
+      return *reinterpret_cast<const f16x8*>(ap + 16 * t);
+    };
+    // (the fragment of a step is read from LDS one step ahead: with one wave per SIMD nothing
+    // else would cover the LDS latency)
+    f16x8 a_next;
+    auto step = [&](int s, const u32x4 (&ws)[8]) __attribute__((always_inline)) {
+      const f16x8 a = a_next;
+      if (s + 1 < steps) a_next = fragment(s + 1);
+      // 8x8 transpose of halves inside the lane: operand j, word q = (ws[2q][j], ws[2q+1][j])
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          u32x4 packed;
+      for (int j = 0; j < 8; ++j) {
+        u32x4 packed;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const unsigned sel = (j & 1) ? 0x07060302u : 0x05040100u;
-            packed[q] = __builtin_amdgcn_perm(ws[2 * q + 1][j / 2], ws[2 * q][j / 2], sel);
-          }
-          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(f16x8, packed), acc[j], 0, 0, 0);
+        for (int q = 0; q < 4; ++q) {
+          const unsigned sel = (j & 1) ? 0x07060302u : 0x05040100u;
+          packed[q] = __builtin_amdgcn_perm(ws[2 * q + 1][j / 2], ws[2 * q][j / 2], sel);
         }
-      };
-      if (steps > 0) a_next = fragment(0);
-      for (int s0 = 0; s0 < full_steps; s0 += NS) {
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-          const int s = s0 + u;
-          load_rows(s + NS - 1, w[(u + NS - 1) % NS]);
-          await_rows(w[u]);
-          if (s < full_steps) step(s, w[u]);
-        }
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(f16x8, packed), acc[j], 0, 0, 0);
       }
-      // (every load has landed before its registers serve anything else)
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    if (steps > 0) a_next = fragment(0);
+    for (int s0 = 0; s0 < full_steps; s0 += NS) {
 #pragma unroll
-      for (int u = 0; u < NS; ++u) hold_rows(w[u]);
-      if (ragged_last) {
-        const int k0 = kc0 + 16 * (s_begin + full_steps);
-        u32x4 tail[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-          tail[r] = __builtin_bit_cast(u32x4, (f16x8)*reinterpret_cast<const f16x8_any*>(bp + (size_t)min(k0 + 8 * h + r, k - 1) * n));
-        step(full_steps, tail);
+      for (int u = 0; u < NS; ++u) {
+        const int s = s0 + u;
+        load_rows(s + NS - 1, w[(u + NS - 1) % NS]);
+        await_rows(w[u]);
+        if (s < full_steps) step(s, w[u]);
       }
+    }
+    // (every load has landed before its registers serve anything else)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < NS; ++u) hold_rows(w[u]);
+    if (ragged_last) {
+      const int k0 = kc0 + 16 * (s_begin + full_steps);
+      u32x4 tail[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        tail[r] = __builtin_bit_cast(u32x4, (f16x8)*reinterpret_cast<const f16x8_any*>(bp + (size_t)min(k0 + 8 * h + r, k - 1) * n));
+      step(full_steps, tail);
     }
   }
   // Register t of lane (c, h) in accumulator j is row 8*(t/4) + 4h + t%4, column `col` + j.  Wave `kpart`
