@@ -771,15 +771,18 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   const bool window_ok = sizeof(T) == 4 && vec_ok && aligned(L, 16) && aligned(R, 16) && n <= 2 * kWinTile && nnz > 0 &&
                          (int64_t)k * n < ((int64_t)1 << 29);
   // The caller says that the entries form a band (a problem the window kernel cannot take keeps the
-  // choice made above).  Two of the window kernel's workgroups, 16 rows, are at work on a compute unit: its
+  // choice made above).  At most 64 columns: two of the window kernel's workgroups, 16 rows, are at work on a compute unit: its
   // time goes in steps of 4096 rows, and below 2048 it is one workgroup's, while the nonzero-split kernel's goes with the
   // entries and is the shorter one unless the steps come out nearly even (64 columns, 4096 rows of 410: 21 us
-  // against 25; 2994 of 425: 21.5 against 20.3; 1374 of 360: 12.2 against 10.3).  Beyond 64 columns a window fills the
-  // LDS of a compute unit and is no gain (4096 rows of 492, 96 columns: 45 us against 46; 2000 of 340: 22.7
-  // against 20.4; 1129 of 341, 128 columns: 23.3 against 12.8).
+  // against 25; 2994 of 425: 21.5 against 20.3; 1374 of 360: 12.2 against 10.3).  Beyond 64 columns the window fills the
+  // LDS of a compute unit, one workgroup of 16 rows: whole steps of 4096 rows only, where it is level on long rows and up to
+  // 8 % faster on shorter ones (128 columns, window against nonzero-split kernel: 4096 rows of 456: 40.3 us and 43.8, of 620:
+  // 53.4 and 52.8; 8192 of 783: 128 and 135; 3800 of 432: 38.3 and 39.2, of 584: 50.1 and 46.9; 3500 of 548: 47.5 and 43.3;
+  // 4300 of 472: 52 and 44; 7000 of 688: 110 and 102; 2048 of 374: 27.5 and 21.9; 1024 of 292: 19.3 and 11.4).
   if (free_choice && hint == kHintBanded && window_ok) {
-    const int64_t stepped = (m + 2047) / 2048 * (int64_t)2048;
-    variant = n <= kWinTile && 5 * stepped <= 6 * (int64_t)m ? kSddmmWindow : kSddmmGroup;
+    const bool wide = n > kWinTile;
+    const int64_t step = wide ? 4096 : 2048, stepped = (m + step - 1) / step * step;
+    variant = (wide ? 20 * stepped <= 21 * (int64_t)m : 5 * stepped <= 6 * (int64_t)m) ? kSddmmWindow : kSddmmGroup;
   }
   // the caller says that the row lengths are strongly unequal: the nonzero-split kernel, which does not
   // care, or for dot products of more than 128 columns the lane kernel in passes where the estimate

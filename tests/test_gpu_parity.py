@@ -463,6 +463,23 @@ def test_window_kernels_on_banded_masks(g, oracle_lib, force, n):
         assert np.array_equal(ob.cpu().numpy(), got)
 
 
+@pytest.mark.parametrize("n", [68, 96, 128])
+@pytest.mark.parametrize("m", [3900, 3901, 4096, 4097])
+def test_banded_sddmm_of_wide_heads_at_the_edges_of_its_rule(g, oracle_lib, m, n):
+    """65 .. 128 columns: the window kernel where its workgroups fill whole steps of 4096 rows (3901 rows on), the
+    nonzero-split kernel elsewhere; the two give the same bits."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = wl.banded_attention_csr(m, 32, 0.012, 2120 + m)
+    L, R = wl.dense(m, n, 2121 + n), wl.dense(m, n, 2122 + n)
+    ref, S = oracle_lib.sddmm(m, m, n, A.row_offsets, A.column_indices, L, R)
+    d = g.DevCsr(A)
+    out = torch.full((A.nnz,), float("nan"), device="cuda")
+    spdl.spdl_sddmm_banded(m, m, n, A.nnz, d.ro, d.ci, g.dev(L), g.dev(R), out)
+    torch.cuda.synchronize()
+    g.assert_close(out.cpu().numpy(), ref, S, g.TOL_F32, f"sddmm_banded m={m} n={n}")
+
+
 def test_banded_entry_points_fall_back_when_the_window_kernels_do_not_apply(g, oracle_lib):
     """n % 4 != 0 (SpMM), dot products of more than 128 columns (SDDMM), a matrix without entries:
     the entry points for banded masks then run what spdl_spmm / spdl_sddmm run."""
