@@ -220,18 +220,21 @@ int spdl_validate_csr_host(int m, int k, int nnz, const int* row_offsets_host,
                            const int* column_indices_host, int* sorted_out);
 
 /* Kernel selection (paper Sec. "Experiments", first paragraph: tile sizes and vector widths
- * are picked from the problem shape).  spdl_select_* report what the dispatcher would launch;
- * spdl_force_variant overrides it for ablation runs (variant < 0 restores the heuristic); a
+ * are picked from the problem shape).  spdl_select_* report what the dispatcher would launch for
+ * spdl_spmm / spdl_sddmm and their fp16 forms (forcing the variant that they report changes
+ * nothing); spdl_force_variant overrides it for ablation runs (variant < 0 restores the heuristic); a
  * forced variant that cannot run the problem at hand falls back to one that can.  The override
  * is one process-wide setting per operation, read by every later call on any thread: it is not
  * meant to be changed while other threads are inside the library.
- * The variant ids are listed by spdl_variant_name. */
+ * The variant ids are listed by spdl_variant_name.  SDDMM's rowstrip is the general family, for every
+ * width: from four columns on it deals strips of 16 entries to 16 lanes each, as group does
+ * (lanes_per_row 16), below that entries to lanes (lanes_per_row 64). */
 typedef struct {
   int variant;          /* kernel family id                                        */
   int vec;              /* elements per lane per memory instruction                */
   int lanes_per_row;    /* lanes cooperating on one output row / one dot product   */
-  int rows_per_block;   /* SpMM: sparse rows per block.  SDDMM: waves per row, or for the   */
-                        /* group variant the CSR entries owned by one wave                */
+  int rows_per_block;   /* sparse rows per block; SDDMM's group and rowstrip: CSR entries   */
+                        /* owned by one wave, rowstrip below four columns: waves per row  */
   int block_threads;
   int grid_x, grid_y;
 } spdl_launch_info;

@@ -1,4 +1,5 @@
-// SDDMM, row-strip family: one wave owns strips of 32 consecutive nonzeros of one sparse row
+// SDDMM, row-strip family, dot products of fewer than four columns (wider ones: the strips of
+// sddmm_group.hpp): one wave owns strips of 32 consecutive nonzeros of one sparse row
 // (paper Sec. "Sampled Dense--Dense Matrix Multiplication", 1-D tiling over nonzero strips).
 // The 64 lanes split the dot-product dimension so that rows of L and R are read contiguously;
 // each lane keeps a partial sum for every nonzero of the strip and a transposing butterfly

@@ -280,7 +280,6 @@ template <typename T>
 void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, spdl_launch_info* info,
                     int hint = 0) {
   int variant = g_forced[0].load();
-  const bool free_choice = variant < 0;
   // (n % 8 == 4: rows of whole 8-byte pieces stay with row splitting)
   const bool mfma_ok = sizeof(T) == 2 && n >= 8 && n % 8 != 4 && n < (1 << 24) && k >= 16;
   // nnz == 0: column_indices, values and B may be null, and the slab and matrix-core kernels
@@ -303,6 +302,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     info->grid_y = tiles_n;                     // 256-column tiles (the grid is 1-D)
     return;
   }
+  const bool wide_window = n > 2 * kWinTile && m >= 4096 && k >= 7000 && (double)nnz >= 120.0 * (double)m;   // (see below)
   if (variant < 0) {
     const double reuse = (m > 0 && k > 0) ? 64.0 * (double)nnz / ((double)m * (double)k) : 0.0;
     // one workgroup per CU: below half a machine of 64x64 output tiles the row-splitting
@@ -399,8 +399,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // 175; 19428 x 9075 at 2.1 %, n = 1024: 636 against 1108; 13651 x 3925 at 3.1 %, n = 256: 98
     // against 69, not taken).
     if (variant == kSpmmRowsplit && sizeof(T) == 4 && slab_dma_usable(n, nnz) &&
-        (int64_t)k * n < ((int64_t)1 << 29) && n > 2 * kWinTile && m >= 4096 && k >= 7000 &&
-        (double)nnz >= 120.0 * (double)m)
+        (int64_t)k * n < ((int64_t)1 << 29) && wide_window)
       variant = kSpmmWindow;
     // the caller says that the entries form a band, or that the row lengths are strongly unequal: the
     // window kernel gathers what is not in a band and shares long rows among the waves of a workgroup
@@ -413,8 +412,10 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // slab kernels wait for their longest row)
     if (hint == kHintSkewed && n > 2 * kWinTile && k < 4000) variant = kSpmmRowsplit;
   }
+  // (forced at a width or alignment that needs pieces which overlap: for the widths and shapes that the choice from the
+  // shape may give it)
   if (variant == kSpmmWindow && sizeof(T) == 4 && nnz > 0 && slab_dma_usable(n, nnz) &&
-      (free_choice || slab_usable<T>(n, nnz, B, C)) && (int64_t)k * n < ((int64_t)1 << 29)) {
+      (n <= 2 * kWinTile || wide_window || slab_usable<T>(n, nnz, B, C)) && (int64_t)k * n < ((int64_t)1 << 29)) {
     info->variant = kSpmmWindow;
     info->vec = 4;
     info->lanes_per_row = 16;
@@ -649,8 +650,7 @@ bool sddmm_lane_usable(int n, int nnz, const void* L, const void* R) {
 // per lane take them, the lane at a row's end working on the row's last piece (piece_start).  (LSTM
 // shape at 90 % sparsity, n = 127: 92 us against 1782 for one column per lane.)  Not 129 .. 191 columns,
 // which are two passes of the lane kernel or two chunks of the slab kernel, the second mostly empty:
-// there the nonzero-split kernel serves as the general one.  (A pass of the lane kernel is at least
-// four columns wide.)
+// those go to the general family.  (A pass of the lane kernel is at least four columns wide.)
 inline bool sddmm_any_width(int n) { return n >= 4; }
 inline bool sddmm_wide_any(int n) { return n >= 4 && (n <= 128 || n >= 192); }
 inline bool sddmm_lane_pass_ok(int n) { return n % 128 == 0 || n % 128 >= 4; }
@@ -825,8 +825,9 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_y = sh.ksplit;               // column ranges of A (the grid is 1-D)
     return;
   }
-  // (the general kernel of widths that the choice above leaves to it: the nonzero-split one again)
-  if (variant == kSddmmGroup || (free_choice && variant == kSddmmRowstrip && sddmm_any_width(n))) {
+  // (the general family: from four columns on its strips are those of the nonzero-split kernel, sixteen lanes to a
+  // strip)
+  if (variant == kSddmmGroup || sddmm_any_width(n)) {
     // entries per wave: four strips of 16 while the machine (32 waves on each CU) is not
     // full, then as many as keep the grid at about one wave per slot
     const int64_t slots = (int64_t)kComputeUnits * 32;
@@ -838,10 +839,8 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_x = (int)((waves + 3) / 4);
     return;
   }
-  int vec = pick_vec<T>(n, L, R, 16 / (int)sizeof(T));
-  while (vec > 1 && kWave * vec / 2 >= n) vec /= 2;     // do not idle lanes on short dot products
   const int split = std::max(1, std::min(8, avg / (4 * kStrip)));
-  info->vec = vec;
+  info->vec = 1;
   info->lanes_per_row = kWave;
   info->rows_per_block = split;
   const int64_t waves = (int64_t)m * split;
@@ -889,7 +888,6 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
   spdl_launch_info li;
   fill_sddmm_info<T>(m, k, n, nnz, L, R, &li, hint);
   dim3 grid(li.grid_x), block(256);
-  const int split = li.rows_per_block;
   (void)hipGetLastError();
   if (li.variant == kSddmmMfma) {
     if constexpr (sizeof(T) == 2) {
@@ -972,25 +970,14 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
       return SPDL_ERR_UNSUPPORTED;
     }
   }
-  if (li.lanes_per_row == 16 && (li.variant == kSddmmGroup || li.variant == kSddmmRowstrip)) {
+  if (li.lanes_per_row == 16) {
     // (two waves or fewer on each SIMD: registers for both halves of 128 columns)
     if (n > 64 && (int64_t)grid.x * 4 <= 8 * kComputeUnits)
       sddmm_group_kernel<T, 2><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
     else
       sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
-    return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
-  }
-  switch (li.vec) {
-    case 1: sddmm_rowstrip_kernel<T, 1><<<grid, block, 0, st>>>(m, n, split, ro, ci, L, R, out, scale); break;
-    case 2: sddmm_rowstrip_kernel<T, 2><<<grid, block, 0, st>>>(m, n, split, ro, ci, L, R, out, scale); break;
-    case 4: sddmm_rowstrip_kernel<T, 4><<<grid, block, 0, st>>>(m, n, split, ro, ci, L, R, out, scale); break;
-    case 8:
-      if constexpr (sizeof(T) == 2) {
-        sddmm_rowstrip_kernel<T, 8><<<grid, block, 0, st>>>(m, n, split, ro, ci, L, R, out, scale);
-        break;
-      }
-      return SPDL_ERR_INVALID;
-    default: return SPDL_ERR_INVALID;
+  } else {
+    sddmm_rowstrip_kernel<T, 1><<<grid, block, 0, st>>>(m, n, li.rows_per_block, ro, ci, L, R, out, scale);
   }
   return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
 }

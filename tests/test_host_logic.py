@@ -298,6 +298,31 @@ def test_forced_slab_variants_never_run_an_empty_matrix(spdl):
         spdl.spdl_force_variant(0, -1)
 
 
+@pytest.mark.parametrize("op", [0, 1])
+def test_selection_reports_what_the_reported_variant_launches(spdl, op):
+    """Forcing the variant that spdl_select_* reports changes nothing: random shapes, widths that are multiples of
+    nothing, operands at any element, both types; and the wide outputs over a tall B that the window kernel takes."""
+    import random
+    select = (spdl.spdl_select_spmm, spdl.spdl_select_sddmm)[op]
+    rng = random.Random(20200610 + op)
+    size = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    problems = [(8192, 10240, 130, 8 << 20, 4, 0, 0), (4096, 1024, 189, 400000, 4, 4, 4), (5645, 10453, 183, 1702940, 4, 4, 0),
+                (18687, 4389, 62, 5528594, 4, 0, 4), (4950, 19805, 1443, 1139781, 4, 0, 4), (300, 300, 3, 9000, 4, 0, 0)]
+    while len(problems) < 4000:
+        m, k, n, eb = size(1, 20000), size(1, 20000), rng.choice([size(1, 5000), rng.randint(1, 300)]), rng.choice([2, 4])
+        if max(m, k) * n < 1 << 31:
+            problems.append((m, k, n, int(m * k * 10 ** rng.uniform(-3.5, 0)), eb, *rng.choice([(0, 0), (eb, 0), (0, eb), (8, 8)])))
+    try:
+        for problem in problems:
+            free = select(*problem)
+            spdl.spdl_force_variant(op, free["variant"])
+            forced = select(*problem)
+            spdl.spdl_force_variant(op, -1)
+            assert free == forced, problem
+    finally:
+        spdl.spdl_force_variant(op, -1)
+
+
 def test_status_strings(spdl):
     lib = ctypes.CDLL(spdl.LIB_PATH)
     lib.spdl_status_string.restype = ctypes.c_char_p
