@@ -839,7 +839,7 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_x = (int)((waves + 3) / 4);
     return;
   }
-  const int split = std::max(1, std::min(8, avg / (4 * kStrip)));
+  const int split = std::max(1, std::min(8, avg / (2 * kWave)));
   info->vec = 1;
   info->lanes_per_row = kWave;
   info->rows_per_block = split;
@@ -977,7 +977,7 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     else
       sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
   } else {
-    sddmm_rowstrip_kernel<T, 1><<<grid, block, 0, st>>>(m, n, li.rows_per_block, ro, ci, L, R, out, scale);
+    sddmm_rowstrip_kernel<T><<<grid, block, 0, st>>>(m, n, li.rows_per_block, ro, ci, L, R, out, scale);
   }
   return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
 }

@@ -217,3 +217,20 @@ def test_spmm_matrix_core_kernel_contains_nonfinite_rows_of_B_outside_whole_alig
     spdl.spdl_spmm_bias_relu_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, None, dB, g.dev(bias), relu, dC)
     torch.cuda.synchronize()
     same_where_finite(dC.cpu().numpy(), ref, S, g.TOL_F16, g.ATOL_F16_STORE, f"mfma {m}x{k} n={n}")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_sddmm_of_fewer_than_four_columns_keeps_infinities(g, oracle_lib, dtype, n):
+    """An Inf in the first column stays one (no lane without a column of its own multiplies it by zero); rows shorter
+    and longer than a strip of 64 entries, and long enough for several waves."""
+    A = wl.row_lengths_csr(60, 2500, [0, 1, 63, 64, 65, 129, 600, 2000, 3, 128, 2500, 0] * 5, 4500 + n)
+    L, R = wl.dense(A.m, n, 4501, dtype), wl.dense(A.k, n, 4502, dtype)
+    L[L == 0] = 1
+    R[7, 0], R[8, n - 1], R[2499, 0] = np.inf, np.nan, -np.inf
+    L[10, 0] = np.inf
+    with np.errstate(invalid="ignore", over="ignore"):
+        out, S = oracle_lib.sddmm(A.m, A.k, n, A.row_offsets, A.column_indices, L, R)
+    assert np.isinf(out).any() and np.isnan(out).any()
+    tol, atol = (g.TOL_F32, 0.0) if dtype == np.float32 else (g.TOL_F16, g.ATOL_F16_STORE)
+    same_where_finite(g.gpu_sddmm(A, L, R, n), out, S, tol, atol, f"sddmm n={n}")
