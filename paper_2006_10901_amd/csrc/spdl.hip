@@ -971,8 +971,12 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     }
   }
   if (li.lanes_per_row == 16) {
-    // (two waves or fewer on each SIMD: registers for both halves of 128 columns)
-    if (n > 64 && (int64_t)grid.x * 4 <= 8 * kComputeUnits)
+    // Two waves or fewer on each SIMD and dot products of 65 .. 128 columns: the gathers of both halves in flight.
+    // (Inputs out of the caches, 1024 rows, n = 128: 125 thousand entries, 1.9 waves per SIMD, 7.25 us against 7.87, fp16
+    // 7.42 against 7.71; 26 thousand, 512 rows: 6.30 and 6.61; 150 thousand, 2.3 waves: 10.55 against 8.93.  192 columns,
+    // half of the second pair idle: 11.8 against 10.2 at 1.9 waves; 256 columns 12.6 and 12.9, fp16 11.8 and 11.3; 1024
+    // columns 40.7 and 38.6.)
+    if (n > 64 && n <= 128 && (int64_t)grid.x * 4 <= 8 * kComputeUnits)
       sddmm_group_kernel<T, 2><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
     else
       sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
