@@ -1,4 +1,5 @@
-"""Builds libspdl.so (HIP, gfx950 only) next to this file with hipcc, and the binding's native half."""
+"""Builds libspdl.so (HIP, gfx950 only) next to this file with hipcc, and the binding's native half
+(python -m paper_2006_10901_amd.build; with --library the C library alone)."""
 from __future__ import annotations
 
 import glob
@@ -76,7 +77,8 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build(verbose: bool = False) -> str:
+def build_library(verbose: bool = False) -> str:
+    """The C library alone: needs hipcc, neither torch nor g++."""
     cmd = [HIPCC, *HIP_FLAGS, "-o", LIB_PATH, *sources()]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -84,11 +86,22 @@ def build(verbose: bool = False) -> str:
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + proc.stdout)
     loads_in_flight.check(LIB_PATH, os.path.dirname(os.path.dirname(HIPCC)))
+    return LIB_PATH
+
+
+def build(verbose: bool = False) -> str:
+    """The library and what the Python binding needs beside it."""
+    build_library(verbose)
     build_native(verbose)
     return LIB_PATH
 
 
 if __name__ == "__main__":
-    print(build(verbose=True))
-    print(build_microbench(verbose=True))
-    print(build_phase_clocks(verbose=True))
+    import sys
+
+    if "--library" in sys.argv[1:]:
+        print(build_library(verbose=True))
+    else:
+        print(build(verbose=True))
+        print(build_microbench(verbose=True))
+        print(build_phase_clocks(verbose=True))

@@ -347,6 +347,23 @@ def test_bench_reads_its_traffic_figures_from_the_profile_summary():
         assert nbytes > 1e6
 
 
+def test_c_library_builds_without_torch_and_the_host_compiler(monkeypatch):
+    """A user of the C ABI needs hipcc only: no other compiler is run and torch is not imported."""
+    import builtins
+    import subprocess
+    from paper_2006_10901_amd import build
+    ran, plain_import = [], builtins.__import__
+
+    def no_torch(name, *a, **kw):
+        assert name.split(".")[0] != "torch", "the C library's build imports torch"
+        return plain_import(name, *a, **kw)
+    monkeypatch.setattr(builtins, "__import__", no_torch)
+    monkeypatch.setattr(subprocess, "run", lambda cmd, **kw: ran.append(cmd) or subprocess.CompletedProcess(cmd, 0, ""))
+    monkeypatch.setattr(build.loads_in_flight, "check", lambda *a: 8)
+    assert build.build_library() == build.LIB_PATH
+    assert [cmd[0] for cmd in ran] == [build.HIPCC]
+
+
 def test_workload_statistics():
     A = wl.tiny()["A"]
     assert A.m == 512 and abs(A.nnz / 512 / 512 - 0.10) < 0.01
