@@ -252,3 +252,64 @@ def test_sddmm_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
     assert np.all(np.abs(got[fin] - ref[fin]) <= g.TOL_F32 * S[fin])
+
+
+def poke_last_pieces(L, R):
+    """Infinities and a NaN in columns that the last two pieces of a row share, and in the rows after it."""
+    n = R.shape[1]
+    L[L == 0] = 1
+    R[77, n - 4], R[78, n - 1], R[79, 0], R[639, n - 2] = np.inf, np.nan, -np.inf, np.inf
+
+
+def assert_same_where_finite(got, ref, tol, atol=0.0):
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+    assert np.all(np.abs(got[fin] - ref[fin]) <= tol[fin] + atol)
+
+
+@pytest.mark.parametrize("n", [63, 127, 129, 261])
+@pytest.mark.parametrize("kernel", ["group", "mfma"])
+def test_sddmm_f16_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib, n, kernel):
+    """Half precision, rows that start two bytes past a multiple of four."""
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(1, v): v for v in range(16) if spdl.spdl_variant_name(1, v)}
+    A = wl.uniform_mask_csr(600, 640, 0.1, 7410 + n)
+    A.values = A.values.astype(np.float16)
+    chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float16, ids[kernel], 1, poke=poke_last_pieces)
+    assert chosen == kernel and 0 < np.count_nonzero(~np.isfinite(ref)) < ref.size // 8
+    assert_same_where_finite(got.astype(np.float64), ref, g.TOL_F16 * S, g.ATOL_F16_STORE)
+
+
+@pytest.mark.parametrize("n", [5, 63, 67, 127, 261])
+@pytest.mark.parametrize("kernel,dtype", [("rowsplit", np.float32), ("rowsplit", np.float16), ("slabdma", np.float32),
+                                          ("window", np.float32)])
+def test_spmm_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib, n, kernel, dtype):
+    """Rows of B with infinities and a NaN in the columns that two lanes share reach the rows of A that store them, at
+    widths that are multiples of nothing and operands one element off."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    ids = {spdl.spdl_variant_name(0, v): v for v in range(16) if spdl.spdl_variant_name(0, v)}
+    A = wl.uniform_mask_csr(600, 640, 0.05, 7420 + n)
+    A.values = A.values.astype(dtype)
+    A.values[A.values == 0] = 1
+    B = wl.dense(640, n, 7421 + n, dtype)
+    poke_last_pieces(np.ones((1, n), dtype), B)
+    with np.errstate(invalid="ignore", over="ignore"):
+        C, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
+    assert 0 < np.count_nonzero(~np.isfinite(C)) < C.size // 4
+    d = g.DevCsr(A)
+    _, dB, _ = framed(B, 1)
+    cbuf, dC, at = framed(np.full((A.m, n), np.nan, dtype), 1, 777.0)
+    spdl.spdl_force_variant(0, ids[kernel])
+    try:
+        chosen = spdl.spdl_select_spmm(A.m, A.k, n, A.nnz, B.itemsize, dB, dC)["variant"]
+        assert spdl.spdl_variant_name(0, chosen) == (kernel if kernel != "window" or n <= 128 else "rowsplit")
+        fn = spdl.spdl_spmm_f16 if dtype == np.float16 else spdl.spdl_spmm
+        fn(A.m, A.k, n, A.nnz, d.ro, d.ci, d.val, None, dB, dC)
+        torch.cuda.synchronize()
+    finally:
+        spdl.spdl_force_variant(0, -1)
+    tol = (g.TOL_F16 if dtype == np.float16 else g.TOL_F32) * np.where(np.isfinite(S), S, 0.0)
+    assert_same_where_finite(dC.cpu().numpy().astype(np.float64), C, tol, g.ATOL_F16_STORE if dtype == np.float16 else 0.0)
+    assert frame_intact(cbuf, at, A.m * n)
