@@ -81,10 +81,25 @@ template <typename T>
 void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C, spdl_launch_info* info) {
   constexpr int kWide = 16 / (int)sizeof(T);
   int vec = pick_vec<T>(n, B, C, kWide);
+  auto waves = [&](int v) {
+    const int g = pick_group(n, v);
+    return (int64_t)m * g * pick_segments<T>(m, nnz, v, g) / kWave * ((n + g * v - 1) / (g * v));
+  };
   // (Rows of B at any alignment: 16 bytes per lane all the same, the lane at the row's end taking the
   // row's last ones.  Not for small problems, where more lanes per row count for more: 512 x 512
   // at 10 %, n = 127: 5.1 us against 6.3.)
-  if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2))) vec = kWide;
+  // Half-precision rows at odd elements: sixteen such bytes a lane take the memory path long enough that a wave which
+  // walks a long row alone is the slower for it.  4 bytes a lane where 16 would leave fewer than 2500 waves, below 800
+  // waves 2, as narrow as before; not where lane groups share a row.  (382 x 674 at 4 %, log-normal rows, n = 1195: 24.4 us
+  // with 16 bytes, 15.0 with 4, 15.5 with 2; uniform rows, means over 94 shapes of 2 .. 30 %, 16 and 4 bytes against 2: 1.03
+  // and 0.97 at 400 .. 800 waves, 0.95 and 0.93 to 1200, 0.85 and 0.81 to 1800, 0.77 and 0.81 to 2500, 0.56 and 0.70 beyond;
+  // log-normal rows, 134 shapes: 1.31 and 1.03, 1.30 and 1.01, 1.24 and 0.93, 1.04 and 0.85, 0.88 and 0.81.  Rows at even
+  // elements take 16 bytes at any number of waves: below 1800, against as narrow as before, 0.88 on uniform rows and 1.10 on
+  // log-normal ones, which the host cannot tell apart.)
+  if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2))) {
+    if (sizeof(T) == 4 || vec > 1 || pick_segments<T>(m, nnz, kWide, pick_group(n, kWide)) > 1 || waves(kWide) >= 2500) vec = kWide;
+    else if (waves(kWide) >= 800) vec = 2;
+  }
   // fp32, few waves: narrower loads, so that a wave has a row to itself (its indices are then scalar loads) and
   // the row is spread over more waves.  Below 1280 waves (five per compute unit) to a wave per row, two rows per wave
   // being no gain (3000 x 3000 at 1 %, n = 64: 4.3 us with four rows per wave, 5.2 with two, 4.0 with one), and on
@@ -96,10 +111,6 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   // as it is, 6.9 narrower; n = 32, rows of 100, m = 2000: 5.1 and 6.3; rows of 40, m = 4000: 4.75 and 4.57,
   // m = 8000: 5.75 and 6.7).
   if (sizeof(T) == 4 && vec == kWide && (n >= 256 || (nnz < 3 << 16 && nnz <= 64 * (int64_t)m))) {
-    auto waves = [&](int v) {
-      const int g = pick_group(n, v);
-      return (int64_t)m * g * pick_segments<T>(m, nnz, v, g) / kWave * ((n + g * v - 1) / (g * v));
-    };
     auto padded = [&](int v) { return (n + pick_group(n, v) * v - 1) / (pick_group(n, v) * v) * (pick_group(n, v) * v); };
     if (waves(vec) < 5 * kComputeUnits && waves(1) > waves(vec))
       while (vec > 1 && pick_group(n, vec) < kWave) vec /= 2;

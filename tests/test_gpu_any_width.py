@@ -106,6 +106,32 @@ def test_spmm_row_splitting_with_wide_loads_at_any_width(g, oracle_lib, n, dtype
     assert frame_intact(cbuf, at, m * n)
 
 
+@pytest.mark.parametrize("m,n,shift,vec", [(300, 515, 0, 1), (600, 515, 0, 2), (1300, 515, 0, 8), (600, 1030, 0, 8),
+                                           (600, 1030, 1, 2), (450, 513, 1, 2), (1500, 1029, 1, 8)])
+@pytest.mark.parametrize("lognormal", [False, True])
+def test_spmm_row_splitting_in_half_precision_at_odd_elements(g, oracle_lib, m, n, shift, vec, lognormal):
+    """Half-precision rows that start at odd elements: 1, 2 or 8 columns per lane by the number of waves, the row's last
+    lane on its last columns."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = (wl.lognormal_rows_csr if lognormal else wl.uniform_mask_csr)(m, 300, 0.05, 7150 + n)
+    A.values = A.values.astype(np.float16)
+    B = wl.dense(300, n, 7151 + n, np.float16)
+    C, S = oracle_lib.spmm(m, 300, n, A.row_offsets, A.column_indices, A.values, B)
+    d = g.DevCsr(A)
+    _, dB, _ = framed(B, shift)
+    cbuf, dC, at = framed(np.full((m, n), np.nan, np.float16), shift, 777.0)
+    spdl.spdl_force_variant(0, 0)
+    try:
+        assert spdl.spdl_select_spmm(m, 300, n, A.nnz, 2, dB, dC)["vec"] == vec
+        spdl.spdl_spmm_f16(m, 300, n, A.nnz, d.ro, d.ci, d.val, None, dB, dC)
+        torch.cuda.synchronize()
+    finally:
+        spdl.spdl_force_variant(0, -1)
+    g.assert_close(dC.cpu().numpy(), C, S, g.TOL_F16, f"row splitting m={m} n={n} shift={shift}")
+    assert frame_intact(cbuf, at, m * n)
+
+
 @pytest.mark.parametrize("n", [1, 8, 16, 20, 64, 100, 128, 200, 256, 300, 515])
 @pytest.mark.parametrize("longer", [0, 16, 140])
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
