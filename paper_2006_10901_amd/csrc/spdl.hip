@@ -784,8 +784,10 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   // The caller says that the entries form a band (a problem the window kernel cannot take keeps the
   // choice made above).  At most 64 columns: two of the window kernel's workgroups, 16 rows, are at work on a compute unit: its
   // time goes in steps of 4096 rows, and below 2048 it is one workgroup's, while the nonzero-split kernel's goes with the
-  // entries and is the shorter one unless the steps come out nearly even (64 columns, 4096 rows of 410: 21 us
-  // against 25; 2994 of 425: 21.5 against 20.3; 1374 of 360: 12.2 against 10.3).  Beyond 64 columns the window fills the
+  // entries and is the shorter one unless the steps come out nearly even, or the rows are short (64 columns, window against
+  // nonzero-split kernel, 4096 rows of 456: 24.2 us and 26.6; 2048 of 374: 13.4 and 14.3; 2152 of 300: 11.3 and 12.8, of 386:
+  // 14.2 and 14.8; 2994 of 368: 16.8 and 17.7, of 487: 24.2 and 21.3; 4800 of 512: 34.6 and 31.9; 6144 of 620: 42.8 and
+  // 46.6; 1500 of 292: 10.1 and 9.5; 1024 of 374: 11.9 and 8.6).  Beyond 64 columns the window fills the
   // LDS of a compute unit, one workgroup of 16 rows: whole steps of 4096 rows only, where it is level on long rows and up to
   // 8 % faster on shorter ones (128 columns, window against nonzero-split kernel: 4096 rows of 456: 40.3 us and 43.8, of 620:
   // 53.4 and 52.8; 8192 of 783: 128 and 135; 3800 of 432: 38.3 and 39.2, of 584: 50.1 and 46.9; 3500 of 548: 47.5 and 43.3;
@@ -793,7 +795,9 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   if (free_choice && hint == kHintBanded && window_ok) {
     const bool wide = n > kWinTile;
     const int64_t step = wide ? 4096 : 2048, stepped = (m + step - 1) / step * step;
-    variant = (wide ? 20 * stepped <= 21 * (int64_t)m : 5 * stepped <= 6 * (int64_t)m) ? kSddmmWindow : kSddmmGroup;
+    const bool even = wide ? 20 * stepped <= 21 * (int64_t)m : 5 * stepped <= 6 * (int64_t)m;
+    const bool short_rows = !wide && m > 2048 && m <= 4096 && nnz <= 400 * (int64_t)m;
+    variant = even || short_rows ? kSddmmWindow : kSddmmGroup;
   }
   // the caller says that the row lengths are strongly unequal: the nonzero-split kernel, which does not
   // care, or for dot products of more than 128 columns the lane kernel in passes where the estimate

@@ -463,14 +463,15 @@ def test_window_kernels_on_banded_masks(g, oracle_lib, force, n):
         assert np.array_equal(ob.cpu().numpy(), got)
 
 
-@pytest.mark.parametrize("n", [68, 96, 128])
-@pytest.mark.parametrize("m", [3900, 3901, 4096, 4097])
-def test_banded_sddmm_of_wide_heads_at_the_edges_of_its_rule(g, oracle_lib, m, n):
+@pytest.mark.parametrize("m,n", [(m, n) for m in (3900, 3901, 4096, 4097) for n in (68, 96, 128)] +
+                         [(m, n) for m in (1706, 1707, 2048, 2049, 2152) for n in (32, 64)])
+def test_banded_sddmm_at_the_edges_of_its_rule(g, oracle_lib, m, n):
     """65 .. 128 columns: the window kernel where its workgroups fill whole steps of 4096 rows (3901 rows on), the
-    nonzero-split kernel elsewhere; the two give the same bits."""
+    nonzero-split kernel elsewhere; up to 64 columns from 1707 rows on, beyond 2048 while rows are short.  The two
+    kernels give the same bits."""
     import torch
     import paper_2006_10901_amd as spdl
-    A = wl.banded_attention_csr(m, 32, 0.012, 2120 + m)
+    A = wl.banded_attention_csr(m, 32, 49 / m, 2120 + m)
     L, R = wl.dense(m, n, 2121 + n), wl.dense(m, n, 2122 + n)
     ref, S = oracle_lib.sddmm(m, m, n, A.row_offsets, A.column_indices, L, R)
     d = g.DevCsr(A)
