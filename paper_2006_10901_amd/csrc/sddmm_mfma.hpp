@@ -127,6 +127,8 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
   if (!sddmm_mfma_tile(blockIdx.x, (m + 63) >> 6, tiles_k, n, tile_i, tile_c)) return;   // whole workgroup, before any barrier
   const int i0 = tile_i * 64;
   const int c0 = tile_c * 64;
+  PhaseClocks clocks;
+  clocks.start();
 
   constexpr int kAdvance = ODD ? kSmPieces - 1 : kSmPieces;         // pieces from stage to stage
   const int pieces = ODD ? max(0, n / 8 - 1) : n / 8;               // multiplied in stages; the rest at the end
@@ -185,8 +187,10 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
       }
       return v;
     };
+    clocks.lap(kPhaseSetup);
     for (int s = 0; s < stages; ++s) {
       __syncthreads();                                 // stage s has arrived
+      clocks.lap(kPhaseBarrier);
       const char* buf = lds_raw + (s % kSmRing) * kSmStageBytes;
       const bool ragged = (s + 1) * kAdvance > pieces;
 #pragma unroll
@@ -207,6 +211,7 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
         acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, y0, acc[1][0], 0, 0, 0);
         acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, y1, acc[1][1], 0, 0, 0);
       }
+      clocks.lap(kPhaseSteps);
     }
     if (tail) {
 #pragma unroll
@@ -214,7 +219,9 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(at[i], bt[j], acc[i][j], 0, 0, 0);
     }
+    clocks.lap(kPhaseRest);
     __syncthreads();                                   // the ring is free: it now holds the four partial blocks
+    clocks.lap(kPhaseBarrier);
     // Register t of lane (r, half) in acc[i][j] is element (32*i + 8*(t/4) + 4*half + t%4, 32*j + r).
     float (*mine)[65] = part[wave];
 #pragma unroll
@@ -258,18 +265,24 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
                      :: "s"(m0v), "v"(off), "s"(base) : "memory", "m0");
       }
     };
+    clocks.lap(kPhaseSetup);
 #pragma unroll
     for (int s = 0; s < kSmRing - 1; ++s)
       if (s < stages) issue_stage(s);
+    clocks.lap(kPhaseIssue);
     for (int s = 0; s < stages; ++s) {
       // stage s has arrived when at most the copies of the (up to two) later stages are outstanding
       if (s + 2 < stages) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
       else if (s + 1 < stages) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      clocks.lap(kPhaseWait);
       __syncthreads();                                 // ... and stage s-1 is consumed
+      clocks.lap(kPhaseBarrier);
       if (s + kSmRing - 1 < stages) issue_stage(s + kSmRing - 1);
+      clocks.lap(kPhaseIssue);
     }
     __syncthreads();
+    clocks.lap(kPhaseBarrier);
   } else {
     // Range of row i0 + lane that this block owns, and its first column indices: one step of the searches
     // for both ends in every other stage (a chain of dependent loads), what is left after the loop.
@@ -297,12 +310,15 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
     };
     auto searching = [&]() { return __builtin_amdgcn_ballot_w64(lo[0] < hi[0] || lo[1] < hi[1]) != 0; };
     look();
+    clocks.lap(kPhaseSetup);
     for (int s = 0; s < stages; ++s) {
       __syncthreads();
+      clocks.lap(kPhaseBarrier);
       if ((s & 1) && searching()) {
         halve();
         look();
       }
+      clocks.lap(kPhaseScan);
     }
     while (searching()) {
       halve();
@@ -313,14 +329,21 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
     int pre[kSmAhead];
 #pragma unroll
     for (int e = 0; e < kSmAhead; ++e) pre[e] = lo[0] + e < lo[1] ? column_indices[lo[0] + e] : 0;
+    clocks.lap(kPhaseScan);
     __syncthreads();
+    clocks.lap(kPhaseBarrier);
     bound[0][lane] = lo[0];
     bound[1][lane] = lo[1];
 #pragma unroll
     for (int e = 0; e < kSmAhead; ++e) ahead[e][lane] = pre[e];
   }
+  clocks.lap(kPhaseRest);
   __syncthreads();
-  if (tid >= 512) return;
+  clocks.lap(kPhaseBarrier);
+  if (tid >= 512) {
+    clocks.store(blockIdx.x * (kSmThreads / 64) + wave);
+    return;
+  }
 
   // Eight threads per row take alternate entries of its range.
   const int rr = tid >> 3;
@@ -334,6 +357,8 @@ __global__ __launch_bounds__(kSmThreads) void sddmm_mfma_kernel(
     else val = sddmm_lane_dot(L + (size_t)row * n, R + (size_t)c * n, n);
     sddmm_store<_Float16>(out, scale, p, val);
   }
+  clocks.lap(kPhaseRest);
+  clocks.store(blockIdx.x * (kSmThreads / 64) + wave);
 }
 
 }  // namespace spdl

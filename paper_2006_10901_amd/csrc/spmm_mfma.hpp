@@ -67,6 +67,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
   constexpr int PRE = 2;                                // sixty-fours of a row fetched ahead
   constexpr int FLAT = 64 / NW;                         // sixty-fours of the panel's entries fetched ahead by a wave
   static_assert(KP == 2 || KP == 4, "a part of the rows for each wave of a tile");
+  PhaseClocks clocks;
+  clocks.start();
   const int kc_max = min((k + 15) & ~15, kMfmaChunk);
   const int stride = kc_max + kMfmaPad;                 // halves per panel row
   _Float16* panel = reinterpret_cast<_Float16*>(lds_raw);
@@ -208,7 +210,9 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
       load_rows(0, w[0]);
       load_rows(1, w[1]);
       clear_sums();
+      clocks.lap(kPhaseSetup);
       __syncthreads();
+      clocks.lap(kPhaseBarrier);
       // Ascending rows have ascending places in the panel, across rows too: an entry whose place is not above
       // its predecessor's shows a row that is not ascending.
       int row = __builtin_popcountll(__builtin_amdgcn_ballot_w64(row_start <= mine)) - 1;
@@ -312,6 +316,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
       __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll
       for (int u = 0; u < NS / 2; ++u) hold_rows(w[u]);
+      clocks.lap(kPhaseSetup);
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
         const int rr = wave + NW * i;
@@ -357,7 +362,9 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
 #pragma unroll
       for (int u = NS / 2; u < NS - 1; ++u) load_rows(u, w[u]);
     }
+    clocks.lap(kPhaseScan);
     __syncthreads();
+    clocks.lap(kPhaseBarrier);
     // first operands: rows c of the panel, columns 16*s + 8h .. +7 of the chunk
     const _Float16* ap = panel + c * stride + 8 * h + 16 * s_begin;
     auto fragment = [&](int s) __attribute__((always_inline)) {        // (the ragged step is the last in any order)
@@ -396,6 +403,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
     for (int u = 0; u < NS; ++u) hold_rows(w[u]);
+    clocks.lap(kPhaseSteps);
     if (ragged_last) {
       const int k0 = kc0 + 16 * (s_begin + full_steps);
       u32x4 tail[8];
@@ -404,6 +412,7 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
         tail[r] = __builtin_bit_cast(u32x4, (f16x8)*reinterpret_cast<const f16x8_any*>(bp + (size_t)min(k0 + 8 * h + r, k - 1) * n));
       step(full_steps, tail);
     }
+    clocks.lap(kPhaseGather);
   }
   // Register t of lane (c, h) in accumulator j is row 8*(t/4) + 4h + t%4, column `col` + j.  Wave `kpart`
   // of a tile finishes the quarters G * kpart .. of t; the others hand it theirs through LDS (the panel
@@ -479,15 +488,22 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
       }
     }
   };
+  clocks.lap(kPhaseRest);
   __syncthreads();
+  clocks.lap(kPhaseBarrier);
   if (active) {
     if (kpart == 0) hand_over(std::integral_constant<int, 0>{});
     else if (kpart == 1) hand_over(std::integral_constant<int, 1>{});
     else if (KP > 2 && kpart == 2) hand_over(std::integral_constant<int, KP - 2>{});
     else hand_over(std::integral_constant<int, KP - 1>{});
   }
+  clocks.lap(kPhaseRest);
   __syncthreads();
-  if (!active) return;
+  clocks.lap(kPhaseBarrier);
+  if (!active) {
+    clocks.store(blockIdx.x * NW + wave);
+    return;
+  }
   const unsigned unexpanded = (unsigned)__builtin_amdgcn_ballot_w64(lane < 32 && bad[lane & 31] != 0);
   bad_mask = unexpanded;
   if (kpart == 0) finish(std::integral_constant<int, 0>{});
@@ -523,6 +539,8 @@ __global__ __launch_bounds__(64 * WAVES * KP) void spmm_mfma_kernel(
     spmm_epilogue<_Float16, 4>(v, bias, row, relu);
     if (ok) Pack<_Float16, 4>::store(C + (size_t)row * n + col4, v);
   }
+  clocks.lap(kPhaseRest);
+  clocks.store(blockIdx.x * NW + wave);
 }
 
 }  // namespace spdl
