@@ -19,8 +19,10 @@
  *     values          [nnz]
  *   Dense matrices are row-major with no padding (leading dimension == number of columns).
  *   Sizes: m, k, n, nnz >= 0 and m*n, k*n < 2^31.  m == 0, n == 0 and nnz == 0 are valid.
- *   Base pointers must be aligned to their element type; 16-byte aligned bases and n % 4 == 0
- *   (n % 8 == 0 for fp16) select the widest vector path, anything else a narrower one.
+ *   Base pointers must be aligned to their element type.  The fast kernels take any alignment and
+ *   any n from 4 on (fp16 on the matrix cores: 8); rows that are whole 16-byte pieces at 16-byte
+ *   aligned addresses are the fastest, by a few percent in fp32 (n = 127: 95 us where n = 128
+ *   takes 90), and half-precision rows that start at odd elements (n odd) the slowest, by half.
  *   Non-finite inputs.  With finite inputs every result is the definition's.  An Inf or NaN in
  *   a row of a dense operand reaches the outputs that the definition makes depend on that row
  *   in every kernel; all SDDMM kernels, the fp32 SpMM kernels and the direct fp16 SpMM kernel
@@ -59,8 +61,8 @@ typedef enum {
  *               The result does not depend on it.
  *   B : DEVICE fp32[k*n];   C : DEVICE fp32[m*n], fully overwritten (empty rows become +0).
  *   Products and sums are fp32 (fused multiply-adds).  Most kernels add a row's products in
- *   stored order; when few long rows are spread over several lane groups, and in the kernel for
- *   attention-shaped problems (33..64 columns, which keeps a window of B around a band of A in
+ *   stored order; when few long rows are spread over several lane groups, and in the window kernel
+ *   (attention-shaped problems among others: it keeps a window of B around a band of A in
  *   on-chip memory and takes rows in their natural order), partial sums are added at the end.
  *   Either way the result is deterministic and does not depend on row_order. */
 int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
@@ -83,8 +85,10 @@ int spdl_sddmm(int m, int k, int n, int nnz, const int* row_offsets, const int* 
  * topology on the host: a window of the dense operand around the band is kept in on-chip memory
  * and only the scattered entries are gathered.  Where the band is, and whether there is one, is
  * found on the device; without a band every entry is gathered and the result is still right.
- * Used as given for fp32 with n % 4 == 0, 16-byte aligned dense operands and k*n < 2^29 (SDDMM:
- * n <= 128); any other problem runs exactly as through spdl_spmm / spdl_sddmm.  spdl_spmm and
+ * The hint takes effect for fp32 with n % 4 == 0, 16-byte aligned dense operands and k*n < 2^29
+ * (SDDMM: n <= 128); any other problem runs exactly as through spdl_spmm / spdl_sddmm.  Where it
+ * does, outputs of at most 32 columns (SpMM) and masks whose rows would leave much of the machine idle in
+ * the window kernel (SDDMM, by m and nnz) are gathered all the same.  spdl_spmm and
  * spdl_sddmm pick these kernels themselves for shapes like that of an attention head (thousands of
  * rows of a hundred entries or more, 33..128 columns), where they are also the faster way to
  * gather. */
@@ -100,7 +104,7 @@ int spdl_sddmm_banded(int m, int k, int n, int nnz, const int* row_offsets, cons
  * difference is the choice of kernel, which the library cannot make by itself because it never
  * reads the row lengths on the host: kernels whose work per wave does not depend on the length of
  * a row (SpMM: a wave per row, what a row holds beyond its share dealt to all waves of the
- * workgroup; SDDMM: the entries split evenly over the waves, or for dot products of more than 256
+ * workgroup; SDDMM: the entries split evenly over the waves, or for dot products of more than 128
  * columns the kernel estimated faster without the one that keeps partial sums per row).  fp32,
  * n % 4 == 0, 16-byte aligned dense operands and k*n < 2^29; any other problem runs exactly as
  * through spdl_spmm / spdl_sddmm.  On matrices with rows of similar length these entry points are

@@ -27,7 +27,7 @@ MICROBENCH_BIN = os.path.join(_HERE, "microbench", "inner_loop_rates")
 
 def build_microbench(verbose: bool = False) -> str:
     """The stand-alone program that measures the issue rates bounding the kernels' inner loops
-    (run it on the GPU machine: paper_2006_10901_amd/microbench/inner_loop_rates)."""
+    (run it on the GPU: paper_2006_10901_amd/microbench/inner_loop_rates)."""
     flags = [f for f in HIP_FLAGS if f not in ("-fPIC", "-shared")]
     cmd = [HIPCC, *flags, "-o", MICROBENCH_BIN, MICROBENCH_SRC]
     if verbose:

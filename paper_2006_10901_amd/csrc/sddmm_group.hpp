@@ -6,7 +6,7 @@
 // lane t, which stores it (same section: partial results for all outputs of the tile, then a
 // reduction with shuffles).  Column indices are loaded once per strip, pre-scaled to row
 // offsets of R, and handed out by DPP row broadcasts.
-// Needs n % 4 == 0, 16-byte aligned L and R (8-byte for fp16) and k*n < 2^31.
+// Any n from 4 on, any element alignment; k*n < 2^31.
 #pragma once
 #include "common.hpp"
 

@@ -34,7 +34,8 @@
 // Rows must be ascending for the slab walk; a row that is not is noticed when its nonzeros
 // inside a slab are not a prefix of the look-ahead, its cursor is frozen, and the row is redone
 // by direct gathers after the last slab.
-// Needs n % 4 == 0, n <= 128 per launch, 16-byte aligned L and R.
+// 4 <= n <= 128 per launch, any element alignment: the lane at a row's end works on the row's last piece, L zero
+// where the piece before has the column, and a sum that came out as NaN is looked at again.  (NT: see below.)
 //
 // Row order (optional): see the row setup below.
 //
@@ -50,8 +51,8 @@
 // the same section's footnote).  A slab is then 128 consecutive columns of every row of Rn.  It
 // is fetched as it lies (rows of 512 contiguous bytes, direct-to-LDS, while the previous slab
 // is being worked on) into a staging area and transposed from there into the layout above by
-// LDS reads and writes, between two barriers; one slab buffer instead of two.  Needs k % 4 == 0
-// and a 16-byte aligned Rn as well.
+// LDS reads and writes, between two barriers; one slab buffer instead of two.  Needs n % 4 == 0, k % 4 == 0
+// and 16-byte aligned L and Rn.
 #pragma once
 #include "common.hpp"
 #include "sddmm_group.hpp"

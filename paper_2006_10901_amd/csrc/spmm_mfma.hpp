@@ -31,9 +31,9 @@
 // first loads of B go out before the offsets of the rows are there, ahead of the entries of the panel; steps
 // past the end load nothing (with no lane active) instead of something unused; workgroups that share a
 // tile's columns of B run on one XCD; and the waves that share a tile each finish their part of its rows.  
-// (1024 x 1024 at 10 %, n = 3136: 23.4 us before all of this, 18.7 with it; with B in memory rather than
-// in a cache, a third more in both.  Of some 17 us in the kernel: 2 until the entries are here and the panel is clear, 2.5 to fill it, 10 main
-// loop, 2 to exchange, convert and store.)
+// (1024 x 1024 at 10 %, n = 3136: 23.4 us before all of this, 18.3 with it; with B in memory rather than
+// in a cache, a quarter more.  Of a wave's time, by clocks inside the kernel: 14 % until the entries are here and the panel
+// is clear, 13 to fill it, 54 main loop, 12 to exchange, convert and store, 7 at barriers.)
 #pragma once
 #include <type_traits>
 #include "common.hpp"

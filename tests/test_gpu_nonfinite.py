@@ -2,8 +2,9 @@
 that the definition makes depend on that row (paper Sec. "Sparse Matrix Computation": SpMM sums
 over the stored entries of a row only, SDDMM takes one dot product per stored entry).  Every fp32
 kernel family and the direct fp16 kernels are held to that; the fp16 matrix-core SpMM multiplies
-the zeros of its expanded 32-row panels by whole rows of B, and the documented consequence (NaN in
-that column of C for every row, no other column touched) is asserted instead."""
+the zeros of its expanded 32-row panels by whole rows of B, and for whole aligned pieces of matrices
+with one position in 32 stored the documented consequence (NaN in that column of C for every row, no other
+column touched) is asserted instead."""
 import numpy as np
 import pytest
 

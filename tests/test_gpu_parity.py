@@ -677,7 +677,7 @@ def test_mfma_kernels_edge_cases(g, oracle_lib, force, n):
         assert spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 2, 0, 0)["variant"]) == "mfma"
         spmm_case(g, oracle_lib, A, B, n, g.TOL_F16, "sorted", f"mfma spmm n={n} m={A.m} k={A.k}")
         sddmm_case(g, oracle_lib, A, L, R, n, g.TOL_F16, f"mfma sddmm n={n} m={A.m} k={A.k}")
-        # the direct-gather kernels on the same inputs (what n % 8 != 0 or a sparser matrix would run)
+        # the direct-gather kernels on the same inputs (what a sparser matrix would run)
         force(0, 0)
         force(1, 1)
         spmm_case(g, oracle_lib, A, B, n, g.TOL_F16, "sorted", f"rowsplit spmm f16 n={n}")
@@ -761,7 +761,7 @@ def test_mfma_kernels_are_the_default_for_moderately_sparse_fp16(g):
     assert spdl.spdl_variant_name(0, spdl.spdl_select_spmm(1024, 1024, 3136, 10400, 2, 0, 0)["variant"]) == "rowsplit"
     assert spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(1024, 1024, 3136, 10400, 2, 0, 0)["variant"]) == "mfma"
     assert spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(2048, 2048, 64, 41000, 2, 0, 0)["variant"]) == "group"
-    # fp32 never takes them, n % 8 != 0 neither
+    # fp32 never takes them, SpMM with n % 8 == 4 neither
     assert spdl.spdl_variant_name(0, spdl.spdl_select_spmm(1024, 1024, 3136, 104000, 4, 0, 0)["variant"]) != "mfma"
     assert spdl.spdl_variant_name(0, spdl.spdl_select_spmm(1024, 1024, 3132, 104000, 2, 0, 0)["variant"]) == "rowsplit"
 
