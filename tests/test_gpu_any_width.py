@@ -339,3 +339,16 @@ def test_spmm_any_width_keeps_non_finite_values_where_they_belong(g, oracle_lib,
     tol = (g.TOL_F16 if dtype == np.float16 else g.TOL_F32) * np.where(np.isfinite(S), S, 0.0)
     assert_same_where_finite(dC.cpu().numpy().astype(np.float64), C, tol, g.ATOL_F16_STORE if dtype == np.float16 else 0.0)
     assert frame_intact(cbuf, at, A.m * n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_sddmm_of_fewer_than_four_columns_at_any_element(g, oracle_lib, n):
+    """An entry per lane: scaled and not, rows that are not ascending, operands one element off, half precision."""
+    for A in (wl.uniform_mask_csr(700, 1111, 0.12, 7500 + n), wl.adversarial_csr(203, 700, 7501 + n, sorted_cols=False)):
+        for shift, scaled in ((0, False), (1, True)):
+            chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float32, -1, shift, scaled)
+            assert chosen == "rowstrip"
+            g.assert_close(got, ref, S, g.TOL_F32, f"sddmm n={n} shift={shift} scaled={scaled}")
+        A.values = A.values.astype(np.float16)
+        chosen, got, ref, S = sddmm_any(g, oracle_lib, A, n, np.float16, -1, 1)
+        g.assert_close(got, ref, S, g.TOL_F16, f"sddmm f16 n={n}")
