@@ -139,6 +139,12 @@ bool slab_usable(int n, int nnz, const void* B, const void* C) {
 // against 256 for row splitting with one column per lane; 4096 x 1024 at 10 %, n = 1001: 38 against 93.)
 inline bool slab_dma_usable(int n, int nnz) { return n >= 4 && n < (1 << 21) && nnz < (1 << 29); }
 
+// Chain of work in front of the slowest compute unit when every panel's work is dealt to `parts` workgroups of `units`
+// each (see split_for_machine).
+double split_chain(int panels, int parts, int units, int slots = kComputeUnits) {
+  return (double)((slab_xcd_load(panels, parts) + slots / 8 - 1) / (slots / 8)) * (units + 2.0);
+}
+
 // A slab kernel's workgroup fills a compute unit (LDS), so a grid of more than `slots` workgroups
 // runs in rounds.  `total` units of work per panel (tiles of C, slabs of A's columns), walked back
 // to back by one workgroup, are dealt to the number of workgroups per panel that gives the shortest
@@ -152,8 +158,7 @@ int split_for_machine(int panels, int total, int slots = kComputeUnits) {
   double best = 1e300;
   for (int parts = 1; parts <= std::min(total, slots); ++parts) {
     const int units = (total + parts - 1) / parts;
-    const int64_t wgs = slab_xcd_load(panels, (total + units - 1) / units);
-    const double cost = (double)((wgs + slots / 8 - 1) / (slots / 8)) * (units + 2.0);
+    const double cost = split_chain(panels, (total + units - 1) / units, units, slots);
     if (cost < best - 1e-9) {
       best = cost;
       best_units = units;
@@ -718,11 +723,29 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       const bool slab = fp32_fast && reuse >= 2.0 &&
                         (n >= 128 || reuse >= 8.0 || (reuse >= 5.0 && m >= 8192) || (reuse >= 4.0 && whole_rounds) ||
                          (reuse >= 4.2 && m >= 2048 && m != k && n > 16));
-      // (Few entries: the nonzero-split kernel is done before the others have filled their first slabs.  850 x 434
-      // at 25 %, n = 40, 93 thousand: 5.4 us against 10.3; 2792 x 2079 at 2 %, n = 96, 120 thousand: 9.1 against
-      // 10.6; 2124 x 2983 at 4 %, n = 72, 230 thousand: 11.9 against 11.3; 2328 x 1585 at 7 %, n = 43, 270 thousand: 9.4 against
-      // 11.4.)
-      variant = nnz < (n <= 64 ? 300000 : 170000) ? kSddmmGroup : lane ? kSddmmLane : slab ? kSddmmSlabDma : kSddmmGroup;
+      // Few entries: the nonzero-split kernel may be done before the others have filled their first slabs (850 x 434
+      // at 25 %, n = 40, 93 thousand: 5.4 us against 10.3), unless rows are short, which leaves most of a strip of 16
+      // empty (4096 x 128, rows of 4, n = 128: 12.0 against 6.3 in the lane kernel), or the slabs few (2048 x 1000, rows of 40,
+      // n = 128: 8.4 against 6.9).  Estimates in microseconds, from the chain of slabs, the entries that a lane group meets in
+      // its slabs and the strips; fitted on 720 uniform shapes of 512 .. 10000 rows, 128 .. 10000 columns, rows of 3 .. 200
+      // and n = 20 .. 128 (the choice takes 1.01 times the faster one's time on average, 1.14 at worst beyond 64 columns).
+      bool few = nnz < (n <= 64 ? 300000 : 170000);
+      if (few && (lane || slab)) {
+        const double entries = 1e-5 * (double)nnz, row = (double)nnz / (double)m, strips = std::max(1.0, 16.0 / std::max(row, 1e-3));
+        const double t_group = n <= 64 ? 2.5 + 1.5 * entries + 1.6 * strips : 2.5 + 2.9 * entries + 2.3 * strips;
+        double t_other;
+        if (lane) {
+          const SddmmLaneShape sh = sddmm_lane_shape(m, k, nnz);
+          const double met = sh.rpg * row * std::min(1.0, (double)sh.spp * kLaneS / (double)k);
+          t_other = (sh.rpg == 2 ? 3.5 : 2.1) + 1.1 * split_chain(sh.panels, sh.ksplit, sh.spp) + 0.052 * met + 1.1 * entries;
+        } else {
+          const SddmmSlabShape sh = sddmm_slab_shape(m, k, n);
+          const double met = row * std::min(1.0, (double)sh.spp * sh.S / (double)k);
+          t_other = 1.4 + 1.1 * split_chain(sh.panels, sh.ksplit, sh.spp) + 0.057 * met + 0.6 * entries;
+        }
+        few = t_group <= t_other;
+      }
+      variant = few ? kSddmmGroup : lane ? kSddmmLane : slab ? kSddmmSlabDma : kSddmmGroup;
       // The shape of an attention head (33..64 columns, thousands of rows of a few hundred entries,
       // at most 1/8 dense; paper Sec. "Application: Sparse Transformer"): the window kernel, which is
       // the nonzero-split kernel with the rows of R around a band taken from LDS and the four lane

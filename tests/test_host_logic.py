@@ -179,6 +179,19 @@ def test_sddmm_selection_for_long_dot_products(spdl):
     assert chosen(760, 231, 2048, 0.43) == "group"              # 24 workgroups of slabs on 256 compute units
 
 
+def test_sddmm_selection_with_few_entries(spdl):
+    """Few entries: the nonzero-split kernel, unless rows are short (strips of 16 mostly empty) or the slabs few."""
+    def chosen(m, k, n, nnz):
+        return spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(m, k, n, nnz, 4, 0, 0)["variant"])
+    assert chosen(850, 434, 40, 92225) == "group"             # measured: 5.4 us against 10.3
+    assert chosen(2792, 2079, 96, 120000) == "group"          # 9.1 against 10.6
+    assert chosen(4096, 128, 128, 4096 * 4) == "lane"         # 6.3 against 12.0
+    assert chosen(2048, 1000, 128, 2048 * 40) == "lane"       # 6.9 against 8.4
+    assert chosen(5995, 203, 128, 5995 * 3) == "group"        # a panel does not meet every row of R
+    assert chosen(512, 512, 128, 26214) == "group"
+    assert chosen(4096, 512, 128, 1) == "group"
+
+
 def test_spmm_selection_of_the_window_kernel(spdl):
     """One or two 64-column tiles, a few hundred entries per row or more, thousands of rows, and a
     shape the slab kernel does not take: the shape of an attention head (paper Sec. "Application:
