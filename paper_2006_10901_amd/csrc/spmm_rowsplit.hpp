@@ -47,12 +47,17 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
   // before the gathers of the current one are waited for, so a batch costs one memory latency
   // (the rows of B), not two in a row (indices, then rows).  The indices go first: the gathers' addresses
   // wait for them alone.  (The values first, with lane groups of 8 and 16 and narrow pieces: 8000 rows of 300, n = 5: 30.7 us
-  // against 23.0; 1420 rows of 184, n = 11: 13.5 against 10.8; elsewhere level.)
+  // against 23.0; 1420 rows of 184, n = 11: 13.5 against 10.8; elsewhere level.  Not where a wave has one row: scalar loads.)
+  auto fetch = [&](int q, float& value, int& column) __attribute__((always_inline)) {
+    if (G == kWave) value = (float)values[q];
+    column = (int)column_indices[q];
+    if (G < kWave) value = (float)values[q];
+  };
   float a[U];
   int c[U];
   if (p + U <= end) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) { c[u] = (int)column_indices[p + u]; a[u] = (float)values[p + u]; }
+    for (int u = 0; u < U; ++u) fetch(p + u, a[u], c[u]);
   }
   for (; p + U <= end; p += SEG * U) {
     float b[U][VEC];
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
     const int pn = p + SEG * U;
     if (pn + U <= end) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) { cn[u] = (int)column_indices[pn + u]; an[u] = (float)values[pn + u]; }
+      for (int u = 0; u < U; ++u) fetch(pn + u, an[u], cn[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
