@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 
 from . import loads_in_flight
@@ -85,7 +86,7 @@ def build_library(verbose: bool = False) -> str:
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + proc.stdout)
-    loads_in_flight.check(LIB_PATH, os.path.dirname(os.path.dirname(HIPCC)))
+    loads_in_flight.check(LIB_PATH, os.path.dirname(os.path.dirname(shutil.which(HIPCC) or HIPCC)))
     return LIB_PATH
 
 
