@@ -26,6 +26,7 @@
 #include "spmm_window.hpp"
 #include "spmm_slab_tiles.hpp"
 #include "sddmm_window.hpp"
+#include "sddmm_split.hpp"
 
 namespace {
 
@@ -656,6 +657,43 @@ int launch_sddmm_lane(const SddmmLaneShape& sh, int grid, int m, int k, int n, i
              ? SPDL_OK : SPDL_ERR_LAUNCH;
 }
 
+// Launch shape of the matrix-core form: 64 sparse rows per workgroup, the steps of 256 columns dealt to `parts`
+// workgroups per panel; sixteens of the dot product (an odd number of them only where that is five, 65 .. 80 columns);
+// sixty-fours of a row's entries fetched a step ahead (mean + 1.5 sigma).
+struct SddmmSplitShape { int parts, spp, ksteps, ahead, panels, grid; };
+SddmmSplitShape sddmm_split_shape(int m, int k, int n, int nnz) {
+  SddmmSplitShape sh;
+  sh.panels = (m + kSpRows - 1) / kSpRows;
+  const int total = std::max(1, (k + kSpCols - 1) / kSpCols);
+  sh.spp = split_for_machine(sh.panels, total);
+  sh.parts = (total + sh.spp - 1) / sh.spp;
+  sh.ksteps = std::max(2, (n + 15) / 16);
+  if (sh.ksteps != 5) sh.ksteps = (sh.ksteps + 1) / 2 * 2;
+  const double mean = (double)nnz / ((double)m * (double)k) * kSpCols;
+  sh.ahead = mean + 1.5 * std::sqrt(mean) <= 64.0 ? 1 : 2;
+  sh.grid = 8 * (int)(((int64_t)sh.panels * sh.parts + 7) / 8);
+  return sh;
+}
+// Waves that pick: what the entries of a step take is covered by its multiplications where they last long enough, and
+// a multiplying wave then has a third of a SIMD's registers; for up to 32 columns eight waves (8192 x 10240 at 20 %, n = 32:
+// 51 us against 66 with four; n = 64: 94 against 76).
+constexpr int sddmm_split_pickers(int ksteps) { return ksteps <= 2 ? 8 : 4; }
+
+template <int KSTEPS, int AHEAD, int PICKERS>
+int launch_sddmm_split(const SddmmSplitShape& sh, int m, int k, int n, int nnz, const int* ro, const int* ci, const float* L,
+                       const float* R, float* out, const float* scale, hipStream_t st) {
+  static std::atomic<bool> configured[2];
+  constexpr int lds = sddmm_split_lds_bytes(KSTEPS);
+  auto kernel = scale ? sddmm_split_kernel<KSTEPS, AHEAD, PICKERS, true> : sddmm_split_kernel<KSTEPS, AHEAD, PICKERS, false>;
+  if (!configured[scale != nullptr].load()) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+      return SPDL_ERR_LAUNCH;
+    configured[scale != nullptr].store(true);
+  }
+  kernel<<<dim3(sh.grid), dim3(64 * (kSpWaves + PICKERS)), lds, st>>>(m, k, n, nnz, sh.parts, sh.spp, ro, ci, L, R, out, scale);
+  return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
+}
+
 template <typename T>
 bool sddmm_lane_usable(int n, int nnz, const void* L, const void* R) {
   // (dot products longer than 128 columns take one pass per 128 columns; 32-bit byte offsets inside
@@ -671,6 +709,35 @@ bool sddmm_lane_usable(int n, int nnz, const void* L, const void* R) {
 inline bool sddmm_any_width(int n) { return n >= 4; }
 inline bool sddmm_wide_any(int n) { return n >= 4 && (n <= 128 || n >= 192); }
 inline bool sddmm_lane_pass_ok(int n) { return n % 128 == 0 || n % 128 >= 4; }
+
+// Dense matrices, dot products of up to 128 columns: whether the matrix-core form takes the place of the lane and slab
+// kernels.  Estimates in microseconds: rounds of one workgroup per compute unit, each of so many steps (slabs) and
+// thousand entries.  Fitted on 400 uniform shapes (256 .. 12000 rows, 256 .. 10200 columns, 3 .. 40 %, n = 9 .. 128: 7 % off for
+// the matrix cores, 14 % and 6 % for the lane and slab kernels, 10 % for the nonzero-split one; the choice takes 1.005 times
+// the faster one's time on average, 0.84 times that of never).
+inline double sddmm_split_estimate(int m, int k, int n, int nnz) {
+  const SddmmSplitShape sh = sddmm_split_shape(m, k, n, nnz);
+  const double rounds = split_chain(sh.panels, sh.parts, -1), density = (double)nnz / ((double)m * (double)k);
+  const double entries = 1e-3 * kSpRows * std::min((double)k, (double)sh.spp * kSpCols) * density;
+  return 0.2 + rounds * (4.4 + sh.spp * (0.28 + 0.63 * sh.ksteps) + 0.27 * entries);
+}
+bool sddmm_split_runs(int variant, int m, int k, int n, int nnz) {
+  if ((variant != kSddmmLane && variant != kSddmmSlabDma) || n < 4 || n > 128 || m < 256 || k < kSpCols / 2 || nnz <= 0 ||
+      nnz >= (1 << 29))
+    return false;
+  const double density = (double)nnz / ((double)m * (double)k);
+  double other;
+  if (variant == kSddmmLane) {
+    const SddmmLaneShape sh = sddmm_lane_shape(m, k, nnz);
+    const double entries = 1e-3 * kSdRows * sh.rpg * std::min((double)k, (double)sh.spp * kLaneS) * density;
+    other = 5.7 + split_chain(sh.panels, sh.ksplit, -1) * (1.6 * sh.spp - 1.2 + 1.38 * entries);
+  } else {
+    const SddmmSlabShape sh = sddmm_slab_shape(m, k, n);
+    const double entries = 1e-3 * kSdRows * std::min((double)k, (double)sh.spp * sh.S) * density;
+    other = 3.9 + split_chain(sh.panels, sh.ksplit, -1) * (1.28 * sh.spp + 0.4 + 1.38 * entries);
+  }
+  return sddmm_split_estimate(m, k, n, nnz) <= 0.97 * other;
+}
 
 template <typename T>
 void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R, spdl_launch_info* info,
@@ -722,7 +789,10 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       // against 23.3 for gathers and 27.1 for the window kernel; 7500 x 4019 at 11 %, n = 48: 33.5 against 40.4)
       const bool slab = fp32_fast && reuse >= 2.0 &&
                         (n >= 128 || reuse >= 8.0 || (reuse >= 5.0 && m >= 8192) || (reuse >= 4.0 && whole_rounds) ||
-                         (reuse >= 4.2 && m >= 2048 && m != k && n > 16));
+                         (reuse >= 4.2 && m >= 2048 && m != k && n > 16)) ||
+                        // (the matrix-core form where it is estimated below gathering as well; not for square matrices)
+                        (fp32_fast && n <= 64 && m != k && sddmm_split_runs(kSddmmSlabDma, m, k, n, nnz) &&
+                         sddmm_split_estimate(m, k, n, nnz) <= 4.0 + 12.3e-6 * (double)nnz);
       // Few entries: the nonzero-split kernel may be done before the others have filled their first slabs (850 x 434
       // at 25 %, n = 40, 93 thousand: 5.4 us against 10.3), unless rows are short, which leaves most of a strip of 16
       // empty (4096 x 128, rows of 4, n = 128: 12.0 against 6.3 in the lane kernel), or the slabs few (2048 x 1000, rows of 40,
@@ -743,6 +813,8 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
           const double met = row * std::min(1.0, (double)sh.spp * sh.S / (double)k);
           t_other = 1.4 + 1.1 * split_chain(sh.panels, sh.ksplit, sh.spp) + 0.057 * met + 0.6 * entries;
         }
+        if (m != k && sddmm_split_runs(lane ? kSddmmLane : kSddmmSlabDma, m, k, n, nnz))
+          t_other = std::min(t_other, sddmm_split_estimate(m, k, n, nnz));
         few = t_group <= t_other;
       }
       variant = few ? kSddmmGroup : lane ? kSddmmLane : slab ? kSddmmSlabDma : kSddmmGroup;
@@ -844,6 +916,16 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_x = (m + waves - 1) / waves;
     return;
   }
+  if (sizeof(T) == 4 && sddmm_split_runs(variant, m, k, n, nnz)) {
+    const SddmmSplitShape sh = sddmm_split_shape(m, k, n, nnz);
+    info->vec = 8;
+    info->lanes_per_row = kWave;
+    info->rows_per_block = kSpRows;
+    info->block_threads = 64 * (kSpWaves + sddmm_split_pickers(sh.ksteps));
+    info->grid_x = sh.grid;
+    info->grid_y = sh.parts;                // column ranges of A (the grid is 1-D)
+    return;
+  }
   if (variant == kSddmmLane) {
     const SddmmLaneShape sh = sddmm_lane_shape(m, k, nnz, n > 128);
     info->vec = 8;
@@ -943,6 +1025,18 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
       kernel<<<dim3(li.grid_x), dim3(kSmThreads), kSddmmMfmaLdsBytes, st>>>(m, k, n, li.grid_y, ro, ci, L, R, out, scale);
       return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
     } else {
+      return SPDL_ERR_UNSUPPORTED;
+    }
+  }
+  if constexpr (sizeof(T) == 4) {
+    if (sddmm_split_runs(li.variant, m, k, n, nnz)) {
+      const SddmmSplitShape sh = sddmm_split_shape(m, k, n, nnz);
+#define SPDL_SPLIT(KSTEPS, AHEAD)               \
+  if (sh.ksteps == KSTEPS && sh.ahead == AHEAD) \
+    return launch_sddmm_split<KSTEPS, AHEAD, sddmm_split_pickers(KSTEPS)>(sh, m, k, n, nnz, ro, ci, L, R, out, scale, st);
+      SPDL_SPLIT(2, 1) SPDL_SPLIT(4, 1) SPDL_SPLIT(5, 1) SPDL_SPLIT(6, 1) SPDL_SPLIT(8, 1)
+      SPDL_SPLIT(2, 2) SPDL_SPLIT(4, 2) SPDL_SPLIT(5, 2) SPDL_SPLIT(6, 2) SPDL_SPLIT(8, 2)
+#undef SPDL_SPLIT
       return SPDL_ERR_UNSUPPORTED;
     }
   }

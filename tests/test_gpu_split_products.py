@@ -1,0 +1,117 @@
+"""fp32 on the bf16 matrix cores (three terms per number): the dense forms of the SDDMM lane and slab kernels, against
+the oracle.  Tolerance: a product of terms leaves out less than 2^-23 of it, a sum of n products rounds at most n times:
+(n + 8) 2^-24 of the sum of absolute products."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def g():
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.fixture
+def force():
+    import paper_2006_10901_amd as spdl
+    yield spdl.spdl_force_variant
+    spdl.spdl_force_variant(0, -1)
+    spdl.spdl_force_variant(1, -1)
+
+
+def close(gpu, ref, S, n, what):
+    assert np.all(np.isfinite(gpu)), what
+    err = np.abs(gpu.astype(np.float64) - ref)
+    assert np.all(err <= (n + 8) * 2.0 ** -24 * S + 2.0 ** -149), (what, float(np.max(err / np.maximum(S, 1e-300))))
+
+
+def mask_csr(m, k, density, seed, odd_rows=True):
+    """A uniform mask; with `odd_rows` also empty and full rows, a row with a run of neighbours, rows in no order, duplicates."""
+    rng = np.random.default_rng(seed)
+    mask = rng.random((m, k)) < density
+    if odd_rows:
+        mask[[0, m // 2, m - 1]] = False
+        mask[[1, m - 2]] = True
+        mask[2] = False
+        mask[2, k // 3:k // 3 + 200] = True
+    ro = np.zeros(m + 1, np.int32)
+    ro[1:] = np.cumsum(mask.sum(1))
+    ci = np.nonzero(mask)[1].astype(np.int32)
+    if odd_rows:
+        for i in (5, m // 3, m - 3):
+            rng.shuffle(ci[ro[i]:ro[i + 1]])
+        ci[ro[7] + 3:ro[7] + 6] = ci[ro[7] + 3]
+    values = rng.standard_normal(len(ci)).astype(np.float32)
+    return wl.Csr(m, k, ro, ci, values)
+
+
+def runs_split(A, n):
+    import paper_2006_10901_amd as spdl
+    spdl.spdl_force_variant(1, 3 if n <= 64 else 5)
+    info = spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 4, 0, 0)
+    return info["lanes_per_row"] == 64 and info["rows_per_block"] == 64
+
+
+# (rows and columns around whole panels of 64 and whole steps of 256; densities on both sides of one and two sixty-fours
+# of look-ahead; widths around whole sixteens, the copies' 32, and the odd five sixteens)
+@pytest.mark.parametrize("m,k,density", [(300, 500, 0.8), (321, 513, 0.8), (256, 128, 0.85), (700, 1500, 0.6)])
+@pytest.mark.parametrize("n", [4, 7, 16, 17, 31, 32, 33, 64, 65, 75, 80, 81, 96])
+def test_sddmm_split_products(g, oracle_lib, force, m, k, density, n):
+    A = mask_csr(m, k, density, 9000 + m + n)
+    L, R = wl.dense(m, n, 9001 + n), wl.dense(k, n, 9002 + n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_split(A, n)
+    close(g.gpu_sddmm(A, L, R, n), ref, S, n, f"{m} x {k}, n = {n}")
+
+
+@pytest.mark.parametrize("m,k,n,density", [(517, 700, 127, 0.85), (517, 700, 128, 0.85), (4100, 2570, 128, 0.19),
+                                           (2049, 2305, 64, 0.12), (1999, 1025, 24, 0.07)])
+def test_sddmm_split_products_scaled_and_at_odd_addresses(g, oracle_lib, force, m, k, n, density):
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = mask_csr(m, k, density, 9100 + n)
+    L, R = wl.dense(m, n, 9101 + n), wl.dense(k, n, 9102 + n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_split(A, n)
+    d = g.DevCsr(A)
+    out = torch.full((A.nnz + 2,), float("nan"), device="cuda")
+    lpad, rpad = torch.full((m * n + 3,), float("nan"), device="cuda"), torch.full((k * n + 3,), float("nan"), device="cuda")
+    lpad[1:1 + m * n], rpad[2:2 + k * n] = g.dev(L).view(-1), g.dev(R).view(-1)
+    spdl.spdl_sddmm(m, k, n, A.nnz, d.ro, d.ci, lpad[1:1 + m * n].view(m, n), rpad[2:2 + k * n].view(k, n), out[1:-1])
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.isnan(got[0]) and np.isnan(got[-1])
+    close(got[1:-1], ref, S, n, f"odd addresses, {m} x {k}, n = {n}")
+    spdl.spdl_sddmm_scaled(m, k, n, A.nnz, d.ro, d.ci, d.val, g.dev(L), g.dev(R), out[1:-1])
+    torch.cuda.synchronize()
+    v = A.values.astype(np.float64)
+    close(out[1:-1].cpu().numpy(), v * ref, np.abs(v) * S, n, f"scaled, {m} x {k}, n = {n}")
+
+
+@pytest.mark.parametrize("n", [24, 75])
+def test_sddmm_split_products_keep_non_finite_values_and_the_whole_range(g, oracle_lib, force, n):
+    """Infinities and NaN reach the entries that depend on them and no others; numbers that no bf16 term can hold (too large
+    for a scaled high term, too small for a low one) cost time, not bits."""
+    m, k = 321, 513
+    A = mask_csr(m, k, 0.8, 9200 + n)
+    L, R = wl.dense(m, n, 9201 + n), wl.dense(k, n, 9202 + n)
+    assert runs_split(A, n)
+    for scale_l, scale_r in ((2.0 ** -100, 2.0 ** -20), (2.0 ** -126, 1.0), (2.0 ** -126, 2.0 ** 100), (2.0 ** 105, 2.0 ** -90), (2.0 ** 60, 2.0 ** 50)):
+        l, r = (L * np.float32(scale_l)).astype(np.float32), (R * np.float32(scale_r)).astype(np.float32)
+        ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, l, r)
+        # (a denormal product or sum is a multiple of 2^-149)
+        got = g.gpu_sddmm(A, l, r, n)
+        err = np.abs(got.astype(np.float64) - ref)
+        assert np.all(err <= (n + 8) * 2.0 ** -24 * S + n * 2.0 ** -149), (scale_l, scale_r)
+    L[3, 1], L[200, n - 1], R[100, 0], R[400, 2], R[512, n - 1] = np.inf, np.nan, -np.inf, np.nan, np.float32(3e38)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    got = g.gpu_sddmm(A, L, R, n).astype(np.float64)
+    inside = np.abs(ref) < 1e38
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < A.nnz // 20
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.all(np.abs(got[inside] - ref[inside]) <= (n + 8) * 2.0 ** -24 * S[inside])
