@@ -177,14 +177,38 @@ int slab_rows_per_group(int m, int n) {
   return tiles128 >= 2 * kComputeUnits ? 2 : 1;
 }
 
-// Workgroups of 8 waves (panels of 32 rows) for the copy-based kernel when panels of 64 rows would leave half
-// of the compute units or more without a workgroup: one workgroup per CU, as with panels of 64 rows.
-// (With slabs of 128 rows of B, so that two would share a CU, the scan, the waits and the barrier come twice as
-// often: 8192 x 5000 at 5 %, n = 64: 36.7 us against 26.7; 3976 x 4475 at 19 %, n = 76: 53.5 against 45.6.)  With
-// 130 tiles of 64 x 64 and more the full form is faster although some compute units
-// stay idle, because every slab of B is copied for 64 rows instead of 32 (130 tiles, 4104 x 5093 at
-// 11 %, n = 112: 61 us in halves, 50 whole; 188 tiles, 12000 x 4000, n = 64: 51 and 39; 240 tiles,
+// Products with so few positions keep a lane group per row: its sums are added in stored order and are the bits of the
+// other families, and it is on such small ones that results are compared between families.  (The launches take 5 .. 11 us;
+// sharing rows takes a tenth to a fifth off them: 203 x 700 at 15 %, n = 75: 8.4 us against 6.7, row-splitting 5.0.)
+inline bool slab_rows_stay_whole(int m, int k) { return (int64_t)m * (int64_t)k <= 384 * 384; }
+
+// Panels for the copy-based kernel when panels of 64 rows would leave half of the compute units or more without a
+// workgroup: rows shared by two or four lane groups (panels of 32 or 16 rows), one workgroup per CU as with panels of 64 rows.
+// Twice as many workgroups as compute units cost more than a half-empty machine (two groups instead of four, and
+// the reverse: 94 tiles, 3000 x 3000 at 10 %, n = 128: 19.4 us against 34.1; 64 tiles, 2048 x 8000 at 20 %, n = 100:
+// 65.8 against 48.1).  With 130 tiles of 64 x 64 and more the full form is faster although some compute units
+// stay idle, because every slab of B is copied for 64 rows instead of 32 (in halves of eight waves: 130 tiles, 4104 x
+// 5093 at 11 %, n = 112: 61 us in halves, 50 whole; 188 tiles, 12000 x 4000, n = 64: 51 and 39; 240 tiles,
 // 7640 x 4322 at 5 %, n = 104: 48 and 30).
+int slab_groups_per_row(int m, int k, int n) {
+  const int64_t tiles = (int64_t)((m + kSlabRows - 1) / kSlabRows) * ((n + kSlabTile - 1) / kSlabTile);
+  if (slab_rows_stay_whole(m, k)) return 1;
+  return 4 * tiles <= kComputeUnits ? 4 : 2 * tiles <= kComputeUnits ? 2 : 1;
+}
+
+// Pairs of a row that a lane of the copy-based slab kernel fetches at once: as few as make the rounds per slab fewest, for
+// a row with two standard deviations more than the mean of them.  (A longer piece takes longer to bring, a second
+// round waits for everything: 8192 x 10240, n = 128, with 2 / 3 / 4 pairs: 8 % 75.3 / 76.3 / 76.8 us, 10 % 89.4 / 85.9 /
+// 86.8, 15 % 120.9 / 112.5 / 109.3, 20 % 142.7 / 148.9 / 139.0, 25 % 175.5 / 172.5 / 179.7, 30 % 204 / 195 / 200.  Two pieces
+// per lane and round: 5 .. 15 us more at any density.)
+int slab_pairs_per_lane(int m, int k, int nnz, int share) {
+  const double mean = kSlabS * ((m > 0 && k > 0) ? (double)nnz / ((double)m * (double)k) : 1.0);
+  const double pairs = mean + 2.0 * std::sqrt(mean);
+  int best = 1;
+  for (int pw = 2; pw <= 4; ++pw)
+    if (std::ceil(pairs / (16.0 * share * pw)) < std::ceil(pairs / (16.0 * share * best))) best = pw;
+  return best;
+}
 
 // The tile-inner slab kernel looks 48 pairs ahead per row: usable where the mean count of a row's
 // pairs in one slab plus three standard deviations fits into that (a row with more takes extra
@@ -198,9 +222,12 @@ constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators th
 
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
-  const bool half = variant == kSpmmSlabDma && (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles <= kComputeUnits / 2;
-  const int rpg = (variant == kSpmmSlabDma && !half) ? slab_rows_per_group(m, n) : 1;
-  const int rows = (half ? kSlabRows / 2 : kSlabRows) * rpg;
+  // (small products with few tiles: workgroups of eight waves)
+  const bool half = variant == kSpmmSlabDma && slab_rows_stay_whole(m, k) &&
+                    (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles <= kComputeUnits / 2;
+  const int share = variant == kSpmmSlabDma ? slab_groups_per_row(m, k, n) : 1;
+  const int rpg = (variant == kSpmmSlabDma && share == 1 && !half) ? slab_rows_per_group(m, n) : 1;
+  const int rows = kSlabRows / (half ? 2 : share) * rpg;
   const int panels = (m + rows - 1) / rows;
   int tpw = slab_tiles_per_wg(panels, tiles);
   // wide outputs, two rows per group: the tile-inner kernel, at most kSlabTilesMax tiles per workgroup
@@ -208,7 +235,7 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   const int groups = (tiles + tpw - 1) / tpw;
   info->variant = variant;
   info->vec = 4;
-  info->lanes_per_row = 16;
+  info->lanes_per_row = 16 * share;
   info->rows_per_block = rows;
   info->block_threads = half ? kSlabThreads / 2 : kSlabThreads;
   info->grid_x = slab_grid_size(panels, groups);
@@ -330,9 +357,6 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // of at most 32 columns use half of a slab tile's lanes or less.  8192 x 8192 at 5 % density:
     // slab 58 us against 26 for gathers at n = 32, 56 against 45 at n = 64; at 10 % the slab kernel
     // wins at n = 64, 66 us against 82, and still loses at n = 32, 68 against 46.)
-    // (Wide outputs that leave half the compute units without a full-size workgroup run the slab kernel
-    // with workgroups of 8 waves and twice as many stages: 4096 x 4096 at 6 % density, n = 128: 31 us
-    // against 24 for the window kernel's gathers; at 12 % 39 against 42.)
     // (Two to four tiles and a B of fewer than 8192 rows, which the gathers then find in L2: the slab
     // kernel pays from 64 * density = 3 on; 16995 x 3895 at 3.2 %, n = 128: 89 us against 62 for
     // row-splitting, 5006 x 2875 at 4.1 %, n = 256: 38 against 26, while the LSTM matrix at 95 %
@@ -355,16 +379,19 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // hyperbola in the number of tiles.  n = 80 and 128, 2048 .. 9000 columns: 64 * density = 3.1 at 138
     // tiles, 2.5 at 170, 2.0 at 200, 1.7 at 250 (8000 x 5000 at 6 %, n = 128: 34 us against 52); n = 40 and
     // 64 some 15 % later (15800 x 5000 at 5 %, n = 64: 33 us against 47).)
-    // (At most half full: workgroups of half the rows, the same hyperbola.  On 110 random shapes of 50 .. 260
-    // tiles the two meet at 64 * density * tiles = 440 .. 480, below 72 tiles at 600: 779 x 3116 at 9 %, n = 392,
-    // 91 tiles: 22.8 us for both; 780 x 3120 at 6 %, n = 576, 117 tiles: 21 against 25; 598 x 2392 at 19 %, n = 296, 50
-    // tiles: 27 against 33.)
-    const double one_round_reuse = m == k || out_tiles > kComputeUnits        ? 5.0
-                                   : 2 * out_tiles <= kComputeUnits           ? (out_tiles < 72 ? 600.0 : 460.0) / (double)std::max<int64_t>(out_tiles, 1)
-                                                                              : (n <= kSlabTile ? 500.0 : 430.0) / (double)out_tiles;
+    // (At most half full: rows shared by lane groups, the same hyperbola.  On 200 random shapes of 4 .. 128 tiles, 256 .. 9000
+    // rows, 256 .. 10240 columns, 1 .. 40 %, n = 12 .. 1024, the two meet at 64 * density * tiles = 420, up to 32 columns at
+    // 640; the choice then takes 1.010 times the faster one's time on average.  2376 x 1055 at 11 %, n = 84, 76 tiles: 9.8 us against
+    // 10.6; 703 x 6857 at 24 %, n = 171, 33 tiles: 41 against 57; 6300 x 1681 at 9 %, n = 30, 99 tiles: 13.3 against 11.5.)
+    const bool few_tiles = m != k && 2 * out_tiles <= kComputeUnits && !slab_rows_stay_whole(m, k);
+    const double one_round_reuse = few_tiles                                   ? (n <= 32 ? 640.0 : 420.0) / (double)std::max<int64_t>(out_tiles, 1)
+                                   : m == k || out_tiles > kComputeUnits       ? 5.0
+                                   : 2 * out_tiles <= kComputeUnits            ? (out_tiles < 72 ? 600.0 : 460.0) / (double)std::max<int64_t>(out_tiles, 1)
+                                                                               : (n <= kSlabTile ? 500.0 : 430.0) / (double)out_tiles;
     // (fewer than 16 columns use a quarter of a tile's lanes or less: 9957 x 8063 at 28 %, n = 8: 182 us
     // against 135 for row-splitting)
     const double min_reuse = n < 16                                           ? 1.0e9
+                             : few_tiles                                      ? one_round_reuse
                              : n <= 32                                        ? 12.0
                              : n <= 64                                        ? (2 * out_tiles < kComputeUnits ? one_round_reuse : std::min(narrow_reuse, one_round_reuse))
                              : out_tiles < kComputeUnits                      ? one_round_reuse
@@ -375,9 +402,11 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     // (Dense matrices gain so much from the slab kernel that it pays with most compute units idle:
     // 6144 x 2048 at 35 %, n = 64, 96 workgroups: 36 us against 54 for row-splitting; 4096 x 4096 at
     // 50 %, 64 workgroups: 87 against 98; at 20 % and 35 % respectively the two are level.  48 tiles
-    // are enough at the densities above if the output is wider than one, 64 if B has more than 2048 rows (6064 x 3050
+    // are enough at the densities above if the output is wider than one, 33 if B has more than 2048 rows (6064 x 3050
     // at 18 %, n = 42, 95 tiles: 31 us against 40; up to there the gathers find B in L2), else 97.  Not square matrices.)
-    const int64_t min_tiles = (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
+    const int64_t min_tiles = (few_tiles && (n > kSlabTile || n <= 32))         ? 1
+                              : (few_tiles && (k > 2048 || reuse >= 16.0))    ? kComputeUnits / 8 + 1
+                              : (n > 32 && n <= 2 * kSlabTile && reuse >= 32.0)   ? kComputeUnits / 4
                               : (n > 32 && n <= 2 * kSlabTile && reuse >= 16.0) ? 3 * kComputeUnits / 8
                               : (m != k && n > kSlabTile)                       ? 3 * kComputeUnits / 16
                               : (m != k && n > 32 && k > 2048)                  ? kComputeUnits / 4
@@ -544,24 +573,30 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
     if constexpr (sizeof(T) == 4 && kInt32) {
       static std::atomic<bool> configured{false};
       auto kernel = spmm_slab_kernel<T, kSlabS>;
-      // 32 pairs fetched ahead per row.  Deeper look-ahead (4 or 6 chunks of 16) was measured
-      // on the 70-90 % sparse shapes: the longer scan per round costs more than the waits it saves.
-      const bool half = li.block_threads != kSlabThreads;
       const bool two_rows = li.rows_per_block == 2 * kSlabRows;
-      const void* dma_kernel_c = half       ? (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2, 8>
-                               : two_rows ? (const void*)spmm_slab_dma_kernel<kSlabS, 2, 2>
-                                          : (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2>;
-      const void* dma_kernel = dma_kernel_c;
+      const bool half = li.block_threads != kSlabThreads;
+#define SPDL_SLAB_FORMS(RPG, SHARE)                                                                               \
+  {(const void*)spmm_slab_dma_kernel<kSlabS, RPG, 1, SHARE>, (const void*)spmm_slab_dma_kernel<kSlabS, RPG, 2, SHARE>, \
+   (const void*)spmm_slab_dma_kernel<kSlabS, RPG, 3, SHARE>, (const void*)spmm_slab_dma_kernel<kSlabS, RPG, 4, SHARE>}
+      static const void* const forms[4][4] = {SPDL_SLAB_FORMS(2, 1), SPDL_SLAB_FORMS(1, 1), SPDL_SLAB_FORMS(1, 2),
+                                              SPDL_SLAB_FORMS(1, 4)};
+#undef SPDL_SLAB_FORMS
+      const void* const half_form = (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2, 1, 8>;
+      const int share = two_rows || half ? 1 : kSlabRows / li.rows_per_block;
+      const void* dma_kernel = half ? half_form
+                                    : forms[two_rows ? 0 : share == 1 ? 1 : share == 2 ? 2 : 3][slab_pairs_per_lane(m, k, nnz, share) - 1];
       // (two rows per group and 2 .. kSlabTilesMax tiles per workgroup: scanned once per slab for all tiles)
       if (li.variant == kSpmmSlabDma && two_rows && li.grid_y >= 2 && li.grid_y <= kSlabTilesMax &&
           slab_tiles_fits(m, k, nnz))
         dma_kernel = (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>;
       if (!configured.load()) {
-        for (const void* f : {(const void*)kernel, (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2>,
-                              (const void*)spmm_slab_dma_kernel<kSlabS, 2, 2>, (const void*)spmm_slab_dma_kernel<kSlabS, 1, 2, 8>,
-                              (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>})
+        for (const void* f : {(const void*)kernel, (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>, half_form})
           if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes) != hipSuccess)
             return SPDL_ERR_LAUNCH;
+        for (const auto& row : forms)
+          for (const void* f : row)
+            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes) != hipSuccess)
+              return SPDL_ERR_LAUNCH;
         configured.store(true);
       }
       const int panels = (m + li.rows_per_block - 1) / li.rows_per_block;

@@ -99,6 +99,97 @@ __device__ __forceinline__ void slab_steps(float (&acc)[4], float av, int off, c
   }
 }
 
+// The same steps for pairs that were fetched PW at a time: pair PW t + e of a group (value av[e], LDS offset off[e]) is in
+// its lane t.  Blocks of four pairs, in stored order.
+template <int PW, int BLOCK>
+__device__ __forceinline__ void wide_load(f32x4 (&bq)[4], const int (&off)[PW], const char* buf, int lane_b) {
+  constexpr int P = 4 * BLOCK;
+  bq[0] = *reinterpret_cast<const f32x4*>(buf + __builtin_amdgcn_update_dpp(0, off[(P + 0) % PW], 0x150 + (P + 0) / PW, 0xf, 0xf, false) + lane_b);
+  bq[1] = *reinterpret_cast<const f32x4*>(buf + __builtin_amdgcn_update_dpp(0, off[(P + 1) % PW], 0x150 + (P + 1) / PW, 0xf, 0xf, false) + lane_b);
+  bq[2] = *reinterpret_cast<const f32x4*>(buf + __builtin_amdgcn_update_dpp(0, off[(P + 2) % PW], 0x150 + (P + 2) / PW, 0xf, 0xf, false) + lane_b);
+  bq[3] = *reinterpret_cast<const f32x4*>(buf + __builtin_amdgcn_update_dpp(0, off[(P + 3) % PW], 0x150 + (P + 3) / PW, 0xf, 0xf, false) + lane_b);
+}
+#define SPDL_WIDE_FMA4(AV, B0, B1, B2, B3, LANE)                                              \
+  "v_fmac_f32_dpp %0, %" #AV ", %" #B0 " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_fmac_f32_dpp %1, %" #AV ", %" #B1 " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_fmac_f32_dpp %2, %" #AV ", %" #B2 " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_fmac_f32_dpp %3, %" #AV ", %" #B3 " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"
+template <int PW, int BLOCK>
+__device__ __forceinline__ void wide_fma(float (&acc)[4], const float (&av)[PW], const f32x4 (&bq)[4]) {
+  constexpr int P = 4 * BLOCK;
+#define SPDL_WIDE_FMA16(PRE)                                                                                         \
+  asm volatile(PRE SPDL_WIDE_FMA4(4, 8, 9, 10, 11, 24) SPDL_WIDE_FMA4(5, 12, 13, 14, 15, 25)                         \
+               SPDL_WIDE_FMA4(6, 16, 17, 18, 19, 26) SPDL_WIDE_FMA4(7, 20, 21, 22, 23, 27)                           \
+               : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])                                              \
+               : "v"(av[(P + 0) % PW]), "v"(av[(P + 1) % PW]), "v"(av[(P + 2) % PW]), "v"(av[(P + 3) % PW]),         \
+                 "v"(bq[0].x), "v"(bq[0].y), "v"(bq[0].z), "v"(bq[0].w), "v"(bq[1].x), "v"(bq[1].y),                 \
+                 "v"(bq[1].z), "v"(bq[1].w), "v"(bq[2].x), "v"(bq[2].y), "v"(bq[2].z), "v"(bq[2].w),                 \
+                 "v"(bq[3].x), "v"(bq[3].y), "v"(bq[3].z), "v"(bq[3].w),                                             \
+                 "n"((P + 0) / PW), "n"((P + 1) / PW), "n"((P + 2) / PW), "n"((P + 3) / PW))
+  if constexpr (BLOCK == 0) SPDL_WIDE_FMA16("s_nop 1\n\t");
+  else SPDL_WIDE_FMA16("");
+#undef SPDL_WIDE_FMA16
+}
+#undef SPDL_WIDE_FMA4
+// Block BLOCK is in `now`; the one after it is on its way into `next`.
+template <int PW, int BLOCK>
+__device__ __forceinline__ void wide_blocks(float (&acc)[4], const float (&av)[PW], const int (&off)[PW], const char* buf,
+                                            int lane_b, unsigned used, f32x4 (&now)[4], f32x4 (&next)[4]) {
+  constexpr int kBlocks = 4 * PW;
+  wide_fma<PW, BLOCK>(acc, av, now);
+  if constexpr (BLOCK + 1 < kBlocks) {
+    if ((used >> (4 * (BLOCK + 1) / PW)) != 0) {
+      if constexpr (BLOCK + 2 < kBlocks) wide_load<PW, BLOCK + 2>(now, off, buf, lane_b);
+      wide_blocks<PW, BLOCK + 1>(acc, av, off, buf, lane_b, used, next, now);
+    }
+  }
+}
+// `used`: lanes whose first pair some group needs.
+template <int PW>
+__device__ __forceinline__ void wide_steps(float (&acc)[4], const float (&av)[PW], const int (&off)[PW], const char* buf,
+                                           int lane_b, unsigned used) {
+  f32x4 bx[4], by[4];
+  wide_load<PW, 0>(bx, off, buf, lane_b);
+  wide_load<PW, 1>(by, off, buf, lane_b);
+  wide_blocks<PW, 0>(acc, av, off, buf, lane_b, used, bx, by);
+}
+
+// PW consecutive words of the column indices or the values, at any element alignment.
+template <typename V, int PW> struct __attribute__((packed, aligned(4))) SlabPiece { V v[PW]; };
+// A piece of pairs that was moved back by `by` places from the arrays' end (by <= 0: not moved).
+template <int PW>
+__device__ __forceinline__ void slab_piece_shift(int (&c)[PW], float (&a)[PW], int by) {
+#pragma unroll
+  for (int step = 0; step < PW - 1; ++step)
+#pragma unroll
+    for (int e = 0; e + 1 < PW; ++e) {
+      c[e] = step < by ? c[e + 1] : c[e];
+      a[e] = step < by ? a[e + 1] : a[e];
+    }
+}
+
+// Which pairs of a wave's rows lie in the slab, when lane t of the SHARE lane groups that share a row holds PW consecutive ones
+// of them: pair PW (SHARE t + g) + e of the row is in lane t of its group g, bit e of whose mask says that it lies there.
+template <int SHARE>
+struct SlabMask {
+  static constexpr unsigned long long kFirst = SHARE == 1 ? 0x0001000100010001ull : SHARE == 2 ? 0x0000000100000001ull : 1ull;
+  // each lane <- the lane with the pairs before; the first ones of their rows <- 0
+  static __device__ __forceinline__ unsigned long long lane_before(unsigned long long mk) {
+    if constexpr (SHARE == 1) return (mk << 1) & ~kFirst;
+    else if constexpr (SHARE == 2) return ((mk << 16) & 0xffff0000ffff0000ull) | ((mk >> 15) & 0x0000fffe0000fffeull);
+    else return (mk << 16) | ((mk >> 47) & 0xfffeull);
+  }
+  // whether some row's last lane is among them
+  static __device__ __forceinline__ bool full(unsigned long long mk) {
+    return (mk & (kFirst << (SHARE == 1 ? 15 : SHARE == 2 ? 31 : 63))) != 0;
+  }
+  // lanes of a group that some group needs
+  static __device__ __forceinline__ unsigned used(unsigned long long mk) {
+    const unsigned both = (unsigned)mk | (unsigned)(mk >> 32);
+    return (both | (both >> 16)) & 0xffffu;
+  }
+};
+
 // State of one sparse row inside a 16-lane group.
 struct SlabRow {
   int row, p_begin, p, row_end;
