@@ -25,6 +25,7 @@
 #include "spmm_slab_dma.hpp"
 #include "spmm_window.hpp"
 #include "spmm_slab_tiles.hpp"
+#include "spmm_slab_wide.hpp"
 #include "sddmm_window.hpp"
 #include "sddmm_split.hpp"
 
@@ -197,13 +198,13 @@ int slab_groups_per_row(int m, int k, int n) {
 }
 
 // Pairs of a row that a lane of the copy-based slab kernel fetches at once: as few as make the rounds per slab fewest, for
-// a row with two standard deviations more than the mean of them.  (A longer piece takes longer to bring, a second
+// a row with 1.75 standard deviations more than the mean of them.  (A longer piece takes longer to bring, a second
 // round waits for everything: 8192 x 10240, n = 128, with 2 / 3 / 4 pairs: 8 % 75.3 / 76.3 / 76.8 us, 10 % 89.4 / 85.9 /
 // 86.8, 15 % 120.9 / 112.5 / 109.3, 20 % 142.7 / 148.9 / 139.0, 25 % 175.5 / 172.5 / 179.7, 30 % 204 / 195 / 200.  Two pieces
 // per lane and round: 5 .. 15 us more at any density.)
 int slab_pairs_per_lane(int m, int k, int nnz, int share) {
   const double mean = kSlabS * ((m > 0 && k > 0) ? (double)nnz / ((double)m * (double)k) : 1.0);
-  const double pairs = mean + 2.0 * std::sqrt(mean);
+  const double pairs = mean + 1.75 * std::sqrt(mean);
   int best = 1;
   for (int pw = 2; pw <= 4; ++pw)
     if (std::ceil(pairs / (16.0 * share * pw)) < std::ceil(pairs / (16.0 * share * best))) best = pw;
@@ -220,6 +221,48 @@ inline bool slab_tiles_fits(int m, int k, int nnz) {
 }
 constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators that kernel keeps in registers
 
+// When the compute unit that is done last ends, in twentieths of the time of one 64-column tile of 128 rows: workgroups of `units`
+// tiles, `unit` twentieths each and a quarter of a tile of set-up, a panel's last one with what is left of its `tiles`, started in
+// order on the 32 compute units of the XCD with the most of them (slab_wg_map).  (unit * units below 500.)
+int slab_makespan(int panels, int tiles, int units, int unit) {
+  const int groups = (tiles + units - 1) / units, left = tiles - (groups - 1) * units;
+  const int jobs = slab_xcd_load(panels, groups);
+  constexpr int kSpan = 512;
+  int done[kSpan] = {}, now = 0, last = 0;        // compute units that end at a time (modulo kSpan)
+  done[0] = kComputeUnits / 8;
+  for (int i = 0; i < jobs; ++i) {
+    while (done[now % kSpan] == 0) ++now;
+    --done[now % kSpan];
+    const int end = now + 5 + unit * (i < panels / 8 * groups && i % groups == groups - 1 ? left : units);
+    ++done[end % kSpan];
+    last = std::max(last, end);
+  }
+  return last;
+}
+
+// Tiles of 128 columns (a lane owns eight) for outputs of two rows per group: where the last compute unit is estimated to end
+// earlier than with tiles of 64.  A tile of 128 costs 1.9 tiles of 64 in the form that scans once for up to four, 1.7 in the
+// other.  (110 random shapes, 512 .. 2048 by four times as many, both ways round, n = 256 .. 4096, 3 .. 25 %, both forms in turn:
+// the estimate's ratio is off by 4 and 5 % (one standard deviation); it picks the wide tiles for 39 of them, for 0.91 of the
+// time on average, 1.000 at worst, and leaves 0.1 % to a choice of the better one each time.)  The look-ahead holds at most 64 pairs per
+// row and slab: up to 48 for the mean and three standard deviations.
+bool slab_wide_runs(int m, int k, int n, int nnz) {
+  const double mean = (double)kWideS * (double)nnz / ((double)m * (double)k);
+  if (mean + 3.0 * std::sqrt(mean) + 1.0 > 48.0 || slab_rows_per_group(m, n) != 2 || slab_groups_per_row(m, k, n) != 1) return false;
+  const int tiles = (n + kSlabTile - 1) / kSlabTile, panels = (m + kWideRows - 1) / kWideRows;
+  int tpw = slab_tiles_per_wg(panels, tiles);
+  const bool inner = tpw >= 2 && slab_tiles_fits(m, k, nnz);
+  if (inner) tpw = std::min(tpw, kSlabTilesMax);
+  if (tpw > 24 || slab_xcd_load(panels, (tiles + tpw - 1) / tpw) > 4096) return false;       // (many rounds: all the same)
+  return slab_makespan(panels, (n + kWideTile - 1) / kWideTile, kWideTiles, inner ? 38 : 34) < slab_makespan(panels, tiles, tpw, 20);
+}
+// index of the look-ahead's 1, 2 or 4 pairs per lane: two standard deviations over the mean (4996 x 1249, 5 %: one pair 3 % faster than
+// two; 14 .. 17 %: two 1 .. 3 % faster than four; from 20 % on four as fast or up to 7 % faster)
+int slab_wide_pairs(int m, int k, int nnz) {
+  const double mean = (double)kWideS * (double)nnz / ((double)m * (double)k), pairs = mean + 2.0 * std::sqrt(mean);
+  return pairs <= 16.0 ? 0 : pairs <= 32.0 ? 1 : 2;
+}
+
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
   // (small products with few tiles: workgroups of eight waves)
@@ -232,6 +275,8 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   int tpw = slab_tiles_per_wg(panels, tiles);
   // wide outputs, two rows per group: the tile-inner kernel, at most kSlabTilesMax tiles per workgroup
   if (rpg == 2 && tpw >= 2 && slab_tiles_fits(m, k, nnz)) tpw = std::min(tpw, kSlabTilesMax);
+  // (tiles of 128 columns: two of them, reported as tiles of 64)
+  if (rpg == 2 && slab_wide_runs(m, k, n, nnz)) tpw = 2 * kWideTiles;
   const int groups = (tiles + tpw - 1) / tpw;
   info->variant = variant;
   info->vec = 4;
@@ -589,9 +634,16 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       if (li.variant == kSpmmSlabDma && two_rows && li.grid_y >= 2 && li.grid_y <= kSlabTilesMax &&
           slab_tiles_fits(m, k, nnz))
         dma_kernel = (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>;
+      const bool wide = li.variant == kSpmmSlabDma && two_rows && slab_wide_runs(m, k, n, nnz);
+      static const void* const wide_forms[3] = {(const void*)spmm_slab_wide_kernel<1>, (const void*)spmm_slab_wide_kernel<2>,
+                                                (const void*)spmm_slab_wide_kernel<4>};
+      if (wide) dma_kernel = wide_forms[slab_wide_pairs(m, k, nnz)];
       if (!configured.load()) {
         for (const void* f : {(const void*)kernel, (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>, half_form})
           if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes) != hipSuccess)
+            return SPDL_ERR_LAUNCH;
+        for (const void* f : wide_forms)
+          if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kWideLdsBytes) != hipSuccess)
             return SPDL_ERR_LAUNCH;
         for (const auto& row : forms)
           for (const void* f : row)
@@ -600,16 +652,21 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         configured.store(true);
       }
       const int panels = (m + li.rows_per_block - 1) / li.rows_per_block;
-      const int tiles = (n + kSlabTile - 1) / kSlabTile;
+      int tiles = (n + kSlabTile - 1) / kSlabTile;
       const dim3 grid(li.grid_x), block(li.block_threads);
       if (li.variant == kSpmmSlab) {
         kernel<<<grid, block, kSlabLdsBytes, st>>>(m, k, n, nnz, tiles, li.grid_y, panels, ro, ci, val, order, B, C,
                                                    bias, relu);
       } else {
-        int tpw = li.grid_y;
+        int tpw = li.grid_y, lds = kSlabLdsBytes;
+        if (wide) {
+          tiles = (n + kWideTile - 1) / kWideTile;
+          tpw = kWideTiles;
+          lds = kWideLdsBytes;
+        }
         void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, &tpw, (void*)&panels, &ro, &ci, &val, &order, &B, &C,
                         &bias, &relu};
-        if (hipLaunchKernel(dma_kernel, grid, block, args, kSlabLdsBytes, st) != hipSuccess) return SPDL_ERR_LAUNCH;
+        if (hipLaunchKernel(dma_kernel, grid, block, args, lds, st) != hipSuccess) return SPDL_ERR_LAUNCH;
       }
     } else {
       return SPDL_ERR_UNSUPPORTED;

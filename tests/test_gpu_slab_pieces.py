@@ -99,6 +99,19 @@ def test_slab_pieces(g, oracle_lib, force, m, k, n, density):
     assert np.array_equal(plain, got)
 
 
+# (tiles of 128 columns, two to a workgroup: whole, ragged, the last one alone, half a tile; one, two and four pairs per lane and
+# rows beyond them; rows and columns around whole panels and slabs of 128)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [(4100, 129, 2048), (4096, 260, 2046), (4000, 383, 1985), (2050, 128, 4100), (3970, 90, 2177)])
+@pytest.mark.parametrize("density", [0.03, 0.1, 0.2])
+def test_slab_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
+    A = odd_csr(m, k, density, 7200 + m + int(100 * density))
+    bias = np.random.default_rng(7201).standard_normal(m).astype(np.float32)
+    B, got = run(g, A, n, force, 7202 + n, oracle_lib.row_order(A.m, A.row_offsets), bias)
+    ref, S = oracle_lib.spmm_bias_relu(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B, bias, True)
+    close(A, got, ref, S + np.abs(bias)[:, None], f"{m} x {k}, n = {n}, {density}")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("nnz", [1, 2, 3, 4, 5, 63, 64, 65])
 @pytest.mark.parametrize("m,k", [(700, 400), (200, 400), (4200, 60)])
