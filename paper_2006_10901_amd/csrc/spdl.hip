@@ -240,6 +240,21 @@ int slab_makespan(int panels, int tiles, int units, int unit) {
   return last;
 }
 
+// Tiles of 128 columns that a workgroup computes, two at a time: as many as let the last compute unit end first.  (The next
+// two tiles' first slab is copied while the ones before are multiplied, and the rows' set-up is done once.  Two rounds of
+// workgroups made one, us: 4096 x 1024 at 10 %, n = 4096, 117.6 -> 112.6, at 15 % 152.4 -> 146.9, at 5 % 83.1 -> 78.8; 4804 x 1201 at 22 %,
+// n = 2992, 233 -> 227.  Where the longer workgroups do not fit the machine, the estimate keeps the short ones: 5444 x 1361 at 5 %,
+// n = 3992, 161.6 and 169.5.)
+int slab_wide_tiles(int m, int n) {
+  const int panels = (m + kWideRows - 1) / kWideRows, tiles = (n + kWideTile - 1) / kWideTile;
+  int best = kWideTiles, span = slab_makespan(panels, tiles, best, 38);
+  for (int t = 2 * kWideTiles; t <= 4 * kWideTiles && t <= tiles; t += kWideTiles) {
+    const int s = slab_makespan(panels, tiles, t, 38);
+    if (s < span) { best = t; span = s; }
+  }
+  return best;
+}
+
 // Tiles of 128 columns (a lane owns eight) for outputs of two rows per group: where the last compute unit is estimated to end
 // earlier than with tiles of 64.  A tile of 128 costs 1.9 tiles of 64 in the form that scans once for up to four, 1.7 in the
 // other.  (110 random shapes, 512 .. 2048 by four times as many, both ways round, n = 256 .. 4096, 3 .. 25 %, both forms in turn:
@@ -254,7 +269,7 @@ bool slab_wide_runs(int m, int k, int n, int nnz) {
   const bool inner = tpw >= 2 && slab_tiles_fits(m, k, nnz);
   if (inner) tpw = std::min(tpw, kSlabTilesMax);
   if (tpw > 24 || slab_xcd_load(panels, (tiles + tpw - 1) / tpw) > 4096) return false;       // (many rounds: all the same)
-  return slab_makespan(panels, (n + kWideTile - 1) / kWideTile, kWideTiles, inner ? 38 : 34) < slab_makespan(panels, tiles, tpw, 20);
+  return slab_makespan(panels, (n + kWideTile - 1) / kWideTile, slab_wide_tiles(m, n), inner ? 38 : 34) < slab_makespan(panels, tiles, tpw, 20);
 }
 // index of the look-ahead's 1, 2 or 4 pairs per lane: two standard deviations over the mean (4996 x 1249, 5 %: one pair 3 % faster than
 // two; 14 .. 17 %: two 1 .. 3 % faster than four; from 20 % on four as fast or up to 7 % faster)
@@ -275,7 +290,7 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   int tpw = slab_tiles_per_wg(panels, tiles);
   // wide outputs, two rows per group: the tile-inner kernel, at most kSlabTilesMax tiles per workgroup
   if (rpg == 2 && tpw >= 2 && slab_tiles_fits(m, k, nnz)) tpw = std::min(tpw, kSlabTilesMax);
-  // (tiles of 128 columns: two of them, reported as tiles of 64)
+  // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
   if (rpg == 2 && slab_wide_runs(m, k, n, nnz)) tpw = 2 * kWideTiles;
   const int groups = (tiles + tpw - 1) / tpw;
   info->variant = variant;
@@ -653,7 +668,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       }
       const int panels = (m + li.rows_per_block - 1) / li.rows_per_block;
       int tiles = (n + kSlabTile - 1) / kSlabTile;
-      const dim3 grid(li.grid_x), block(li.block_threads);
+      dim3 grid(li.grid_x), block(li.block_threads);
       if (li.variant == kSpmmSlab) {
         kernel<<<grid, block, kSlabLdsBytes, st>>>(m, k, n, nnz, tiles, li.grid_y, panels, ro, ci, val, order, B, C,
                                                    bias, relu);
@@ -661,7 +676,8 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         int tpw = li.grid_y, lds = kSlabLdsBytes;
         if (wide) {
           tiles = (n + kWideTile - 1) / kWideTile;
-          tpw = kWideTiles;
+          tpw = slab_wide_tiles(m, n);
+          grid.x = slab_grid_size(panels, (tiles + tpw - 1) / tpw);
           lds = kWideLdsBytes;
         }
         void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, &tpw, (void*)&panels, &ro, &ci, &val, &order, &B, &C,

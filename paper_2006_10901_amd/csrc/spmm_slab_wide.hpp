@@ -100,10 +100,11 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
   const int groups_n = (tiles_n + tiles_per_wg - 1) / tiles_per_wg;
   int panel, tile_group;
   if (!slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
-  const int tile_begin = tile_group * tiles_per_wg;
-  const int ntiles = min(tiles_n, tile_begin + tiles_per_wg) - tile_begin;      // 1 .. TPW
+  int tile_begin = tile_group * tiles_per_wg;
+  const int tile_end = min(tiles_n, tile_begin + tiles_per_wg);
+  int ntiles = min(tile_end - tile_begin, TPW);             // of the tiles that are being computed
   const int nslabs = nnz < PW ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
-  const int stages = ntiles * nslabs;                       // stage q = (slab q / ntiles, tile q % ntiles)
+  const int stages = (tile_end - tile_begin) * nslabs;      // by TPW tiles, by slabs, by tiles
 
   if (tid < 2 * kWideTile)
     *reinterpret_cast<float*>(lds_raw + (tid >> 7) * kBufBytes + kZeroOff + (tid & 127) * 4) = 0.f;
@@ -119,11 +120,11 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
   }
   const size_t slab_bytes = (size_t)S * (size_t)n * 4;
   const char* slab_base = reinterpret_cast<const char*>(B);
-  int cp_slab = 0, cp_t = 0;
+  int cp_slab = 0, cp_t = 0, cp_begin = tile_begin, cp_tiles = ntiles;
   unsigned cp_dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_raw + (unsigned)wave * (2 * kWideRowBytes);
   unsigned cp_flip = (unsigned)kBufBytes;
   auto copy_stage = [&]() {
-    const int piece = piece_start((tile_begin + cp_t) * kWideTile + (lane & 31) * 4, n, 4);
+    const int piece = piece_start((cp_begin + cp_t) * kWideTile + (lane & 31) * 4, n, 4);
     const unsigned col_off = piece < n ? (unsigned)piece * 4u : 0u;
     const char* base = slab_base;
     const bool last = cp_slab == nslabs - 1;
@@ -136,10 +137,15 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
     }
     cp_dst += cp_flip;
     cp_flip = 0u - cp_flip;
-    if (++cp_t == ntiles) {
+    if (++cp_t == cp_tiles) {
       cp_t = 0;
-      ++cp_slab;
       slab_base += slab_bytes;
+      if (++cp_slab == nslabs) {                            // the next tiles' first slab
+        cp_slab = 0;
+        slab_base = reinterpret_cast<const char*>(B);
+        cp_begin += TPW;
+        cp_tiles = min(tile_end - cp_begin, TPW);
+      }
     }
   };
 
@@ -169,12 +175,6 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
     return __builtin_popcount((unsigned)mk & row_lo) + __builtin_popcount((unsigned)(mk >> 32) & row_hi);
   };
   float acc[TPW][RPG][8];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int j = 0; j < RPG; ++j)
-#pragma unroll
-      for (int v = 0; v < 8; ++v) acc[t][j][v] = 0.f;
 
   int cc[RPG][PW];
   float aa[RPG][PW];
@@ -203,112 +203,124 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
   clocks.lap(kPhaseSetup);
 
   int q = 0;
-  for (int s = 0; s < nslabs; ++s) {
-    float av[RPG][PW];
-    int off[RPG][PW];
-    unsigned used[RPG][(PW + 1) / 2];
-    bool over[RPG];                       // wave-uniform
-    const int slab_start = s * S;
-    // (a use of the youngest pair register, so that the wait for the pairs is placed here, where it is satisfied)
-    asm volatile("v_mov_b32 %0, %0" : "+v"(aa[RPG - 1][PW - 1]));
-    if (q + 1 < stages) copy_stage();
-    clocks.lap(kPhaseIssue);
+  for (; tile_begin < tile_end; tile_begin += TPW) {
+    ntiles = min(tile_end - tile_begin, TPW);
+    const bool again = tile_begin + TPW < tile_end;           // other tiles follow: the rows once more
 #pragma unroll
     for (int j = 0; j < RPG; ++j) {
-      const int first = rows[j].p + lane_pair, left = rows[j].row_end - first;
-      if (__builtin_amdgcn_ballot_w64(first > last_start && left > 0) != 0) slab_piece_shift<PW>(cc[j], aa[j], first - last_start);
-      unsigned long long mk[PW];
+      rows[j].p = rows[j].p_begin;
 #pragma unroll
-      for (int e = 0; e < PW; ++e) {
-        const unsigned rel = (unsigned)(cc[j][e] - slab_start);
-        mk[e] = __builtin_amdgcn_ballot_w64(left > e) & __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
-        if (e > 0) strays[j] |= mk[e] & ~mk[e - 1];
-        if (e % 2 == 0) used[j][e / 2] = Mask::used(mk[e]);
-        rows[j].p += of_row(mk[e]);
-        const bool in = __builtin_amdgcn_inverse_ballot_w64(mk[e]);
-        av[j][e] = in ? aa[j][e] : 0.f;
-        off[j][e] = in ? (int)(rel * kWideRowBytes) : kZeroOff;
-      }
-      strays[j] |= mk[0] & ~(Mask::lane_before(mk[PW - 1]) | Mask::kFirst);
-      over[j] = Mask::full(mk[PW - 1]);
-      fetch_pairs(j, rows[j].p);
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int v = 0; v < 8; ++v) acc[t][j][v] = 0.f;
     }
-    clocks.lap(kPhaseScan);
+    for (int s = 0; s < nslabs; ++s) {
+      float av[RPG][PW];
+      int off[RPG][PW];
+      unsigned used[RPG][(PW + 1) / 2];
+      bool over[RPG];                       // wave-uniform
+      const int slab_start = s * S;
+      // (a use of the youngest pair register, so that the wait for the pairs is placed here, where it is satisfied)
+      asm volatile("v_mov_b32 %0, %0" : "+v"(aa[RPG - 1][PW - 1]));
+      if (q + 1 < stages) copy_stage();
+      clocks.lap(kPhaseIssue);
+#pragma unroll
+      for (int j = 0; j < RPG; ++j) {
+        const int first = rows[j].p + lane_pair, left = rows[j].row_end - first;
+        if (__builtin_amdgcn_ballot_w64(first > last_start && left > 0) != 0) slab_piece_shift<PW>(cc[j], aa[j], first - last_start);
+        unsigned long long mk[PW];
+#pragma unroll
+        for (int e = 0; e < PW; ++e) {
+          const unsigned rel = (unsigned)(cc[j][e] - slab_start);
+          mk[e] = __builtin_amdgcn_ballot_w64(left > e) & __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
+          if (e > 0) strays[j] |= mk[e] & ~mk[e - 1];
+          if (e % 2 == 0) used[j][e / 2] = Mask::used(mk[e]);
+          rows[j].p += of_row(mk[e]);
+          const bool in = __builtin_amdgcn_inverse_ballot_w64(mk[e]);
+          av[j][e] = in ? aa[j][e] : 0.f;
+          off[j][e] = in ? (int)(rel * kWideRowBytes) : kZeroOff;
+        }
+        strays[j] |= mk[0] & ~(Mask::lane_before(mk[PW - 1]) | Mask::kFirst);
+        over[j] = Mask::full(mk[PW - 1]);
+        fetch_pairs(j, again && s == nslabs - 1 && !over[j] ? rows[j].p_begin : rows[j].p);
+      }
+      clocks.lap(kPhaseScan);
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) {
+        if (t < ntiles) {
+          if (t > 0 && q + 1 < stages) copy_stage();
+          const char* buf = lds_raw + (q & 1) * kBufBytes;
+          clocks.lap(kPhaseIssue);
+#pragma unroll
+          for (int j = 0; j < RPG; ++j)
+            if (used[j][0] != 0) wide8_steps<PW>(acc[t][j], av[j], off[j], buf, lane_b, used[j]);
+          clocks.lap(kPhaseSteps);
+          // The rare rest of a row that has more pairs in this slab than the look-ahead holds.
+#pragma unroll
+          for (int j = 0; j < RPG; ++j) {
+            if (over[j]) {
+              int pe = rows[j].p;                 // where the scan stopped (the same in every tile's stage)
+              while (true) {
+                const int at = pe + l16;
+                const unsigned o = (unsigned)min(at, nnz - 1) << 2;
+                const int c = *reinterpret_cast<const int*>(cbase + o);
+                const float a = *reinterpret_cast<const float*>(vbase + o);
+                const unsigned rel = (unsigned)(c - slab_start);
+                const unsigned long long mk = __builtin_amdgcn_ballot_w64(at < rows[j].row_end) &
+                                              __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
+                if (mk == 0) break;
+                strays[j] |= mk & ~(Mask::lane_before(mk) | Mask::kFirst);
+                pe += of_row(mk);
+                const bool in = __builtin_amdgcn_inverse_ballot_w64(mk);
+                const float xv[1] = {in ? a : 0.f};
+                const int xo[1] = {in ? (int)(rel * kWideRowBytes) : kZeroOff};
+                const unsigned xu[1] = {Mask::used(mk)};
+                wide8_steps<1>(acc[t][j], xv, xo, buf, lane_b, xu);
+                if (!Mask::full(mk)) break;
+              }
+              if (t == ntiles - 1) {              // the slab is done with: the cursor and the look-ahead move on
+                rows[j].p = pe;
+                fetch_pairs(j, again && s == nslabs - 1 ? rows[j].p_begin : pe);
+              }
+            }
+          }
+          wait_everything();
+          clocks.lap(kPhaseWait);
+          __builtin_amdgcn_s_barrier();
+          clocks.lap(kPhaseBarrier);
+          ++q;
+        }
+      }
+    }
+
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
       if (t < ntiles) {
-        if (t > 0 && q + 1 < stages) copy_stage();
-        const char* buf = lds_raw + (q & 1) * kBufBytes;
-        clocks.lap(kPhaseIssue);
-#pragma unroll
-        for (int j = 0; j < RPG; ++j)
-          if (used[j][0] != 0) wide8_steps<PW>(acc[t][j], av[j], off[j], buf, lane_b, used[j]);
-        clocks.lap(kPhaseSteps);
-        // The rare rest of a row that has more pairs in this slab than the look-ahead holds.
 #pragma unroll
         for (int j = 0; j < RPG; ++j) {
-          if (over[j]) {
-            int pe = rows[j].p;                 // where the scan stopped (the same in every tile's stage)
-            while (true) {
-              const int at = pe + l16;
-              const unsigned o = (unsigned)min(at, nnz - 1) << 2;
-              const int c = *reinterpret_cast<const int*>(cbase + o);
-              const float a = *reinterpret_cast<const float*>(vbase + o);
-              const unsigned rel = (unsigned)(c - slab_start);
-              const unsigned long long mk = __builtin_amdgcn_ballot_w64(at < rows[j].row_end) &
-                                            __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
-              if (mk == 0) break;
-              strays[j] |= mk & ~(Mask::lane_before(mk) | Mask::kFirst);
-              pe += of_row(mk);
-              const bool in = __builtin_amdgcn_inverse_ballot_w64(mk);
-              const float xv[1] = {in ? a : 0.f};
-              const int xo[1] = {in ? (int)(rel * kWideRowBytes) : kZeroOff};
-              const unsigned xu[1] = {Mask::used(mk)};
-              wide8_steps<1>(acc[t][j], xv, xo, buf, lane_b, xu);
-              if (!Mask::full(mk)) break;
+          const bool redo = rows[j].p != rows[j].row_end || (strays[j] & row_mask) != 0;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int col = piece_start((tile_begin + t) * kWideTile + h * 64 + l16 * 4, n, 4);
+            const bool col_ok = col < n;
+            float sum[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum[v] = acc[t][j][4 * h + v];
+            if (redo) {
+              sum[0] = sum[1] = sum[2] = sum[3] = 0.f;
+              const float* Bcol = B + (col_ok ? col : 0);
+              for (int e = rows[j].p_begin; e < rows[j].row_end; ++e) {
+                const float a = values[e];
+                float b[4];
+                Pack<float, 4>::load(Bcol + (size_t)column_indices[e] * n, b);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[v] = __builtin_fmaf(a, b[v], sum[v]);
+              }
             }
-            if (t == ntiles - 1) {              // the slab is done with: the cursor and the look-ahead move on
-              rows[j].p = pe;
-              fetch_pairs(j, pe);
+            if (rows[j].row >= 0 && col_ok) {
+              spmm_epilogue<float, 4>(sum, bias, rows[j].row, relu);
+              Pack<float, 4>::store(C + (size_t)rows[j].row * n + col, sum);
             }
-          }
-        }
-        wait_everything();
-        clocks.lap(kPhaseWait);
-        __builtin_amdgcn_s_barrier();
-        clocks.lap(kPhaseBarrier);
-        ++q;
-      }
-    }
-  }
-
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    if (t < ntiles) {
-#pragma unroll
-      for (int j = 0; j < RPG; ++j) {
-        const bool redo = rows[j].p != rows[j].row_end || (strays[j] & row_mask) != 0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int col = piece_start((tile_begin + t) * kWideTile + h * 64 + l16 * 4, n, 4);
-          const bool col_ok = col < n;
-          float sum[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sum[v] = acc[t][j][4 * h + v];
-          if (redo) {
-            sum[0] = sum[1] = sum[2] = sum[3] = 0.f;
-            const float* Bcol = B + (col_ok ? col : 0);
-            for (int e = rows[j].p_begin; e < rows[j].row_end; ++e) {
-              const float a = values[e];
-              float b[4];
-              Pack<float, 4>::load(Bcol + (size_t)column_indices[e] * n, b);
-#pragma unroll
-              for (int v = 0; v < 4; ++v) sum[v] = __builtin_fmaf(a, b[v], sum[v]);
-            }
-          }
-          if (rows[j].row >= 0 && col_ok) {
-            spmm_epilogue<float, 4>(sum, bias, rows[j].row, relu);
-            Pack<float, 4>::store(C + (size_t)rows[j].row * n + col, sum);
           }
         }
       }

@@ -100,9 +100,9 @@ def test_slab_pieces(g, oracle_lib, force, m, k, n, density):
 
 
 # (tiles of 128 columns, two to a workgroup: whole, ragged, the last one alone, half a tile; one, two and four pairs per lane and
-# rows beyond them; rows and columns around whole panels and slabs of 128)
+# rows beyond them; rows and columns around whole panels and slabs of 128; the last shape: two pairs of tiles per workgroup)
 @pytest.mark.gpu
-@pytest.mark.parametrize("m,k,n", [(4100, 129, 2048), (4096, 260, 2046), (4000, 383, 1985), (2050, 128, 4100), (3970, 90, 2177)])
+@pytest.mark.parametrize("m,k,n", [(4100, 129, 2048), (4096, 260, 2046), (4000, 383, 1985), (2050, 128, 4100), (3970, 90, 2177), (4096, 130, 4092)])
 @pytest.mark.parametrize("density", [0.03, 0.1, 0.2])
 def test_slab_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
     A = odd_csr(m, k, density, 7200 + m + int(100 * density))
