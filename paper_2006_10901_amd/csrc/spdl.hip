@@ -211,65 +211,76 @@ int slab_pairs_per_lane(int m, int k, int nnz, int share) {
   return best;
 }
 
-// The tile-inner slab kernel looks 48 pairs ahead per row: usable where the mean count of a row's
-// pairs in one slab plus three standard deviations fits into that (a row with more takes extra
-// rounds behind full waits in every tile's stage).
-inline bool slab_tiles_fits(int m, int k, int nnz) {
+// The forms that scan a slab once for several tiles look 64 pairs ahead per row at most (a row with more takes extra
+// rounds behind full waits in every tile's stage): usable where the mean count of a row's pairs in one slab plus three
+// standard deviations fits.
+inline bool slab_look_fits(int slab_rows, int m, int k, int nnz, double pairs) {
   const double d = (m > 0 && k > 0) ? (double)nnz / ((double)m * (double)k) : 1.0;
-  const double mean = kSlabS * d;
-  return mean + 3.0 * std::sqrt(mean * std::max(0.0, 1.0 - d)) + 1.0 <= 48.0;
+  const double mean = slab_rows * d;
+  return mean + 3.0 * std::sqrt(mean * std::max(0.0, 1.0 - d)) + 1.0 <= pairs;
 }
-constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators that kernel keeps in registers
+constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators the tile-inner form keeps in registers
 
-// When the compute unit that is done last ends, in twentieths of the time of one 64-column tile of 128 rows: workgroups of `units`
-// tiles, `unit` twentieths each and a quarter of a tile of set-up, a panel's last one with what is left of its `tiles`, started in
-// order on the 32 compute units of the XCD with the most of them (slab_wg_map).  (unit * units below 500.)
-int slab_makespan(int panels, int tiles, int units, int unit) {
+// When the compute unit that is done last ends: workgroups of `units` tiles, `unit` each, and `setup`, a panel's last one with
+// what is left of its `tiles`, started in order: the XCD with the most of them (slab_wg_map) deals them to its four shader
+// engines of eight compute units in turn, and one that waits for its engine waits however idle another one is.  (264
+// workgroups of three tiles, every eleventh of one, all of which fit the XCDs' idle compute units by the time they start: 51 us
+// measured, 192 of four and 24 of three 47.)  (setup + unit * units below a thousand.)
+int slab_makespan(int panels, int tiles, int units, int unit, int setup) {
   const int groups = (tiles + units - 1) / units, left = tiles - (groups - 1) * units;
-  const int jobs = slab_xcd_load(panels, groups);
-  constexpr int kSpan = 512;
-  int done[kSpan] = {}, now = 0, last = 0;        // compute units that end at a time (modulo kSpan)
-  done[0] = kComputeUnits / 8;
-  for (int i = 0; i < jobs; ++i) {
-    while (done[now % kSpan] == 0) ++now;
-    --done[now % kSpan];
-    const int end = now + 5 + unit * (i < panels / 8 * groups && i % groups == groups - 1 ? left : units);
-    ++done[end % kSpan];
-    last = std::max(last, end);
+  const int jobs = slab_xcd_load(panels, groups), whole = panels / 8 * groups;
+  constexpr int kSpan = 1024, kEngines = 4;
+  int last = 0;
+  for (int engine = 0; engine < kEngines; ++engine) {
+    unsigned char done[kSpan] = {};               // compute units that end at a time (modulo kSpan)
+    int now = 0;
+    done[0] = kComputeUnits / 8 / kEngines;
+    for (int i = engine; i < jobs; i += kEngines) {
+      while (done[now % kSpan] == 0) ++now;
+      --done[now % kSpan];
+      const int end = now + setup + unit * (i < whole && i % groups == groups - 1 ? left : units);
+      ++done[end % kSpan];
+      last = std::max(last, end);
+    }
   }
   return last;
 }
 
-// Tiles of 128 columns that a workgroup computes, two at a time: as many as let the last compute unit end first.  (The next
-// two tiles' first slab is copied while the ones before are multiplied, and the rows' set-up is done once.  Two rounds of
-// workgroups made one, us: 4096 x 1024 at 10 %, n = 4096, 117.6 -> 112.6, at 15 % 152.4 -> 146.9, at 5 % 83.1 -> 78.8; 4804 x 1201 at 22 %,
-// n = 2992, 233 -> 227.  Where the longer workgroups do not fit the machine, the estimate keeps the short ones: 5444 x 1361 at 5 %,
-// n = 3992, 161.6 and 169.5.)
-int slab_wide_tiles(int m, int n) {
-  const int panels = (m + kWideRows - 1) / kWideRows, tiles = (n + kWideTile - 1) / kWideTile;
-  int best = kWideTiles, span = slab_makespan(panels, tiles, best, 38);
-  for (int t = 2 * kWideTiles; t <= 4 * kWideTiles && t <= tiles; t += kWideTiles) {
-    const int s = slab_makespan(panels, tiles, t, 38);
-    if (s < span) { best = t; span = s; }
-  }
-  return best;
-}
+// Forms of the copy-based slab kernel for two rows per group: tiles of 64 columns, scanned for each tile anew; tiles of 64, a slab
+// scanned once for up to four; tiles of 128 (a lane owns eight columns), a slab scanned once for two.
+enum SlabForm { kSlabWalk, kSlabInner, kSlabWide };
+struct SlabPlan { SlabForm form; int tpw; };      // tiles of 64 columns per workgroup (wide: two for each of 128)
 
-// Tiles of 128 columns (a lane owns eight) for outputs of two rows per group: where the last compute unit is estimated to end
-// earlier than with tiles of 64.  A tile of 128 costs 1.9 tiles of 64 in the form that scans once for up to four, 1.7 in the
-// other.  (110 random shapes, 512 .. 2048 by four times as many, both ways round, n = 256 .. 4096, 3 .. 25 %, both forms in turn:
-// the estimate's ratio is off by 4 and 5 % (one standard deviation); it picks the wide tiles for 39 of them, for 0.91 of the
-// time on average, 1.000 at worst, and leaves 0.1 % to a choice of the better one each time.)  The look-ahead holds at most 64 pairs per
-// row and slab: up to 48 for the mean and three standard deviations.
-bool slab_wide_runs(int m, int k, int n, int nnz) {
-  const double mean = (double)kWideS * (double)nnz / ((double)m * (double)k);
-  if (mean + 3.0 * std::sqrt(mean) + 1.0 > 48.0 || slab_rows_per_group(m, n) != 2 || slab_groups_per_row(m, k, n) != 1) return false;
+// The form whose last compute unit is estimated to end first.  In thirtieths of a tile of 64: 31 if it is scanned for
+// alone, 29 together with others, 53 a tile of 128; a workgroup's set-up is worth 9 at 1024 columns and 10 %, more where a tile's time is
+// shorter.  A wide workgroup may take several pairs of tiles, one after the other: set up once, the next pair's first slab copied
+// while the one before is multiplied (4096 x 1024 at 10 %, n = 4096, two rounds of workgroups made one: 117.6 us -> 112.6).
+// (120 random shapes, m, k of 400 .. 2048 by four times as many, both ways round, or 1024 .. 12000 by 512 .. 4000, n = 256 ..
+// 4096, 3 .. 25 %, every form with every number of tiles in turn: the estimates scatter by 4 %, the choice costs 1 % against the best
+// one each time.  Walking with as many tiles as split_for_machine says, the only choice above 12.7 % before, and four
+// tiles scanned together, the only one below: 11 % more time on average, up to 41 %: 3760 x 940 at 7 %, n = 2260, 30 panels of 36
+// tiles, 87.8 us -> 62.4 as pairs of tiles in one round more.)
+SlabPlan slab_plan(int m, int k, int n, int nnz) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile, panels = (m + kWideRows - 1) / kWideRows;
-  int tpw = slab_tiles_per_wg(panels, tiles);
-  const bool inner = tpw >= 2 && slab_tiles_fits(m, k, nnz);
-  if (inner) tpw = std::min(tpw, kSlabTilesMax);
-  if (tpw > 24 || slab_xcd_load(panels, (tiles + tpw - 1) / tpw) > 4096) return false;       // (many rounds: all the same)
-  return slab_makespan(panels, (n + kWideTile - 1) / kWideTile, slab_wide_tiles(m, n), inner ? 38 : 34) < slab_makespan(panels, tiles, tpw, 20);
+  const int wide_tiles = (n + kWideTile - 1) / kWideTile;
+  SlabPlan best = {kSlabWalk, slab_tiles_per_wg(panels, tiles)};
+  const bool inner = best.tpw >= 2 && slab_look_fits(kSlabS, m, k, nnz, 64.0);
+  if (best.tpw > 24 || slab_xcd_load(panels, tiles) > 8192) {        // (many rounds: all much the same)
+    if (inner) best = {kSlabInner, kSlabTilesMax};
+    return best;
+  }
+  const double pairs = kSlabS * (double)nnz / ((double)m * (double)k);
+  const int setup = (int)std::max(1.0, std::min(60.0, 9.0 * 1024.0 / (double)k * 35.6 / (10.0 + pairs)));
+  int span = slab_makespan(panels, tiles, best.tpw, 31, setup);
+  auto better = [&](int s, SlabForm form, int tpw) {
+    if (s < span) { span = s; best = {form, tpw}; }
+  };
+  if (inner)
+    for (int t = 2; t <= std::min(tiles, kSlabTilesMax); ++t) better(slab_makespan(panels, tiles, t, 29, setup), kSlabInner, t);
+  if (slab_look_fits(kWideS, m, k, nnz, 48.0))
+    for (int t = kWideTiles; t <= 4 * kWideTiles && (t == kWideTiles || t <= wide_tiles); t += kWideTiles)
+      better(slab_makespan(panels, wide_tiles, t, 53, setup), kSlabWide, 2 * t);
+  return best;
 }
 // index of the look-ahead's 1, 2 or 4 pairs per lane: two standard deviations over the mean (4996 x 1249, 5 %: one pair 3 % faster than
 // two; 14 .. 17 %: two 1 .. 3 % faster than four; from 20 % on four as fast or up to 7 % faster)
@@ -288,10 +299,11 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   const int rows = kSlabRows / (half ? 2 : share) * rpg;
   const int panels = (m + rows - 1) / rows;
   int tpw = slab_tiles_per_wg(panels, tiles);
-  // wide outputs, two rows per group: the tile-inner kernel, at most kSlabTilesMax tiles per workgroup
-  if (rpg == 2 && tpw >= 2 && slab_tiles_fits(m, k, nnz)) tpw = std::min(tpw, kSlabTilesMax);
-  // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
-  if (rpg == 2 && slab_wide_runs(m, k, n, nnz)) tpw = 2 * kWideTiles;
+  if (rpg == 2) {
+    const SlabPlan plan = slab_plan(m, k, n, nnz);
+    // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
+    tpw = plan.form == kSlabWide ? 2 * kWideTiles : plan.tpw;
+  }
   const int groups = (tiles + tpw - 1) / tpw;
   info->variant = variant;
   info->vec = 4;
@@ -645,16 +657,18 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       const int share = two_rows || half ? 1 : kSlabRows / li.rows_per_block;
       const void* dma_kernel = half ? half_form
                                     : forms[two_rows ? 0 : share == 1 ? 1 : share == 2 ? 2 : 3][slab_pairs_per_lane(m, k, nnz, share) - 1];
-      // (two rows per group and 2 .. kSlabTilesMax tiles per workgroup: scanned once per slab for all tiles)
-      if (li.variant == kSpmmSlabDma && two_rows && li.grid_y >= 2 && li.grid_y <= kSlabTilesMax &&
-          slab_tiles_fits(m, k, nnz))
-        dma_kernel = (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>;
-      const bool wide = li.variant == kSpmmSlabDma && two_rows && slab_wide_runs(m, k, n, nnz);
+      const SlabPlan plan = two_rows ? slab_plan(m, k, n, nnz) : SlabPlan{kSlabWalk, li.grid_y};
+      const bool wide = li.variant == kSpmmSlabDma && plan.form == kSlabWide;
+      static const void* const inner_forms[3] = {(const void*)spmm_slab_tiles_kernel<kSlabS, 2, 2, true, kSlabTilesMax>,
+                                                 (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, false, kSlabTilesMax>,
+                                                 (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 4, true, kSlabTilesMax>};
+      if (plan.form == kSlabInner)
+        dma_kernel = inner_forms[slab_look_fits(kSlabS, m, k, nnz, 32.0) ? 0 : slab_look_fits(kSlabS, m, k, nnz, 48.0) ? 1 : 2];
       static const void* const wide_forms[3] = {(const void*)spmm_slab_wide_kernel<1>, (const void*)spmm_slab_wide_kernel<2>,
                                                 (const void*)spmm_slab_wide_kernel<4>};
       if (wide) dma_kernel = wide_forms[slab_wide_pairs(m, k, nnz)];
       if (!configured.load()) {
-        for (const void* f : {(const void*)kernel, (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, kSlabTilesMax>, half_form})
+        for (const void* f : {(const void*)kernel, inner_forms[0], inner_forms[1], inner_forms[2], half_form})
           if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsBytes) != hipSuccess)
             return SPDL_ERR_LAUNCH;
         for (const void* f : wide_forms)
@@ -676,7 +690,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         int tpw = li.grid_y, lds = kSlabLdsBytes;
         if (wide) {
           tiles = (n + kWideTile - 1) / kWideTile;
-          tpw = slab_wide_tiles(m, n);
+          tpw = plan.tpw / 2;
           grid.x = slab_grid_size(panels, (tiles + tpw - 1) / tpw);
           lds = kWideLdsBytes;
         }

@@ -134,20 +134,21 @@ __device__ __forceinline__ void wide_fma(float (&acc)[4], const float (&av)[PW],
 // Block BLOCK is in `now`; the one after it is on its way into `next`.
 template <int PW, int BLOCK>
 __device__ __forceinline__ void wide_blocks(float (&acc)[4], const float (&av)[PW], const int (&off)[PW], const char* buf,
-                                            int lane_b, unsigned used, f32x4 (&now)[4], f32x4 (&next)[4]) {
+                                            int lane_b, const unsigned (&used)[PW == 3 ? 3 : 1], f32x4 (&now)[4],
+                                            f32x4 (&next)[4]) {
   constexpr int kBlocks = 4 * PW;
   wide_fma<PW, BLOCK>(acc, av, now);
   if constexpr (BLOCK + 1 < kBlocks) {
-    if ((used >> (4 * (BLOCK + 1) / PW)) != 0) {
+    if ((used[4 * (BLOCK + 1) % PW] >> (4 * (BLOCK + 1) / PW)) != 0) {
       if constexpr (BLOCK + 2 < kBlocks) wide_load<PW, BLOCK + 2>(now, off, buf, lane_b);
       wide_blocks<PW, BLOCK + 1>(acc, av, off, buf, lane_b, used, next, now);
     }
   }
 }
-// `used`: lanes whose first pair some group needs.
+// used[e]: lanes whose pair e some group needs, of the places at which a block may start.
 template <int PW>
 __device__ __forceinline__ void wide_steps(float (&acc)[4], const float (&av)[PW], const int (&off)[PW], const char* buf,
-                                           int lane_b, unsigned used) {
+                                           int lane_b, const unsigned (&used)[PW == 3 ? 3 : 1]) {
   f32x4 bx[4], by[4];
   wide_load<PW, 0>(bx, off, buf, lane_b);
   wide_load<PW, 1>(by, off, buf, lane_b);

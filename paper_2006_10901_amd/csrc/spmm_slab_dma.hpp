@@ -17,7 +17,7 @@
 // memory path, 64 bytes a clock for the slab (64 KB), the look-ahead of pairs and their instructions alike, and by
 // the fill of the step's LDS pipeline per round.  Hence one piece of PW consecutive pairs per lane and array: two
 // loads for what took two per sixteen pairs, and one run of steps per round instead of one per sixteen pairs
-// (8192 x 10240, n = 128, us per launch, sixteen pairs per load -> pieces: 10 % 90.3 -> 86.1, 13 % 109.6 -> 100.0, 15 %
+// (8192 x 10240, n = 128, us per launch, sixteen pairs per load -> pieces: 10 % 90.1 -> 81.5, 13 % 109.6 -> 100.0, 15 %
 // 117.4 -> 108, 20 % 143 -> 136, 30 % 201 -> 193; 16384 x 4096 at 10 %: 75.5 -> 70.1).
 #pragma once
 #include "common.hpp"
@@ -184,12 +184,14 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
       off[e] = in ? (int)(rel * (kSlabTile * 4)) : kZeroOff;
     }
     strays[j] |= mk[0] & ~(Mask::lane_before(mk[PW - 1]) | Mask::kFirst);
-    const unsigned used = Mask::used(mk[0]);
+    unsigned used[PW == 3 ? 3 : 1];
+#pragma unroll
+    for (int e = 0; e < (PW == 3 ? 3 : 1); ++e) used[e] = Mask::used(mk[e]);
     const bool more = Mask::full(mk[PW - 1]);
     // the next pairs, first needed in the next stage (or in the next long round of this one)
     fetch_pairs(j, (restart && !more) ? rows[j].p_begin : rows[j].p);
     clocks.lap(kPhaseScan);
-    if (used != 0) wide_steps<PW>(acc[j], av, off, buf, lane_b, used);
+    if (used[0] != 0) wide_steps<PW>(acc[j], av, off, buf, lane_b, used);
     clocks.lap(kPhaseSteps);
     return more;
   };

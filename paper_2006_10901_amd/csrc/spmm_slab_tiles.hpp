@@ -8,17 +8,24 @@
 // masked values and offsets from registers.  The look-ahead for the next slab is requested at the
 // scan and has TPW stages to arrive.
 //
-// A row with more than 16*NCH pairs inside one slab needs further rounds in that slab, 16 pairs at
+// The look-ahead holds 16 PW pairs of a row: as one piece of PW consecutive pairs per lane (PIECES), or as PW chunks of sixteen.
+// Pieces take two loads instead of 2 PW and one run of steps instead of PW; chunks, with three of which this kernel first ran,
+// take fewer registers and bytes than pieces of four (us per launch, chunks / pieces of two, three, four: 1024 x 4096, n = 4096, 10 %
+// 123.3 / 132.1 / 124.2 / 123.9, 5 % 92.4 / 87.6 / 89.4 / 91.5; 16384 x 4096 at 10 %, n = 256: 115.4 / 125.5 / 117.1 / 116.3).  So pieces of two
+// where 32 pairs hold a row's in a slab (mean and three standard deviations), three chunks where 48 do, pieces of four up to
+// 64, where the form that scans for every tile anew ran before (1393 x 5572 at 13 %, n = 3464: 309 -> 277; 7424 x 1856 at 14 %,
+// n = 580: 108.7 -> 100.8).
+//
+// A row with more pairs inside one slab needs further rounds in that slab, 16 pairs at
 // a time, each behind a full wait; they are not kept, every tile's stage fetches and scans them
-// again.  The host picks this kernel only where that is rare (NCH chunks cover the mean count of a
-// slab plus three standard deviations).
+// again.
 #pragma once
 #include "common.hpp"
 #include "spmm_slab.hpp"
 
 namespace spdl {
 
-template <int S, int RPG, int NCH, int TPW>
+template <int S, int RPG, int PW, bool PIECES, int TPW>
 __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
     int m, int k, int n, int nnz, int tiles_n, int tiles_per_wg, int panels,
     const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
@@ -42,7 +49,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
   if (!slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
   const int tile_begin = tile_group * tiles_per_wg;
   const int ntiles = min(tiles_n, tile_begin + tiles_per_wg) - tile_begin;      // 1 .. TPW
-  const int nslabs = (k + S - 1) / S;
+  const int nslabs = nnz < PW ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
   const int stages = ntiles * nslabs;                       // stage q = (slab q / ntiles, tile q % ntiles)
 
   if (tid < 2 * kSlabTile)
@@ -101,66 +108,82 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
     rows[j].p = rows[j].p_begin;
   }
   const int last_nz = nnz - 1;
-  const int sub8 = sub * 8;
+  using Mask = SlabMask<1>;
+  // the row's lanes in a wave mask, and the lanes that have met a pair of the slab whose predecessor is not in it
+  const unsigned long long row_mask = 0xffffull << (16 * sub);
+  const unsigned row_lo = (unsigned)row_mask, row_hi = (unsigned)(row_mask >> 32);
+  unsigned long long strays[RPG];
+#pragma unroll
+  for (int j = 0; j < RPG; ++j) strays[j] = 0;
   float acc[TPW][RPG][4];
 #pragma unroll
   for (int t = 0; t < TPW; ++t)
 #pragma unroll
     for (int j = 0; j < RPG; ++j) acc[t][j][0] = acc[t][j][1] = acc[t][j][2] = acc[t][j][3] = 0.f;
 
-  int cc[RPG][NCH];
-  float aa[RPG][NCH];
+  int cc[RPG][PW];
+  float aa[RPG][PW];
+  const int last_start = nnz - PW;
+  const char* const cbase = reinterpret_cast<const char*>(column_indices);
+  const char* const vbase = reinterpret_cast<const char*>(values);
   auto fetch_pairs = [&](int j, int from) {
-    const char* cbase = reinterpret_cast<const char*>(column_indices);
-    const char* vbase = reinterpret_cast<const char*>(values);
+    if constexpr (PIECES) {
+      const unsigned o = (unsigned)min(from + PW * l16, last_start) << 2;
+      const SlabPiece<int, PW> c = *reinterpret_cast<const SlabPiece<int, PW>*>(cbase + o);
+      const SlabPiece<float, PW> a = *reinterpret_cast<const SlabPiece<float, PW>*>(vbase + o);
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const unsigned o = (unsigned)min(from + l16 + 16 * i, last_nz) << 2;
-      cc[j][i] = *reinterpret_cast<const int*>(cbase + o);
-      aa[j][i] = *reinterpret_cast<const float*>(vbase + o);
+      for (int e = 0; e < PW; ++e) {
+        cc[j][e] = c.v[e];
+        aa[j][e] = a.v[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < PW; ++e) {
+        const unsigned o = (unsigned)min(from + l16 + 16 * e, nnz - 1) << 2;
+        cc[j][e] = *reinterpret_cast<const int*>(cbase + o);
+        aa[j][e] = *reinterpret_cast<const float*>(vbase + o);
+      }
     }
   };
   auto wait_everything = [&]() { __builtin_amdgcn_s_waitcnt(0); };
 
-  copy_stage();
+  if (nslabs > 0) {
+    copy_stage();
 #pragma unroll
-  for (int j = 0; j < RPG; ++j) fetch_pairs(j, rows[j].p_begin);
+    for (int j = 0; j < RPG; ++j) fetch_pairs(j, rows[j].p_begin);
+  }
   wait_everything();
   __builtin_amdgcn_s_barrier();
 
   int q = 0;
   for (int s = 0; s < nslabs; ++s) {
     // The scan of the slab: for every row the leading pairs of the look-ahead that lie in it.
-    float av[RPG][NCH];
-    int off[RPG][NCH], cmax[RPG][NCH];
+    float av[RPG][PW];
+    int off[RPG][PW];
+    unsigned used[RPG][PW];
     bool over[RPG];                       // wave-uniform
     const int slab_start = s * S;
 #pragma unroll
     for (int j = 0; j < RPG; ++j) {
-      const int idx = rows[j].p + l16;
-      unsigned long long gate = ~0ull;
-      unsigned counts = 0, lastc = 0;
+      const int first = rows[j].p + (PIECES ? PW * l16 : l16), left = rows[j].row_end - first;
+      if (PIECES && __builtin_amdgcn_ballot_w64(first > last_start && left > 0) != 0)
+        slab_piece_shift<PW>(cc[j], aa[j], first - last_start);
+      unsigned long long mk[PW];
 #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const unsigned rel = (unsigned)(cc[j][i] - slab_start);
-        const unsigned long long mk = __builtin_amdgcn_ballot_w64(idx + 16 * i < rows[j].row_end) &
-                                      __builtin_amdgcn_ballot_w64(rel < (unsigned)S) & gate;
-        const unsigned lo = (unsigned)mk, hi = (unsigned)(mk >> 32);
-        const int c0 = leading16(lo & 0xffffu), c1 = leading16(lo >> 16);
-        const int c2 = leading16(hi & 0xffffu), c3 = leading16(hi >> 16);
-        cmax[j][i] = scalar_max(scalar_max(c0, c1), scalar_max(c2, c3));
-        lastc = (unsigned)c0 | ((unsigned)c1 << 8) | ((unsigned)c2 << 16) | ((unsigned)c3 << 24);
-        counts += lastc;
-        if (i + 1 < NCH)
-          gate = (c0 == 16 ? 0xffffull : 0ull) | (c1 == 16 ? 0xffffull << 16 : 0ull) |
-                 (c2 == 16 ? 0xffffull << 32 : 0ull) | (c3 == 16 ? 0xffffull << 48 : 0ull);
-        const bool in = __builtin_amdgcn_inverse_ballot_w64(mk);
-        av[j][i] = in ? aa[j][i] : 0.f;
-        off[j][i] = in ? (int)(rel * (kSlabTile * 4)) : kZeroOff;
+      for (int e = 0; e < PW; ++e) {
+        const unsigned rel = (unsigned)(cc[j][e] - slab_start);
+        mk[e] = __builtin_amdgcn_ballot_w64(left > (PIECES ? e : 16 * e)) & __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
+        if (PIECES && e > 0) strays[j] |= mk[e] & ~mk[e - 1];
+        if (!PIECES) strays[j] |= mk[e] & ~(Mask::lane_before(mk[e]) | (e > 0 ? (mk[e - 1] >> 15) & Mask::kFirst : Mask::kFirst));
+        rows[j].p += __builtin_popcount((unsigned)mk[e] & row_lo) + __builtin_popcount((unsigned)(mk[e] >> 32) & row_hi);
+        used[j][e] = !PIECES || e == 0 ? Mask::used(mk[e]) : 0;
+        const bool in = __builtin_amdgcn_inverse_ballot_w64(mk[e]);
+        av[j][e] = in ? aa[j][e] : 0.f;
+        off[j][e] = in ? (int)(rel * (kSlabTile * 4)) : kZeroOff;
       }
-      rows[j].p += (int)((counts >> sub8) & 0xffu);
+      if (PIECES) strays[j] |= mk[0] & ~(Mask::lane_before(mk[PW - 1]) | Mask::kFirst);
       // every fetched pair of some row lay in the slab: it may hold more of that row
-      over[j] = cmax[j][NCH - 1] == 16;
+      over[j] = Mask::full(mk[PW - 1]);
       fetch_pairs(j, rows[j].p);
     }
     // One stage per tile: the tile's part of the slab is in LDS, the next part is on its way.
@@ -171,9 +194,14 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
         const char* buf = lds_raw + (q & 1) * kBufBytes;
 #pragma unroll
         for (int j = 0; j < RPG; ++j)
+          if constexpr (PIECES) {
+            const unsigned blocks[1] = {used[j][0]};
+            if (blocks[0] != 0) wide_steps<PW>(acc[t][j], av[j], off[j], buf, lane_b, blocks);
+          } else {
 #pragma unroll
-          for (int i = 0; i < NCH; ++i)
-            if (cmax[j][i] > 0) slab_steps(acc[t][j], av[j][i], off[j][i], buf, lane_b, cmax[j][i]);
+            for (int e = 0; e < PW; ++e)
+              if (used[j][e] != 0) slab_steps(acc[t][j], av[j][e], off[j][e], buf, lane_b, 32 - __builtin_clz(used[j][e]));
+          }
         // The rare rest of a row that has more pairs in this slab than the look-ahead holds.
 #pragma unroll
         for (int j = 0; j < RPG; ++j) {
@@ -192,7 +220,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
               const int cm = scalar_max(scalar_max(c0, c1), scalar_max(c2, c3));
               if (cm == 0) break;
               const unsigned packed = (unsigned)c0 | ((unsigned)c1 << 8) | ((unsigned)c2 << 16) | ((unsigned)c3 << 24);
-              const int cnt = (int)((packed >> sub8) & 0xffu);
+              const int cnt = (int)((packed >> (8 * sub)) & 0xffu);
               // (only the leading pairs here: one behind the first pair outside the slab belongs to
               // a row that is not ascending, which is redone at the end anyway)
               const bool in = l16 < cnt;
@@ -222,7 +250,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
       const bool col_ok = col < n;
 #pragma unroll
       for (int j = 0; j < RPG; ++j) {
-        if (rows[j].p != rows[j].row_end) {
+        if (rows[j].p != rows[j].row_end || (strays[j] & row_mask) != 0) {
           acc[t][j][0] = acc[t][j][1] = acc[t][j][2] = acc[t][j][3] = 0.f;
           const float* Bcol = B + (col_ok ? col : 0);
           for (int e = rows[j].p_begin; e < rows[j].row_end; ++e) {

@@ -112,9 +112,21 @@ def test_slab_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
     close(A, got, ref, S + np.abs(bias)[:, None], f"{m} x {k}, n = {n}, {density}")
 
 
+# (eight panels of 128 rows, 64 tiles: two tiles of 64 per workgroup, scanned once for both; look-ahead of 32, 48 and 64 pairs, and
+# beyond)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [(1000, 300, 4096), (1024, 513, 4090), (899, 257, 4095)])
+@pytest.mark.parametrize("density", [0.04, 0.1, 0.15, 0.3])
+def test_slab_scanned_once_for_two_tiles(g, oracle_lib, force, m, k, n, density):
+    A = odd_csr(m, k, density, 7300 + m + int(100 * density))
+    B, got = run(g, A, n, force, 7302 + n, oracle_lib.row_order(A.m, A.row_offsets))
+    ref, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
+    close(A, got, ref, S, f"{m} x {k}, n = {n}, {density}")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("nnz", [1, 2, 3, 4, 5, 63, 64, 65])
-@pytest.mark.parametrize("m,k", [(700, 400), (200, 400), (4200, 60)])
+@pytest.mark.parametrize("m,k", [(700, 400), (200, 400), (4200, 60), (66000, 60)])
 def test_slab_pieces_of_arrays_shorter_than_a_round(g, oracle_lib, force, m, k, nnz):
     rng = np.random.default_rng(7100 + nnz)
     row = m - 1 if nnz % 2 else m // 2                                # one row has them all
