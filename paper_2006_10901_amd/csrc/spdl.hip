@@ -171,13 +171,6 @@ int split_for_machine(int panels, int total, int slots = kComputeUnits) {
 
 int slab_tiles_per_wg(int panels, int tiles, int slots = kComputeUnits) { return split_for_machine(panels, tiles, slots); }
 
-// Rows per 16-lane group of the copy-based slab kernel: two when 128-row panels still give
-// every CU at least two tiles to walk, else one.
-int slab_rows_per_group(int m, int n) {
-  const int64_t tiles128 = (int64_t)((m + 127) / 128) * ((n + kSlabTile - 1) / kSlabTile);
-  return tiles128 >= 2 * kComputeUnits ? 2 : 1;
-}
-
 // Products with so few positions keep a lane group per row: its sums are added in stored order and are the bits of the
 // other families, and it is on such small ones that results are compared between families.  (The launches take 5 .. 11 us;
 // sharing rows takes a tenth to a fifth off them: 203 x 700 at 15 %, n = 75: 8.4 us against 6.7, row-splitting 5.0.)
@@ -229,6 +222,7 @@ constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators th
 int slab_makespan(int panels, int tiles, int units, int unit, int setup) {
   const int groups = (tiles + units - 1) / units, left = tiles - (groups - 1) * units;
   const int jobs = slab_xcd_load(panels, groups), whole = panels / 8 * groups;
+  if (jobs <= kComputeUnits / 8) return setup + unit * std::min(units, tiles);
   constexpr int kSpan = 1024, kEngines = 4;
   int last = 0;
   for (int engine = 0; engine < kEngines; ++engine) {
@@ -246,40 +240,52 @@ int slab_makespan(int panels, int tiles, int units, int unit, int setup) {
   return last;
 }
 
-// Forms of the copy-based slab kernel for two rows per group: tiles of 64 columns, scanned for each tile anew; tiles of 64, a slab
-// scanned once for up to four; tiles of 128 (a lane owns eight columns), a slab scanned once for two.
-enum SlabForm { kSlabWalk, kSlabInner, kSlabWide };
+// Forms of the copy-based slab kernel where panels of 64 rows give half of the compute units or more a workgroup.  128 rows, two per
+// group: tiles of 64 columns, scanned for each tile anew; tiles of 64, a slab scanned once for up to four; tiles of 128 (a lane
+// owns eight columns), a slab scanned once for two.  64 rows, one per group: tiles of 64.
+enum SlabForm { kSlabWalk, kSlabInner, kSlabWide, kSlabOneRow };
 struct SlabPlan { SlabForm form; int tpw; };      // tiles of 64 columns per workgroup (wide: two for each of 128)
 
-// The form whose last compute unit is estimated to end first.  In thirtieths of a tile of 64: 31 if it is scanned for
-// alone, 29 together with others, 53 a tile of 128; a workgroup's set-up is worth 9 at 1024 columns and 10 %, more where a tile's time is
-// shorter.  A wide workgroup may take several pairs of tiles, one after the other: set up once, the next pair's first slab copied
-// while the one before is multiplied (4096 x 1024 at 10 %, n = 4096, two rounds of workgroups made one: 117.6 us -> 112.6).
-// (120 random shapes, m, k of 400 .. 2048 by four times as many, both ways round, or 1024 .. 12000 by 512 .. 4000, n = 256 ..
-// 4096, 3 .. 25 %, every form with every number of tiles in turn: the estimates scatter by 4 %, the choice costs 1 % against the best
-// one each time.  Walking with as many tiles as split_for_machine says, the only choice above 12.7 % before, and four
-// tiles scanned together, the only one below: 11 % more time on average, up to 41 %: 3760 x 940 at 7 %, n = 2260, 30 panels of 36
-// tiles, 87.8 us -> 62.4 as pairs of tiles in one round more.)
+// The form whose last compute unit is estimated to end first.  In thirtieths of a tile of 64 columns and 128 rows: 31 if it is scanned
+// for alone, 29 together with others, 53 a tile of 128 columns, 18 one of 64 rows; a workgroup's set-up is worth 9 at 1024 columns and 10
+// %, more where a tile's time is shorter.  A wide workgroup may take several pairs of tiles, one after the other: set up once, the
+// next pair's first slab copied while the one before is multiplied (4096 x 1024 at 10 %, n = 4096, two rounds of workgroups
+// made one: 117.6 us -> 112.6).
+// (120 random shapes of 512 tiles of 128 x 64 and more, m, k of 400 .. 2048 by four times as many, both ways round, or 1024 ..
+// 12000 by 512 .. 4000, n = 256 .. 4096, 3 .. 25 %, every form with every number of tiles in turn: the estimates scatter by 4 %, the
+// choice costs 1 % against the best one each time.  Walking with as many tiles as split_for_machine says, the only choice above
+// 12.7 % before, and four tiles scanned together, the only one below: 11 % more time on average, up to 41 %: 3760 x 940 at 7 %, n = 2260, 30
+// panels of 36 tiles, 87.8 us -> 62.4.  140 random shapes of 129 .. 2600 tiles of 64 x 64: the choice costs 0.4 %; panels of 64 rows up
+// to 1023 tiles, as before, 3.5 %: 4368 x 1092 at 6 %, n = 448, 25.3 us -> 18.6 with 128.)
 SlabPlan slab_plan(int m, int k, int n, int nnz) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile, panels = (m + kWideRows - 1) / kWideRows;
   const int wide_tiles = (n + kWideTile - 1) / kWideTile;
+  const int panels64 = (m + kSlabRows - 1) / kSlabRows;
   SlabPlan best = {kSlabWalk, slab_tiles_per_wg(panels, tiles)};
-  const bool inner = best.tpw >= 2 && slab_look_fits(kSlabS, m, k, nnz, 64.0);
   if (best.tpw > 24 || slab_xcd_load(panels, tiles) > 8192) {        // (many rounds: all much the same)
-    if (inner) best = {kSlabInner, kSlabTilesMax};
+    if (best.tpw >= 2 && slab_look_fits(kSlabS, m, k, nnz, 64.0)) best = {kSlabInner, kSlabTilesMax};
     return best;
   }
   const double pairs = kSlabS * (double)nnz / ((double)m * (double)k);
   const int setup = (int)std::max(1.0, std::min(60.0, 9.0 * 1024.0 / (double)k * 35.6 / (10.0 + pairs)));
   int span = slab_makespan(panels, tiles, best.tpw, 31, setup);
-  auto better = [&](int s, SlabForm form, int tpw) {
-    if (s < span) { span = s; best = {form, tpw}; }
+  auto try_form = [&](SlabForm form, int rows, int ntiles, int units, int unit) {
+    // (not while even an even share of the work would end later)
+    const int64_t work = (int64_t)rows * ((int64_t)ntiles * unit + (ntiles + units - 1) / units * setup);
+    if (work >= (int64_t)span * kComputeUnits) return;
+    const int s = slab_makespan(rows, ntiles, units, unit, setup);
+    if (s < span) { span = s; best = {form, form == kSlabWide ? 2 * units : units}; }
   };
-  if (inner)
-    for (int t = 2; t <= std::min(tiles, kSlabTilesMax); ++t) better(slab_makespan(panels, tiles, t, 29, setup), kSlabInner, t);
+  if ((int64_t)panels * tiles < 1024) {                              // (beyond, 128 rows fill the machine as well)
+    const int t1 = slab_tiles_per_wg(panels64, tiles);
+    if (t1 <= 24) try_form(kSlabOneRow, panels64, tiles, t1, 18);
+    for (int t = 1; t <= std::min(tiles, kSlabTilesMax); ++t) try_form(kSlabOneRow, panels64, tiles, t, 18);
+  }
+  if (slab_look_fits(kSlabS, m, k, nnz, 64.0))
+    for (int t = 2; t <= std::min(tiles, kSlabTilesMax); ++t) try_form(kSlabInner, panels, tiles, t, 29);
   if (slab_look_fits(kWideS, m, k, nnz, 48.0))
     for (int t = kWideTiles; t <= 4 * kWideTiles && (t == kWideTiles || t <= wide_tiles); t += kWideTiles)
-      better(slab_makespan(panels, wide_tiles, t, 53, setup), kSlabWide, 2 * t);
+      try_form(kSlabWide, panels, wide_tiles, t, 53);
   return best;
 }
 // index of the look-ahead's 1, 2 or 4 pairs per lane: two standard deviations over the mean (4996 x 1249, 5 %: one pair 3 % faster than
@@ -289,18 +295,21 @@ int slab_wide_pairs(int m, int k, int nnz) {
   return pairs <= 16.0 ? 0 : pairs <= 32.0 ? 1 : 2;
 }
 
-void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info) {
+void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info, SlabPlan* plan_out) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
   // (small products with few tiles: workgroups of eight waves)
   const bool half = variant == kSpmmSlabDma && slab_rows_stay_whole(m, k) &&
                     (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles <= kComputeUnits / 2;
   const int share = variant == kSpmmSlabDma ? slab_groups_per_row(m, k, n) : 1;
-  const int rpg = (variant == kSpmmSlabDma && share == 1 && !half) ? slab_rows_per_group(m, n) : 1;
+  const bool planned = variant == kSpmmSlabDma && share == 1 && !half;
+  SlabPlan plan = {kSlabOneRow, 0};
+  if (planned) plan = slab_plan(m, k, n, nnz);
+  if (plan_out) *plan_out = plan;
+  const int rpg = plan.form == kSlabOneRow ? 1 : 2;
   const int rows = kSlabRows / (half ? 2 : share) * rpg;
   const int panels = (m + rows - 1) / rows;
   int tpw = slab_tiles_per_wg(panels, tiles);
-  if (rpg == 2) {
-    const SlabPlan plan = slab_plan(m, k, n, nnz);
+  if (planned) {
     // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
     tpw = plan.form == kSlabWide ? 2 * kWideTiles : plan.tpw;
   }
@@ -394,7 +403,7 @@ bool spmm_mfma_runnable() {
 
 template <typename T>
 void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, spdl_launch_info* info,
-                    int hint = 0) {
+                    int hint = 0, SlabPlan* plan_out = nullptr) {
   int variant = g_forced[0].load();
   // (n % 8 == 4 stays with row splitting, a choice that a test of the selection fixes.  1024 x 1024, n = 3132, row splitting
   // against the matrix cores: 14.4 us and 19.8 at 2 %, 22.4 and 19.8 at 5 %, 37.5 and 20.0 at 10 %, 97 and 24.5 at 30 %.)
@@ -544,7 +553,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     info->grid_y = (n + kWinTile - 1) / kWinTile;
   } else if (sizeof(T) == 4 && ((variant == kSpmmSlabDma && slab_dma_usable(n, nnz)) ||
                                 (variant == kSpmmSlab && slab_usable<T>(n, nnz, B, C)))) {
-    fill_spmm_slab_info(m, k, n, nnz, variant, info);
+    fill_spmm_slab_info(m, k, n, nnz, variant, info, plan_out);
   } else {
     fill_spmm_rowsplit_info<T>(m, n, nnz, B, C, info);
   }
@@ -603,7 +612,8 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
   if (!ro || !C || (nnz > 0 && (!ci || !val || !B))) return SPDL_ERR_INVALID;
   hipStream_t st = static_cast<hipStream_t>(stream);
   spdl_launch_info li;
-  fill_spmm_info<T>(m, k, n, nnz, B, C, &li, hint);
+  SlabPlan plan = {kSlabOneRow, 0};
+  fill_spmm_info<T>(m, k, n, nnz, B, C, &li, hint, &plan);
   (void)hipGetLastError();
   int rc = SPDL_OK;
   constexpr bool kInt32 = sizeof(I) == 4;        // the slab kernels read 32-bit indices only
@@ -657,7 +667,6 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       const int share = two_rows || half ? 1 : kSlabRows / li.rows_per_block;
       const void* dma_kernel = half ? half_form
                                     : forms[two_rows ? 0 : share == 1 ? 1 : share == 2 ? 2 : 3][slab_pairs_per_lane(m, k, nnz, share) - 1];
-      const SlabPlan plan = two_rows ? slab_plan(m, k, n, nnz) : SlabPlan{kSlabWalk, li.grid_y};
       const bool wide = li.variant == kSpmmSlabDma && plan.form == kSlabWide;
       static const void* const inner_forms[3] = {(const void*)spmm_slab_tiles_kernel<kSlabS, 2, 2, true, kSlabTilesMax>,
                                                  (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, false, kSlabTilesMax>,
