@@ -16,8 +16,8 @@
 // 64, where the form that scans for every tile anew ran before (1393 x 5572 at 13 %, n = 3464: 309 -> 277; 7424 x 1856 at 14 %,
 // n = 580: 108.7 -> 100.8).
 //
-// A row with more pairs inside one slab needs further rounds in that slab, 16 pairs at
-// a time, each behind a full wait; they are not kept, every tile's stage fetches and scans them
+// A row with more pairs inside one slab needs further rounds in that slab, 64 pairs at
+// a time (16 beside pieces of four), each behind a full wait; they are not kept, every tile's stage fetches and scans them
 // again.
 #pragma once
 #include "common.hpp"
@@ -32,6 +32,8 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
     const float* __restrict__ values, const int* __restrict__ row_order, const float* __restrict__ B,
     float* __restrict__ C, const float* __restrict__ bias, int relu) {
   constexpr int NW = 16;
+  // pairs per lane and round of a row that has more in a slab than the look-ahead (as many as there are registers for)
+  constexpr int kRest = PW == 4 ? 1 : 4;
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int kBufBytes = (S + 1) * kSlabTile * 4;
   constexpr int kZeroOff = S * kSlabTile * 4;
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
   if (!slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
   const int tile_begin = tile_group * tiles_per_wg;
   const int ntiles = min(tiles_n, tile_begin + tiles_per_wg) - tile_begin;      // 1 .. TPW
-  const int nslabs = nnz < PW ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
+  const int nslabs = nnz < 4 ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
   const int stages = ntiles * nslabs;                       // stage q = (slab q / ntiles, tile q % ntiles)
 
   if (tid < 2 * kSlabTile)
@@ -107,7 +109,6 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
     }
     rows[j].p = rows[j].p_begin;
   }
-  const int last_nz = nnz - 1;
   using Mask = SlabMask<1>;
   // the row's lanes in a wave mask, and the lanes that have met a pair of the slab whose predecessor is not in it
   const unsigned long long row_mask = 0xffffull << (16 * sub);
@@ -208,27 +209,33 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
           if (over[j]) {
             int pe = rows[j].p;                 // where the scan stopped (the same in every tile's stage)
             while (true) {
-              const unsigned o = (unsigned)min(pe + l16, last_nz) << 2;
-              const int c = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(column_indices) + o);
-              const float a = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(values) + o);
-              const unsigned rel = (unsigned)(c - slab_start);
-              const unsigned long long mk = __builtin_amdgcn_ballot_w64(pe + l16 < rows[j].row_end) &
-                                            __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
-              const unsigned lo = (unsigned)mk, hi = (unsigned)(mk >> 32);
-              const int c0 = leading16(lo & 0xffffu), c1 = leading16(lo >> 16);
-              const int c2 = leading16(hi & 0xffffu), c3 = leading16(hi >> 16);
-              const int cm = scalar_max(scalar_max(c0, c1), scalar_max(c2, c3));
-              if (cm == 0) break;
-              const unsigned packed = (unsigned)c0 | ((unsigned)c1 << 8) | ((unsigned)c2 << 16) | ((unsigned)c3 << 24);
-              const int cnt = (int)((packed >> (8 * sub)) & 0xffu);
-              // (only the leading pairs here: one behind the first pair outside the slab belongs to
-              // a row that is not ascending, which is redone at the end anyway)
-              const bool in = l16 < cnt;
-              const float xv = in ? a : 0.f;
-              const int xo = in ? (int)(rel * (kSlabTile * 4)) : kZeroOff;
-              pe += cnt;
-              slab_steps(acc[t][j], xv, xo, buf, lane_b, cm);
-              if (cm < 16) break;
+              const int first = pe + kRest * l16, left = rows[j].row_end - first;
+              const unsigned o = (unsigned)min(first, nnz - kRest) << 2;
+              const SlabPiece<int, kRest> pc = *reinterpret_cast<const SlabPiece<int, kRest>*>(cbase + o);
+              const SlabPiece<float, kRest> pa = *reinterpret_cast<const SlabPiece<float, kRest>*>(vbase + o);
+              int xc[kRest], xo[kRest];
+              float xv[kRest];
+#pragma unroll
+              for (int e = 0; e < kRest; ++e) {
+                xc[e] = pc.v[e];
+                xv[e] = pa.v[e];
+              }
+              if (__builtin_amdgcn_ballot_w64(first > nnz - kRest && left > 0) != 0) slab_piece_shift<kRest>(xc, xv, first - (nnz - kRest));
+              unsigned long long mk[kRest];
+#pragma unroll
+              for (int e = 0; e < kRest; ++e) {
+                const unsigned rel = (unsigned)(xc[e] - slab_start);
+                mk[e] = __builtin_amdgcn_ballot_w64(left > e) & __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
+                if (e > 0) strays[j] |= mk[e] & ~mk[e - 1];
+                pe += __builtin_popcount((unsigned)mk[e] & row_lo) + __builtin_popcount((unsigned)(mk[e] >> 32) & row_hi);
+                const bool in = __builtin_amdgcn_inverse_ballot_w64(mk[e]);
+                xv[e] = in ? xv[e] : 0.f;
+                xo[e] = in ? (int)(rel * (kSlabTile * 4)) : kZeroOff;
+              }
+              strays[j] |= mk[0] & ~(Mask::lane_before(mk[kRest - 1]) | Mask::kFirst);
+              const unsigned blocks[1] = {Mask::used(mk[0])};
+              if (blocks[0] != 0) wide_steps<kRest>(acc[t][j], xv, xo, buf, lane_b, blocks);
+              if (!Mask::full(mk[kRest - 1])) break;
             }
             if (t == ntiles - 1) {              // the slab is done with: the cursor and the look-ahead move on
               rows[j].p = pe;

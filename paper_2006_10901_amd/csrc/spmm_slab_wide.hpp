@@ -83,6 +83,8 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
     const float* __restrict__ values, const int* __restrict__ row_order, const float* __restrict__ B,
     float* __restrict__ C, const float* __restrict__ bias, int relu) {
   constexpr int NW = 16, S = kWideS, RPG = kWideRows / 64, TPW = kWideTiles;
+  // pairs per lane and round of a row that has more in a slab than the look-ahead (as many as there are registers for)
+  constexpr int kRest = PW == 4 ? 1 : 2;
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int kBufBytes = (S + 1) * kWideRowBytes;
   constexpr int kZeroOff = S * kWideRowBytes;
@@ -103,7 +105,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
   int tile_begin = tile_group * tiles_per_wg;
   const int tile_end = min(tiles_n, tile_begin + tiles_per_wg);
   int ntiles = min(tile_end - tile_begin, TPW);             // of the tiles that are being computed
-  const int nslabs = nnz < PW ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
+  const int nslabs = nnz < 4 ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)
   const int stages = (tile_end - tile_begin) * nslabs;      // by TPW tiles, by slabs, by tiles
 
   if (tid < 2 * kWideTile)
@@ -261,22 +263,33 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
             if (over[j]) {
               int pe = rows[j].p;                 // where the scan stopped (the same in every tile's stage)
               while (true) {
-                const int at = pe + l16;
-                const unsigned o = (unsigned)min(at, nnz - 1) << 2;
-                const int c = *reinterpret_cast<const int*>(cbase + o);
-                const float a = *reinterpret_cast<const float*>(vbase + o);
-                const unsigned rel = (unsigned)(c - slab_start);
-                const unsigned long long mk = __builtin_amdgcn_ballot_w64(at < rows[j].row_end) &
-                                              __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
-                if (mk == 0) break;
-                strays[j] |= mk & ~(Mask::lane_before(mk) | Mask::kFirst);
-                pe += of_row(mk);
-                const bool in = __builtin_amdgcn_inverse_ballot_w64(mk);
-                const float xv[1] = {in ? a : 0.f};
-                const int xo[1] = {in ? (int)(rel * kWideRowBytes) : kZeroOff};
-                const unsigned xu[1] = {Mask::used(mk)};
-                wide8_steps<1>(acc[t][j], xv, xo, buf, lane_b, xu);
-                if (!Mask::full(mk)) break;
+                const int first = pe + kRest * l16, left = rows[j].row_end - first;
+                const unsigned o = (unsigned)min(first, nnz - kRest) << 2;
+                const SlabPiece<int, kRest> pc = *reinterpret_cast<const SlabPiece<int, kRest>*>(cbase + o);
+                const SlabPiece<float, kRest> pa = *reinterpret_cast<const SlabPiece<float, kRest>*>(vbase + o);
+                int xc[kRest], xo[kRest];
+                float xv[kRest];
+#pragma unroll
+                for (int e = 0; e < kRest; ++e) {
+                  xc[e] = pc.v[e];
+                  xv[e] = pa.v[e];
+                }
+                if (__builtin_amdgcn_ballot_w64(first > nnz - kRest && left > 0) != 0) slab_piece_shift<kRest>(xc, xv, first - (nnz - kRest));
+                unsigned long long mk[kRest];
+#pragma unroll
+                for (int e = 0; e < kRest; ++e) {
+                  const unsigned rel = (unsigned)(xc[e] - slab_start);
+                  mk[e] = __builtin_amdgcn_ballot_w64(left > e) & __builtin_amdgcn_ballot_w64(rel < (unsigned)S);
+                  if (e > 0) strays[j] |= mk[e] & ~mk[e - 1];
+                  pe += of_row(mk[e]);
+                  const bool in = __builtin_amdgcn_inverse_ballot_w64(mk[e]);
+                  xv[e] = in ? xv[e] : 0.f;
+                  xo[e] = in ? (int)(rel * kWideRowBytes) : kZeroOff;
+                }
+                strays[j] |= mk[0] & ~(Mask::lane_before(mk[kRest - 1]) | Mask::kFirst);
+                const unsigned xu[1] = {Mask::used(mk[0])};
+                if (xu[0] != 0) wide8_steps<kRest>(acc[t][j], xv, xo, buf, lane_b, xu);
+                if (!Mask::full(mk[kRest - 1])) break;
               }
               if (t == ntiles - 1) {              // the slab is done with: the cursor and the look-ahead move on
                 rows[j].p = pe;
