@@ -152,8 +152,8 @@ __device__ __forceinline__ int leading16(unsigned piece) { return __builtin_ctz(
 // Workgroup id -> (panel of sparse rows, group = slice of the dense operand) for the slab kernels.
 // Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: all
 // groups of a panel get ids that are equal modulo 8, so the panel's part of A is fetched into
-// one L2 only.  (The opposite choice, one slice of the dense operand per XCD, was measured: same
-// run time, 60 % more HBM reads.)  The panels beyond the last multiple of eight would leave some
+// one L2 only.  (The opposite choice, one slice of the dense operand per XCD, which callers have by exchanging
+// panels and groups, was measured on 8192 rows: same run time, 60 % more HBM reads; with few panels it is faster.)  The panels beyond the last multiple of eight would leave some
 // XCDs a whole panel more than others (9 panels of 25 tiles: 50 workgroups on one XCD, 25 on each of
 // the others): their (panel, group) pairs are dealt to all eight in equal runs.
 // slab_grid_size() is the matching grid, slab_xcd_load() the workgroups of one XCD.

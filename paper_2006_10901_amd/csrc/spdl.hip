@@ -295,6 +295,14 @@ int slab_wide_pairs(int m, int k, int nnz) {
   return pairs <= 16.0 ? 0 : pairs <= 32.0 ? 1 : 2;
 }
 
+// Which of a slab kernel's workgroups share an XCD (and its L2): those of a panel, which read the same part of A, or those of
+// a group of tiles, which read the same part of B.  With up to 2048 rows a group's panels fill no more than an XCD, and a B
+// that every XCD would read whole comes once (512 x 2048 at 10 %, n = 2000: 24.6 us -> 20.4; 256 x 1024 at 10 %, n = 2048: 13.7 -> 9.1; 1024 x
+// 4096 at 5 %, n = 4096: 87.7 -> 80.8, at 10 % 129.8 -> 125.0; 1180 x 1671 at 19 %, n = 2539: 80.8 -> 75.8; 2048 x 8192 at 6 %, n = 2048:
+// 169.3 -> 165.9).  With more rows it changes nothing or costs 1 % (3500 x 7000 at 5 %, n = 1500: 179.9 and 181.3; 4096 x 1024 at 5 %, n =
+// 4096: 79.5 and 80.6).  Fewer than eight groups leave XCDs without one.
+bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
+
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info, SlabPlan* plan_out) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
   // (small products with few tiles: workgroups of eight waves)
@@ -703,8 +711,10 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
           grid.x = slab_grid_size(panels, (tiles + tpw - 1) / tpw);
           lds = kWideLdsBytes;
         }
+        int tiles_first = slab_tiles_first((tiles + tpw - 1) / tpw, m);
+        if (tiles_first) grid.x = slab_grid_size((tiles + tpw - 1) / tpw, panels);
         void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, &tpw, (void*)&panels, &ro, &ci, &val, &order, &B, &C,
-                        &bias, &relu};
+                        &bias, &relu, &tiles_first};
         if (hipLaunchKernel(dma_kernel, grid, block, args, lds, st) != hipSuccess) return SPDL_ERR_LAUNCH;
       }
     } else {

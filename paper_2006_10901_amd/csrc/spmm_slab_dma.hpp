@@ -41,7 +41,7 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
     int m, int k, int n, int nnz, int tiles_n, int tiles_per_wg, int panels,
     const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
     const float* __restrict__ values, const int* __restrict__ row_order, const float* __restrict__ B,
-    float* __restrict__ C, const float* __restrict__ bias, int relu) {
+    float* __restrict__ C, const float* __restrict__ bias, int relu, int tiles_first) {
   using T = float;
   static_assert(RPG == 1 || SHARE == 1, "a row shared by lane groups, or several rows to a group");
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
@@ -60,7 +60,8 @@ __global__ __launch_bounds__(64 * NW) void spmm_slab_dma_kernel(
 
   const int groups_n = (tiles_n + tiles_per_wg - 1) / tiles_per_wg;
   int panel, tile_group;
-  if (!slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
+  if (tiles_first ? !slab_wg_map(blockIdx.x, groups_n, panels, tile_group, panel)
+                  : !slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
   const int tile_begin = tile_group * tiles_per_wg;
   const int tile_end = min(tiles_n, tile_begin + tiles_per_wg);
   const int nslabs = nnz < PW ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)

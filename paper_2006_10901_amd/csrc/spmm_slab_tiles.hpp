@@ -30,7 +30,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
     int m, int k, int n, int nnz, int tiles_n, int tiles_per_wg, int panels,
     const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
     const float* __restrict__ values, const int* __restrict__ row_order, const float* __restrict__ B,
-    float* __restrict__ C, const float* __restrict__ bias, int relu) {
+    float* __restrict__ C, const float* __restrict__ bias, int relu, int tiles_first) {
   constexpr int NW = 16;
   // pairs per lane and round of a row that has more in a slab than the look-ahead (as many as there are registers for)
   constexpr int kRest = PW == 4 ? 1 : 4;
@@ -48,7 +48,8 @@ __global__ __launch_bounds__(1024) void spmm_slab_tiles_kernel(
 
   const int groups_n = (tiles_n + tiles_per_wg - 1) / tiles_per_wg;
   int panel, tile_group;
-  if (!slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
+  if (tiles_first ? !slab_wg_map(blockIdx.x, groups_n, panels, tile_group, panel)
+                  : !slab_wg_map(blockIdx.x, panels, groups_n, panel, tile_group)) return;
   const int tile_begin = tile_group * tiles_per_wg;
   const int ntiles = min(tiles_n, tile_begin + tiles_per_wg) - tile_begin;      // 1 .. TPW
   const int nslabs = nnz < 4 ? 0 : (k + S - 1) / S;       // (rows that are not walked are gathered at the end)

@@ -84,10 +84,10 @@ def close(A, got, ref, S, what):
     assert np.all(np.isfinite(got)) and np.all(err <= (longest + 8) * 2.0 ** -24 * S), (what, float(np.max(err / np.maximum(S, 1e-300))))
 
 
-# (tiles of 64 x 64: up to 64, up to 128 and more; densities for one to four pairs per lane; slabs: whole, ragged, fewer than one)
+# (tiles of 64 x 64: up to 64, up to 128 and more; eight groups of tiles and more, up to 2048 rows and beyond; densities for one to four pairs per lane; slabs: whole, ragged, fewer than one)
 @pytest.mark.gpu
 @pytest.mark.parametrize("m,k,n", [(515, 777, 64), (600, 300, 75), (1030, 515, 260), (2000, 200, 131), (4100, 130, 130), (4100, 513, 260),
-                                   (16500, 70, 128)])
+                                   (16500, 70, 128), (1100, 260, 700), (2048, 140, 516), (2049, 140, 516)])
 @pytest.mark.parametrize("density", [0.02, 0.1, 0.17, 0.3, 0.7])
 def test_slab_pieces(g, oracle_lib, force, m, k, n, density):
     A = odd_csr(m, k, density, 7000 + m + int(100 * density))
