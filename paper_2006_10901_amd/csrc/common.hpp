@@ -138,14 +138,6 @@ struct PhaseClocks {
 };
 #endif
 
-// Maximum of two wave-uniform values on the scalar unit (left to itself the compiler moves such
-// a maximum to the vector unit as soon as one of its uses is a vector select).
-__device__ __forceinline__ int scalar_max(int a, int b) {
-  int r;
-  asm("s_max_i32 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b) : "scc");
-  return r;
-}
-
 // Number of leading set bits of a 16-bit piece of a wave mask (scalar arithmetic).
 __device__ __forceinline__ int leading16(unsigned piece) { return __builtin_ctz(~piece | 0x10000u); }
 

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
     int m, int k, int n, int nnz, int ksplit, int slabs_per_part, int panels,
     const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
     const float* __restrict__ L, const float* __restrict__ R, float* __restrict__ out,
-    const float* __restrict__ scale, const int* __restrict__ row_order) {
+    const float* __restrict__ scale, const int* __restrict__ row_order, int parts_first) {
   using T = float;
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int CW = 64 * U;                    // columns per stage
@@ -36,7 +36,8 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_slab_dma_kernel(
   const int last_nz = nnz - 1;
 
   int panel, kpart;
-  if (!slab_wg_map(blockIdx.x, panels, ksplit, panel, kpart)) return;
+  if (parts_first ? !slab_wg_map(blockIdx.x, ksplit, panels, kpart, panel)
+                  : !slab_wg_map(blockIdx.x, panels, ksplit, panel, kpart)) return;
   const int k0 = kpart * slabs_per_part * S;
   const int k1 = min(k, k0 + slabs_per_part * S);
   const int nslabs = (k1 - k0 + S - 1) / S;

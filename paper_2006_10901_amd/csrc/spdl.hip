@@ -880,6 +880,20 @@ bool sddmm_split_runs(int variant, int m, int k, int n, int nnz) {
   return sddmm_split_estimate(m, k, n, nnz) <= 0.97 * other;
 }
 
+// Which workgroups of sddmm_slab_dma_kernel share an XCD: those of a panel, which read the same rows of L, or those of a
+// range of A's columns, which read the same rows of R.  Up to 1024 rows and a longer R (which every XCD would otherwise read
+// whole) the latter: 1024 x 4096, n = 4096: 142.8 us -> 129.4 at 10 %, 134.0 -> 101.6 at 5 %; 1024 x 8192 at 5 %,
+// n = 2048: 136.8 -> 100.7; 700 x 2800 at 10 %, n = 700: 20.0 -> 18.2.  With more rows, or fewer columns, it is L that
+// would be read again (1800 x 7200 at 10 %, n = 1500: 194.3 and 201.4; 1024 x 2048 at 10 %, n = 3000: 55.5 and 56.5).
+inline bool sddmm_parts_first(int ksplit, int m, int k) {
+  return ksplit >= 8 && m <= 1024 && 2 * (int64_t)k >= 5 * (int64_t)m;
+}
+
+inline int sddmm_slab_grid(const SddmmSlabShape& sh, int m, int k, bool dma) {
+  return dma && sddmm_parts_first(sh.ksplit, m, k) ? slab_grid_size(sh.ksplit, sh.panels)
+                                                   : slab_grid_size(sh.panels, sh.ksplit);
+}
+
 template <typename T>
 void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R, spdl_launch_info* info,
                      int hint = 0) {
@@ -1083,7 +1097,7 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->lanes_per_row = 16;
     info->rows_per_block = kSdRows;
     info->block_threads = kSdThreads;
-    info->grid_x = slab_grid_size(sh.panels, sh.ksplit);
+    info->grid_x = sddmm_slab_grid(sh, m, k, variant == kSddmmSlabDma);
     info->grid_y = sh.ksplit;               // column ranges of A (the grid is 1-D)
     return;
   }
@@ -1125,7 +1139,8 @@ int launch_sddmm_slab(const SddmmSlabShape& sh, int grid, int m, int k, int n, i
       configured_dma.store(true);
     }
     kernel<<<dim3(grid), dim3(kSdThreads), sh.lds_bytes, st>>>(m, k, n, nnz, sh.ksplit, sh.spp, sh.panels, ro, ci,
-                                                               L, R, out, scale, order);
+                                                               L, R, out, scale, order,
+                                                               sddmm_parts_first(sh.ksplit, m, k));
     return SPDL_OK;
   }
   auto kernel = sddmm_slab_kernel<T, U, S, DEFERRED>;

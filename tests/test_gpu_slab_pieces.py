@@ -37,6 +37,7 @@ def force():
     import paper_2006_10901_amd as spdl
     yield spdl.spdl_force_variant
     spdl.spdl_force_variant(0, -1)
+    spdl.spdl_force_variant(1, -1)
 
 
 def odd_csr(m, k, density, seed):
@@ -138,3 +139,26 @@ def test_slab_pieces_of_arrays_shorter_than_a_round(g, oracle_lib, force, m, k, 
         B, got = run(g, A, n, force, 7101 + n, bias=bias)
         ref, S = oracle_lib.spmm_bias_relu(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B, bias, True)
         close(A, got, ref, S + np.abs(bias)[:, None], f"{m} x {k}, n = {n}, {nnz}")
+
+
+# (SDDMM: at most 1024 rows and two and a half times as many columns, whose ranges then share an XCD; eight ranges and more, also
+# not a multiple of eight; a row order)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [(300, 1100, 132), (1000, 2600, 260), (1024, 2560, 257), (1025, 2700, 132), (130, 3000, 61)])
+def test_sddmm_column_ranges_that_share_an_xcd(g, oracle_lib, force, m, k, n):
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = odd_csr(m, k, 0.06, 7400 + m)
+    L, R = wl.dense(m, n, 7401 + n), wl.dense(k, n, 7402 + n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    force(1, 3)
+    assert spdl.spdl_variant_name(1, spdl.spdl_select_sddmm(m, k, n, A.nnz, 4, 0, 0)["variant"]) == "slabdma"
+    got = g.gpu_sddmm(A, L, R, n)
+    err = np.abs(got.astype(np.float64) - ref)
+    assert np.all(np.isfinite(got)) and np.all(err <= (n + 8) * 2.0 ** -24 * S + 2.0 ** -149)
+    d = g.DevCsr(A)
+    out = torch.full((A.nnz,), float("nan"), device="cuda")
+    order = oracle_lib.row_order(A.m, A.row_offsets)
+    spdl.spdl_sddmm_ordered(m, k, n, A.nnz, d.ro, d.ci, g.dev(order), g.dev(L), g.dev(R), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), got)
