@@ -218,24 +218,30 @@ constexpr int kSlabTilesMax = 4;                  // tiles whose accumulators th
 // what is left of its `tiles`, started in order: the XCD with the most of them (slab_wg_map) deals them to its four shader
 // engines of eight compute units in turn, and one that waits for its engine waits however idle another one is.  (264
 // workgroups of three tiles, every eleventh of one, all of which fit the XCDs' idle compute units by the time they start: 51 us
-// measured, 192 of four and 24 of three 47.)  (setup + unit * units below a thousand.)
+// measured, 192 of four and 24 of three 47.)  Equal workgroups run in whole rounds.  Else they are dealt one by one: the
+// engine's compute units are a ring in the order in which they are free, and as no workgroup is longer than a whole one, that one
+// goes to the ring's end as it is and only a panel's last one moves up; 1 .. 2 ns for each.
 int slab_makespan(int panels, int tiles, int units, int unit, int setup) {
+  constexpr int kEngines = 4;
+  constexpr unsigned kUnits = kComputeUnits / 8 / kEngines;            // compute units of an engine
   const int groups = (tiles + units - 1) / units, left = tiles - (groups - 1) * units;
-  const int jobs = slab_xcd_load(panels, groups), whole = panels / 8 * groups;
+  const int jobs = slab_xcd_load(panels, groups), whole = panels / 8 * groups, full = setup + unit * units;
   if (jobs <= kComputeUnits / 8) return setup + unit * std::min(units, tiles);
-  constexpr int kSpan = 1024, kEngines = 4;
+  if (left == units || whole == 0) return (jobs + kComputeUnits / 8 - 1) / (kComputeUnits / 8) * full;
   int last = 0;
   for (int engine = 0; engine < kEngines; ++engine) {
-    unsigned char done[kSpan] = {};               // compute units that end at a time (modulo kSpan)
-    int now = 0;
-    done[0] = kComputeUnits / 8 / kEngines;
-    for (int i = engine; i < jobs; i += kEngines) {
-      while (done[now % kSpan] == 0) ++now;
-      --done[now % kSpan];
-      const int end = now + setup + unit * (i < whole && i % groups == groups - 1 ? left : units);
-      ++done[end % kSpan];
-      last = std::max(last, end);
+    int ends[kUnits] = {};
+    unsigned head = 0;
+    int group = engine;
+    for (int i = engine; i < jobs; i += kEngines, ++head) {
+      while (group >= groups) group -= groups;
+      const int end = ends[head % kUnits] + (group == groups - 1 && i < whole ? setup + unit * left : full);
+      unsigned at = head;
+      for (; at != head + 1 - kUnits && ends[(at - 1) % kUnits] > end; --at) ends[at % kUnits] = ends[(at - 1) % kUnits];
+      ends[at % kUnits] = end;
+      group += kEngines;
     }
+    last = std::max(last, ends[(head - 1) % kUnits]);
   }
   return last;
 }
@@ -268,24 +274,27 @@ SlabPlan slab_plan(int m, int k, int n, int nnz) {
   }
   const double pairs = kSlabS * (double)nnz / ((double)m * (double)k);
   const int setup = (int)std::max(1.0, std::min(60.0, 9.0 * 1024.0 / (double)k * 35.6 / (10.0 + pairs)));
-  int span = slab_makespan(panels, tiles, best.tpw, 31, setup);
+  // The forms likely to be best first, so that an even share of the others' work alone ends later and is all that is looked at
+  // (the host takes 0.9 us for a call on average and 6 for the largest grids; on ties the later form is taken).
+  int span = 1 << 30;
+  const int walked = best.tpw;
   auto try_form = [&](SlabForm form, int rows, int ntiles, int units, int unit) {
-    // (not while even an even share of the work would end later)
     const int64_t work = (int64_t)rows * ((int64_t)ntiles * unit + (ntiles + units - 1) / units * setup);
-    if (work >= (int64_t)span * kComputeUnits) return;
+    if (work > (int64_t)span * kComputeUnits) return;
     const int s = slab_makespan(rows, ntiles, units, unit, setup);
-    if (s < span) { span = s; best = {form, form == kSlabWide ? 2 * units : units}; }
+    if (s <= span) { span = s; best = {form, form == kSlabWide ? 2 * units : units}; }
   };
+  if (slab_look_fits(kWideS, m, k, nnz, 48.0))
+    for (int t = 4 * kWideTiles; t >= kWideTiles; t -= kWideTiles)
+      if (t == kWideTiles || t <= wide_tiles) try_form(kSlabWide, panels, wide_tiles, t, 53);
+  if (slab_look_fits(kSlabS, m, k, nnz, 64.0))
+    for (int t = std::min(tiles, kSlabTilesMax); t >= 2; --t) try_form(kSlabInner, panels, tiles, t, 29);
   if ((int64_t)panels * tiles < 1024) {                              // (beyond, 128 rows fill the machine as well)
+    for (int t = std::min(tiles, kSlabTilesMax); t >= 1; --t) try_form(kSlabOneRow, panels64, tiles, t, 18);
     const int t1 = slab_tiles_per_wg(panels64, tiles);
     if (t1 <= 24) try_form(kSlabOneRow, panels64, tiles, t1, 18);
-    for (int t = 1; t <= std::min(tiles, kSlabTilesMax); ++t) try_form(kSlabOneRow, panels64, tiles, t, 18);
   }
-  if (slab_look_fits(kSlabS, m, k, nnz, 64.0))
-    for (int t = 2; t <= std::min(tiles, kSlabTilesMax); ++t) try_form(kSlabInner, panels, tiles, t, 29);
-  if (slab_look_fits(kWideS, m, k, nnz, 48.0))
-    for (int t = kWideTiles; t <= 4 * kWideTiles && (t == kWideTiles || t <= wide_tiles); t += kWideTiles)
-      try_form(kSlabWide, panels, wide_tiles, t, 53);
+  try_form(kSlabWalk, panels, tiles, walked, 31);
   return best;
 }
 // index of the look-ahead's 1, 2 or 4 pairs per lane: two standard deviations over the mean (4996 x 1249, 5 %: one pair 3 % faster than
@@ -316,11 +325,8 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   const int rpg = plan.form == kSlabOneRow ? 1 : 2;
   const int rows = kSlabRows / (half ? 2 : share) * rpg;
   const int panels = (m + rows - 1) / rows;
-  int tpw = slab_tiles_per_wg(panels, tiles);
-  if (planned) {
-    // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
-    tpw = plan.form == kSlabWide ? 2 * kWideTiles : plan.tpw;
-  }
+  // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
+  const int tpw = !planned ? slab_tiles_per_wg(panels, tiles) : plan.form == kSlabWide ? 2 * kWideTiles : plan.tpw;
   const int groups = (tiles + tpw - 1) / tpw;
   info->variant = variant;
   info->vec = 4;
@@ -1543,6 +1549,11 @@ const char* spdl_status_string(int status) {
 int spdl_version(void) { return 140; }
 
 }  // extern "C"
+
+// Not part of the interface (spdl.h): what the choice among the slab SpMM's forms rests on, for the tests on the CPU.
+extern "C" int spdl_debug_slab_makespan(int panels, int tiles, int units, int unit, int setup) {
+  return slab_makespan(panels, tiles, units, unit, setup);
+}
 
 #ifdef SPDL_PHASE_CLOCKS
 // Diagnostic build only (microbench/phase_clocks.py): the table the instrumented kernels leave.

@@ -416,3 +416,39 @@ def test_work_split_per_panel_avoids_a_second_round_of_workgroups():
     assert spdl.spdl_variant_name(0, info["variant"]) == "slabdma" and info["grid_x"] == 256
     info = spdl.spdl_select_spmm(3072, 3072, 1024, 3072 * 300, 4, 0, 0)     # 48 panels, 16 tiles: 4 x 4 tiles, not 6 x 3
     assert spdl.spdl_variant_name(0, info["variant"]) == "slabdma" and info["grid_x"] == 192
+
+
+@pytest.mark.parametrize("m,k,n,density", [(71371, 1339, 7180, 0.14), (67248, 93, 6194, 0.14), (166570, 392, 2036, 0.14)])
+def test_choosing_a_slab_form_for_a_large_grid_is_quick(spdl, m, k, n, density):
+    """Every call chooses anew: some 6 us here, where dealing out every form's workgroups took 80 .. 200."""
+    import time
+    nnz, best = int(m * k * density), 1.0
+    for _ in range(20):
+        t = time.perf_counter()
+        info = spdl.spdl_select_spmm(m, k, n, nnz, 4, 0, 0)
+        best = min(best, time.perf_counter() - t)
+    assert spdl.spdl_variant_name(0, info["variant"]) == "slabdma" and best < 40e-6
+
+
+def test_estimate_of_the_last_compute_unit_is_that_of_workgroups_dealt_one_by_one():
+    """Against each engine's eight compute units as a heap: the next workgroup starts on the first one that is free."""
+    import heapq
+    import random
+    import paper_2006_10901_amd as spdl
+    lib = ctypes.CDLL(spdl.LIB_PATH)
+    rng = random.Random(20201)
+    for _ in range(1500):
+        panels, tiles = int(2 ** rng.uniform(0, 10)), int(2 ** rng.uniform(0, 8))
+        units, unit, setup = rng.choice([1, 2, 3, 4, 6, 8, rng.randint(1, 24)]), rng.choice([18, 29, 31, 53]), rng.randint(1, 60)
+        groups = -(-tiles // units)
+        left, whole, rest = tiles - (groups - 1) * units, panels // 8 * groups, -(-(panels % 8 * groups) // 8)
+        want = setup + unit * min(units, tiles)
+        if whole + rest > 32:
+            want = 0
+            for engine in range(4):
+                free = [0] * 8
+                for i in range(engine, whole + rest, 4):
+                    ends = heapq.heappop(free) + setup + unit * (left if i < whole and i % groups == groups - 1 else units)
+                    heapq.heappush(free, ends)
+                    want = max(want, ends)
+        assert lib.spdl_debug_slab_makespan(panels, tiles, units, unit, setup) == want, (panels, tiles, units, unit, setup)
