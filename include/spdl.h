@@ -243,7 +243,9 @@ typedef struct {
   int rows_per_block;   /* sparse rows per block; SDDMM's group and rowstrip: CSR entries   */
                         /* owned by one wave, rowstrip below four columns: waves per row  */
   int block_threads;
-  int grid_x, grid_y;   /* (wide slab SpMM: one workgroup may do the work of several of these) */
+  int grid_x, grid_y;   /* (families with one-dimensional grids: grid_y is no extent, but how much of   */
+                        /* a panel of rows a workgroup takes or how many share it; slab SpMM: tiles of   */
+                        /* 64 columns per workgroup)                                                     */
 } spdl_launch_info;
 int spdl_select_spmm(int m, int k, int n, int nnz, int elem_bytes, const void* B, const void* C,
                      spdl_launch_info* info);

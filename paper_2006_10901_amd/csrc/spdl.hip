@@ -325,16 +325,16 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
   const int rpg = plan.form == kSlabOneRow ? 1 : 2;
   const int rows = kSlabRows / (half ? 2 : share) * rpg;
   const int panels = (m + rows - 1) / rows;
-  // (tiles of 128 columns: two of them, reported as tiles of 64; a workgroup may take several such pairs)
-  const int tpw = !planned ? slab_tiles_per_wg(panels, tiles) : plan.form == kSlabWide ? 2 * kWideTiles : plan.tpw;
-  const int groups = (tiles + tpw - 1) / tpw;
+  const int tpw = planned ? plan.tpw : slab_tiles_per_wg(panels, tiles);
+  const int groups = plan.form == kSlabWide ? ((n + kWideTile - 1) / kWideTile + tpw / 2 - 1) / (tpw / 2) : (tiles + tpw - 1) / tpw;
   info->variant = variant;
   info->vec = 4;
   info->lanes_per_row = 16 * share;
   info->rows_per_block = rows;
   info->block_threads = half ? kSlabThreads / 2 : kSlabThreads;
-  info->grid_x = slab_grid_size(panels, groups);
-  info->grid_y = tpw;                       // tiles walked by one workgroup (the grid is 1-D)
+  const bool tiles_first = variant == kSpmmSlabDma && slab_tiles_first(groups, m);
+  info->grid_x = tiles_first ? slab_grid_size(groups, panels) : slab_grid_size(panels, groups);
+  info->grid_y = tpw;                       // tiles of 64 columns that one workgroup takes (the grid is 1-D)
 }
 
 // Kernel selection (paper Sec. "Experiments": tile and vector width from the problem shape).
@@ -713,12 +713,10 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
         int tpw = li.grid_y, lds = kSlabLdsBytes;
         if (wide) {
           tiles = (n + kWideTile - 1) / kWideTile;
-          tpw = plan.tpw / 2;
-          grid.x = slab_grid_size(panels, (tiles + tpw - 1) / tpw);
+          tpw /= 2;
           lds = kWideLdsBytes;
         }
         int tiles_first = slab_tiles_first((tiles + tpw - 1) / tpw, m);
-        if (tiles_first) grid.x = slab_grid_size((tiles + tpw - 1) / tpw, panels);
         void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, &tpw, (void*)&panels, &ro, &ci, &val, &order, &B, &C,
                         &bias, &relu, &tiles_first};
         if (hipLaunchKernel(dma_kernel, grid, block, args, lds, st) != hipSuccess) return SPDL_ERR_LAUNCH;
@@ -1550,7 +1548,14 @@ int spdl_version(void) { return 140; }
 
 }  // extern "C"
 
-// Not part of the interface (spdl.h): what the choice among the slab SpMM's forms rests on, for the tests on the CPU.
+// Not part of the interface (spdl.h), for the tests: the form of the slab SpMM that such a call runs (SlabForm; -1: rows shared by
+// lane groups or eight waves), and what the choice among them rests on.
+extern "C" int spdl_debug_slab_form(int m, int k, int n, int nnz) {
+  spdl_launch_info info;
+  SlabPlan plan = {kSlabOneRow, 0};
+  fill_spmm_slab_info(m, k, n, nnz, kSpmmSlabDma, &info, &plan);
+  return plan.tpw == 0 ? -1 : plan.form;
+}
 extern "C" int spdl_debug_slab_makespan(int panels, int tiles, int units, int unit, int setup) {
   return slab_makespan(panels, tiles, units, unit, setup);
 }

@@ -283,12 +283,12 @@ def test_sddmm_selection_of_the_window_kernel(spdl):
 
 
 def test_spmm_tile_inner_slab_kernel_shape(spdl):
-    """Wide outputs with two rows per lane group walk at most four tiles per workgroup (their
-    accumulators stay in registers while a slab is scanned once for all of them), unless a slab holds
-    more of a row than the 48 pairs of look-ahead (mean + 3 sigma)."""
+    """Wide outputs with two rows per lane group keep the accumulators of at most four tiles of 64 in registers while a
+    slab is scanned once for all of them, unless a slab holds more of a row than the look-ahead (mean + 3 sigma); with
+    tiles of 128 a workgroup may take such fours one after the other, where that makes one round of two."""
     s = spdl.spdl_select_spmm(4096, 1024, 4096, 420757, 4, 0, 0)            # Transformer W1, 10 % dense
     assert spdl.spdl_variant_name(0, s["variant"]) == "slabdma"
-    assert (s["rows_per_block"], s["grid_y"], s["grid_x"]) == (128, 4, 512)
+    assert (s["rows_per_block"], s["grid_y"], s["grid_x"]) == (128, 8, 256)        # two fours: what is launched
     s = spdl.spdl_select_spmm(1024, 4096, 4096, 420099, 4, 0, 0)            # W2: two tiles fill the machine
     assert (s["rows_per_block"], s["grid_y"]) == (128, 2)
     s = spdl.spdl_select_spmm(4096, 1024, 4096, int(4096 * 1024 * 0.3), 4, 0, 0)   # 77 pairs per slab: the other kernel
@@ -452,3 +452,32 @@ def test_estimate_of_the_last_compute_unit_is_that_of_workgroups_dealt_one_by_on
                     heapq.heappush(free, ends)
                     want = max(want, ends)
         assert lib.spdl_debug_slab_makespan(panels, tiles, units, unit, setup) == want, (panels, tiles, units, unit, setup)
+
+
+def test_slab_spmm_reports_the_grid_that_is_launched():
+    """The reported grid is the launch's own: as many workgroups as the reported panels and tiles per workgroup need, dealt to
+    the XCDs by panels or by groups of tiles; with tiles of 128 columns the groups hold whole ones."""
+    import random
+    import paper_2006_10901_amd as spdl
+    lib = ctypes.CDLL(spdl.LIB_PATH)
+    rng = random.Random(20202)
+    size = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    load = lambda panels, groups: panels // 8 * groups + -(-(panels % 8 * groups) // 8)
+    seen, swapped = set(), 0
+    while len(seen) < 5 or swapped < 200:
+        m, k, n, density = size(16, 40000), size(16, 10000), size(8, 12000), 10 ** rng.uniform(-1.6, -0.3)
+        if rng.random() < 0.3:
+            m = size(16, 2048)
+        nnz = int(m * k * density)
+        if max(m, k) * n >= 1 << 31 or nnz >= 1 << 29:
+            continue
+        info = spdl.spdl_select_spmm(m, k, n, nnz, 4, 0, 0)
+        if spdl.spdl_variant_name(0, info["variant"]) != "slabdma":
+            continue
+        form = lib.spdl_debug_slab_form(m, k, n, nnz)
+        seen.add(form)
+        tile, units = (128, info["grid_y"] // 2) if form == 2 else (64, info["grid_y"])
+        panels, groups = -(-m // info["rows_per_block"]), -(-(-(-n // tile)) // units)
+        first = groups >= 8 and m <= 2048
+        swapped += first
+        assert info["grid_x"] == 8 * (load(groups, panels) if first else load(panels, groups)), (m, k, n, nnz, form)
