@@ -1,6 +1,8 @@
 """The copy-based slab SpMM kernel's look-ahead, one piece of consecutive pairs per lane, and its rows shared by several lane
 groups, against the oracle.  Tolerance: a row of r pairs is a chain of at most r multiply-adds and three additions of partial
 sums: (r + 8) 2^-24 of the sum of absolute products."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -11,6 +13,12 @@ def choice(m, k, n, nnz):
     import paper_2006_10901_amd as spdl
     s = spdl.spdl_select_spmm(m, k, n, nnz, 4, 0, 0)
     return spdl.spdl_variant_name(0, s["variant"]), s["rows_per_block"], s["block_threads"]
+
+
+def form(A, n):
+    """Of the slab kernel: tiles scanned for one by one, a slab scanned once for several, tiles of 128 columns, panels of 64 rows."""
+    import paper_2006_10901_amd as spdl
+    return {-1: "shared", 0: "walking", 1: "inner", 2: "wide", 3: "one row"}[ctypes.CDLL(spdl.LIB_PATH).spdl_debug_slab_form(A.m, A.k, n, A.nnz)]
 
 
 def test_rows_are_shared_where_panels_of_64_leave_the_machine_half_empty():
@@ -100,17 +108,32 @@ def test_slab_pieces(g, oracle_lib, force, m, k, n, density):
     assert np.array_equal(plain, got)
 
 
-# (tiles of 128 columns, two to a workgroup: whole, ragged, the last one alone, half a tile; one, two and four pairs per lane and
+def against_the_oracle_with_bias(g, oracle_lib, force, m, k, n, density, forms):
+    A = odd_csr(m, k, density, 7200 + m + int(100 * density))
+    assert form(A, n) == forms
+    bias = np.random.default_rng(7201).standard_normal(m).astype(np.float32)
+    B, got = run(g, A, n, force, 7202 + n, oracle_lib.row_order(A.m, A.row_offsets), bias)
+    ref, S = oracle_lib.spmm_bias_relu(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B, bias, True)
+    close(A, got, ref, S + np.abs(bias)[:, None], f"{m} x {k}, n = {n}, {density}")
+
+
+# (tiles of 128 columns, two to a workgroup, or five of 64: whole, ragged; one, two and four pairs per lane and
 # rows beyond them; rows and columns around whole panels and slabs of 128; the last shape: two pairs of tiles per workgroup)
 @pytest.mark.gpu
 @pytest.mark.parametrize("m,k,n", [(4100, 129, 2048), (4096, 260, 2046), (4000, 383, 1985), (2050, 128, 4100), (3970, 90, 2177), (4096, 130, 4092)])
 @pytest.mark.parametrize("density", [0.03, 0.1, 0.2])
 def test_slab_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
-    A = odd_csr(m, k, density, 7200 + m + int(100 * density))
-    bias = np.random.default_rng(7201).standard_normal(m).astype(np.float32)
-    B, got = run(g, A, n, force, 7202 + n, oracle_lib.row_order(A.m, A.row_offsets), bias)
-    ref, S = oracle_lib.spmm_bias_relu(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B, bias, True)
-    close(A, got, ref, S + np.abs(bias)[:, None], f"{m} x {k}, n = {n}, {density}")
+    against_the_oracle_with_bias(g, oracle_lib, force, m, k, n, density, "wide" if m in (4000, 4096) else "walking")
+
+
+# (nine tiles of 128 columns, two to a workgroup and the last one alone; thirteen and nineteen, four to a workgroup and then one, or
+# two and one; the last tile of 76, 1, 17 and 35 columns and whole; all of B in one slab, which is then every pair's first and last, and
+# in two and three)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [(6000, 127, 1100), (6000, 383, 1152), (6582, 128, 1537), (6609, 129, 1544), (4618, 60, 2321), (4641, 129, 2339)])
+@pytest.mark.parametrize("density", [0.03, 0.1, 0.2])
+def test_slab_odd_numbers_of_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
+    against_the_oracle_with_bias(g, oracle_lib, force, m, k, n, density, "wide")
 
 
 # (eight panels of 128 rows, 64 tiles: two tiles of 64 per workgroup, scanned once for both; look-ahead of 32, 48 and 64 pairs, and
@@ -120,6 +143,7 @@ def test_slab_tiles_of_128_columns(g, oracle_lib, force, m, k, n, density):
 @pytest.mark.parametrize("density", [0.04, 0.1, 0.15, 0.3])
 def test_slab_scanned_once_for_two_tiles(g, oracle_lib, force, m, k, n, density):
     A = odd_csr(m, k, density, 7300 + m + int(100 * density))
+    assert form(A, n) == ("inner" if density < 0.3 else "walking")
     B, got = run(g, A, n, force, 7302 + n, oracle_lib.row_order(A.m, A.row_offsets))
     ref, S = oracle_lib.spmm(A.m, A.k, n, A.row_offsets, A.column_indices, A.values, B)
     close(A, got, ref, S, f"{m} x {k}, n = {n}, {density}")
