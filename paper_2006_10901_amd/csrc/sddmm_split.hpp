@@ -19,7 +19,9 @@
 // against 17.1.
 //
 // A row's entries are met in stored order by a cursor; entries that the cursor has not passed at the end (rows that
-// are not ascending) and results that are not finite are dot products of their own.
+// are not ascending) and results that are not finite are dot products of their own.  The ranges that the parts of such a row
+// find may overlap: an entry is its column's part's wherever that part's range holds it, so that the bits do not depend
+// on which workgroup stores last.
 #pragma once
 #include "bf16_split.hpp"
 
@@ -214,6 +216,10 @@ __global__ __launch_bounds__(64 * (kSpWaves + PICKERS)) void sddmm_split_kernel(
     const int row_begin = row_offsets[min(own_row, m)], row_end = row_offsets[min(own_row + 1, m)];
     barrier();                                                         // (the terms of L)
     const bool is_end = (lane & NR) != 0;
+    auto window_of = [&](int begin, int end, int key) __attribute__((always_inline)) {
+      const int guess = begin + (int)((float)(end - begin) * ((float)key / (float)k)) - kWave / 2;
+      return max(begin, min(guess, end - kWave));
+    };
     int bound;
     int index[NR][AHEAD];                                              // columns of the entries from the cursor on
     // The part's range of each row: the first entries with column step0 * 256 or more, and step1 * 256 (some fixed
@@ -221,8 +227,7 @@ __global__ __launch_bounds__(64 * (kSpWaves + PICKERS)) void sddmm_split_kernel(
     // would give, all bounds at a time; if a bound is not among them, by halves.
     {
       const int key = (is_end ? step1 : step0) * kSpCols;
-      const int guess = row_begin + (int)((float)(row_end - row_begin) * ((float)key / (float)k)) - kWave / 2;
-      const int window = max(row_begin, min(guess, row_end - kWave));
+      const int window = window_of(row_begin, row_end, key);
       int probe[2 * NR], below = 0;
 #pragma unroll
       for (int i = 0; i < 2 * NR; ++i)
@@ -351,10 +356,43 @@ __global__ __launch_bounds__(64 * (kSpWaves + PICKERS)) void sddmm_split_kernel(
       __builtin_amdgcn_s_setprio(0);
       clocks.lap(kPhaseScan);
     }
+    // What is left of rows that are not ascending.  All the row's bounds, found as above but one at a time, where its results were.
+    static_assert(kSpStride >= 4 * (256 + 1), "a bound for each part, of which there are as many as compute units at most");
+    const int part_cols = steps_per_part * kSpCols;
+    unsigned rows_left = 0;
+    int stopped = 0;                                                   // lane l: the cursor of row l
 #pragma unroll
-    for (int rr = 0; rr < NR; ++rr)
-      for (int p = cursor[rr] + lane; p < range_end[rr]; p += 64)
-        sddmm_store<float>(out, SCALED ? scale : nullptr, p, dot(rr, column_indices[p]));
+    for (int rr = 0; rr < NR; ++rr) {
+      rows_left |= (unsigned)(cursor[rr] < range_end[rr]) << rr;
+      stopped = lane == rr ? cursor[rr] : stopped;
+    }
+    for (; rows_left != 0; rows_left &= rows_left - 1) {
+      const int rr = __builtin_ctz(rows_left);
+      const int from = __builtin_amdgcn_readlane(stopped, rr);
+      const int begin = row_offsets[i0 + first_row + rr], end = row_offsets[i0 + first_row + rr + 1];
+      volatile int* const bounds = reinterpret_cast<volatile int*>(block + (first_row + rr) * kSpStride);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      for (int i = 0; i <= parts; ++i) {
+        const int key = i * part_cols, window = window_of(begin, end, key);
+        const int probe = column_indices[max(0, min(window + lane, nnz - 1))];
+        const unsigned long long less = __builtin_amdgcn_ballot_w64(lane < end - window && probe < key);
+        const int below = less == ~0ull ? 64 : __builtin_ctzll(~less);
+        int lo = window + below, hi = lo;
+        if (below == 0 && window > begin) lo = begin;
+        if (below == 64) hi = end;
+        while (lo < hi) {
+          const int mid = (int)(((unsigned)lo + (unsigned)hi) >> 1);
+          if (column_indices[mid] < key) lo = mid + 1; else hi = mid;
+        }
+        if (lane == 0) bounds[i] = i == 0 ? begin : i == parts ? end : lo;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      for (int p = from + lane; p < bounds[part + 1]; p += 64) {
+        const int column = column_indices[p], home = column / part_cols;
+        if (home == part || p < bounds[home] || p >= bounds[home + 1])
+          sddmm_store<float>(out, SCALED ? scale : nullptr, p, dot(rr, column));
+      }
+    }
   }
   clocks.store(blockIdx.x * (kSpWaves + PICKERS) + wave);
 }

@@ -115,3 +115,70 @@ def test_sddmm_split_products_keep_non_finite_values_and_the_whole_range(g, orac
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < A.nnz // 20
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     assert np.all(np.abs(got[inside] - ref[inside]) <= (n + 8) * 2.0 ** -24 * S[inside])
+
+
+def picked(A, k, parts):
+    """Which entries the matrix cores' results are stored for, as the kernel's comments say: the part of an entry's column, if its
+    range of the row holds the entry and its cursor comes by; and which entries another part's range holds as well."""
+    steps, f32 = -(-k // 256), np.float32
+    cols = -(-steps // parts) * 256
+    taken, shared = np.zeros(A.nnz, bool), np.zeros(A.nnz, bool)
+    for i in range(A.m):
+        begin, end = int(A.row_offsets[i]), int(A.row_offsets[i + 1])
+        c = A.column_indices[begin:end].astype(np.int64)
+        bounds = [0]
+        for h in range(1, parts):
+            key = h * cols
+            at = max(0, min(int(f32(end - begin) * (f32(key) / f32(k))) - 32, end - begin - 64))
+            window = c[at:at + 64]
+            below = int(np.argmax(window >= key)) if np.any(window >= key) else len(window)
+            lo = hi = at + below
+            if below == 0 and at > 0:
+                lo = 0
+            if below == 64:
+                hi = end - begin
+            while lo < hi:
+                mid = (lo + hi) // 2
+                lo, hi = (mid + 1, hi) if c[mid] < key else (lo, mid)
+            bounds.append(lo)
+        bounds.append(end - begin)
+        ranges = np.zeros(end - begin, int)
+        for h in range(parts):
+            ranges[bounds[h]:bounds[h + 1]] += 1
+            at = bounds[h]
+            for step in range(h * cols // 256, min((h + 1) * cols // 256, steps)):
+                while at < bounds[h + 1] and c[at] // 256 == step:
+                    taken[begin + at] = True
+                    at += 1
+        shared[begin:end] = ranges > 1
+    return taken, shared
+
+
+@pytest.mark.parametrize("m,k,n,density", [(320, 2570, 128, 0.8), (320, 1500, 96, 0.8), (515, 4097, 64, 0.5), (300, 5000, 75, 0.6),
+                                           (256, 1300, 20, 0.7)])
+def test_sddmm_split_products_of_rows_in_no_order_do_not_depend_on_who_stores_last(g, oracle_lib, force, m, k, n, density):
+    import paper_2006_10901_amd as spdl
+    A = mask_csr(m, k, density, 9300 + n, odd_rows=False)
+    L, R = wl.dense(m, n, 9301 + n), wl.dense(k, n, 9302 + n)
+    assert runs_split(A, n)
+    parts = spdl.spdl_select_sddmm(m, k, n, A.nnz, 4, 0, 0)["grid_y"]
+    assert parts > 1
+    ascending = g.gpu_sddmm(A, L, R, n)                       # every entry from the matrix cores
+    rng = np.random.default_rng(9303)
+    order = np.arange(A.nnz)
+    for i in range(m):
+        row = order[A.row_offsets[i]:A.row_offsets[i + 1]]
+        if i % 5 == 1:
+            rng.shuffle(row)
+        elif i % 5 > 1:                                       # a few ascending runs, exchanged
+            runs = np.split(row.copy(), np.sort(rng.integers(0, len(row), int(rng.integers(2, 8)))))
+            row[:] = np.concatenate([runs[j] for j in rng.permutation(len(runs))])
+    B = wl.Csr(m, k, A.row_offsets, A.column_indices[order].copy(), A.values)
+    taken, shared = picked(B, k, parts)
+    assert np.count_nonzero(taken & shared) > 200 and not np.all(taken)
+    got = g.gpu_sddmm(B, L, R, n)
+    ref, S = oracle_lib.sddmm(m, k, n, B.row_offsets, B.column_indices, L, R)
+    close(got, ref, S, n, f"{m} x {k}, n = {n}")
+    assert np.array_equal(got[taken], ascending[order][taken])
+    for _ in range(3):
+        assert np.array_equal(g.gpu_sddmm(B, L, R, n), got)
