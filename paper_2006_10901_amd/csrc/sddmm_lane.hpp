@@ -518,21 +518,44 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
   clocks.lap(kPhaseRest);
   clocks.store(blockIdx.x * (kSdThreads / 64) + wave);
 
-  // A range whose cursor did not stop exactly at its end was not ascending: redo it directly.
+  // A range whose cursor did not stop exactly at its end was not ascending: redo it directly.  The ranges of the parts cover such
+  // a row but may overlap, and where another part's is ascending, a later chunk of a longer dot product adds to what out holds: an
+  // entry in the range of the part that its column belongs to is left to that part.  (All the bounds by the same searches as in the
+  // set-up, as for a row that is not ascending only the same procedure gives the same ranges; they are kept in LDS, which
+  // nobody reads any more, a bound for each of at most as many parts as there are compute units.)
+  constexpr int kBounds = 256 + 1;
+  static_assert(kBounds * 4 * 64 <= kLaneLdsBytes && kBounds * 4 * 64 <= kLaneNtLdsBytes, "a row's bounds for each lane group");
 #pragma unroll
   for (int j = 0; j < RPG; ++j)
     if (p[j] != p_end[j] && row[j] >= 0) {
-      // (the same searches as in the set-up: for a row that is not ascending only the same procedure
-      // gives the same range, and the ranges of the column parts have to tile the row)
       const int rb = row_offsets[row[j]], re = row_offsets[row[j] + 1];
-      int lo2[2] = {rb, k1 >= k ? re : rb}, hi2[2] = {k0 <= 0 ? rb : re, re};
-      const int key2[2] = {k0, k1};
-      sd_lower_bound16_batch<2>(column_indices, lo2, hi2, key2, sub, l16, last_nz, k);
-      const int b0 = lo2[0];
-      const int e = max(lo2[1], b0);
+      volatile int* const bounds = reinterpret_cast<volatile int*>(lds_raw) + (tid >> 4) * kBounds;
+      const int part_cols = slabs_per_part * S;
+      for (int i = 0; i <= ksplit; i += 2) {
+        int lo2[2], hi2[2], key2[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          lo2[e] = i + e >= ksplit ? re : rb;
+          hi2[e] = i + e == 0 ? rb : re;
+          key2[e] = min(k, (i + e) * part_cols);
+        }
+        sd_lower_bound16_batch<2>(column_indices, lo2, hi2, key2, sub, l16, last_nz, k);
+        if (l16 == 0) {
+          bounds[i] = lo2[0];
+          if (i + 1 <= ksplit) bounds[i + 1] = lo2[1];
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      const int b0 = bounds[kpart];
+      const int e = max(bounds[kpart + 1], b0);
+      auto left_to_us = [&](int t) __attribute__((always_inline)) {
+        const int home = column_indices[t] / part_cols;
+        return home == kpart || t < bounds[home] || t >= bounds[home + 1];
+      };
       if constexpr (NT) {
         // one lane per stored entry, the plain definition
         for (int t = b0 + l16; t < e; t += 16) {
+          if (!left_to_us(t)) continue;
           const float* lrow = L + (size_t)row[j] * n;
           const float* rcol = R + column_indices[t];
           float acc = 0.f;
@@ -545,6 +568,7 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
         const float* lfull = L - c0 + (size_t)row[j] * ld;
         const float* rfull = R - c0;
         for (int t = b0 + l16; t < e; t += 16) {
+          if (!left_to_us(t)) continue;
           const float* rrow = rfull + (size_t)column_indices[t] * ld;
           float acc = 0.f;
           for (int c = 0; c < c0 + n; ++c) acc = __builtin_fmaf(lfull[c], rrow[c], acc);
@@ -552,8 +576,8 @@ __global__ __launch_bounds__(kSdThreads) void sddmm_lane_kernel(
         }
       } else {
         for (int t = b0; t < e; t += 16)
-          sd_strip_direct_call<float>(n, t, e, l16, L + (size_t)row[j] * n, column_indices, R, out,
-                                      SCALED ? scale : nullptr);
+          sd_strip_direct_kept_call<float>(n, t, e, t + l16 < e && left_to_us(t + l16), l16, L + (size_t)row[j] * n, column_indices,
+                                           R, out, SCALED ? scale : nullptr);
       }
     }
 

@@ -138,6 +138,13 @@ __device__ __attribute__((noinline)) void sd_strip_direct_call(int n, int q, int
                                                                const T* scale) {
   sddmm_strip_direct<T>(n, q, end, l16, Lrow, column_indices, R, out, scale);
 }
+// ... of whose results those of the lanes with `keep` are stored.
+template <typename T>
+__device__ __attribute__((noinline)) void sd_strip_direct_kept_call(int n, int q, int end, bool keep, int l16, const T* Lrow,
+                                                                    const int* column_indices, const T* R, T* out,
+                                                                    const T* scale) {
+  sddmm_strip_direct_at<T>(n, q, keep ? end : 0, l16, sddmm_strip_offset(n, q, end, l16, column_indices), Lrow, R, out, scale);
+}
 
 struct SdRow {
   int row, p_start, p_end, row_end, p;

@@ -182,3 +182,70 @@ def test_sddmm_split_products_of_rows_in_no_order_do_not_depend_on_who_stores_la
     assert np.array_equal(got[taken], ascending[order][taken])
     for _ in range(3):
         assert np.array_equal(g.gpu_sddmm(B, L, R, n), got)
+
+
+def lane_bounds(c, k, parts, cols):
+    """Where the lane kernel's parts begin in a row: sixteen probes around the place that evenly spread columns would give, then
+    by sixteenths; rows that are not ascending have some such bounds too."""
+    f32, bounds = np.float32, [0]
+    for h in range(1, parts):
+        key, lo, hi = h * cols, 0, len(c)
+        f = f32(key) / f32(k)
+        gap = int(f32(0.5) * np.sqrt(max(f32(hi) * f * (f32(1) - f), f32(0)))) + 1
+        at = lambda i: min(max(int(f32(len(c)) * f) - ((15 * gap) >> 1) + i * gap, 0), len(c) - 1)
+        less = [c[at(i)] < key for i in range(16)] + [False]
+        count = less.index(False)
+        lo = at(count - 1) + 1 if count > 0 else 0
+        hi = max(at(count) if count < 16 else hi, lo)
+        while lo < hi:
+            step = (hi - lo + 15) >> 4
+            count = ([lo + (i + 1) * step - 1 < hi and c[lo + (i + 1) * step - 1] < key for i in range(16)] + [False]).index(False)
+            hi = max(min(hi, lo + (count + 1) * step - 1), lo + count * step)
+            lo += count * step
+        bounds.append(lo)
+    return bounds + [len(c)]
+
+
+@pytest.mark.parametrize("m,k,n,density", [(300, 1500, 100, 0.3), (515, 2570, 200, 0.3), (2500, 1283, 389, 0.1), (300, 1500, 256, 0.5)])
+def test_sddmm_lane_kernel_adds_no_chunk_to_what_another_part_has_stored(g, oracle_lib, force, m, k, n, density):
+    """Rows of ascending runs, exchanged: the ranges of two parts may overlap, of which one adds the chunks of 128 columns one by
+    one and the other stores whole sums."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = mask_csr(m, k, density, 9400 + n, odd_rows=False)
+    L, R = wl.dense(m, n, 9401 + n), wl.dense(k, n, 9402 + n)
+    rng = np.random.default_rng(9403)
+    ci = A.column_indices
+    for i in range(m):
+        row = ci[A.row_offsets[i]:A.row_offsets[i + 1]]
+        if i % 5 == 1:
+            rng.shuffle(row)
+        elif i % 5 > 1:
+            runs = np.split(row.copy(), np.sort(rng.integers(0, len(row), int(rng.integers(2, 8)))))
+            row[:] = np.concatenate([runs[j] for j in rng.permutation(len(runs))])
+    force(1, 5)
+    info = spdl.spdl_select_sddmm(m, k, n, A.nnz, 4, 0, 0)
+    assert spdl.spdl_variant_name(1, info["variant"]) == "lane" and info["lanes_per_row"] == 2
+    parts = info["grid_y"]
+    cols = -(-(-(-k // 128)) // parts) * 128
+    met = 0
+    for i in range(m):
+        c = ci[A.row_offsets[i]:A.row_offsets[i + 1]]
+        b = lane_bounds(c, k, parts, cols)
+        for h in range(parts):
+            seg = c[b[h]:b[h + 1]]
+            if len(seg) and np.all(np.diff(seg) > 0) and seg[0] >= h * cols and seg[-1] < (h + 1) * cols:
+                met += any(o != h and max(b[o], b[h]) < min(b[o + 1], b[h + 1]) for o in range(parts))
+    assert met > 0
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, ci, L, R)
+    got = g.gpu_sddmm(A, L, R, n)
+    close(got, ref, S, n, f"{m} x {k}, n = {n}")
+    for _ in range(3):
+        assert np.array_equal(g.gpu_sddmm(A, L, R, n), got)
+    if n <= 128:
+        force(1, -1)
+        d, out = g.DevCsr(A), torch.full((A.nnz,), float("nan"), device="cuda")
+        spdl.spdl_sddmm_nt(m, k, n, A.nnz, d.ro, d.ci, d.val, g.dev(L), g.dev(np.ascontiguousarray(R.T)), out)
+        torch.cuda.synchronize()
+        v = A.values.astype(np.float64)
+        close(out.cpu().numpy(), v * ref, np.abs(v) * S, n, f"not transposed, {m} x {k}, n = {n}")
