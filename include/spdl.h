@@ -77,7 +77,8 @@ int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* c
  *   Products and sums are fp32.  Dense A with dot products of up to 128 columns: products from three
  *   bf16 terms per number, which hold all of its 24 bits, of whose nine products the six largest (the others: less than
  *   2^-24 of the whole) are added up in fp32 on the matrix cores.  For normally distributed inputs, where it was measured,
- *   that is no less exact than the other kernels (2-norm of the error at n = 64: 5.0e-8 of the result's, 6.8e-8 there). */
+ *   that is no less exact than the other kernels (2-norm of the error at n = 64: 5.0e-8 of the result's, 6.8e-8 there).
+ *   The result is deterministic, rows in no order included. */
 int spdl_sddmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
                const float* L, const float* R, float* out_values, void* stream);
 
