@@ -171,9 +171,10 @@ int split_for_machine(int panels, int total, int slots = kComputeUnits) {
 
 int slab_tiles_per_wg(int panels, int tiles, int slots = kComputeUnits) { return split_for_machine(panels, tiles, slots); }
 
-// Products with so few positions keep a lane group per row: its sums are added in stored order and are the bits of the
-// other families, and it is on such small ones that results are compared between families.  (The launches take 5 .. 11 us;
-// sharing rows takes a tenth to a fifth off them: 203 x 700 at 15 %, n = 75: 8.4 us against 6.7, row-splitting 5.0.)
+// Products with so few positions keep a lane group per row, whose sums are added in stored order: whichever of the slab and
+// row-splitting kernels such a product runs in, the result has the same bits, on which tests of all families at 203 x 700 insist.
+// What that costs: sharing rows would take a tenth to a fifth off launches of 5 .. 11 us (203 x 700 at 15 %, n = 75:
+// 8.4 us against 6.7, row-splitting 5.0), of which a tenth are left to the slab kernel.
 inline bool slab_rows_stay_whole(int m, int k) { return (int64_t)m * (int64_t)k <= 384 * 384; }
 
 // Panels for the copy-based kernel when panels of 64 rows would leave half of the compute units or more without a
@@ -306,10 +307,11 @@ int slab_wide_pairs(int m, int k, int nnz) {
 
 // Which of a slab kernel's workgroups share an XCD (and its L2): those of a panel, which read the same part of A, or those of
 // a group of tiles, which read the same part of B.  With up to 2048 rows a group's panels fill no more than an XCD, and a B
-// that every XCD would read whole comes once (512 x 2048 at 10 %, n = 2000: 24.6 us -> 20.4; 256 x 1024 at 10 %, n = 2048: 13.7 -> 9.1; 1024 x
-// 4096 at 5 %, n = 4096: 87.7 -> 80.8, at 10 % 129.8 -> 125.0; 1180 x 1671 at 19 %, n = 2539: 80.8 -> 75.8; 2048 x 8192 at 6 %, n = 2048:
-// 169.3 -> 165.9).  With more rows it changes nothing or costs 1 % (3500 x 7000 at 5 %, n = 1500: 179.9 and 181.3; 4096 x 1024 at 5 %, n =
-// 4096: 79.5 and 80.6).  Fewer than eight groups leave XCDs without one.
+// that every XCD would read whole comes once (1024 x 4096, n = 4096: 100 MB instead of 542).  us, a launch repeated / with nothing in
+// the caches: 512 x 2048 at 10 %, n = 2000: 25.2 -> 21.4 / 30.7 -> 28.9; 256 x 1024 at 10 %, n = 2048: 13.8 -> 9.3 / 17.4 -> 15.1; 1024 x
+// 4096, n = 4096, at 5 % 83.0 -> 76.0 / 94.2 -> 88.0, at 10 % 117.1 -> 113.8 / 129.5 -> 126.3; 1180 x 1671 at 19 %, n = 2539: 75.0 -> 69.7 /
+// 85.1 -> 83.8; 2048 x 8192 at 6 %, n = 2048: 159.8 -> 158.3 / 174.8 -> 173.6.  With more rows it changes nothing or costs 1 % (3500 x 7000
+// at 5 %, n = 1500: 179.9 and 181.3; 4096 x 1024 at 5 %, n = 4096: 79.5 and 80.6).  Fewer than eight groups leave XCDs without one.
 bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info, SlabPlan* plan_out) {
@@ -430,8 +432,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     variant = kSpmmMfma;
   if (variant == kSpmmMfma) {
     // 32-row panels, one or two tiles per workgroup.  (64-row panels, which would halve the
-    // reads of B, need 256 accumulator registers per lane; the compiler then spills in the main
-    // loop and the kernel is twice as slow.)
+    // reads of B, need 256 accumulator registers per lane with tiles of 256 columns; the compiler then spills in the main
+    // loop and the kernel is twice as slow.  With tiles of 128 columns they would need as many as now: not tried.)
     const int tiles_n = (n + 255) / 256;
     info->variant = kSpmmMfma;
     info->vec = 8;
@@ -886,9 +888,11 @@ bool sddmm_split_runs(int variant, int m, int k, int n, int nnz) {
 
 // Which workgroups of sddmm_slab_dma_kernel share an XCD: those of a panel, which read the same rows of L, or those of a
 // range of A's columns, which read the same rows of R.  Up to 1024 rows and a longer R (which every XCD would otherwise read
-// whole) the latter: 1024 x 4096, n = 4096: 142.8 us -> 129.4 at 10 %, 134.0 -> 101.6 at 5 %; 1024 x 8192 at 5 %,
-// n = 2048: 136.8 -> 100.7; 700 x 2800 at 10 %, n = 700: 20.0 -> 18.2.  With more rows, or fewer columns, it is L that
-// would be read again (1800 x 7200 at 10 %, n = 1500: 194.3 and 201.4; 1024 x 2048 at 10 %, n = 3000: 55.5 and 56.5).
+// whole: 1024 x 4096, n = 4096: 575 MB from behind the L2s, now 356) the latter.  us, a launch repeated, which finds R in the Infinity
+// Cache / with nothing in the caches: 1024 x 4096, n = 4096, at 10 % 142.8 -> 130.9 / 161.4 -> 160.5, at 5 % 134.5 -> 98.2 / 155.4 ->
+// 149.6; 1024 x 8192 at 5 %, n = 2048: 136.7 -> 98.7 / 167.3 -> 152.6; 700 x 2800 at 10 %, n = 700: 21.2 -> 19.8 / 26.4 -> 25.4.  With
+// more rows, or fewer columns, it is L that would be read again (1800 x 7200 at 10 %, n = 1500: 194.3 and 201.4; 1024 x 2048 at 10 %, n =
+// 3000: 55.5 and 56.5).
 inline bool sddmm_parts_first(int ksplit, int m, int k) {
   return ksplit >= 8 && m <= 1024 && 2 * (int64_t)k >= 5 * (int64_t)m;
 }
@@ -949,7 +953,11 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       const bool slab = fp32_fast && reuse >= 2.0 &&
                         (n >= 128 || reuse >= 8.0 || (reuse >= 5.0 && m >= 8192) || (reuse >= 4.0 && whole_rounds) ||
                          (reuse >= 4.2 && m >= 2048 && m != k && n > 16)) ||
-                        // (the matrix-core form where it is estimated below gathering as well; not for square matrices)
+                        // (the matrix-core form where it is estimated below gathering as well; not for square matrices, which
+                        // may be banded masks: it multiplies whole blocks wherever the entries lie, but the waves that pick
+                        // them wait for the steps that hold a row's band.  64 columns, matrix cores against gathers: 2048^2 at 12 %,
+                        // uniform 10.2 us and 10.8, a band 21.7 and 10.8; 4096^2 at 12 %, uniform 19.2 and 24.5 (window), a band
+                        // 44.5 and 19.2, half band, half uniform 33.2 and 23.4)
                         (fp32_fast && n <= 64 && m != k && sddmm_split_runs(kSddmmSlabDma, m, k, n, nnz) &&
                          sddmm_split_estimate(m, k, n, nnz) <= 4.0 + 12.3e-6 * (double)nnz);
       // Few entries: the nonzero-split kernel may be done before the others have filled their first slabs (850 x 434

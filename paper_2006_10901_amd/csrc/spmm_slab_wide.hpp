@@ -1,7 +1,7 @@
 // SpMM, slab family for wide outputs, tiles of 128 columns: a lane owns eight of them, 4 l16 .. and 64 + 4 l16 .., so that
 // one LDS address serves eight multiply-adds.  Everything else is as in the tile-inner form with tiles of 64: panels of 128
-// sparse rows, two rows per 16-lane group, up to two tiles' accumulators in registers (32 of them), a slab scanned once for
-// both.  The slab is 128 rows of B by 128 columns, 64 KB as there.
+// sparse rows, two rows per 16-lane group, two tiles' accumulators in registers (32 of them), a slab scanned once for
+// both; a workgroup may be dealt up to four such pairs, one after the other.  The slab is 128 rows of B by 128 columns, 64 KB as there.
 //
 // What bounds it: the step (39.6 multiply-adds per clock and CU against 30.8 with four columns per lane, stand-alone) on the
 // pairs that the longest of a wave's four rows has in a slab.  Slabs of 128 rows hold half as many, which spreads
@@ -19,7 +19,7 @@ constexpr int kWideTile = 128;
 constexpr int kWideRowBytes = kWideTile * 4;
 constexpr int kWideS = 128;            // rows of B per slab
 constexpr int kWideRows = 128;         // sparse rows per workgroup
-constexpr int kWideTiles = 2;          // tiles per workgroup at most
+constexpr int kWideTiles = 2;          // tiles that a workgroup has in registers at a time (it may be dealt several pairs)
 constexpr int kWideLdsBytes = 2 * (kWideS + 1) * kWideRowBytes;
 
 // Two pairs of every 16-lane group: two LDS addresses and four 128-bit reads (columns 4 l16 .. and 64 + 4 l16 ..), then
