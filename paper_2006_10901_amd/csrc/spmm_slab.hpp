@@ -198,6 +198,19 @@ struct SlabRow {
   float a_next;
 };
 
+// A row whose columns are not ascending, from the start: four columns of it by direct gathers.
+__device__ __forceinline__ void slab_gather_row(float (&sum)[4], const SlabRow& r, const int* __restrict__ column_indices,
+                                                const float* __restrict__ values, const float* __restrict__ Bcol, int n) {
+  sum[0] = sum[1] = sum[2] = sum[3] = 0.f;
+  for (int e = r.p_begin; e < r.row_end; ++e) {
+    const float a = values[e];
+    float b[4];
+    Pack<float, 4>::load(Bcol + (size_t)column_indices[e] * n, b);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sum[v] = __builtin_fmaf(a, b[v], sum[v]);
+  }
+}
+
 // The loads are unconditional (index clamped into the arrays, result discarded past the row
 // end): a load under a branch would make the compiler wait for it at once, and the point of
 // fetching a round ahead is to leave it in flight.  Byte offsets are 32-bit so that the loads

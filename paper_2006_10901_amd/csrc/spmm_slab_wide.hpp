@@ -320,17 +320,7 @@ __global__ __launch_bounds__(1024) void spmm_slab_wide_kernel(
             float sum[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) sum[v] = acc[t][j][4 * h + v];
-            if (redo) {
-              sum[0] = sum[1] = sum[2] = sum[3] = 0.f;
-              const float* Bcol = B + (col_ok ? col : 0);
-              for (int e = rows[j].p_begin; e < rows[j].row_end; ++e) {
-                const float a = values[e];
-                float b[4];
-                Pack<float, 4>::load(Bcol + (size_t)column_indices[e] * n, b);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sum[v] = __builtin_fmaf(a, b[v], sum[v]);
-              }
-            }
+            if (redo) slab_gather_row(sum, rows[j], column_indices, values, B + (col_ok ? col : 0), n);
             if (rows[j].row >= 0 && col_ok) {
               spmm_epilogue<float, 4>(sum, bias, rows[j].row, relu);
               Pack<float, 4>::store(C + (size_t)rows[j].row * n + col, sum);
