@@ -64,6 +64,11 @@ typedef enum {
  *   stored order; when few long rows are spread over several lane groups, and in the window kernel
  *   (attention-shaped problems among others: it keeps a window of B around a band of A in
  *   on-chip memory and takes rows in their natural order), partial sums are added at the end.
+ *   Dense A (about one position in five and more, from 33 columns of B on, where the output fills the machine): products from
+ *   three bf16 terms per number, which hold all of its 24 bits, of whose nine products the six largest (the others: less than
+ *   2^-23 of the whole) are added up in fp32 on the matrix cores, zeros of A included; what comes out as Inf or NaN, and rows that
+ *   are not ascending, are gathered.  For normally distributed inputs, where it was measured, that is no less exact than the
+ *   other kernels (2-norm of the error, 8192 x 10240 at 20 %: 6.6e-7 of the result's, 8.1e-7 there).
  *   Either way the result is deterministic and does not depend on row_order. */
 int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
               const float* values, const int* row_order, const float* B, float* C, void* stream);

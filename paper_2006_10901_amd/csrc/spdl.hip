@@ -26,6 +26,7 @@
 #include "spmm_window.hpp"
 #include "spmm_slab_tiles.hpp"
 #include "spmm_slab_wide.hpp"
+#include "spmm_split.hpp"
 #include "sddmm_window.hpp"
 #include "sddmm_split.hpp"
 
@@ -249,9 +250,10 @@ int slab_makespan(int panels, int tiles, int units, int unit, int setup) {
 
 // Forms of the copy-based slab kernel where panels of 64 rows give half of the compute units or more a workgroup.  128 rows, two per
 // group: tiles of 64 columns, scanned for each tile anew; tiles of 64, a slab scanned once for up to four; tiles of 128 (a lane
-// owns eight columns), a slab scanned once for two.  64 rows, one per group: tiles of 64.
-enum SlabForm { kSlabWalk, kSlabInner, kSlabWide, kSlabOneRow };
-struct SlabPlan { SlabForm form; int tpw; };      // tiles of 64 columns per workgroup (wide: two for each of 128)
+// owns eight columns), a slab scanned once for two.  64 rows, one per group: tiles of 64.  Dense matrices: whole blocks on the matrix cores.
+enum SlabForm { kSlabWalk, kSlabInner, kSlabWide, kSlabOneRow, kSlabSplit };
+// tiles of 64 columns per workgroup (wide: two for each of 128); when the last compute unit ends (slab_makespan; 0: not worked out)
+struct SlabPlan { SlabForm form; int tpw; int span; };
 
 // The form whose last compute unit is estimated to end first.  In thirtieths of a tile of 64 columns and 128 rows: 31 if it is scanned
 // for alone, 29 together with others, 53 a tile of 128 columns, 18 one of 64 rows; a workgroup's set-up is worth 9 at 1024 columns and 10
@@ -268,9 +270,9 @@ SlabPlan slab_plan(int m, int k, int n, int nnz) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile, panels = (m + kWideRows - 1) / kWideRows;
   const int wide_tiles = (n + kWideTile - 1) / kWideTile;
   const int panels64 = (m + kSlabRows - 1) / kSlabRows;
-  SlabPlan best = {kSlabWalk, slab_tiles_per_wg(panels, tiles)};
+  SlabPlan best = {kSlabWalk, slab_tiles_per_wg(panels, tiles), 0};
   if (best.tpw > 24 || slab_xcd_load(panels, tiles) > 8192) {        // (many rounds: all much the same)
-    if (best.tpw >= 2 && slab_look_fits(kSlabS, m, k, nnz, 64.0)) best = {kSlabInner, kSlabTilesMax};
+    if (best.tpw >= 2 && slab_look_fits(kSlabS, m, k, nnz, 64.0)) best = {kSlabInner, kSlabTilesMax, 0};
     return best;
   }
   const double pairs = kSlabS * (double)nnz / ((double)m * (double)k);
@@ -283,7 +285,7 @@ SlabPlan slab_plan(int m, int k, int n, int nnz) {
     const int64_t work = (int64_t)rows * ((int64_t)ntiles * unit + (ntiles + units - 1) / units * setup);
     if (work > (int64_t)span * kComputeUnits) return;
     const int s = slab_makespan(rows, ntiles, units, unit, setup);
-    if (s <= span) { span = s; best = {form, form == kSlabWide ? 2 * units : units}; }
+    if (s <= span) { span = s; best = {form, form == kSlabWide ? 2 * units : units, s}; }
   };
   if (slab_look_fits(kWideS, m, k, nnz, 48.0))
     for (int t = 4 * kWideTiles; t >= kWideTiles; t -= kWideTiles)
@@ -314,6 +316,30 @@ int slab_wide_pairs(int m, int k, int nnz) {
 // at 5 %, n = 1500: 179.9 and 181.3; 4096 x 1024 at 5 %, n = 4096: 79.5 and 80.6).  Fewer than eight groups leave XCDs without one.
 bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 
+// Whether the matrix-core form (spmm_split.hpp) takes the place of the plan's.  Estimates in microseconds: rounds of one workgroup per
+// compute unit, each of so many stages of 128 columns; the plan's end (slab_makespan), whose unit is a thirtieth of a tile's
+// walk over A's columns.  Fitted on 200 uniform shapes of 129 tiles of 64 x 64 and more (1024 .. 18800 rows, 720 .. 11600 columns, n = 33 ..
+// 4096, 11 .. 50 %: 5 % off for the matrix cores, 4 % and 6 % for the forms that walk and with one row per group); the choice takes
+// 1.005 times the faster one's time on average, 0.81 times the plan's.  The two meet at 17 .. 22 %, earlier where the rounds
+// fit (8192 x 10240, n = 128: 15 % 109 us and 122, 20 % 132 and 127, 30 % 185 and 135).
+// Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
+// 1024 at 30 %, n = 4096, among others) stay with the forms that tests of them fix there.
+bool spmm_split_runs(int m, int k, int n, int nnz, const SlabPlan& plan) {
+  if (n <= 32 || n > 2048 || k < 800 || nnz >= (1 << 28) || plan.span == 0) return false;
+  const double density = (double)nnz / ((double)m * (double)k);
+  if (density < 0.12) return false;
+  const int load = slab_xcd_load((m + kDsRows - 1) / kDsRows, (n + kDsCols - 1) / kDsCols);
+  const double rounds = std::ceil(load / (kComputeUnits / 8.0)), stages = (double)((k + kDsS - 1) / kDsS);
+  const double t_split = -0.55 + rounds * (5.09 + stages * (1.138 + 1.18 * density));
+  const double form = plan.form == kSlabWalk || plan.form == kSlabWide ? 1.08 : plan.form == kSlabOneRow ? 0.957 : 1.0;
+  return t_split <= 0.97 * form * plan.span * (double)k * (0.173e-3 + 2.876e-3 * density);
+}
+// sixteens of a row's entries fetched a stage ahead (two standard deviations over the mean)
+int spmm_split_chunks(int m, int k, int nnz) {
+  const double mean = (double)kDsS * (double)nnz / ((double)m * (double)k), entries = mean + 2.0 * std::sqrt(mean);
+  return entries <= 32.0 ? 2 : entries <= 48.0 ? 3 : 4;
+}
+
 void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_info* info, SlabPlan* plan_out) {
   const int tiles = (n + kSlabTile - 1) / kSlabTile;
   // (small products with few tiles: workgroups of eight waves)
@@ -321,8 +347,20 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
                     (int64_t)((m + kSlabRows - 1) / kSlabRows) * tiles <= kComputeUnits / 2;
   const int share = variant == kSpmmSlabDma ? slab_groups_per_row(m, k, n) : 1;
   const bool planned = variant == kSpmmSlabDma && share == 1 && !half;
-  SlabPlan plan = {kSlabOneRow, 0};
+  SlabPlan plan = {kSlabOneRow, 0, 0};
   if (planned) plan = slab_plan(m, k, n, nnz);
+  if (planned && spmm_split_runs(m, k, n, nnz, plan)) {
+    const int panels = (m + kDsRows - 1) / kDsRows;
+    if (plan_out) *plan_out = {kSlabSplit, 1, 0};
+    info->variant = variant;
+    info->vec = 4;
+    info->lanes_per_row = kWave;
+    info->rows_per_block = kDsRows;
+    info->block_threads = kDsThreads;
+    info->grid_x = slab_tiles_first(tiles, m) ? slab_grid_size(tiles, panels) : slab_grid_size(panels, tiles);
+    info->grid_y = 1;                       // tiles of 64 columns that one workgroup takes (the grid is 1-D)
+    return;
+  }
   if (plan_out) *plan_out = plan;
   const int rpg = plan.form == kSlabOneRow ? 1 : 2;
   const int rows = kSlabRows / (half ? 2 : share) * rpg;
@@ -628,7 +666,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
   if (!ro || !C || (nnz > 0 && (!ci || !val || !B))) return SPDL_ERR_INVALID;
   hipStream_t st = static_cast<hipStream_t>(stream);
   spdl_launch_info li;
-  SlabPlan plan = {kSlabOneRow, 0};
+  SlabPlan plan = {kSlabOneRow, 0, 0};
   fill_spmm_info<T>(m, k, n, nnz, B, C, &li, hint, &plan);
   (void)hipGetLastError();
   int rc = SPDL_OK;
@@ -683,6 +721,21 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       const int share = two_rows || half ? 1 : kSlabRows / li.rows_per_block;
       const void* dma_kernel = half ? half_form
                                     : forms[two_rows ? 0 : share == 1 ? 1 : share == 2 ? 2 : 3][slab_pairs_per_lane(m, k, nnz, share) - 1];
+      if (plan.form == kSlabSplit) {
+        static std::atomic<bool> split_configured{false};
+        static const void* const split_forms[3] = {(const void*)spmm_split_kernel<2>, (const void*)spmm_split_kernel<3>,
+                                                   (const void*)spmm_split_kernel<4>};
+        if (!split_configured.load()) {
+          for (const void* f : split_forms)
+            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kDsLdsBytes) != hipSuccess)
+              return SPDL_ERR_LAUNCH;
+          split_configured.store(true);
+        }
+        int tiles = (n + kDsCols - 1) / kDsCols, panels = (m + kDsRows - 1) / kDsRows, tiles_first = slab_tiles_first(tiles, m);
+        void* args[] = {&m, &k, &n, &nnz, (void*)&tiles, (void*)&panels, &ro, &ci, &val, &B, &C, &bias, &relu, &tiles_first};
+        return hipLaunchKernel(split_forms[spmm_split_chunks(m, k, nnz) - 2], dim3(li.grid_x), dim3(li.block_threads), args, kDsLdsBytes,
+                               st) == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
+      }
       const bool wide = li.variant == kSpmmSlabDma && plan.form == kSlabWide;
       static const void* const inner_forms[3] = {(const void*)spmm_slab_tiles_kernel<kSlabS, 2, 2, true, kSlabTilesMax>,
                                                  (const void*)spmm_slab_tiles_kernel<kSlabS, 2, 3, false, kSlabTilesMax>,
@@ -1560,7 +1613,7 @@ int spdl_version(void) { return 140; }
 // lane groups or eight waves), and what the choice among them rests on.
 extern "C" int spdl_debug_slab_form(int m, int k, int n, int nnz) {
   spdl_launch_info info;
-  SlabPlan plan = {kSlabOneRow, 0};
+  SlabPlan plan = {kSlabOneRow, 0, 0};
   fill_spmm_slab_info(m, k, n, nnz, kSpmmSlabDma, &info, &plan);
   return plan.tpw == 0 ? -1 : plan.form;
 }

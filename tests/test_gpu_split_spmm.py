@@ -1,0 +1,123 @@
+"""fp32 SpMM of dense sparse matrices on the bf16 matrix cores (three terms per number), against the oracle.  Tolerance: a result is four
+chains, each of six products of terms for every sixteen of a quarter of A's columns, whose sixteen products are added to the sum with no
+more than four roundings; what is left out of a product is below 2^-23 of it: (24 (k / 64 + 1) + 16) 2^-24 of the sum of
+absolute products."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import workloads as wl
+from tests.test_gpu_slab_pieces import odd_csr
+
+
+@pytest.fixture
+def g():
+    from tests import gpu_util
+    return gpu_util
+
+
+def runs_split(m, k, n, nnz):
+    import paper_2006_10901_amd as spdl
+    s = spdl.spdl_select_spmm(m, k, n, nnz, 4, 0, 0)
+    form = ctypes.CDLL(spdl.LIB_PATH).spdl_debug_slab_form(m, k, n, nnz)
+    return spdl.spdl_variant_name(0, s["variant"]) == "slabdma" and form == 4 and (s["rows_per_block"], s["block_threads"], s["grid_y"]) == (64, 1024, 1)
+
+
+def test_where_dense_matrices_are_multiplied_whole():
+    assert runs_split(8192, 10240, 128, int(8192 * 10240 * 0.3)) and not runs_split(8192, 10240, 128, int(8192 * 10240 * 0.15))
+    assert runs_split(6765, 2169, 120, int(6765 * 2169 * 0.28)) and runs_split(4096, 1024, 1024, int(4096 * 1024 * 0.3))
+    assert not runs_split(4096, 1024, 4096, int(4096 * 1024 * 0.3))       # wide outputs
+    assert not runs_split(8192, 799, 128, int(8192 * 799 * 0.5))          # few columns
+    assert not runs_split(4096, 4096, 128, int(4096 * 4096 * 0.4))        # 128 tiles: rows shared
+    assert not runs_split(8192, 10240, 32, int(8192 * 10240 * 0.4))       # half a tile
+
+
+def spmm(g, A, n, B, order=None, bias=None):
+    """The arrays of A, B and C at odd element addresses with NaN and far columns around."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    assert runs_split(A.m, A.k, n, A.nnz)
+    d = g.DevCsr(A)
+    ci = torch.full((A.nnz + 2,), 1 << 30, dtype=torch.int32, device="cuda")
+    val, b, c = (torch.full((size + 2,), float("nan"), device="cuda") for size in (A.nnz, A.k * n, A.m * n))
+    ci[1:-1], val[1:-1], b[1:-1] = d.ci, d.val, g.dev(B).view(-1)
+    C = c[1:-1].view(A.m, n)
+    args = (A.m, A.k, n, A.nnz, d.ro, ci[1:-1], val[1:-1], g.dev(order) if order is not None else None, b[1:-1].view(A.k, n))
+    spdl.spdl_spmm(*args, C) if bias is None else spdl.spdl_spmm_bias_relu(*args, g.dev(bias), True, C)
+    torch.cuda.synchronize()
+    got = c.cpu().numpy()
+    assert np.isnan(got[0]) and np.isnan(got[-1])
+    return got[1:-1].reshape(A.m, n)
+
+
+def tolerance(k):
+    return (24 * (k // 64 + 1) + 16) * 2.0 ** -24
+
+
+# (rows around whole panels; columns around whole stages of 128 and sixteens, and fewer than a quarter of a stage over; columns of C around whole
+# tiles, halves and fours; two, three and four sixteens of look-ahead and rows beyond; eight groups of tiles and up to 2048 rows)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n,density", [(8256, 1039, 65, 0.3), (8200, 816, 33, 0.5), (4161, 896, 130, 0.3), (4100, 1030, 127, 0.7), (4159, 801, 189, 0.9),
+                                           (1000, 1025, 700, 0.4), (2049, 1153, 322, 0.33), (8197, 1001, 64, 0.25), (1100, 1552, 512, 0.22)])
+def test_split_spmm(g, oracle_lib, m, k, n, density):
+    A = odd_csr(m, k, density, 7500 + m)
+    B = wl.dense(k, n, 7501 + n)
+    ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    got = spmm(g, A, n, B, oracle_lib.row_order(m, A.row_offsets))
+    assert np.all(np.isfinite(got)) and np.all(np.abs(got - ref) <= tolerance(k) * S)
+    assert np.array_equal(spmm(g, A, n, B), got)
+    bias = np.random.default_rng(7502).standard_normal(m).astype(np.float32)
+    ref, S = oracle_lib.spmm_bias_relu(m, k, n, A.row_offsets, A.column_indices, A.values, B, bias, True)
+    assert np.all(np.abs(spmm(g, A, n, B, None, bias) - ref) <= tolerance(k) * (S + np.abs(bias)[:, None]))
+
+
+@pytest.mark.gpu
+def test_split_spmm_of_rows_in_no_order(g, oracle_lib):
+    """Rows of ascending runs, exchanged, and columns stored twice, next to each other and not: every way in which the cursor can be misled."""
+    m, k, n = 4161, 1025, 130
+    A = odd_csr(m, k, 0.35, 7600)
+    rng = np.random.default_rng(7601)
+    for i in range(m):
+        row = A.column_indices[A.row_offsets[i]:A.row_offsets[i + 1]]
+        if len(row) < 100:
+            continue
+        if i % 4 == 1:
+            runs = np.split(row.copy(), np.sort(rng.integers(0, len(row), int(rng.integers(2, 8)))))
+            row[:] = np.concatenate([runs[j] for j in rng.permutation(len(runs))])
+        elif i % 4 == 2:
+            at = int(rng.integers(0, len(row) - 40))
+            row[at + int(rng.integers(1, 40))] = row[at]
+        elif i % 4 == 3 and i % 8 == 3:
+            at = int(rng.integers(0, len(row) - 1))
+            row[at], row[at + 1] = row[at + 1], row[at]
+    B = wl.dense(k, n, 7602)
+    ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    got = spmm(g, A, n, B)
+    longest = int(np.max(np.diff(A.row_offsets)))                     # (gathered: a chain of the row's entries)
+    assert np.all(np.isfinite(got)) and np.all(np.abs(got - ref) <= max(tolerance(k), (longest + 8) * 2.0 ** -24) * S)
+
+
+@pytest.mark.gpu
+def test_split_spmm_keeps_non_finite_values_and_the_whole_range(g, oracle_lib):
+    """Infinities and NaN reach the results that depend on them and no others, though zeros are multiplied; numbers that no bf16 term
+    can hold (too large for a scaled first term, too small for a last one) cost time, not bits."""
+    m, k, n = 4161, 1025, 130
+    A = odd_csr(m, k, 0.35, 7700)
+    B = wl.dense(k, n, 7701)
+    values = A.values
+    for scale_a, scale_b in ((2.0 ** -100, 2.0 ** -20), (2.0 ** -126, 1.0), (2.0 ** -126, 2.0 ** 100), (2.0 ** 105, 2.0 ** -90), (2.0 ** 60, 2.0 ** 50)):
+        A.values, b = (values * np.float32(scale_a)).astype(np.float32), (B * np.float32(scale_b)).astype(np.float32)
+        ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, b)
+        # (a denormal product or sum is a multiple of 2^-149)
+        assert np.all(np.abs(spmm(g, A, n, b) - ref) <= max(tolerance(k), (k + 8) * 2.0 ** -24) * S + k * 2.0 ** -149), (scale_a, scale_b)
+    A.values = values.copy()
+    B[5, 0], B[700, 64], B[k - 1, n - 1], B[300, 33] = np.inf, np.nan, -np.inf, np.float32(3e38)
+    A.values[A.row_offsets[200] + 3], A.values[A.row_offsets[3000]] = np.inf, np.nan
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    got = spmm(g, A, n, B).astype(np.float64)
+    inside = np.abs(ref) < 1e38
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < m * n // 20
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.all(np.abs(got[inside] - ref[inside]) <= max(tolerance(k), (k + 8) * 2.0 ** -24) * S[inside])
