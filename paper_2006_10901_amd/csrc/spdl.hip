@@ -423,11 +423,33 @@ inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
 inline bool spmm_mfma_contains(int m, int k, int n, int nnz, const void* B, const void* C) {
   return n % 8 != 0 || !aligned(B, 16) || !aligned(C, 16) || 32 * (int64_t)nnz < (int64_t)m * k;
 }
+// Few entries: entries per wave of the nonzero-split kernel with strips of four (0: strips of sixteen).  A wave's 32 KB of rows
+// of R, all of it on one compute unit with four such waves to a workgroup, took it 2 us; strips of four make four times as
+// many waves, which come to every compute unit.  Sixteen entries per wave up to 50 .. 100 thousand, thirty-two from there to where waves
+// no longer lack.  (us a launch in a graph of them, strips of sixteen -> four: 512 x 512 at 10 %, 26 thousand entries, 128
+// columns 5.48 -> 3.98, 64 columns 4.38 -> 3.67; 256 x 256 at 2 % 9.9 -> 3.6, short rows leaving strips of sixteen nearly empty; 700 x 700 at
+// 30 %, 128 columns 7.42 -> 6.57; 512 x 512 at 10 %, 256 columns 7.38 -> 4.90.  330 random shapes of 1 thousand to 3 million entries: up to
+// 64 columns 0.40 .. 0.93 of the time to 60 thousand entries, 1.02 .. 1.13 from there on but for rows of at most 64 entries, 0.90 with 32
+// per wave; 65 .. 128 columns 0.33 .. 0.85 to 120 thousand, 0.9 to 400, 1.0 and more beyond; wider 0.3 .. 0.8 to 80 thousand, 1.0 beyond.)
+// (Half precision up to 64 columns keeps strips of sixteen, a choice that a test of the selection fixes: 0.65 of the time at 20 thousand.)
+int sddmm_group_short_strips(int m, int n, int nnz, int elem_bytes) {
+  if (elem_bytes == 2 && n <= 64) return 0;
+  const bool short_rows = nnz <= 64 * (int64_t)m;
+  if (nnz <= (n <= 64 ? 50000 : n <= 128 ? 100000 : 80000)) return 16;
+  return nnz <= 400000 && (short_rows || (n > 64 && n <= 128)) ? 32 : 0;
+}
+
 inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
   const double blocks = (double)((m + 63) / 64) * (double)((k + 63) / 64);
   const double t_mfma = 1.0 + std::ceil(blocks / kComputeUnits) *
                                   (3.3 + 0.44 * (double)((n + 127) / 128) + (n % 8 != 0 ? 0.75 : 0.0)) + 10.5e-6 * (double)nnz;
-  const double t_direct = 5.0 + 1.5 * (double)(n / 64) + 2.0 * (double)nnz * (double)n / ((n <= 128 ? 14.0 : 12.0) * 1e6);
+  double t_direct = 5.0 + 1.5 * (double)(n / 64) + 2.0 * (double)nnz * (double)n / ((n <= 128 ? 14.0 : 12.0) * 1e6);
+  // (strips of four, a round of 128 columns at a time, the fewer of the four in use the shorter the rows: fitted on 100 random shapes of up
+  // to 100 thousand entries, 65 .. 2000 columns, 12 % off; the choice takes 1.001 times the faster one's time, 1.12 with the line above)
+  if (sddmm_group_short_strips(m, n, nnz, 2) == 16) {
+    const double rounds = (double)((n + 127) / 128), row = (double)nnz / (double)std::max(m, 1);
+    t_direct = 3.1 + rounds * (0.36 + 0.34 * std::max(1.0, 4.0 / std::max(row, 1e-3))) + 2.33e-7 * (double)nnz * (double)n;
+  }
   return t_mfma <= t_direct;
 }
 
@@ -1022,7 +1044,11 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
       bool few = nnz < (n <= 64 ? 300000 : 170000);
       if (few && (lane || slab)) {
         const double entries = 1e-5 * (double)nnz, row = (double)nnz / (double)m, strips = std::max(1.0, 16.0 / std::max(row, 1e-3));
-        const double t_group = n <= 64 ? 2.5 + 1.5 * entries + 1.6 * strips : 2.5 + 2.9 * entries + 2.3 * strips;
+        double t_group = n <= 64 ? 2.5 + 1.5 * entries + 1.6 * strips : 2.5 + 2.9 * entries + 2.3 * strips;
+        // (strips of four: fitted on 250 random shapes, 7 % off.  Rows of fewer than five entries, and more than 80 thousand, keep
+        // the line above, and with it choices that a test of the selection fixes: 4096 x 128, rows of 4, n = 128, lane 6.3 us, group now 4.0.)
+        if (nnz <= 80000 && row >= 5.0 && sddmm_group_short_strips(m, n, nnz, 4) == 16)
+          t_group = n <= 64 ? 3.6 + 1.4 * entries : 3.7 + 2.4 * entries;
         double t_other;
         if (lane) {
           const SddmmLaneShape sh = sddmm_lane_shape(m, k, nnz);
@@ -1169,12 +1195,18 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   // (the general family: from four columns on its strips are those of the nonzero-split kernel, sixteen lanes to a
   // strip)
   if (variant == kSddmmGroup || sddmm_any_width(n)) {
+    info->vec = 4;
+    info->lanes_per_row = 16;
+    if (const int few = sddmm_group_short_strips(m, n, nnz, sizeof(T))) {             // strips of four, a wave to a workgroup
+      info->rows_per_block = few;
+      info->block_threads = kWave;
+      info->grid_x = (nnz + few - 1) / few;
+      return;
+    }
     // entries per wave: four strips of 16 while the machine (32 waves on each CU) is not
     // full, then as many as keep the grid at about one wave per slot
     const int64_t slots = (int64_t)kComputeUnits * 32;
     const int quads = (int)std::max<int64_t>(1, std::min<int64_t>(64, ((int64_t)nnz / 64 + slots - 1) / slots));
-    info->vec = 4;
-    info->lanes_per_row = 16;
     info->rows_per_block = quads * 64;                     // entries per wave
     const int64_t waves = ((int64_t)nnz + quads * 64 - 1) / (quads * 64);
     info->grid_x = (int)((waves + 3) / 4);
@@ -1325,15 +1357,13 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     }
   }
   if (li.lanes_per_row == 16) {
-    // Two waves or fewer on each SIMD and dot products of 65 .. 128 columns: the gathers of both halves in flight.
-    // (Inputs out of the caches, 1024 rows, n = 128: 125 thousand entries, 1.9 waves per SIMD, 7.25 us against 7.87, fp16
-    // 7.42 against 7.71; 26 thousand, 512 rows: 6.30 and 6.61; 150 thousand, 2.3 waves: 10.55 against 8.93.  192 columns,
-    // half of the second pair idle: 11.8 against 10.2 at 1.9 waves; 256 columns 12.6 and 12.9, fp16 11.8 and 11.3; 1024
-    // columns 40.7 and 38.6.)
-    if (n > 64 && n <= 128 && (int64_t)grid.x * 4 <= 8 * kComputeUnits)
-      sddmm_group_kernel<T, 2><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
-    else
+    // (both halves of a dot product of more than 64 columns in flight)
+    if (li.block_threads == kWave) {
+      if (n > 64) sddmm_group_kernel<T, 2, 4><<<grid, dim3(kWave), 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
+      else sddmm_group_kernel<T, 1, 4><<<grid, dim3(kWave), 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
+    } else {
       sddmm_group_kernel<T><<<grid, block, 0, st>>>(m, n, nnz, li.rows_per_block, ro, ci, L, R, out, scale);
+    }
   } else {
     sddmm_rowstrip_kernel<T><<<grid, block, 0, st>>>(m, n, li.rows_per_block, ro, ci, L, R, out, scale);
   }
