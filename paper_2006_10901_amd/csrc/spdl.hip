@@ -69,14 +69,27 @@ constexpr int kSlabS = 256;                       // B rows per LDS slab
 constexpr int kSlabLdsBytes = 2 * (kSlabS + 1) * kSlabTile * 4;
 constexpr int kComputeUnits = 256;
 
-// Lane groups per row of the row-splitting kernel: one, unless the rows are too few to fill the
-// machine (about 16 waves per CU) and long enough to share; only with the widest vectors.
+// Lane groups per row of the row-splitting kernel, only with the widest vectors: a group that walks a row alone takes a memory
+// latency for every eight entries.  Groups of a wave share a row while the machine has room (16 waves on each compute unit) and every
+// group 32 entries; with fewer waves shorter lists will do, 16 entries up to 2048 waves, 5 up to 1024.  Up to 2048 rows all four
+// waves of a workgroup share one (256 / g groups: a row and 64 columns sixteen), from 3 entries per group on, 4.5 beyond 1024 rows.
+// (us a launch in a graph of them, of which an empty one takes 1.9, one group or few -> now: 512 x 512 at 10 %, n = 128, 3.81 -> 3.43; 526 x
+// 576, rows of 113, n = 42, 7.5 -> 3.9; 305 x 926, rows of 272, n = 40, 6.1 -> 4.5; rows of unequal length more so: 1001 x 1936, rows
+// of 99, log-normal, n = 52, 28 -> 7.  330 random shapes of 180 .. 8000 rows and 8 thousand to 1 million entries, those that come to this
+// kernel: fp32 uniform 0.83 of the time before and 1.08 at worst, with log-normal rows among them 0.78; fp16 0.79 and 0.65.  Lower
+// bounds on the entries cost up to 1.17 on rows of 16 .. 50.  Outputs wider than a wave's 256 columns, whose groups are whole waves:
+// 0.6 .. 1.6, not taken.)
 template <typename T>
 int pick_segments(int m, int nnz, int vec, int g) {
   if (vec != 16 / (int)sizeof(T) || m <= 0) return 1;
-  int seg = 1;
   const int64_t avg = nnz / m;
-  while (g * seg * 2 <= kWave && (int64_t)m * g * seg / kWave < 16 * kComputeUnits && avg / (seg * 2) >= 32) seg *= 2;
+  auto waves = [&](int seg) { return (int64_t)m * g * seg / kWave; };
+  int seg = 1;
+  while (g * seg * 2 <= kWave && waves(seg) < 16 * kComputeUnits &&
+         avg >= std::max(16, 2 * seg * (waves(2 * seg) > 2048 ? 32 : waves(2 * seg) > 1024 ? 16 : 5)))
+    seg *= 2;
+  const int all = 256 / g;
+  if (g < kWave && g * seg == kWave && m <= 2048 && 2 * avg >= (m <= 1024 ? 6 : 9) * all) seg = all;
   return seg;
 }
 
@@ -99,8 +112,10 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   // log-normal rows, 134 shapes: 1.31 and 1.03, 1.30 and 1.01, 1.24 and 0.93, 1.04 and 0.85, 0.88 and 0.81.  Rows at even
   // elements take 16 bytes at any number of waves: below 1800, against as narrow as before, 0.88 on uniform rows and 1.10 on
   // log-normal ones, which the host cannot tell apart.)
-  if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2))) {
-    if (sizeof(T) == 4 || vec > 1 || pick_segments<T>(m, nnz, kWide, pick_group(n, kWide)) > 1 || waves(kWide) >= 2500) vec = kWide;
+  // (also where groups share a row)
+  const bool shared = n >= kWide && pick_segments<T>(m, nnz, kWide, pick_group(n, kWide)) > 1;
+  if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2) || shared)) {
+    if (sizeof(T) == 4 || vec > 1 || shared || waves(kWide) >= 2500) vec = kWide;
     else if (waves(kWide) >= 800) vec = 2;
   }
   // fp32, few waves: narrower loads, so that a wave has a row to itself (its indices are then scalar loads) and
@@ -113,7 +128,7 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   // the number of load instructions counts, which narrow pieces multiply (n = 128, rows of 150, m = 1000: 6.2 us
   // as it is, 6.9 narrower; n = 32, rows of 100, m = 2000: 5.1 and 6.3; rows of 40, m = 4000: 4.75 and 4.57,
   // m = 8000: 5.75 and 6.7).
-  if (sizeof(T) == 4 && vec == kWide && (n >= 256 || (nnz < 3 << 16 && nnz <= 64 * (int64_t)m))) {
+  if (sizeof(T) == 4 && vec == kWide && !shared && (n >= 256 || (nnz < 3 << 16 && nnz <= 64 * (int64_t)m))) {
     auto padded = [&](int v) { return (n + pick_group(n, v) * v - 1) / (pick_group(n, v) * v) * (pick_group(n, v) * v); };
     if (waves(vec) < 5 * kComputeUnits && waves(1) > waves(vec))
       while (vec > 1 && pick_group(n, vec) < kWave) vec /= 2;
@@ -640,8 +655,8 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, const int* 
                            const T* val, const int* order, const T* B, T* C, const T* bias, int relu, hipStream_t st) {
   dim3 grid(li.grid_x, li.grid_y), block(256);
   const int seg = 256 / (li.rows_per_block * li.lanes_per_row);       // lane groups per row
-#define SPDL_ROWSPLIT(G, SEG)                                                                                  \
-  spmm_rowsplit_kernel<T, VEC, G, I, SEG><<<grid, block, 0, st>>>(m, n, ro, ci, val, order, B, C, bias, relu); \
+#define SPDL_ROWSPLIT(G, SEG, ...)                                                                                            \
+  spmm_rowsplit_kernel<T, VEC, G, I, SEG __VA_OPT__(,) __VA_ARGS__><<<grid, block, 0, st>>>(m, n, ro, ci, val, order, B, C, bias, relu); \
   return SPDL_OK;
   if (seg == 1) {
     switch (li.lanes_per_row) {
@@ -658,6 +673,10 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, const int* 
       case 16 * 16 + 2: SPDL_ROWSPLIT(16, 2)
       case 16 * 16 + 4: SPDL_ROWSPLIT(16, 4)
       case 32 * 16 + 2: SPDL_ROWSPLIT(32, 2)
+      // (a row to a workgroup)
+      case 8 * 16 + 32: SPDL_ROWSPLIT(8, 8, 4)
+      case 16 * 16 + 16: SPDL_ROWSPLIT(16, 4, 4)
+      case 32 * 16 + 8: SPDL_ROWSPLIT(32, 2, 4)
     }
   }
 #undef SPDL_ROWSPLIT

@@ -12,12 +12,15 @@ namespace spdl {
 // SEG lane groups of one wave share a row: group s takes the batches s, s+SEG, ... of the row's
 // nonzeros and the partial sums are added across the groups at the end.  Used when there are too
 // few rows to fill the machine with one group per row (each lane then walks a shorter list).
-template <typename T, int VEC, int G, typename I = int, int SEG = 1>
+// WAVES = 4: all four waves of a workgroup share a row, the waves' sums are added through LDS.  (What bounds the smallest problems is the
+// chain of latencies: offsets, indices, a batch of rows of B after the other.)
+template <typename T, int VEC, int G, typename I = int, int SEG = 1, int WAVES = 1>
 __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
     int m, int n, const int* __restrict__ row_offsets,
     const I* __restrict__ column_indices, const T* __restrict__ values, const int* __restrict__ row_order,
     const T* __restrict__ B, T* __restrict__ C, const T* __restrict__ bias, int relu) {
-  static_assert(G * SEG <= kWave, "the groups that share a row sit in one wave");
+  static_assert(G * SEG <= kWave && (WAVES == 1 || (WAVES == 4 && G * SEG == kWave)), "groups of one wave, or of all four");
+  constexpr int ALL = SEG * WAVES;
   constexpr int U = (G == kWave && VEC * sizeof(T) <= 16) ? 16 : 8;   // nonzeros in flight per lane
   const int sub = threadIdx.x / G;
   const int lane = threadIdx.x % G;
@@ -27,8 +30,8 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
   // every block, and with it every CU, gets the same mix of long and short rows.
   constexpr int RPW = kWave / (G * SEG);               // rows per wave
   const int wave_in_block = threadIdx.x / kWave;
-  const int seg = sub % SEG;
-  const int slot = (wave_in_block * (int)gridDim.x + (int)blockIdx.x) * RPW + (sub / SEG) % RPW;
+  const int seg = WAVES == 1 ? sub % SEG : sub;
+  const int slot = WAVES == 1 ? (wave_in_block * (int)gridDim.x + (int)blockIdx.x) * RPW + (sub / SEG) % RPW : (int)blockIdx.x;
   if (slot >= m) return;
   int row = row_order ? row_order[slot] : slot;          // row swizzle: one extra load
   if (G * SEG == kWave) row = uniform(row);              // whole wave on one row: scalar loads
@@ -59,13 +62,13 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) fetch(p + u, a[u], c[u]);
   }
-  for (; p + U <= end; p += SEG * U) {
+  for (; p + U <= end; p += ALL * U) {
     float b[U][VEC];
 #pragma unroll
     for (int u = 0; u < U; ++u) Pack<T, VEC>::load(Bcol + (size_t)c[u] * n, b[u]);
     float an[U];
     int cn[U];
-    const int pn = p + SEG * U;
+    const int pn = p + ALL * U;
     if (pn + U <= end) {
 #pragma unroll
       for (int u = 0; u < U; ++u) fetch(pn + u, an[u], cn[u]);
@@ -112,8 +115,21 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
     for (int d = G; d < G * SEG; d *= 2)
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] += __shfl_xor(acc[v], d, kWave);
-    if (seg != 0) return;
   }
+  if constexpr (WAVES > 1) {
+    __shared__ float sums[WAVES - 1][VEC][G];
+    if (wave_in_block > 0 && threadIdx.x % kWave < G) {
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) sums[wave_in_block - 1][v][lane] = acc[v];
+    }
+    __syncthreads();
+    if (wave_in_block > 0) return;
+#pragma unroll
+    for (int w = 0; w < WAVES - 1; ++w)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[v] += sums[w][v][lane];
+  }
+  if (seg != 0) return;
   spmm_epilogue<T, VEC>(acc, bias, row, relu);
   if (active) Pack<T, VEC>::store(C + (size_t)row * n + col, acc);
 }
