@@ -77,10 +77,12 @@ constexpr int kComputeUnits = 256;
 // 576, rows of 113, n = 42, 7.5 -> 3.9; 305 x 926, rows of 272, n = 40, 6.1 -> 4.5; rows of unequal length more so: 1001 x 1936, rows
 // of 99, log-normal, n = 52, 28 -> 7.  330 random shapes of 180 .. 8000 rows and 8 thousand to 1 million entries, those that come to this
 // kernel: fp32 uniform 0.83 of the time before and 1.08 at worst, with log-normal rows among them 0.78; fp16 0.79 and 0.65.  Lower
-// bounds on the entries cost up to 1.17 on rows of 16 .. 50.  Outputs wider than a wave's 256 columns, whose groups are whole waves:
-// 0.6 .. 1.6, not taken.)
+// bounds on the entries cost up to 1.17 on rows of 16 .. 50.)
+// Wider outputs, whose groups are whole waves: in half precision up to 800 waves of one group per row, up to 1600 for rows of 50 entries, with
+// even n (0.82 of the time on uniform rows and 0.48 on log-normal ones, 0.99 and 0.66 in the second range; short rows there 1.06 .. 1.4,
+// 1600 .. 3200 waves 1.27 on uniform rows; odd n, whose narrower loads make more waves of it, 0.97.  fp32 1.0 .. 1.7).
 template <typename T>
-int pick_segments(int m, int nnz, int vec, int g) {
+int pick_segments(int m, int n, int nnz, int vec, int g) {
   if (vec != 16 / (int)sizeof(T) || m <= 0) return 1;
   const int64_t avg = nnz / m;
   auto waves = [&](int seg) { return (int64_t)m * g * seg / kWave; };
@@ -90,6 +92,10 @@ int pick_segments(int m, int nnz, int vec, int g) {
     seg *= 2;
   const int all = 256 / g;
   if (g < kWave && g * seg == kWave && m <= 2048 && 2 * avg >= (m <= 1024 ? 6 : 9) * all) seg = all;
+  if (sizeof(T) == 2 && g == kWave && n % 2 == 0) {
+    const int64_t tiles = (n + g * vec - 1) / (g * vec);
+    if (avg >= (m * tiles < 800 ? 16 : 50) && m * tiles < 1600) seg = all;
+  }
   return seg;
 }
 
@@ -99,7 +105,7 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   int vec = pick_vec<T>(n, B, C, kWide);
   auto waves = [&](int v) {
     const int g = pick_group(n, v);
-    return (int64_t)m * g * pick_segments<T>(m, nnz, v, g) / kWave * ((n + g * v - 1) / (g * v));
+    return (int64_t)m * g * pick_segments<T>(m, n, nnz, v, g) / kWave * ((n + g * v - 1) / (g * v));
   };
   // (Rows of B at any alignment: 16 bytes per lane all the same, the lane at the row's end taking the
   // row's last ones.  Not for small problems, where more lanes per row count for more: 512 x 512
@@ -113,7 +119,7 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
   // elements take 16 bytes at any number of waves: below 1800, against as narrow as before, 0.88 on uniform rows and 1.10 on
   // log-normal ones, which the host cannot tell apart.)
   // (also where groups share a row)
-  const bool shared = n >= kWide && pick_segments<T>(m, nnz, kWide, pick_group(n, kWide)) > 1;
+  const bool shared = n >= kWide && pick_segments<T>(m, n, nnz, kWide, pick_group(n, kWide)) > 1;
   if (vec < kWide && n >= kWide && ((int64_t)nnz * n >= (1 << 24) || (n >= 512 && sizeof(T) == 2) || shared)) {
     if (sizeof(T) == 4 || vec > 1 || shared || waves(kWide) >= 2500) vec = kWide;
     else if (waves(kWide) >= 800) vec = 2;
@@ -137,7 +143,7 @@ void fill_spmm_rowsplit_info(int m, int n, int nnz, const void* B, const void* C
       vec /= 2;
   }
   const int g = pick_group(n, vec);
-  const int seg = pick_segments<T>(m, nnz, vec, g);
+  const int seg = pick_segments<T>(m, n, nnz, vec, g);
   info->variant = kSpmmRowsplit;
   info->vec = vec;
   info->lanes_per_row = g;
@@ -651,19 +657,27 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
 }
 
 template <typename T, int VEC, typename I>
-int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, const int* ro, const I* ci,
+int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, int nnz, const int* ro, const I* ci,
                            const T* val, const int* order, const T* B, T* C, const T* bias, int relu, hipStream_t st) {
   dim3 grid(li.grid_x, li.grid_y), block(256);
   const int seg = 256 / (li.rows_per_block * li.lanes_per_row);       // lane groups per row
+  // (Twice the mean: equal rows do not get there, with 24 entries even random ones.  One and a half times, 48 entries: level.)
+  const int team_above = std::max(64, 2 * std::min(nnz / std::max(m, 1), 1 << 29));
 #define SPDL_ROWSPLIT(G, SEG, ...)                                                                                            \
-  spmm_rowsplit_kernel<T, VEC, G, I, SEG __VA_OPT__(,) __VA_ARGS__><<<grid, block, 0, st>>>(m, n, ro, ci, val, order, B, C, bias, relu); \
+  spmm_rowsplit_kernel<T, VEC, G, I, SEG __VA_OPT__(,) __VA_ARGS__><<<grid, block, 0, st>>>(m, n, ro, ci, val, order, B, C, bias, relu, team_above); \
   return SPDL_OK;
   if (seg == 1) {
     switch (li.lanes_per_row) {
       case 8: SPDL_ROWSPLIT(8, 1)
       case 16: SPDL_ROWSPLIT(16, 1)
       case 32: SPDL_ROWSPLIT(32, 1)
-      case 64: SPDL_ROWSPLIT(64, 1)
+      case 64:
+        // (Long rows by four waves.  Half precision, 600 shapes of 2 .. 30 % and up to 3584 columns, of the time before: log-normal rows 0.61, uniform
+        // ones 1.00.  Shorter rows cost 1.03 .. 1.06 where rows are equal, with narrow loads 1.1 .. 1.2.)
+        if constexpr (sizeof(T) == 2) {
+          if (nnz / std::max(m, 1) >= (VEC == 8 ? 16 : 24)) { SPDL_ROWSPLIT(64, 1, 1, true) }
+        }
+        SPDL_ROWSPLIT(64, 1)
     }
   } else if constexpr (VEC == 16 / (int)sizeof(T)) {
     switch (li.lanes_per_row * 16 + seg) {
@@ -677,6 +691,7 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, const int* 
       case 8 * 16 + 32: SPDL_ROWSPLIT(8, 8, 4)
       case 16 * 16 + 16: SPDL_ROWSPLIT(16, 4, 4)
       case 32 * 16 + 8: SPDL_ROWSPLIT(32, 2, 4)
+      case 64 * 16 + 4: SPDL_ROWSPLIT(64, 1, 4)
     }
   }
 #undef SPDL_ROWSPLIT
@@ -684,15 +699,15 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, const int* 
 }
 
 template <typename T, typename I>
-int launch_spmm_rowsplit(const spdl_launch_info& li, int m, int n, const int* ro, const I* ci,
+int launch_spmm_rowsplit(const spdl_launch_info& li, int m, int n, int nnz, const int* ro, const I* ci,
                          const T* val, const int* order, const T* B, T* C, const T* bias, int relu,
                          hipStream_t st) {
   switch (li.vec) {
-    case 1: return launch_spmm_rowsplit_g<T, 1, I>(li, m, n, ro, ci, val, order, B, C, bias, relu, st);
-    case 2: return launch_spmm_rowsplit_g<T, 2, I>(li, m, n, ro, ci, val, order, B, C, bias, relu, st);
-    case 4: return launch_spmm_rowsplit_g<T, 4, I>(li, m, n, ro, ci, val, order, B, C, bias, relu, st);
+    case 1: return launch_spmm_rowsplit_g<T, 1, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
+    case 2: return launch_spmm_rowsplit_g<T, 2, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
+    case 4: return launch_spmm_rowsplit_g<T, 4, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
     case 8:
-      if constexpr (sizeof(T) == 2) return launch_spmm_rowsplit_g<T, 8, I>(li, m, n, ro, ci, val, order, B, C, bias, relu, st);
+      if constexpr (sizeof(T) == 2) return launch_spmm_rowsplit_g<T, 8, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
       return SPDL_ERR_INVALID;
     default: return SPDL_ERR_INVALID;
   }
@@ -821,7 +836,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       return SPDL_ERR_UNSUPPORTED;
     }
   } else {
-    rc = launch_spmm_rowsplit<T, I>(li, m, n, ro, ci, val, order, B, C, bias, relu, st);
+    rc = launch_spmm_rowsplit<T, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
   }
   if (rc != SPDL_OK) return rc;
   return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;

@@ -1,0 +1,80 @@
+"""Row-splitting SpMM in half precision, outputs wider than 256 columns: rows of more than twice the mean length (at least 64 entries) are
+walked by the four waves of a workgroup, and with few waves every row is.  Against the oracle; tolerance: a chain of at most as many
+multiply-adds as the longest row has entries and three additions, (r + 3) 2^-24 of the sum of absolute products, rounded once more to
+half precision."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+
+@pytest.fixture
+def g():
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.fixture
+def force():
+    import paper_2006_10901_amd as spdl
+    yield spdl.spdl_force_variant
+    spdl.spdl_force_variant(0, -1)
+
+
+def rows_csr(k, lens, seed):
+    rng = np.random.default_rng(seed)
+    ro = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k, size=l, replace=False)) for l in lens] + [np.zeros(0, int)]).astype(np.int32)
+    return wl.Csr(len(lens), k, ro, ci, rng.standard_normal(len(ci)).astype(np.float16))
+
+
+def test_when_a_workgroup_has_one_row(force):
+    import paper_2006_10901_amd as spdl
+    force(0, 0)
+    rows = lambda m, n, avg, eb=2: spdl.spdl_select_spmm(m, 900, n, m * avg, eb, 0, 0)["rows_per_block"]
+    assert rows(799, 512, 16) == 1 and rows(799, 512, 15) == 4 and rows(800, 512, 49) == 4 and rows(800, 512, 50) == 1
+    assert rows(1599, 400, 50) == 1 and rows(1600, 400, 300) == 4 and rows(799, 1024, 50) == 1 and rows(800, 1024, 50) == 4
+    assert rows(300, 511, 100) == 4 and rows(300, 400, 100, 4) == 4
+
+
+# 97 and 800 rows: the last workgroup is incomplete; mean lengths from 24 to 34 put the line at 64 .. 68 entries: rows on both
+# sides of it, empty ones, one of every column, and two to four long ones among the rows of one workgroup (i, i + 25, i + 50, i + 75 of 97)
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [257, 263, 400, 511, 513, 516, 1000, 2049])
+@pytest.mark.parametrize("m", [97, 1601])
+def test_long_rows(g, oracle_lib, force, m, n):
+    import torch
+    import paper_2006_10901_amd as spdl
+    k = 300
+    rng = np.random.default_rng(9000 + m)
+    lens = rng.integers(0, 48, m)
+    grid = -(-m // 4)
+    for at, long in ((0, (300, 0, 65, 63)), (5, (64, 65, 66, 67)), (7, (200, 180, 1, 210)), (grid - 1, (80, 90, 100, 0))):
+        for w, l in enumerate(long):
+            if w * grid + at < m:
+                lens[w * grid + at] = l
+    lens[1::7] = np.maximum(lens[1::7], 40)
+    A = rows_csr(k, lens, 9001 + m)
+    assert 24 <= A.nnz // m < 40
+    force(0, 0)
+    s = spdl.spdl_select_spmm(m, k, n, A.nnz, 2, 0, 0)
+    assert spdl.spdl_variant_name(0, s["variant"]) == "rowsplit" and s["lanes_per_row"] == 64
+    B = wl.dense(k, n, 9002 + n, np.float16)
+    bias = rng.standard_normal(m).astype(np.float16)
+    d = g.DevCsr(A)
+    b, c = (torch.full((size + 2,), float("nan"), dtype=torch.float16, device="cuda") for size in (k * n, m * n))
+    b[1:-1] = g.dev(B).view(-1)
+    ref, S = oracle_lib.spmm_bias_relu(m, k, n, A.row_offsets, A.column_indices, A.values.astype(np.float32), B.astype(np.float32), bias.astype(np.float32), True)
+    S = S + np.abs(bias.astype(np.float64))[:, None]
+    bound = (int(lens.max()) + 3) * 2.0 ** -24 * S + 2.0 ** -11 * np.abs(ref) + 2.0 ** -25
+    bits = []
+    for order in (None, oracle_lib.row_order(m, A.row_offsets), rng.permutation(m).astype(np.int32)):
+        c[1:-1] = float("nan")
+        spdl.spdl_spmm_bias_relu_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, None if order is None else g.dev(order), b[1:-1].view(k, n), g.dev(bias), True,
+                                     c[1:-1].view(m, n))
+        torch.cuda.synchronize()
+        got = c.cpu().numpy()
+        assert np.isnan(got[0]) and np.isnan(got[-1]) and np.all(np.isfinite(got[1:-1]))
+        assert np.all(np.abs(got[1:-1].reshape(m, n).astype(np.float64) - ref) <= bound)
+        bits.append(got[1:-1])
+    assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])        # the order of the rows moves work, not bits
