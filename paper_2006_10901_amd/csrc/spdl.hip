@@ -658,7 +658,7 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
 
 template <typename T, int VEC, typename I>
 int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, int nnz, const int* ro, const I* ci,
-                           const T* val, const int* order, const T* B, T* C, const T* bias, int relu, hipStream_t st) {
+                           const T* val, const int* order, const T* B, T* C, const T* bias, int relu, int hint, hipStream_t st) {
   dim3 grid(li.grid_x, li.grid_y), block(256);
   const int seg = 256 / (li.rows_per_block * li.lanes_per_row);       // lane groups per row
   // (Twice the mean: equal rows do not get there, with 24 entries even random ones.  One and a half times, 48 entries: level.)
@@ -673,10 +673,10 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, int nnz, co
       case 32: SPDL_ROWSPLIT(32, 1)
       case 64:
         // (Long rows by four waves.  Half precision, 600 shapes of 2 .. 30 % and up to 3584 columns, of the time before: log-normal rows 0.61, uniform
-        // ones 1.00.  Shorter rows cost 1.03 .. 1.06 where rows are equal, with narrow loads 1.1 .. 1.2.)
-        if constexpr (sizeof(T) == 2) {
-          if (nnz / std::max(m, 1) >= (VEC == 8 ? 16 : 24)) { SPDL_ROWSPLIT(64, 1, 1, true) }
-        }
+        // ones 1.00.  Shorter rows cost 1.03 .. 1.06 where rows are equal, with narrow loads 1.1 .. 1.2.  fp32, 46 shapes: log-normal rows 0.80 at any
+        // length, uniform ones 1.00 from 96 entries on, 1.03 at 16 .. 64, so these only where the caller has said that rows are unequal: 1024 x
+        // 1024 at 10 %, n = 3136: 114 us -> 93.)
+        if (nnz / std::max(m, 1) >= (VEC == 8 || hint == kHintSkewed ? 16 : sizeof(T) == 2 ? 24 : 96)) { SPDL_ROWSPLIT(64, 1, 1, true) }
         SPDL_ROWSPLIT(64, 1)
     }
   } else if constexpr (VEC == 16 / (int)sizeof(T)) {
@@ -701,13 +701,13 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, int nnz, co
 template <typename T, typename I>
 int launch_spmm_rowsplit(const spdl_launch_info& li, int m, int n, int nnz, const int* ro, const I* ci,
                          const T* val, const int* order, const T* B, T* C, const T* bias, int relu,
-                         hipStream_t st) {
+                         int hint, hipStream_t st) {
   switch (li.vec) {
-    case 1: return launch_spmm_rowsplit_g<T, 1, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
-    case 2: return launch_spmm_rowsplit_g<T, 2, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
-    case 4: return launch_spmm_rowsplit_g<T, 4, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
+    case 1: return launch_spmm_rowsplit_g<T, 1, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, hint, st);
+    case 2: return launch_spmm_rowsplit_g<T, 2, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, hint, st);
+    case 4: return launch_spmm_rowsplit_g<T, 4, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, hint, st);
     case 8:
-      if constexpr (sizeof(T) == 2) return launch_spmm_rowsplit_g<T, 8, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
+      if constexpr (sizeof(T) == 2) return launch_spmm_rowsplit_g<T, 8, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, hint, st);
       return SPDL_ERR_INVALID;
     default: return SPDL_ERR_INVALID;
   }
@@ -836,7 +836,7 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
       return SPDL_ERR_UNSUPPORTED;
     }
   } else {
-    rc = launch_spmm_rowsplit<T, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, st);
+    rc = launch_spmm_rowsplit<T, I>(li, m, n, nnz, ro, ci, val, order, B, C, bias, relu, hint, st);
   }
   if (rc != SPDL_OK) return rc;
   return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;

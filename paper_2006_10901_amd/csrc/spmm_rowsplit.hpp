@@ -134,6 +134,8 @@ __global__ __launch_bounds__(256) void spmm_rowsplit_kernel(
         c[u] = 0;
         if (p + u < to) { ra[u] = values[p + u]; c[u] = (int)column_indices[p + u]; }
       }
+      // (the first value is needed last, and the compiler would load it after the rows of B, a latency later)
+      if constexpr (G == kWave && sizeof(T) == 4 && SEG * WAVES == 1) asm volatile("" : "+s"(ra[0]));
 #pragma unroll
       for (int u = 0; u < R; ++u) {
         rb[u] = (raw)(T)0.f;

@@ -1,7 +1,7 @@
-"""Row-splitting SpMM in half precision, outputs wider than 256 columns: rows of more than twice the mean length (at least 64 entries) are
-walked by the four waves of a workgroup, and with few waves every row is.  Against the oracle; tolerance: a chain of at most as many
-multiply-adds as the longest row has entries and three additions, (r + 3) 2^-24 of the sum of absolute products, rounded once more to
-half precision."""
+"""Row-splitting SpMM with a wave per row: rows of more than twice the mean length (at least 64 entries) are
+walked by the four waves of a workgroup, in fp32 from a mean of 96 entries on, and in half precision with few waves every row is.  Against the oracle; tolerance: a chain of at most as many
+multiply-adds as the longest row has entries and three additions, (r + 3) 2^-24 of the sum of absolute products, in half precision rounded once
+more."""
 import numpy as np
 import pytest
 
@@ -37,40 +37,42 @@ def test_when_a_workgroup_has_one_row(force):
     assert rows(300, 511, 100) == 4 and rows(300, 400, 100, 4) == 4
 
 
-# 97 and 800 rows: the last workgroup is incomplete; mean lengths from 24 to 34 put the line at 64 .. 68 entries: rows on both
-# sides of it, empty ones, one of every column, and two to four long ones among the rows of one workgroup (i, i + 25, i + 50, i + 75 of 97)
+# 97 and 1601 rows: the last workgroup is incomplete.  Mean lengths from 24 to 34 put the line at 64 .. 68 entries, in fp32 from 100 to 120 at 200 .. 240:
+# rows on both sides of it, empty ones, one of every column, and two to four long ones among the rows of one workgroup (i, i + 25, i + 50, i + 75 of 97)
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [257, 263, 400, 511, 513, 516, 1000, 2049])
+@pytest.mark.parametrize("n,dtype", [(n, np.float16) for n in (257, 263, 400, 511, 513, 516, 1000, 2049)] + [(n, np.float32) for n in (257, 260, 515, 1024)])
 @pytest.mark.parametrize("m", [97, 1601])
-def test_long_rows(g, oracle_lib, force, m, n):
+def test_long_rows(g, oracle_lib, force, m, n, dtype):
     import torch
     import paper_2006_10901_amd as spdl
-    k = 300
+    f16, k = dtype == np.float16, 300
     rng = np.random.default_rng(9000 + m)
-    lens = rng.integers(0, 48, m)
+    lens = rng.integers(0, 48, m) if f16 else rng.integers(80, 130, m)
     grid = -(-m // 4)
-    for at, long in ((0, (300, 0, 65, 63)), (5, (64, 65, 66, 67)), (7, (200, 180, 1, 210)), (grid - 1, (80, 90, 100, 0))):
+    for at, long in ((0, (300, 0, 65, 63)), (5, (64, 65, 66, 67)), (7, (200, 180, 1, 210)), (grid - 1, (80, 90, 100, 0))) + (() if f16 else ((8, (199, 241, 260, 300)),)):
         for w, l in enumerate(long):
             if w * grid + at < m:
                 lens[w * grid + at] = l
-    lens[1::7] = np.maximum(lens[1::7], 40)
+    if f16:
+        lens[1::7] = np.maximum(lens[1::7], 40)
     A = rows_csr(k, lens, 9001 + m)
-    assert 24 <= A.nnz // m < 40
+    A.values = A.values.astype(dtype)
+    assert 24 <= A.nnz // m < 40 if f16 else 96 <= A.nnz // m < 120
     force(0, 0)
-    s = spdl.spdl_select_spmm(m, k, n, A.nnz, 2, 0, 0)
-    assert spdl.spdl_variant_name(0, s["variant"]) == "rowsplit" and s["lanes_per_row"] == 64
-    B = wl.dense(k, n, 9002 + n, np.float16)
-    bias = rng.standard_normal(m).astype(np.float16)
+    s = spdl.spdl_select_spmm(m, k, n, A.nnz, 2 if f16 else 4, 0, 0)
+    assert spdl.spdl_variant_name(0, s["variant"]) == "rowsplit" and s["lanes_per_row"] == 64 and (f16 or s["rows_per_block"] == 4)
+    B = wl.dense(k, n, 9002 + n, dtype)
+    bias = rng.standard_normal(m).astype(dtype)
     d = g.DevCsr(A)
-    b, c = (torch.full((size + 2,), float("nan"), dtype=torch.float16, device="cuda") for size in (k * n, m * n))
+    b, c = (torch.full((size + 2,), float("nan"), dtype=torch.float16 if f16 else torch.float32, device="cuda") for size in (k * n, m * n))
     b[1:-1] = g.dev(B).view(-1)
     ref, S = oracle_lib.spmm_bias_relu(m, k, n, A.row_offsets, A.column_indices, A.values.astype(np.float32), B.astype(np.float32), bias.astype(np.float32), True)
     S = S + np.abs(bias.astype(np.float64))[:, None]
-    bound = (int(lens.max()) + 3) * 2.0 ** -24 * S + 2.0 ** -11 * np.abs(ref) + 2.0 ** -25
+    bound = (int(lens.max()) + 3) * 2.0 ** -24 * S + (2.0 ** -11 * np.abs(ref) + 2.0 ** -25 if f16 else 0.0)
     bits = []
     for order in (None, oracle_lib.row_order(m, A.row_offsets), rng.permutation(m).astype(np.int32)):
         c[1:-1] = float("nan")
-        spdl.spdl_spmm_bias_relu_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, None if order is None else g.dev(order), b[1:-1].view(k, n), g.dev(bias), True,
+        (spdl.spdl_spmm_bias_relu_f16 if f16 else spdl.spdl_spmm_bias_relu)(m, k, n, A.nnz, d.ro, d.ci, d.val, None if order is None else g.dev(order), b[1:-1].view(k, n), g.dev(bias), True,
                                      c[1:-1].view(m, n))
         torch.cuda.synchronize()
         got = c.cpu().numpy()
