@@ -87,8 +87,8 @@ __device__ __forceinline__ float sddmm_plain_dot(int n, const T* l, const T* r) 
 // n >= 4.  With n % 4 != 0 the lane at the row's end takes the row's last four columns (piece_start)
 // and leaves out of its sum, with zeros for L, those that the lane before it has; an Inf there would
 // still make the result NaN, so a NaN is looked at again.
-// P: pieces of 64 columns whose gathers are all in flight at once.  Two cost 64 registers more and take
-// a memory latency off every strip of more than 64 columns: for launches that leave the SIMDs nearly empty.
+// P: pieces of 64 columns whose gathers are all in flight at once.  Two, with strips of four, cost 16 registers more and take
+// a memory latency off every strip of more than 64 columns.
 // STRIP: nonzeros of a strip, 16 or 4 (lane l16 then has the offset of nonzero l16 / 4).
 template <typename T, int P = 1, int STRIP = 16>
 __device__ __forceinline__ void sddmm_strip_direct_at(int n, int q, int end, int l16, int roff,

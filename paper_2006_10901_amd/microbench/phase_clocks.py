@@ -78,7 +78,8 @@ def main():
         out = torch.empty(A.nnz, device="cuda")
         report(f"SpMM {sparsity} %", spdl.spdl_select_spmm(A.m, A.k, n, A.nnz, 4, 0, 0), 16,
                lambda: spdl.spdl_spmm(A.m, A.k, n, A.nnz, ro, ci, val, order, B, C))
-        report(f"SDDMM {sparsity} %", spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 4, 0, 0), 16,
+        info = spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 4, 0, 0)
+        report(f"SDDMM {sparsity} %", info, info["block_threads"] // 64,
                lambda: spdl.spdl_sddmm(A.m, A.k, n, A.nnz, ro, ci, L, R, out))
     w = wl.attention()
     A, n = w["A"], w["n"]
