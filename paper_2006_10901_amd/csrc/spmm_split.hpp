@@ -225,11 +225,13 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       fetch(j);
       __builtin_amdgcn_sched_barrier(0);
       // An ascending row's entry comes right after a smaller column of the same stage or is its first one.  (Rows with one that
-      // does not: what was counted says nothing, they are gathered.)
+      // does not: what was counted says nothing, they are gathered.)  Every entry of the stage is looked at, also behind a sixteen that has
+      // none in any of the four rows: what is counted is written or gives its row away.  So `last` needs no look at where the row
+      // ends: a row that is not given away has an entry of the stage in the next round's first place only if all of this round's are the stage's.
       const unsigned base = row_base[j] + (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)block;
 #pragma unroll
       for (int e = 0; e < NC; ++e) {
-        if (e > 0 && mk[e] == 0) break;
+        if (e > 0 && mk[e] == 0) continue;
         unsigned before;
         if (e == 0 && !again) {
           before = (unsigned)__builtin_amdgcn_mov_dpp((int)rel[e], 0x111, 0xf, 0xf, true);                                  // row_shr:1

@@ -99,6 +99,30 @@ def test_split_spmm_of_rows_in_no_order(g, oracle_lib):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("density", [0.6, 0.5])                       # four and three sixteens of look-ahead
+def test_split_spmm_of_rows_whose_middle_lies_in_a_later_stage(g, oracle_lib, density):
+    """Four adjacent rows, one of which takes another round of its first stage, and a sixteen of which no row has an entry in the stage with
+    entries of the stage behind it."""
+    m, k, n = 4161, 1025, 130
+    A = odd_csr(m, k, density, 7650)
+    rows = np.split(A.column_indices, A.row_offsets[1:-1])
+    run, far = lambda first, count: np.arange(first, first + count), np.arange(300, 316)
+    patterns = [[[run(0, 16), far, run(20, 40)], [], [], [run(0, 16), far, run(100, 16)]],
+                [[run(0, 16), far, run(20, 70)], [], [run(0, 16), far, run(100, 16)], [run(0, 16), far, far + 16, run(90, 16)]],
+                [[run(0, 16), run(20, 40)], [run(0, 16), far, run(100, 16)], [], [run(0, 32), far, run(100, 16)]]]
+    for i in range(0, m - 8, 8):
+        for j, parts in enumerate(patterns[i // 8 % 3]):
+            rows[i + j] = np.concatenate(parts).astype(np.int32) if parts else np.zeros(0, np.int32)
+    lens = np.array([len(r) for r in rows])
+    values = np.random.default_rng(7651).standard_normal(lens.sum()).astype(np.float32)
+    A = wl.Csr(m, k, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), np.concatenate(rows), values)
+    B = wl.dense(k, n, 7652)
+    ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    got = spmm(g, A, n, B)
+    assert np.all(np.abs(got - ref) <= max(tolerance(k), (int(lens.max()) + 8) * 2.0 ** -24) * S)
+
+
+@pytest.mark.gpu
 def test_split_spmm_keeps_non_finite_values_and_the_whole_range(g, oracle_lib):
     """Infinities and NaN reach the results that depend on them and no others, though zeros are multiplied; numbers that no bf16 term
     can hold (too large for a scaled first term, too small for a last one) cost time, not bits."""
