@@ -23,7 +23,7 @@
 // 42 %, n = 128: 155 -> 87; at 10 % 84 us -> 116, which is why the density decides.
 //
 // Rows that are not ascending, or hold a column twice, are noticed (an entry that does not come right after a smaller column of the
-// same stage; a cursor short of the row's end) and gathered at the end, as is what is not finite: a zero of the
+// same stage; a cursor short of the row's end) and gathered at the end (split_gather), as is what is not finite: a zero of the
 // block times an infinity of B must not reach the result.
 #pragma once
 #include "bf16_split.hpp"
@@ -39,6 +39,89 @@ constexpr int kDsBuf = 3 * kDsPlane;
 constexpr int kDsLdsBytes = 3 * kDsBuf + kDsRows * 4;
 constexpr int kDsMulWaves = 8, kDsScatterWaves = 8;
 constexpr int kDsThreads = 64 * (kDsMulWaves + kDsScatterWaves);
+
+// Lane i gets the place of the (i + 1)-th one of `set`.  (Lanes beyond the last one: those of the zeros.)
+__device__ __forceinline__ int nth_one(unsigned long long set) {
+  const int lane = threadIdx.x & 63;
+  const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0u));
+  const int to = (set >> lane & 1) ? before : __builtin_popcountll(set) + lane - before;
+  return __builtin_amdgcn_ds_permute(to * 4, lane);
+}
+
+// Results that the matrix cores cannot give, from the rows of B themselves: row i of the workgroup (bit i of `rows`) in the fours of
+// columns that lane i's `mask` names.  All threads of the workgroup share out the rows, and a row's among the fours of columns that any
+// row needs and parts of the row's entries, sixteen of them in flight for each thread: a single row waits for a few gathers, not for
+// as many as it has sixteens, and where all rows need four columns (an infinity in B) no lane idles.  A part whose sums are
+// all NaN already is done.  (8192 x 10240 at 30 %, n = 128, 143 us with nothing to gather; by the thread that has the result, eight entries in
+// flight -> here: one infinity in B 727 us -> 286, a row of them 2960 -> 692, B all NaN 121, one NaN in A 364 -> 149, one row
+// in 64 not ascending 342 -> 151, none 2970 -> 694.)
+__device__ __forceinline__ void split_gather(unsigned long long rows, unsigned mask, int i0, int j0, int m, int n,
+                                             const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
+                                             const float* __restrict__ values, const float* __restrict__ B, float* __restrict__ C,
+                                             const float* __restrict__ bias, int relu, char* lds) {
+  const int tid = threadIdx.x;
+  unsigned any = mask;
+#pragma unroll
+  for (int d = 1; d < kWave; d *= 2) any |= (unsigned)__shfl_xor((int)any, d, kWave);
+  const int nrows = __builtin_popcountll(rows), nfours = __builtin_popcount(any);
+  const int row_bits = nrows > 1 ? 32 - __builtin_clz(nrows - 1) : 0, four_bits = nfours > 1 ? 32 - __builtin_clz(nfours - 1) : 0;
+  const int per_row = kDsThreads >> row_bits, mine = tid & (per_row - 1), index = tid / per_row;
+  const int part = mine >> four_bits, parts = min(per_row >> four_bits, 64);
+  const int local = __shfl(nth_one(rows), index, kWave), four = __shfl(nth_one(any), mine & ((1 << four_bits) - 1), kWave);
+  const unsigned wanted = (unsigned)__shfl((int)mask, local, kWave);
+  const bool on = index < nrows && (mine & ((1 << four_bits) - 1)) < nfours && (wanted >> four & 1) && part < parts;
+  const int row = i0 + local, first = j0 + 4 * four, col = min(first, n - 4);               // (the last four columns of B's row at its end)
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  if (on) {
+    const int end = row_offsets[row + 1];
+    const float* const Bcol = B + col;
+    constexpr int U = 16;
+    for (int p = row_offsets[row] + U * part; p < end; p += U * parts) {
+      int c[U];
+      float a[U], b[U][4];
+      if (p + U <= end) {
+        typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int u = 0; u < U; u += 4) {
+          const i32x4_any x = *reinterpret_cast<const i32x4_any*>(column_indices + p + u);
+          const f32x4_any y = *reinterpret_cast<const f32x4_any*>(values + p + u);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) { c[u + t] = x[t]; a[u + t] = y[t]; }
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = column_indices[min(p + u, end - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = values[min(p + u, end - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) Pack<float, 4>::load(Bcol + (size_t)c[u] * n, b[u]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p + u < end) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = __builtin_fmaf(a[u], b[u][t], v[t]);
+        }
+      if (v[0] != v[0] && v[1] != v[1] && v[2] != v[2] && v[3] != v[3]) break;
+    }
+  }
+  f32x4* const sums = reinterpret_cast<f32x4*>(lds);                   // (the products' sums before have been read)
+  sums[tid] = f32x4{v[0], v[1], v[2], v[3]};
+  __syncthreads();
+  if (!on || part > 0) return;
+#pragma unroll 4
+  for (int i = 1; i < parts; ++i) {
+    const f32x4 x = sums[tid + (i << four_bits)];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] += x[t];
+  }
+  spmm_epilogue<float, 4>(v, bias, row, relu);
+  float* const c = C + (size_t)row * n + col;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    if (col + t >= first) c[t] = v[t];
+}
 
 // NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, 0 < nnz < 2^28.)
 template <int NC>
@@ -294,7 +377,6 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
   // The four sums of each result; four columns to a thread.
   static_assert(kDsThreads * 4 == kDsRows * kDsCols, "a thread for every four results");
   const int local = tid >> 4, c4 = (tid & 15) * 4, row = i0 + local, col = tile * kDsCols + c4;
-  if (row >= m || col >= n) return;
   float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
@@ -302,31 +384,32 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
     for (int t = 0; t < 4; ++t) v[t] += x[t];
   }
-  const int count = min(4, n - col);
+  const int count = row < m ? min(4, n - col) : 0;
   bool failed = redo[local] != 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     v[t] *= kSplitUnscale;
     failed |= split_failed(v[t]);
   }
-  if (failed) {
-    v[0] = v[1] = v[2] = v[3] = 0.f;
-#pragma unroll 8
-    for (int p = row_offsets[row]; p < row_offsets[row + 1]; ++p) {
-      const float* b = B + (size_t)column_indices[p] * n + col;
+  failed &= count > 0;
+  const unsigned long long fails = __builtin_amdgcn_ballot_w64(failed);
+  if ((tid & 15) == 0) redo[local] = (int)((unsigned)(fails >> (lane & 48)) & 0xffffu);      // (fours of columns to be gathered)
+  if (!failed) {
+    if (count > 0) spmm_epilogue<float, 4>(v, bias, row, relu);
+    float* c = C + (size_t)row * n + col;
+    if (count >= 4) {
+      Pack<float, 4>::store(c, v);
+    } else {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = __builtin_fmaf(values[p], b[min(t, count - 1)], v[t]);
+      for (int t = 0; t < 3; ++t)
+        if (t < count) c[t] = v[t];
     }
   }
-  spmm_epilogue<float, 4>(v, bias, row, relu);
-  float* c = C + (size_t)row * n + col;
-  if (count == 4) {
-    Pack<float, 4>::store(c, v);
-  } else {
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (t < count) c[t] = v[t];
-  }
+  barrier();
+  const unsigned mask = (unsigned)redo[lane];
+  const unsigned long long rows = __builtin_amdgcn_ballot_w64(mask != 0);
+  if (rows == 0) return;
+  split_gather(rows, mask, i0, tile * kDsCols, m, n, row_offsets, column_indices, values, B, C, bias, relu, lds_raw);
 }
 
 }  // namespace spdl

@@ -145,3 +145,64 @@ def test_split_spmm_keeps_non_finite_values_and_the_whole_range(g, oracle_lib):
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < m * n // 20
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     assert np.all(np.abs(got[inside] - ref[inside]) <= max(tolerance(k), (k + 8) * 2.0 ** -24) * S[inside])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad_rows", [1, 2, 3, 5, 33, 64])            # of each panel of 64
+@pytest.mark.parametrize("bad_columns", [(), (7,), (0, 66, 129), (1, 21, 45, 62, 128)])
+def test_split_spmm_shares_out_what_is_gathered(g, oracle_lib, bad_rows, bad_columns):
+    """Few and many rows that have to be gathered (one column stored twice, or a NaN) and few and many fours of columns (an infinity in B): rows, fours
+    and parts of a row for every power of two of threads, rows of 0, 1, 16, 17 and all entries among them."""
+    m, k, n = 4161, 1025, 130
+    A = odd_csr(m, k, 0.35, 7800)
+    rows = [r.copy() for r in np.split(A.column_indices, A.row_offsets[1:-1])]
+    for i, r in enumerate(rows):
+        if i % 64 % 29 == 11:
+            rows[i] = np.arange((0, 1, 16, 17, k)[i // 64 % 5], dtype=np.int32)
+    lens = np.array([len(r) for r in rows])
+    A = wl.Csr(m, k, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), np.concatenate(rows),
+               np.random.default_rng(7801).standard_normal(lens.sum()).astype(np.float32))
+    for i in range(m):
+        at, end = A.row_offsets[i], A.row_offsets[i + 1]
+        if (i % 64) * 37 % 64 < bad_rows and end - at > 1:
+            if i % 3 == 0:
+                A.values[end - 1] = np.nan
+            else:
+                A.column_indices[at + (end - at) // 2] = A.column_indices[at + (end - at) // 2 - 1]
+    B = wl.dense(k, n, 7802)
+    for c in bad_columns:
+        B[(c * 31 + 400) % k, c] = np.inf if c % 2 else -np.inf
+    with np.errstate(invalid="ignore"):
+        ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    got = spmm(g, A, n, B).astype(np.float64)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    inside = np.isfinite(ref)
+    assert np.all(np.abs(got[inside] - ref[inside]) <= max(tolerance(k), (k + 8) * 2.0 ** -24) * S[inside])
+
+
+@pytest.mark.gpu
+def test_split_spmm_gathers_no_slower_than_this(g):
+    """What an infinity in every result costs: 4.8 times the whole time where it was measured, 21 times with each result left to the thread that has
+    it."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    m, k, n = 8192, 4096, 128
+    A = odd_csr(m, k, 0.3, 7900)
+    assert runs_split(m, k, n, A.nnz)
+    d, C = g.DevCsr(A), torch.empty((m, n), device="cuda")
+    B = wl.dense(k, n, 7901)
+    bad = B.copy()
+    bad[k // 2] = np.inf
+    times = []
+    for b in (g.dev(B), g.dev(bad)):
+        runs = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(5):
+                spdl.spdl_spmm(m, k, n, A.nnz, d.ro, d.ci, d.val, None, b, C)
+            end.record()
+            end.synchronize()
+            runs.append(start.elapsed_time(end))
+        times.append(min(runs))
+    assert times[1] < 9 * times[0], times
