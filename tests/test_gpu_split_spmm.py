@@ -187,7 +187,7 @@ def test_split_spmm_gathers_no_slower_than_this(g):
     import torch
     import paper_2006_10901_amd as spdl
     m, k, n = 8192, 4096, 128
-    A = odd_csr(m, k, 0.3, 7900)
+    A = wl.uniform_mask_csr(m, k, 0.3, 7900)
     assert runs_split(m, k, n, A.nnz)
     d, C = g.DevCsr(A), torch.empty((m, n), device="cuda")
     B = wl.dense(k, n, 7901)
