@@ -343,6 +343,8 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 // 4096, 11 .. 50 %: 5 % off for the matrix cores, 4 % and 6 % for the forms that walk and with one row per group); the choice takes
 // 1.005 times the faster one's time on average, 0.81 times the plan's.  The two meet at 17 .. 22 %, earlier where the rounds
 // fit (8192 x 10240, n = 128: 15 % 109 us and 122, 20 % 132 and 127, 30 % 185 and 135).
+// Rows of few entries are gathered there (spmm_split_entries): uniform shapes that come out have their mean 3.2 standard deviations and more
+// above that, on 200 thousand of 800 .. 1400 columns.
 // Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
 // 1024 at 30 %, n = 4096, among others) stay with the forms that tests of them fix there.
 bool spmm_split_runs(int m, int k, int n, int nnz, const SlabPlan& plan) {

@@ -10,9 +10,11 @@
 // a multiplying wave reaches with what it still needs of the block in registers, so that half a step of products lies behind it.
 //
 // One accumulator, not two as in the SDDMM: a sum is four chains, and 6 k / 64 roundings each leave a smaller error than one
-// chain of the row's entries (8192 x 10240, n = 128, 2-norm of the error over that of the result, here and in the slab kernel: 15 % 6.1e-7
-// and 7.0e-7, 20 % 6.6 and 8.1, 30 % 7.2 and 9.9; 1024 columns at 20 % 2.2 and 2.6).  The terms of A are cut off, not rounded (two
-// instructions less per entry): what is left out of a product stays below 2^-24 of it, for the terms of B are rounded.
+// chain of the row's entries, if these are enough: against the slab kernel, 2-norm of the error, normally distributed values, rows of 10 % / 20 %
+// / 30 % of 10240 columns 0.90 / 0.79 / 0.72 of it, of 1025 columns 0.995 / 0.85 / 0.73.  With fewer entries the six roundings for each of
+// them count (2.0 times the error for rows of two, 1.3 for 20 of 1025, 1.06 for 205 of 10240): such rows are gathered (spmm_split_entries).  What
+// is left out of a product is below 2^-24 of it: the terms of both operands are rounded.  (A's cut off, up to 2.9 times that: 1.01 .. 1.04
+// times the error, and the same time.  6765 x 2169 at 28 %, n = 120: 30 us; every other row of 40 entries: 34.8, gathered 43.4, slab kernel 66.)
 //
 // What bounds it: the issue of vector instructions beside the MFMA.  A stage is 48 MFMA of 32 clocks on each SIMD, 240 vector
 // instructions of the multiplying waves and 120 (10 %) to 230 (30 %) of the scattering ones; it takes 3000 .. 3400 clocks, the sum of
@@ -73,10 +75,11 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
   const int row = i0 + local, first = j0 + 4 * four, col = min(first, n - 4);               // (the last four columns of B's row at its end)
   float v[4] = {0.f, 0.f, 0.f, 0.f};
   if (on) {
-    const int end = row_offsets[row + 1];
-    const float* const Bcol = B + col;
     constexpr int U = 16;
-    for (int p = row_offsets[row] + U * part; p < end; p += U * parts) {
+    const int begin = row_offsets[row], end = row_offsets[row + 1];
+    const int share = end - begin > 2 * U ? parts : 1;                 // (an entry by itself would be rounded once more)
+    const float* const Bcol = B + col;
+    for (int p = part < share ? begin + U * part : end; p < end; p += U * share) {
       int c[U];
       float a[U], b[U][4];
       if (p + U <= end) {
@@ -122,6 +125,10 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
   for (int t = 0; t < 4; ++t)
     if (col + t >= first) c[t] = v[t];
 }
+
+// Entries from which on a row's sum on the matrix cores is no less exact than a chain of multiply-adds.  (It is as exact at 100 entries of
+// 1025 columns, 155 of 2169, 290 of 5120, 460 of 10240.)
+__host__ __device__ constexpr int spmm_split_entries(int k) { return 72 + k / 24; }
 
 // NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, 0 < nnz < 2^28.)
 template <int NC>
@@ -276,8 +283,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int e = 0; e < NC; ++e)
         aa[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(value_rsrc, at[j] + 64 * e, 0, 0));
     };
-    auto cut = [](float x) __attribute__((always_inline)) {            // to its first term
-      return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & 0xffff0000u);
+    auto term = [](float x) __attribute__((always_inline)) {           // x rounded to its first term, in the upper half
+      return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{0.f, x}), bf16x2));
     };
     const int shift16 = 16 * (sub & 1);
     const bool upper = sub >= 2;
@@ -331,10 +338,12 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
           asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(rel[e] & 7u), "s"(2 - kDsGroup / 8), "v"(d));
           typedef __attribute__((address_space(3))) unsigned short LdsHalf;
           LdsHalf* const to = (LdsHalf*)(uintptr_t)d;
-          const float x = v[e], y = x - cut(x), z = y - cut(y);
-          to[0] = (unsigned short)(__builtin_bit_cast(unsigned, x) >> 16);
-          to[kDsPlane / 2] = (unsigned short)(__builtin_bit_cast(unsigned, y) >> 16);
-          to[kDsPlane] = (unsigned short)(__builtin_bit_cast(unsigned, z) >> 16);
+          const unsigned x = term(v[e]);
+          const float rest = v[e] - __builtin_bit_cast(float, x);
+          const unsigned y = term(rest), z = term(rest - __builtin_bit_cast(float, y));
+          to[0] = (unsigned short)(x >> 16);
+          to[kDsPlane / 2] = (unsigned short)(y >> 16);
+          to[kDsPlane] = (unsigned short)(z >> 16);
         }
       }
       const bool more = (mk[NC - 1] & (kFirst << 15)) != 0;
@@ -368,7 +377,10 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const unsigned long long mine = 0xffffull << (16 * sub);
-      if (l16 == 0) redo[first_row + 4 * j + sub] = at[j] != row_end[j][0] || (strays[j] & mine) != 0;
+      const int local = first_row + 4 * j + sub, row = min(i0 + local, m);
+      const int entries = row_offsets[min(row + 1, m)] - row_offsets[row];
+      if (l16 == 0)
+        redo[local] = at[j] != row_end[j][0] || (strays[j] & mine) != 0 || (entries > 0 && entries < spmm_split_entries(k));
     }
   }
   clocks.lap(kPhaseRest);
