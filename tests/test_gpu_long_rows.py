@@ -1,5 +1,5 @@
 """Row-splitting SpMM with a wave per row: rows of more than twice the mean length (at least 64 entries) are
-walked by the four waves of a workgroup, in fp32 from a mean of 96 entries on, and in half precision with few waves every row is.  Against the oracle; tolerance: a chain of at most as many
+walked by the four waves of a workgroup, in fp32 from a mean of 96 entries on, or of 16 where the caller says that rows are unequal, and in half precision with few waves every row is.  Against the oracle; tolerance: a chain of at most as many
 multiply-adds as the longest row has entries and three additions, (r + 3) 2^-24 of the sum of absolute products, in half precision rounded once
 more."""
 import numpy as np
@@ -80,3 +80,72 @@ def test_long_rows(g, oracle_lib, force, m, n, dtype):
         assert np.all(np.abs(got[1:-1].reshape(m, n).astype(np.float64) - ref) <= bound)
         bits.append(got[1:-1])
     assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])        # the order of the rows moves work, not bits
+
+
+# (means of 19 .. 38: the line at 64 .. 76 entries.  The call that says nothing about the rows walks each by one wave there, in one chain: which rows
+# are shared shows in the last bits.)
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [257, 260, 515, 1024])
+@pytest.mark.parametrize("m,least", [(97, 0), (97, 16), (1601, 0), (1601, 8)])
+def test_long_rows_of_a_caller_who_knows_them(g, oracle_lib, force, m, least, n):
+    import torch
+    import paper_2006_10901_amd as spdl
+    k = 300
+    rng = np.random.default_rng(9100 + m)
+    lens = rng.integers(least, 40, m)
+    grid = -(-m // 4)
+    for at, long in ((0, (300, 0, 71, 63)), (5, (64, 65, 66, 67)), (7, (200, 180, 1, 210)), (grid - 1, (80, 90, 100, 0))):
+        for w, l in enumerate(long):
+            if w * grid + at < m:
+                lens[w * grid + at] = l
+    A = rows_csr(k, lens, 9101 + m)
+    A.values = A.values.astype(np.float32)
+    mean = A.nnz // m
+    assert 16 <= mean < 40
+    force(0, 0)
+    s = spdl.spdl_select_spmm(m, k, n, A.nnz, 4, 0, 0)
+    assert spdl.spdl_variant_name(0, s["variant"]) == "rowsplit" and (s["lanes_per_row"], s["rows_per_block"]) == (64, 4)
+    B = wl.dense(k, n, 9102 + n)
+    ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values, B)
+    d = g.DevCsr(A)
+    b = torch.full((k * n + 2,), float("nan"), device="cuda")
+    b[1:-1] = g.dev(B).view(-1)
+    plain, c = torch.empty((m, n), device="cuda"), torch.full((m * n + 2,), float("nan"), device="cuda")
+    spdl.spdl_spmm(m, k, n, A.nnz, d.ro, d.ci, d.val, None, b[1:-1].view(k, n), plain)
+    spdl.spdl_spmm_skewed(m, k, n, A.nnz, d.ro, d.ci, d.val, b[1:-1].view(k, n), c[1:-1].view(m, n))
+    torch.cuda.synchronize()
+    got = c.cpu().numpy()
+    assert np.isnan(got[0]) and np.isnan(got[-1])
+    got = got[1:-1].reshape(m, n)
+    assert np.all(np.abs(got - ref) <= (int(lens.max()) + 3) * 2.0 ** -24 * S)
+    moved = np.any(got != plain.cpu().numpy(), axis=1)
+    shared = lens > max(64, 2 * mean)
+    assert np.all(moved[lens >= 80]) and not np.any(moved[~shared]) and np.count_nonzero(shared) >= 5
+
+
+# (a wave per row, rows shared by four, and a row to a workgroup: the same products and sums by either kind of index)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,rows", [(97, 257, 4), (97, 516, 1), (799, 512, 1), (1601, 400, 4), (1601, 2049, 4)])
+def test_long_rows_by_indices_of_two_bytes(g, oracle_lib, force, m, n, rows):
+    import torch
+    import paper_2006_10901_amd as spdl
+    k = 300
+    rng = np.random.default_rng(9200 + m)
+    lens = rng.integers(16, 48, m)
+    lens[::9] = rng.integers(60, 300, len(lens[::9]))
+    A = rows_csr(k, lens, 9201 + m)
+    assert A.nnz // m >= 24
+    force(0, 0)
+    s = spdl.spdl_select_spmm(m, k, n, A.nnz, 2, 0, 0)
+    assert spdl.spdl_variant_name(0, s["variant"]) == "rowsplit" and (s["lanes_per_row"], s["rows_per_block"]) == (64, rows)
+    B = wl.dense(k, n, 9202 + n, np.float16)
+    ref, S = oracle_lib.spmm(m, k, n, A.row_offsets, A.column_indices, A.values.astype(np.float32), B.astype(np.float32))
+    d, b = g.DevCsr(A), g.dev(B)
+    c4, c2 = (torch.full((m, n), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    order = g.dev(oracle_lib.row_order(m, A.row_offsets))
+    spdl.spdl_spmm_f16(m, k, n, A.nnz, d.ro, d.ci, d.val, order, b, c4)
+    spdl.spdl_spmm_f16_i16(m, k, n, A.nnz, d.ro, d.ci.to(torch.int16), d.val, order, b, c2)
+    torch.cuda.synchronize()
+    got = c2.cpu().numpy()
+    assert np.array_equal(got, c4.cpu().numpy())
+    assert np.all(np.abs(got - ref) <= (int(lens.max()) + 3) * 2.0 ** -24 * S + 2.0 ** -11 * np.abs(ref) + 2.0 ** -25)

@@ -24,7 +24,7 @@ def strips(m, k, n, nnz, eb):
     """Entries per wave, waves per workgroup, workgroups."""
     import paper_2006_10901_amd as spdl
     s = spdl.spdl_select_sddmm(m, k, n, nnz, eb, 0, 0)
-    assert spdl.spdl_variant_name(1, s["variant"]) == "group" and s["lanes_per_row"] == 16
+    assert spdl.spdl_variant_name(1, s["variant"]) in ("group", "rowstrip") and s["lanes_per_row"] == 16      # (rowstrip: fp32 widths of 129 .. 191 that are no multiple of four)
     return s["rows_per_block"], s["block_threads"] // 64, s["grid_x"]
 
 
@@ -65,17 +65,18 @@ def against_the_oracle(g, oracle_lib, A, n, dtype, scaled):
     assert np.all(np.abs(got[1:-1] - ref) <= bound)
 
 
-# (columns around whole pieces of four, sixty-fours and pairs of those; entries for 16 and 32 per wave; empty and full rows, rows in
-# no order and duplicates; every array at odd elements)
+# (columns around whole pieces of four, sixty-fours and pairs of those; entries for 16 and 32 per wave, the latter in long rows (65 .. 128 columns; the
+# other widths take strips of sixteen there) and in short ones; empty and full rows, rows in no order and duplicates; every array at odd elements)
 @pytest.mark.gpu
-@pytest.mark.parametrize("m,k,density", [(90, 70, 0.1), (515, 300, 0.1), (400, 700, 0.4)])
+@pytest.mark.parametrize("m,k,density", [(90, 70, 0.1), (515, 300, 0.1), (400, 700, 0.4), (4000, 300, 0.08)])
 @pytest.mark.parametrize("n,dtype", [(4, np.float32), (7, np.float32), (63, np.float32), (64, np.float32), (65, np.float32), (127, np.float32),
                                      (128, np.float32), (129, np.float32), (260, np.float32), (67, np.float16), (128, np.float16), (189, np.float16)])
 def test_strips_of_four(g, oracle_lib, force, m, k, density, n, dtype):
     A = odd_csr(m, k, density, 7800 + m)
     force(1, 1)
-    if n > 64 and n <= 128:
-        assert strips(m, k, n, A.nnz, 4)[:2] == (32 if m == 400 else 16, 1)
+    both = 64 < n <= 128
+    want = ((32, 1) if both else (64, 4)) if m == 400 else ((16, 1) if both else (32, 1)) if m == 4000 else (16, 1)
+    assert strips(m, k, n, A.nnz, np.dtype(dtype).itemsize)[:2] == want
     against_the_oracle(g, oracle_lib, A, n, dtype, scaled=n % 2 == 0)
 
 
