@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
           LdsHalf* const to = (LdsHalf*)(uintptr_t)d;
           const unsigned x = term(v[e]);
           const float rest = v[e] - __builtin_bit_cast(float, x);
-          const unsigned y = term(rest), z = term(rest - __builtin_bit_cast(float, y));
+          const unsigned y = term(rest), z = __builtin_bit_cast(unsigned, rest - __builtin_bit_cast(float, y));      // (eight bits at most are left)
           to[0] = (unsigned short)(x >> 16);
           to[kDsPlane / 2] = (unsigned short)(y >> 16);
           to[kDsPlane] = (unsigned short)(z >> 16);
