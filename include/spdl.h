@@ -60,10 +60,10 @@ typedef enum {
  *               handed to workgroups (paper Sec. "Row Swizzle Load Balancing"); NULL = identity.
  *               The result does not depend on it.
  *   B : DEVICE fp32[k*n];   C : DEVICE fp32[m*n], fully overwritten (empty rows become +0).
- *   Products and sums are fp32 (fused multiply-adds).  Most kernels add a row's products in
- *   stored order; when few long rows are spread over several lane groups, and in the window kernel
- *   (attention-shaped problems among others: it keeps a window of B around a band of A in
- *   on-chip memory and takes rows in their natural order), partial sums are added at the end.
+ *   Products and sums are fp32 (fused multiply-adds).  A row's products are added in stored order, or in a few parts, each in
+ *   stored order, that are added up at the end: where rows are too few to fill the machine (fp32 rows of a few dozen entries among
+ *   them), rows much longer than the mean, and in the window kernel (attention-shaped problems among others: it keeps a window of
+ *   B around a band of A in on-chip memory and takes rows in their natural order).
  *   Dense A (about one position in five and more, from 33 columns of B on, where the output fills the machine): products from
  *   three bf16 terms per number, which hold all of its 24 bits, of whose nine products the six largest (the others: less than
  *   2^-24 of the whole) are added up in fp32 on the matrix cores, zeros of A included.  Rows of fewer than 72 + k / 24 entries,

@@ -342,7 +342,7 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 // walk over A's columns.  Fitted on 200 uniform shapes of 129 tiles of 64 x 64 and more (1024 .. 18800 rows, 720 .. 11600 columns, n = 33 ..
 // 4096, 11 .. 50 %: 5 % off for the matrix cores, 4 % and 6 % for the forms that walk and with one row per group); the choice takes
 // 1.005 times the faster one's time on average, 0.81 times the plan's.  The two meet at 17 .. 22 %, earlier where the rounds
-// fit (8192 x 10240, n = 128: 15 % 109 us and 122, 20 % 132 and 127, 30 % 185 and 135).
+// fit (8192 x 10240, n = 128: 15 % 109 us and 122, 20 % 142 and 136, 30 % 202 and 148).
 // Rows of few entries are gathered there (spmm_split_entries): uniform shapes that come out have their mean 3.2 standard deviations and more
 // above that, on 200 thousand of 800 .. 1400 columns.
 // Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
@@ -516,7 +516,8 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
   if (variant == kSpmmMfma) {
     // 32-row panels, one or two tiles per workgroup.  (64-row panels, which would halve the
     // reads of B, need 256 accumulator registers per lane with tiles of 256 columns; the compiler then spills in the main
-    // loop and the kernel is twice as slow.  With tiles of 128 columns they would need as many as now: not tried.)
+    // loop and the kernel is twice as slow.  With tiles of 128 columns they halve B's traffic and double the filling: 18.5 -> 18.3 us with
+    // even n, 20.5 -> 27 with odd n (1024 x 1024 at 10 %, some 3136 columns).)
     const int tiles_n = (n + 255) / 256;
     info->variant = kSpmmMfma;
     info->vec = 8;
@@ -677,7 +678,7 @@ int launch_spmm_rowsplit_g(const spdl_launch_info& li, int m, int n, int nnz, co
         // (Long rows by four waves.  Half precision, 600 shapes of 2 .. 30 % and up to 3584 columns, of the time before: log-normal rows 0.61, uniform
         // ones 1.00.  Shorter rows cost 1.03 .. 1.06 where rows are equal, with narrow loads 1.1 .. 1.2.  fp32, 46 shapes: log-normal rows 0.80 at any
         // length, uniform ones 1.00 from 96 entries on, 1.03 at 16 .. 64, so these only where the caller has said that rows are unequal: 1024 x
-        // 1024 at 10 %, n = 3136: 114 us -> 93.)
+        // 1024 at 10 %, n = 3136: 121 us -> 116; the slab kernel with a row order 89.)
         if (nnz / std::max(m, 1) >= (VEC == 8 || hint == kHintSkewed ? 16 : sizeof(T) == 2 ? 24 : 96)) { SPDL_ROWSPLIT(64, 1, 1, true) }
         SPDL_ROWSPLIT(64, 1)
     }

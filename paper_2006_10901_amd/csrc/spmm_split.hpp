@@ -21,8 +21,8 @@
 // both.  Without scattered stores 10 .. 25 us less of 146 at 30 %, without loads of B 10, without the splitting 13, reading A back costs
 // nothing; rows of B requested two steps further ahead, half a stage between the two multiplying waves of a SIMD, 64 columns and an
 // eighth of the stage per wave, splitting by dot products of bf16 pairs (fewer instructions, but none beside an MFMA) gain nothing.
-// 8192 x 10240, n = 128, slab kernel -> here: 20 % 132 us -> 127, 30 % 185 -> 135; 6765 x 2169 at 28 %, n = 120: 40.7 -> 30.7; 5923 x 6704 at
-// 42 %, n = 128: 155 -> 87; at 10 % 84 us -> 116, which is why the density decides.
+// 8192 x 10240, n = 128, slab kernel -> here, inputs in turn: 20 % 142 us -> 136, 30 % 202 -> 148 (188 -> 144 on a faster card); 6765 x 2169 at
+// 28 %, n = 120: 41.0 -> 30.4; 5923 x 6704 at 42 %, n = 128: 157 -> 94; at 10 % 84 us -> 116, which is why the density decides.
 //
 // Rows that are not ascending, or hold a column twice, are noticed (an entry that does not come right after a smaller column of the
 // same stage; a cursor short of the row's end) and gathered at the end (split_gather), as is what is not finite: a zero of the
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       if (more) last = (unsigned)__builtin_amdgcn_mov_dpp((int)rel[NC - 1], 0x121, 0xf, 0xf, true);
       return more;
     };
-    // (ahead of the multiplying waves, which have the MFMA to wait for: 30 %, 144 us -> 135)
+    // (ahead of the multiplying waves, which have the MFMA to wait for: 30 %, 157 us -> 147; 42 %, 111 -> 96)
     __builtin_amdgcn_s_setprio(1);
     auto fill = [&](int q, int x) __attribute__((always_inline)) {
       char* block = lds_raw + x * kDsBuf;
