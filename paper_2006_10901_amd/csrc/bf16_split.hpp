@@ -17,8 +17,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // then, as do infinities and NaN (Inf - Inf): what comes out like that is computed again without the
 // matrix cores.
 // (Against 64 bits, normally distributed values, 2-norm of the error over that of the result: dot products of 32 / 64 / 128 columns
-// 3.9 / 5.0 / 6.5e-8, where the direct kernels have 6.2 / 6.8 / 7.7e-8 and the lane kernel 7.9 / 8.3 / 8.8e-8; rows of
-// 3072 of 10240 columns 4.5e-7, where the slab kernel has 9.9e-7.  With one accumulator for all six: 1.6e-7 and 1.4e-6.)
+// 3.9 / 5.0 / 6.5e-8, where the direct kernels have 6.2 / 6.8 / 7.7e-8 and the lane kernel 7.9 / 8.3 / 8.8e-8.  With one accumulator for all
+// six: 1.6e-7.)
 constexpr float kSplitScale = 16777216.f;                // 2^24
 constexpr float kSplitUnscale = 0x1p-48f;
 

@@ -339,10 +339,11 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 
 // Whether the matrix-core form (spmm_split.hpp) takes the place of the plan's.  Estimates in microseconds: rounds of one workgroup per
 // compute unit, each of so many stages of 128 columns; the plan's end (slab_makespan), whose unit is a thirtieth of a tile's
-// walk over A's columns.  Fitted on 200 uniform shapes of 129 tiles of 64 x 64 and more (1024 .. 18800 rows, 720 .. 11600 columns, n = 33 ..
-// 4096, 11 .. 50 %: 5 % off for the matrix cores, 4 % and 6 % for the forms that walk and with one row per group); the choice takes
-// 1.005 times the faster one's time on average, 0.81 times the plan's.  The two meet at 17 .. 22 %, earlier where the rounds
-// fit (8192 x 10240, n = 128: 15 % 109 us and 122, 20 % 142 and 136, 30 % 202 and 148).
+// walk over A's columns.  Fitted on 80 uniform shapes of 129 tiles of 64 x 64 and more (1024 .. 16000 rows, 836 .. 10800 columns, n = 33 ..
+// 2048, 11 .. 35 %: 4 % off for the matrix cores; on 200 for the forms that walk and with one row per group, 4 % and 6 %).  The two meet at 15 .. 18 %
+// (us, here and in the plan's form: 8192 x 10240, n = 128, 14 % 116 and 112, 16 % 116 and 120, 20 % 127 and 143, 30 % 133 and 200; 5494 x 3943 at
+// 15 %, n = 369, 119 and 121; 2621 x 1436 at 31 %, n = 540, 41 and 55; 14741 x 1257 at 28 %, n = 748, 203 and 251); below 15.5 % of 17 shapes
+// two were faster here, by 2 and 10 %.
 // Rows of few entries are gathered there (spmm_split_entries): uniform shapes that come out have their mean 3.2 standard deviations and more
 // above that, on 200 thousand of 800 .. 1400 columns.
 // Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
@@ -350,10 +351,10 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 bool spmm_split_runs(int m, int k, int n, int nnz, const SlabPlan& plan) {
   if (n <= 32 || n > 2048 || k < 800 || nnz >= (1 << 28) || plan.span == 0) return false;
   const double density = (double)nnz / ((double)m * (double)k);
-  if (density < 0.12) return false;
+  if (density < 0.155) return false;
   const int load = slab_xcd_load((m + kDsRows - 1) / kDsRows, (n + kDsCols - 1) / kDsCols);
   const double rounds = std::ceil(load / (kComputeUnits / 8.0)), stages = (double)((k + kDsS - 1) / kDsS);
-  const double t_split = -0.55 + rounds * (5.09 + stages * (1.138 + 1.18 * density));
+  const double t_split = 1.2 + rounds * (5.23 + stages * (0.991 + 0.922 * density));
   const double form = plan.form == kSlabWalk || plan.form == kSlabWide ? 1.08 : plan.form == kSlabOneRow ? 0.957 : 1.0;
   return t_split <= 0.97 * form * plan.span * (double)k * (0.173e-3 + 2.876e-3 * density);
 }

@@ -1,32 +1,36 @@
-// SpMM of dense sparse matrices on the matrix cores, fp32: whole blocks of A, zeros included, times B, from three-term bf16
-// products (bf16_split.hpp).
+// SpMM of dense sparse matrices on the matrix cores, fp32: whole blocks of A, zeros included, times B, from products of two
+// fp16 terms per number.
+//
+// A number taken times a power of two is high + low / 2048, both fp16: low is the rounded rest, which has at most one bit more than fp16
+// holds, so what is left out is no more than 2^-23 of the number.  All four products of terms are taken: high high in one
+// accumulator, the three small ones in another, so that these are not rounded to the large sum's last place one by one.  The power of two
+// is chosen for each row of A and for each column of B (and quarter of A's columns), from the first numbers that are not zero, whose
+// largest comes to 2^10 .. 2^11; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers below
+// 2^-24 of the row's or column's largest lose bits of `low` to fp16's smallest exponent: 2^-46 of the largest at most.
 //
 // A workgroup owns 64 sparse rows and 64 columns of C and walks A's columns in stages of 128.  Eight waves scatter: sixteen lanes to
 // a row, they find the row's entries of the stage by a cursor, take each apart into its terms and write these into a block of
 // zeros in LDS, in the order in which the lanes read them as MFMA operands.  Eight waves multiply: each has 32 of the 64 columns and a
-// quarter of the stage's columns of A, brings in its rows of B straight into registers (a lane's operand is eight rows of its column),
-// splits them there, one step of sixteen ahead, and multiplies them with both 32-row tiles of the block; the quarters are
+// quarter of the stage's columns of A, copies its rows of B into a ring of its own in LDS (16 bytes per lane: loaded into registers, a lane's operand
+// takes an instruction for each of its numbers, 18 clocks of the compute unit's address path apiece), splits
+// them in registers, one step of sixteen ahead, and multiplies them with both 32-row tiles of the block; the quarters are
 // added at the end.  Three blocks: one is multiplied, the next one written, the one before cleared, a barrier per stage, which
 // a multiplying wave reaches with what it still needs of the block in registers, so that half a step of products lies behind it.
 //
-// One accumulator, not two as in the SDDMM: a sum is four chains, and 6 k / 64 roundings each leave a smaller error than one
-// chain of the row's entries, if these are enough: against the slab kernel, 2-norm of the error, normally distributed values, rows of 10 % / 20 %
-// / 30 % of 10240 columns 0.90 / 0.79 / 0.72 of it, of 1025 columns 0.995 / 0.85 / 0.73.  With fewer entries the six roundings for each of
-// them count (2.0 times the error for rows of two, 1.3 for 20 of 1025, 1.06 for 205 of 10240): such rows are gathered (spmm_split_entries).  What
-// is left out of a product is below 2^-24 of it: the terms of both operands are rounded.  (A's cut off, up to 2.9 times that: 1.01 .. 1.04
-// times the error, and the same time.  6765 x 2169 at 28 %, n = 120: 30 us; every other row of 40 entries: 34.8, gathered 43.4, slab kernel 66.)
+// Against 64 bits, normally distributed values, 2-norm of the error over that of the result: rows of 30 % of 10240 columns 3.2e-7, where six
+// products of three bf16 terms in one accumulator have 7.0e-7 and the slab kernel 9.9e-7.  With few entries the roundings of a sum that are no
+// entry's count: such rows are gathered (spmm_split_entries).
 //
-// What bounds it: the issue of vector instructions beside the MFMA.  A stage is 48 MFMA of 32 clocks on each SIMD, 240 vector
-// instructions of the multiplying waves and 120 (10 %) to 230 (30 %) of the scattering ones; it takes 3000 .. 3400 clocks, the sum of
-// both.  Without scattered stores 10 .. 25 us less of 146 at 30 %, without loads of B 10, without the splitting 13, reading A back costs
-// nothing; rows of B requested two steps further ahead, half a stage between the two multiplying waves of a SIMD, 64 columns and an
-// eighth of the stage per wave, splitting by dot products of bf16 pairs (fewer instructions, but none beside an MFMA) gain nothing.
-// 8192 x 10240, n = 128, slab kernel -> here, inputs in turn: 20 % 142 us -> 136, 30 % 202 -> 148 (188 -> 144 on a faster card); 6765 x 2169 at
-// 28 %, n = 120: 41.0 -> 30.4; 5923 x 6704 at 42 %, n = 128: 157 -> 94; at 10 % 84 us -> 116, which is why the density decides.
+// What bounds it: the power limit (1.5 .. 1.7 GHz) and the issue of vector instructions beside the MFMA.  A stage is 64 MFMA of 32 clocks on two of a
+// SIMD's waves, 170 vector instructions of these and 130 (10 %) to 260 (30 %) of the scattering waves, 4 clocks each or 5 where a wave is
+// alone; it takes 2900 clocks.  8192 x 10240 at 10 %, n = 128, 141 us: without MFMA 105, without scattering 108, without copies of B 131, without the
+// three small products' smallest 131.  A step's operands all read a step ahead, one accumulator and registers for
+// two blocks instead: 7 % slower.  8192 x 10240, n = 128, three bf16 terms and six products -> here, inputs in turn: 20 % 136.8 us -> 126.5, 30 %
+// 149.8 -> 132.9; 5923 x 6704 at 20 % 77.6 -> 69.6; 4368 x 5000 at 20 % 56.4 -> 53.6 (slab kernel at these: 143, 200, 86.6, 65.1).
 //
 // Rows that are not ascending, or hold a column twice, are noticed (an entry that does not come right after a smaller column of the
 // same stage; a cursor short of the row's end) and gathered at the end (split_gather), as is what is not finite: a zero of the
-// block times an infinity of B must not reach the result.
+// block times an infinity of B must not reach the result.  (Sums from some 2^100 of B's numbers' on come out as infinities too, and are gathered.)
 #pragma once
 #include "bf16_split.hpp"
 
@@ -37,10 +41,26 @@ constexpr int kDsCols = 64;                              // columns of C per wor
 constexpr int kDsS = 128;                                // columns of A per stage
 constexpr int kDsGroup = kDsRows * 16 + 16;              // bytes of eight columns, one term: the next eight lie four banks on
 constexpr int kDsPlane = kDsS / 8 * kDsGroup;            // one term of a stage's block of A
-constexpr int kDsBuf = 3 * kDsPlane;
-constexpr int kDsLdsBytes = 3 * kDsBuf + kDsRows * 4;
+constexpr int kDsBuf = 2 * kDsPlane;
 constexpr int kDsMulWaves = 8, kDsScatterWaves = 8;
 constexpr int kDsThreads = 64 * (kDsMulWaves + kDsScatterWaves);
+constexpr int kDsRing = 3, kDsChunk = 16 * 32 * 4;       // a multiplying wave's sixteen rows of 32 columns of B, as they come
+constexpr int kDsRingOff = 3 * kDsBuf;
+constexpr int kDsRedoOff = kDsRingOff + kDsMulWaves * kDsRing * kDsChunk;
+constexpr int kDsScaleOff = kDsRedoOff + kDsRows * 4;
+constexpr int kDsShiftOff = kDsScaleOff + kDsRows * 4;
+constexpr int kDsLdsBytes = kDsShiftOff + 3 * kDsRows * 8 + 16;
+
+// Powers of two, as exponents of fp32 (127: one), that bring the largest number of a row or a column to 2^10 .. 2^11; the
+// number from which on another one is needed, 2^15 after scaling.  (Infinities: the smallest; nothing seen yet: kDsNoScale, with limit 0.)
+constexpr int kDsNoScale = 254;
+constexpr float kDsLow = 2048.f;                         // the low terms are taken times this, so that they are as far from fp16's smallest exponent as the high ones
+__device__ __forceinline__ int scale_for(float largest) {
+  return max(1, min(254, 264 - (int)(__builtin_bit_cast(unsigned, largest) >> 23)));
+}
+__device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_cast(float, min(255, 269 - scale) << 23); }
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
 
 // Lane i gets the place of the (i + 1)-th one of `set`.  (Lanes beyond the last one: those of the zeros.)
 __device__ __forceinline__ int nth_one(unsigned long long set) {
@@ -130,7 +150,7 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
 // 1025 columns, 155 of 2169, 290 of 5120, 460 of 10240.)
 __host__ __device__ constexpr int spmm_split_entries(int k) { return 72 + k / 24; }
 
-// NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, 0 < nnz < 2^28.)
+// NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, n >= 4, 0 < nnz < 2^28.)
 template <int NC>
 __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
     int m, int k, int n, int nnz, int tiles_n, int panels, const int* __restrict__ row_offsets,
@@ -145,7 +165,11 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
   const int nst = (k + kDsS - 1) / kDsS;
   PhaseClocks clocks;
   clocks.start();
-  int* const redo = reinterpret_cast<int*>(lds_raw + 3 * kDsBuf);       // rows to be gathered
+  int* const redo = reinterpret_cast<int*>(lds_raw + kDsRedoOff);       // rows to be gathered
+  int* const row_scale = reinterpret_cast<int*>(lds_raw + kDsScaleOff);
+  // {stage + 1, by how many powers of two the row's sums go down before it}, and the stage + 1 of which a row has such
+  i32x2* const row_shift = reinterpret_cast<i32x2*>(lds_raw + kDsShiftOff);
+  int* const shifted = reinterpret_cast<int*>(lds_raw + kDsShiftOff + 3 * kDsRows * 8);
   auto barrier = [&]() __attribute__((always_inline)) {                // (no wait for memory)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
@@ -154,95 +178,165 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
     for (int i = 0; i < (3 * kDsBuf + 16 * kDsThreads - 1) / (16 * kDsThreads); ++i)
       if ((i * kDsThreads + tid) * 16 < 3 * kDsBuf) *reinterpret_cast<f32x4*>(lds_raw + (i * kDsThreads + tid) * 16) = zero;
+    if (tid < 3 * kDsRows) row_shift[tid] = i32x2{0, 0};
+    if (tid < 3) shifted[tid] = 0;
   }
   barrier();
 
   if (wave < kDsMulWaves) {
     const int r = lane & 31, h = lane >> 5, quarter = wave & 3, half = wave >> 2;
-    const int col = tile * kDsCols + half * 32 + r;                    // (columns past n: the last one again, not stored)
+    const int col0 = tile * kDsCols + half * 32;
+    // B's rows come by way of LDS, sixteen of them in a kilobyte pair of this wave's own, three steps ahead: row 8 h + e, column
+    // r of them is at 256 e + 128 h + 4 r, so that the lanes read 256 bytes in a row.  A lane brings four columns of a row;
+    // the four that would reach past the row's end start at n - 4.  (Columns past n: those of the last four.)
+    char* const ring = lds_raw + kDsRingOff + wave * (kDsRing * kDsChunk);
+    const unsigned ring_m0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
     const unsigned row_bytes = (unsigned)n * 4u;
-    const unsigned lane_off = (unsigned)(8 * h) * row_bytes + (unsigned)min(col, n - 1) * 4u;
-    float raw[2][8];
+    const unsigned lane_off = (unsigned)(8 * ((lane >> 3) & 1) + (lane >> 4)) * row_bytes + (unsigned)min(col0 + 4 * (lane & 7), n - 4) * 4u;
+    const int piece = min(col0 + (r & ~3), n - 4);
+    const char* const ring_lane = ring + h * 128 + (r & ~3) * 4 + min(col0 + r - piece, 3) * 4;
     // Rows of the wave's columns: step 2 q + s is columns 128 q + 32 quarter + 16 s .. of A.  The sixteen that k ends in, and steps
     // past it, take A's last sixteen: an entry of theirs is scattered to where its row of B then comes.
-    auto load_b = [&](float (&x)[8], int step) __attribute__((always_inline)) {
-      const int k0 = uniform(min((step >> 1) * kDsS + quarter * 32 + (step & 1) * 16, k - 16));
-      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B) + (size_t)k0 * (unsigned)n, 0, 0x7fffffff, 0x00020000);
+    auto bring = [&](int q, int s, unsigned slot) __attribute__((always_inline)) {
+      const int k0 = uniform(min(q * kDsS + quarter * 32 + s * 16, k - 16));
+      const float* const base = B + (size_t)k0 * (unsigned)n;
+      const unsigned to = ring_m0 + slot * kDsChunk;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4"
+                   :: "s"(to), "s"(to + kDsChunk / 2), "v"(lane_off), "s"(base), "s"(base + (size_t)4 * (unsigned)n) : "memory", "m0");
+    };
+    float raw[8];
+    auto read_b = [&](unsigned slot) __attribute__((always_inline)) {  // (all but the last two chunks that were asked for are there)
+      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      const char* const p = ring_lane + slot * kDsChunk;
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane_off, (int)((unsigned)e * row_bytes), 0));
+      for (int e = 0; e < 8; ++e) raw[e] = *reinterpret_cast<const float*>(p + e * 256);
+    };
+    int scale = kDsNoScale, shift = 0;                                 // of the lane's column: the exponent of the power of two it is taken times
+    float limit = 0.f;
+    unsigned long long raised = 0;
+    struct Terms { f16x8 high, low; };
+    auto split = [&]() __attribute__((always_inline)) -> Terms {
+      float largest = __builtin_fabsf(raw[0]);
+#pragma unroll
+      for (int e = 1; e < 8; ++e) largest = fmaxf(largest, __builtin_fabsf(raw[e]));
+      raised = __builtin_amdgcn_ballot_w64(largest > limit);
+      if (__builtin_expect(raised != 0, 0)) {
+        const u32x2 both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, largest), __builtin_bit_cast(unsigned, largest), false, false);
+        largest = fmaxf(__builtin_bit_cast(float, both[0]), __builtin_bit_cast(float, both[1]));      // (the column's other half)
+        const int to = largest > limit ? scale_for(largest) : scale;
+        shift = to - scale;
+        scale = to;
+        limit = largest > limit ? scale_limit(to) : limit;
+      }
+      const float times = __builtin_bit_cast(float, scale << 23);
+      Terms t;
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const f16x2 x = __builtin_convertvector((f32x2{raw[e] * times, raw[e + 1] * times}), f16x2);
+        const f32x2 rest = {__builtin_fmaf(raw[e], times, -(float)x[0]), __builtin_fmaf(raw[e + 1], times, -(float)x[1])};
+        const f16x2 y = __builtin_convertvector((f32x2{rest[0] * kDsLow, rest[1] * kDsLow}), f16x2);
+        t.high[e] = x[0]; t.high[e + 1] = x[1];
+        t.low[e] = y[0]; t.low[e + 1] = y[1];
+      }
+      return t;
     };
     // A lane's operand of a term, eight columns of row 32 i + r: 16 bytes at group * kDsGroup + 512 i + 16 r.
-    unsigned a_off[2];
+    const unsigned a_off = (unsigned)((4 * quarter + h) * kDsGroup + (r << 4));
+    f16x8 high[2], low[2];
+    auto load_a = [&](f16x8 (&x)[2], const char* p) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) a_off[s] = (unsigned)((2 * (2 * quarter + s) + h) * kDsGroup + (r << 4));
-    bf16x8 high[2], mid[2], low[2];
-    auto load_a = [&](bf16x8 (&x)[2], const char* p) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const bf16x8*>(p + i * 512);
+      for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const f16x8*>(p + i * 512);
     };
-    acc32x32 sum[2];
+    acc32x32 sum[2], rest[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int x = 0; x < 16; ++x) sum[i][x] = 0.f;
-    auto two = [&](const bf16x8 (&x)[2], const bf16x8& y) __attribute__((always_inline)) {
-      sum[0] = mfma_bf16(x[0], y, sum[0]);
-      sum[1] = mfma_bf16(x[1], y, sum[1]);
+      for (int x = 0; x < 16; ++x) sum[i][x] = rest[i][x] = 0.f;
+    auto two = [&](acc32x32 (&to)[2], const f16x8 (&x)[2], const f16x8& y) __attribute__((always_inline)) {
+      to[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y, to[0], 0, 0, 0);
+      to[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y, to[1], 0, 0, 0);
     };
-#pragma unroll
-    for (int i = 0; i < 2; ++i) load_b(raw[i], i);
+    // (chunk t is in slot t % kDsRing)
+    unsigned slot = 0;
+    auto next_slot = [](unsigned x) { return x == kDsRing - 1 ? 0u : x + 1u; };
+    int bring_q = 0, bring_s = 0;
+    auto bring_next = [&](unsigned to) __attribute__((always_inline)) {
+      bring(bring_q, bring_s, to);
+      bring_s ^= 1;
+      if (bring_s == 0) ++bring_q;
+    };
+    for (unsigned i = 0; i < kDsRing; ++i) bring_next(i);
+    read_b(0);
+    Terms b = split();
+    asm volatile("" :: "v"(b.high), "v"(b.low));                       // (the chunk has been read)
+    bring_next(0);
+    read_b(1);
+    slot = 1;                                                          // of the chunk in `raw`
     barrier();                                                         // the first stage's block is there
-    load_a(high, lds_raw + a_off[0]);
-    load_a(mid, lds_raw + a_off[0] + kDsPlane);
-    load_a(low, lds_raw + a_off[0] + 2 * kDsPlane);
-    Split8 b = split8(raw[0]);
+    load_a(high, lds_raw + a_off);
+    load_a(low, lds_raw + a_off + kDsPlane);
     clocks.lap(kPhaseSetup);
     char* const clear = lds_raw + wave * (kDsBuf / kDsMulWaves) + lane * 16;
     static_assert(kDsBuf / kDsGroup % kDsMulWaves == 0, "whole groups for a wave");
     // One step of sixteen columns; `next` is where the next one's operands are, each read as soon as its registers are done
     // with.  `last` of a stage: half of the products need nothing of the stage's block that is not in registers.
-    auto step = [&](const char* next, int at, bool last, int before, float (&now)[8], float (&after)[8])
-                    __attribute__((always_inline)) {
-      load_b(now, at + 2);
-      const Split8 c = split8(after);
-      two(high, b.low);
-      two(high, b.mid);
-      two(high, b.high);
-#pragma unroll
-      for (int g = 0; g < 6; ++g) {
-        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x2, 5, 0);
-      }
+    auto step = [&](const char* next, bool last, int before, int q, int x) __attribute__((always_inline)) {
+      const Terms c = split();
+      two(rest, low, b.low * (_Float16)(1.f / kDsLow));
+      two(rest, low, b.high);
+      asm volatile("" :: "v"(c.high), "v"(c.low));
+      bring_next(slot);
+      slot = next_slot(slot);
       if (last) {
         clocks.lap(kPhaseSteps);
         __builtin_amdgcn_sched_barrier(0);
         barrier();                                                     // this block may be cleared; the next one is there
         clocks.lap(kPhaseBarrier);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      load_a(high, next);
+      const int other_scales = last ? shifted[x] : 0;
+      load_a(low, next + kDsPlane);
+      read_b(slot);
       if (!last) {
         const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int i = 0; i < kDsBuf / kDsGroup / kDsMulWaves; ++i) *reinterpret_cast<u32x4*>(clear + before * kDsBuf + i * kDsGroup) = zero;
       }
-      two(mid, b.mid);
-      two(mid, b.high);
-      load_a(mid, next + kDsPlane);
-      two(low, b.high);
-      load_a(low, next + 2 * kDsPlane);
+      two(rest, high, b.low);
+      two(sum, high, b.high);
+      load_a(high, next);
+      if (__builtin_expect(raised != 0, 0)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < 16; ++t) {
+            sum[i][t] = __builtin_ldexpf(sum[i][t], shift);
+            rest[i][t] = __builtin_ldexpf(rest[i][t], shift);
+          }
+        shift = 0;
+      }
+      if (last && __builtin_expect(uniform(other_scales) == q + 2, 0)) {   // rows of the next stage go by another power of two
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < 16; ++t) {
+            const i32x2 down = row_shift[x * kDsRows + 32 * i + 8 * (t / 4) + 4 * h + t % 4];
+            const int by = down.x == q + 2 ? down.y : 0;
+            sum[i][t] = __builtin_ldexpf(sum[i][t], by);
+            rest[i][t] = __builtin_ldexpf(rest[i][t], by);
+          }
+      }
       b = c;
       __builtin_amdgcn_sched_barrier(0);
     };
     int x = 0, before = 2;
     for (int q = 0; q < nst; ++q) {
       const int next = x == 2 ? 0 : x + 1;
-      step(lds_raw + x * kDsBuf + a_off[1], 2 * q, false, before, raw[0], raw[1]);
-      step(lds_raw + next * kDsBuf + a_off[0], 2 * q + 1, true, before, raw[1], raw[0]);
+      step(lds_raw + x * kDsBuf + 2 * kDsGroup + a_off, false, before, q, next);
+      step(lds_raw + next * kDsBuf + a_off, true, before, q, next);
       before = x;
       x = next;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // (what was asked for past the end)
     barrier();
     // This wave's sums.  Register t of lane (r, h) is row 8 (t / 4) + 4 h + t % 4 of the tile, column r.
 #pragma unroll
@@ -250,7 +344,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
         const int row = 32 * i + 8 * (t / 4) + 4 * h + t % 4;
-        *reinterpret_cast<float*>(lds_raw + quarter * (kDsRows * kDsCols * 4) + row * (kDsCols * 4) + (half * 32 + r) * 4) = sum[i][t];
+        *reinterpret_cast<float*>(lds_raw + quarter * (kDsRows * kDsCols * 4) + row * (kDsCols * 4) + (half * 32 + r) * 4) =
+            __builtin_ldexpf(__builtin_fmaf(rest[i][t], 1.f / kDsLow, sum[i][t]), 127 - scale);
       }
   } else {
     const int tail = k & ~15, tail_shift = tail == k ? 0 : 16 - (k & 15);
@@ -267,6 +362,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
     unsigned long long strays[NR];
     int cc[NR][NC];
     float aa[NR][NC];
+    int scale[NR];
+    float limit[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int local = first_row + 4 * j + sub, row = min(i0 + local, m);
@@ -275,6 +372,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int e = 0; e < NC; ++e) row_end[j][e] = row_offsets[min(row + 1, m)] * 4 - 64 * e;
       row_base[j] = (unsigned)((local >> 5) * 512 + ((local & 31) << 4));
       strays[j] = 0;
+      scale[j] = kDsNoScale;
+      limit[j] = 0.f;
     }
     auto fetch = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
@@ -283,24 +382,23 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int e = 0; e < NC; ++e)
         aa[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(value_rsrc, at[j] + 64 * e, 0, 0));
     };
-    auto term = [](float x) __attribute__((always_inline)) {           // x rounded to its first term, in the upper half
-      return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{0.f, x}), bf16x2));
-    };
     const int shift16 = 16 * (sub & 1);
     const bool upper = sub >= 2;
     unsigned last = 0;                                                 // the last column of the round before, in a group's first lane
     // The fetched entries of row j in the stage's columns; whether there may be more of them.  What is fetched is used up
     // before the next fetch, which then has the same registers: the compiler copies nothing, and so waits for nothing, before the next stage.
-    auto round = [&](int j, char* block, int start, bool again) __attribute__((always_inline)) -> bool {
-      unsigned long long mk[NC];
+    auto round = [&](int j, char* block, int q, int x, bool again) __attribute__((always_inline)) -> bool {
+      const int start = q * kDsS;
+      unsigned long long mk[NC], over = 0;
       unsigned rel[NC];
       float v[NC];
       unsigned count = 0;
 #pragma unroll
       for (int e = 0; e < NC; ++e) {
         rel[e] = (unsigned)(cc[j][e] - start);
-        v[e] = aa[j][e] * kSplitScale;
+        v[e] = aa[j][e];
         mk[e] = __builtin_amdgcn_ballot_w64(at[j] < row_end[j][e]) & __builtin_amdgcn_ballot_w64(rel[e] < (unsigned)kDsS);
+        over |= mk[e] & __builtin_amdgcn_ballot_w64(__builtin_fabsf(v[e]) > limit[j]);
         unsigned mine = upper ? (unsigned)(mk[e] >> 32) : (unsigned)mk[e];
         mine = (mine >> shift16) & 0xffffu;
         asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(count) : "v"(mine), "v"(count));
@@ -314,6 +412,27 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       __builtin_amdgcn_sched_barrier(0);
       fetch(j);
       __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_expect(over != 0, 0)) {
+        // A row's scale comes from the largest entry of the stage that first has one, and falls where a later one is above its
+        // limit: the sums go down with it (row_shift).  Not in a further round of a stage, whose entries are in the block already: the
+        // row is gathered then (unless all before were zeros).
+        float largest = 0.f;
+#pragma unroll
+        for (int e = 0; e < NC; ++e)
+          if (__builtin_amdgcn_inverse_ballot_w64(mk[e])) largest = fmaxf(largest, __builtin_fabsf(v[e]));
+#pragma unroll
+        for (int d = 1; d < 16; d *= 2) largest = fmaxf(largest, __shfl_xor(largest, d, kWave));
+        const bool raise = largest > limit[j], fresh = limit[j] == 0.f;
+        const int to = raise ? scale_for(largest) : scale[j];
+        strays[j] |= __builtin_amdgcn_ballot_w64(raise && again && !fresh);
+        if (raise && !again && l16 == 0) {
+          row_shift[x * kDsRows + first_row + 4 * j + sub] = i32x2{q + 1, to - scale[j]};
+          shifted[x] = q + 1;
+        }
+        scale[j] = to;
+        if (raise) limit[j] = scale_limit(to);
+      }
+      const float times = __builtin_bit_cast(float, scale[j] << 23);
       // An ascending row's entry comes right after a smaller column of the same stage or is its first one.  (Rows with one that
       // does not: what was counted says nothing, they are gathered.)  Every entry of the stage is looked at, also behind a sixteen that has
       // none in any of the four rows: what is counted is written or gives its row away.  So `last` needs no look at where the row
@@ -336,28 +455,25 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
           unsigned d;                                                  // the next column: two bytes on, eight columns: a group
           asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(rel[e]), "s"(kDsGroup / 8), "v"(base));
           asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(rel[e] & 7u), "s"(2 - kDsGroup / 8), "v"(d));
-          typedef __attribute__((address_space(3))) unsigned short LdsHalf;
+          typedef __attribute__((address_space(3))) _Float16 LdsHalf;
           LdsHalf* const to = (LdsHalf*)(uintptr_t)d;
-          const unsigned x = term(v[e]);
-          const float rest = v[e] - __builtin_bit_cast(float, x);
-          const unsigned y = term(rest), z = __builtin_bit_cast(unsigned, rest - __builtin_bit_cast(float, y));      // (eight bits at most are left)
-          to[0] = (unsigned short)(x >> 16);
-          to[kDsPlane / 2] = (unsigned short)(y >> 16);
-          to[kDsPlane] = (unsigned short)(z >> 16);
+          const _Float16 y = (_Float16)(v[e] * times);
+          to[0] = y;
+          to[kDsPlane / 2] = (_Float16)(__builtin_fmaf(v[e], times, -(float)y) * kDsLow);
         }
       }
       const bool more = (mk[NC - 1] & (kFirst << 15)) != 0;
       if (more) last = (unsigned)__builtin_amdgcn_mov_dpp((int)rel[NC - 1], 0x121, 0xf, 0xf, true);
       return more;
     };
-    // (ahead of the multiplying waves, which have the MFMA to wait for: 30 %, 157 us -> 147; 42 %, 111 -> 96)
+    // (ahead of the multiplying waves, which have the MFMA to wait for)
     __builtin_amdgcn_s_setprio(1);
     auto fill = [&](int q, int x) __attribute__((always_inline)) {
       char* block = lds_raw + x * kDsBuf;
 #pragma unroll
       for (int j = 0; j < NR; ++j)
-        if (round(j, block, q * kDsS, false))
-          while (round(j, block, q * kDsS, true)) {}
+        if (round(j, block, q, x, false))
+          while (round(j, block, q, x, true)) {}
     };
 #pragma unroll
     for (int j = 0; j < NR; ++j) fetch(j);
@@ -379,8 +495,10 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       const unsigned long long mine = 0xffffull << (16 * sub);
       const int local = first_row + 4 * j + sub, row = min(i0 + local, m);
       const int entries = row_offsets[min(row + 1, m)] - row_offsets[row];
-      if (l16 == 0)
+      if (l16 == 0) {
         redo[local] = at[j] != row_end[j][0] || (strays[j] & mine) != 0 || (entries > 0 && entries < spmm_split_entries(k));
+        row_scale[local] = 127 - scale[j];
+      }
     }
   }
   clocks.lap(kPhaseRest);
@@ -400,7 +518,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
   bool failed = redo[local] != 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    v[t] *= kSplitUnscale;
+    v[t] = __builtin_ldexpf(v[t], row_scale[local]);
     failed |= split_failed(v[t]);
   }
   failed &= count > 0;
