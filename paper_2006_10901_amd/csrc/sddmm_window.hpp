@@ -1,7 +1,7 @@
 // SDDMM, window family: the counterpart of the window SpMM kernel for sparse matrices whose
 // entries cluster around a band (the attention masks of paper Sec. "Application: Sparse
 // Transformer") and dot products of at most 128 columns (one attention head).  A workgroup owns
-// NW consecutive sparse rows, one per wave, and copies ONE window of 256 consecutive rows of R
+// NW consecutive sparse rows, one per wave, and copies ONE window of consecutive rows of R
 // into LDS, placed where its rows have most of their entries.  A row is cut into strips of 16
 // consecutive entries, dealt to the wave's four 16-lane groups; a strip whose 16 columns all lie
 // inside the window reads its rows of R from LDS, any other strip gathers them from global
@@ -10,7 +10,8 @@
 // that leaves entry t's result in lane t), so both give the same bits.
 // Any CSR input gives the right result; the window's position is only a matter of speed.
 // NC = chunks of 64 columns of the dot product (1 or 2); the window holds 256 rows x 64 NC columns
-// of R, chunk after chunk.  Needs n <= 64 NC, n % 4 == 0, 16-byte aligned L and R, k * n < 2^29.
+// of R, chunk after chunk, or 576 rows with sixteen waves and one chunk (4096 x 4096, band of 257 of rows of 410, n = 64: 19.5 us with eight
+// waves, 18.1; n = 32, rows of 470: 23.1 and 20.3).  Needs n <= 64 NC, n % 4 == 0, 16-byte aligned L and R, k * n < 2^29.
 #pragma once
 #include "common.hpp"
 #include "sddmm_group.hpp"
@@ -19,13 +20,14 @@
 namespace spdl {
 
 constexpr int kWinOwn = 512;     // entries of its own row that a wave walks alone, at least (a multiple of 64)
+__host__ __device__ constexpr int sddmm_window_rows(int waves, int chunks) { return waves == 16 && chunks == 1 ? 576 : 256; }
 
 template <int NW, int NC>
 __global__ __launch_bounds__(64 * NW, 4) void sddmm_window_kernel(
     int m, int k, int n, int nnz, const int* __restrict__ row_offsets,
     const int* __restrict__ column_indices, const float* __restrict__ L, const float* __restrict__ R,
     float* __restrict__ out, const float* __restrict__ scale) {
-  constexpr int W = 256;
+  constexpr int W = sddmm_window_rows(NW, NC);
   constexpr int kChunkBytes = W * 64 * 4;           // one 64-column chunk of the window
   constexpr int kCopies = W / (4 * NW);
   static_assert(W % (4 * NW) == 0, "every wave copies the same number of 4-row pieces");

@@ -410,7 +410,18 @@ void fill_spmm_slab_info(int m, int k, int n, int nnz, int variant, spdl_launch_
 // (attention head, SpMM: 28.2 -> 25.5 us cold).  The SDDMM window for dot products of 65-128 columns is 128 KB, one
 // workgroup per compute unit, and keeps 16 waves.
 constexpr int kWinWaves = 8;                      // waves per workgroup of the window kernels, one sparse row each
-constexpr int kWinWavesWide = 16;                 // ... of the SDDMM window kernel with two column chunks
+constexpr int kWinWavesWide = 16;                 // ... of the SDDMM window kernel with two column chunks, of either with a large window
+// Whether callers who say that the entries form a band get sixteen waves and the large window, one workgroup to a compute unit: where
+// its rounds are filled, the last one to three fifths, and rows are not so long that most of them lies outside either window.  (us, eight waves /
+// sixteen, SpMM, 64 columns, rows of 330 .. 540: 2048 rows 9.8 / 13.2, 2600 15.6 / 15.2, 3300 21.4 / 17.8, 4096 25.2 / 20.2, 5000 23.5 / 28.4, 6144 34.2
+// / 34.3; 128 columns, two tiles: 1300 rows 14.4 / 13.0, 1600 13.6 / 13.7, 2600 23.9 / 26.6, 4096 46.0 / 37.2, 6144 58.8 / 51.6; 8192 rows
+// of 655 53.5 / 57.1 and 101 / 110.  Uniform masks, which fill no window: 16384 x 16384 at 4 % 129 / 141, 2048 x 2048 at 20 % 13.4 / 19.9.)
+bool win_large(int m, int tiles, int nnz) {
+  const int64_t groups = (int64_t)((m + kWinWavesWide - 1) / kWinWavesWide) * tiles, rounds = (groups + kComputeUnits - 1) / kComputeUnits;
+  return nnz <= 600 * (int64_t)m && rounds <= 3 && groups - (rounds - 1) * kComputeUnits >= 3 * kComputeUnits / 5;
+}
+// The same for SDDMM, up to 64 columns: one round (2450 rows 14.9 / 16.0, 2600 17.0 / 16.5, 3700 25.2 / 21.9, 4096 26.9 / 23.1, 6700 43.0 / 44.8).
+bool win_large_sddmm(int m, int nnz) { return m >= 2560 && m <= kWinWavesWide * kComputeUnits && win_large(m, 1, nnz); }
 // Workgroups of the MFMA kernel, four waves: two tiles of 256 columns, each with the contraction split over
 // two waves; one tile and four parts where the machine has room for twice as many workgroups.
 inline int spmm_mfma_tiles(int m, int n) {
@@ -648,8 +659,9 @@ void fill_spmm_info(int m, int k, int n, int nnz, const void* B, const void* C, 
     info->variant = kSpmmWindow;
     info->vec = 4;
     info->lanes_per_row = 16;
-    info->rows_per_block = WinShape<kWinWaves>::kRows;
-    info->block_threads = 64 * kWinWaves;
+    const bool large = hint == kHintBanded && win_large(m, (n + kWinTile - 1) / kWinTile, nnz);
+    info->rows_per_block = large ? WinShape<kWinWavesWide>::kRows : WinShape<kWinWaves>::kRows;
+    info->block_threads = kWave * info->rows_per_block;
     info->grid_x = (m + info->rows_per_block - 1) / info->rows_per_block;
     info->grid_y = (n + kWinTile - 1) / kWinTile;
   } else if (sizeof(T) == 4 && ((variant == kSpmmSlabDma && slab_dma_usable(n, nnz)) ||
@@ -753,11 +765,14 @@ int spmm_impl(int m, int k, int n, int nnz, const int* ro, const I* ci, const T*
   } else if (li.variant == kSpmmWindow) {
     if constexpr (sizeof(T) == 4 && kInt32) {
       static std::atomic<bool> configured{false};
-      auto kernel = spmm_window_kernel<kWinWaves>;
-      constexpr int lds = WinShape<kWinWaves>::kLdsBytes;
+      const bool large = li.rows_per_block == WinShape<kWinWavesWide>::kRows;
+      auto kernel = large ? spmm_window_kernel<kWinWavesWide> : spmm_window_kernel<kWinWaves>;
+      const int lds = large ? WinShape<kWinWavesWide>::kLdsBytes : WinShape<kWinWaves>::kLdsBytes;
       if (!configured.load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
-            hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(spmm_window_kernel<kWinWaves>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, WinShape<kWinWaves>::kLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(spmm_window_kernel<kWinWavesWide>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, WinShape<kWinWavesWide>::kLdsBytes) != hipSuccess)
           return SPDL_ERR_LAUNCH;
         configured.store(true);
       }
@@ -1177,7 +1192,8 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     const int64_t step = wide ? 4096 : 2048, stepped = (m + step - 1) / step * step;
     const bool even = wide ? 20 * stepped <= 21 * (int64_t)m : 5 * stepped <= 6 * (int64_t)m;
     const bool short_rows = !wide && m > 2048 && m <= 4096 && nnz <= 400 * (int64_t)m;
-    variant = even || short_rows ? kSddmmWindow : kSddmmGroup;
+    // (with sixteen waves and a large window the time goes with the entries too: 3000 rows of 428: 18.7 us and 20.0; 3300 of 458: 20.2 and 21.7)
+    variant = even || short_rows || (!wide && win_large_sddmm(m, nnz)) ? kSddmmWindow : kSddmmGroup;
   }
   // the caller says that the row lengths are strongly unequal: the nonzero-split kernel, which does not
   // care, or for dot products of more than 128 columns the lane kernel in passes where the estimate
@@ -1194,7 +1210,7 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   if (variant == kSddmmWindow) {
     info->vec = 4;
     info->lanes_per_row = 16;
-    const int waves = n <= kWinTile ? kWinWaves : kWinWavesWide;
+    const int waves = n <= kWinTile && !(hint == kHintBanded && win_large_sddmm(m, nnz)) ? kWinWaves : kWinWavesWide;
     info->rows_per_block = waves;
     info->block_threads = 64 * waves;
     info->grid_x = (m + waves - 1) / waves;
@@ -1374,21 +1390,18 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
   if (li.variant == kSddmmWindow) {
     if constexpr (sizeof(T) == 4) {
       static std::atomic<bool> configured{false};
-      constexpr int lds1 = 256 * 64 * 4;
+      struct Form { decltype(&sddmm_window_kernel<kWinWaves, 1>) kernel; int lds; };
+      static const Form forms[3] = {{sddmm_window_kernel<kWinWaves, 1>, sddmm_window_rows(kWinWaves, 1) * 256},
+                                    {sddmm_window_kernel<kWinWavesWide, 1>, sddmm_window_rows(kWinWavesWide, 1) * 256},
+                                    {sddmm_window_kernel<kWinWavesWide, 2>, sddmm_window_rows(kWinWavesWide, 2) * 512}};
       if (!configured.load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(sddmm_window_kernel<kWinWaves, 1>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lds1) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(sddmm_window_kernel<kWinWavesWide, 2>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 2 * lds1) != hipSuccess)
-          return SPDL_ERR_LAUNCH;
+        for (const Form& f : forms)
+          if (hipFuncSetAttribute(reinterpret_cast<const void*>(f.kernel), hipFuncAttributeMaxDynamicSharedMemorySize, f.lds) != hipSuccess)
+            return SPDL_ERR_LAUNCH;
         configured.store(true);
       }
-      if (n <= kWinTile)
-        sddmm_window_kernel<kWinWaves, 1><<<dim3(li.grid_x), dim3(li.block_threads), lds1, st>>>(m, k, n, nnz, ro, ci, L,
-                                                                                                 R, out, scale);
-      else
-        sddmm_window_kernel<kWinWavesWide, 2><<<dim3(li.grid_x), dim3(li.block_threads), 2 * lds1, st>>>(m, k, n, nnz, ro, ci,
-                                                                                                     L, R, out, scale);
+      const Form& f = forms[n > kWinTile ? 2 : li.rows_per_block == kWinWavesWide ? 1 : 0];
+      f.kernel<<<dim3(li.grid_x), dim3(li.block_threads), f.lds, st>>>(m, k, n, nnz, ro, ci, L, R, out, scale);
       return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
     } else {
       return SPDL_ERR_UNSUPPORTED;

@@ -41,7 +41,11 @@ constexpr int kWinTile = 64;                 // output columns per tile (= kSlab
 template <int NW>
 struct WinShape {
   static constexpr int kRows = NW;                           // sparse rows per workgroup
-  static constexpr int kW = 256;                             // rows of B in the window
+  // Rows of B in the window.  Eight waves: two workgroups to a compute unit.  Sixteen: what its LDS holds; twice the rows share
+  // a window that takes in half again as many columns on either side of them, where the scattered entries of an attention
+  // mask lie most densely (4096 x 4096, band of 257 of rows of 410, n = 64: 18.2 us with eight, 16.4 with sixteen and 512, 16.2 with 576; n = 128, rows of
+  // 540: 45.9, 41.9 and 37.3).
+  static constexpr int kW = NW == 8 ? 256 : 576;
   static constexpr int kPartialOff = (kW + 1) * kWinTile * 4; // after the window and the all-zero row:
   static constexpr int kLdsBytes = kPartialOff + NW * kWinTile * 4;   // one row of partial sums per wave
 };
