@@ -1,6 +1,6 @@
 // Single-precision products on the bf16 matrix cores: a number as the sum of three bf16 terms.
 #pragma once
-#include "common.hpp"
+#include "f16_split.hpp"
 
 namespace spdl {
 
@@ -44,7 +44,6 @@ __device__ __forceinline__ Split8 split8(const float (&v)[8]) {
   return {__builtin_bit_cast(bf16x8, high), __builtin_bit_cast(bf16x8, mid), __builtin_bit_cast(bf16x8, low)};
 }
 
-typedef float acc32x32 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ acc32x32 mfma_bf16(bf16x8 a, bf16x8 b, acc32x32 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -56,7 +55,5 @@ __device__ __forceinline__ float split_lane_dot(const float* __restrict__ l, con
   for (int j = 0; j < n; ++j) acc = __builtin_fmaf(l[j], r[j], acc);
   return acc;
 }
-
-__device__ __forceinline__ bool split_failed(float v) { return !(__builtin_fabsf(v) < __builtin_inff()); }
 
 }  // namespace spdl

@@ -1,0 +1,40 @@
+// Single-precision products on the fp16 matrix cores: a number, taken times a power of two, as the sum of two fp16 terms.
+#pragma once
+#include "common.hpp"
+
+namespace spdl {
+
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef float acc32x32 __attribute__((ext_vector_type(16)));
+
+// Powers of two, as exponents of fp32 (127: one), that bring the largest number of a row or a column to 2^10 .. 2^11; the
+// number from which on another one is needed, 2^15 after scaling.  (Numbers from 2^123 on, infinities: the smallest one, whose limit is infinity.
+// Nothing seen yet: kNoScale, with limit 0.)
+constexpr int kNoScale = 254;
+constexpr float kLowScale = 2048.f;      // the low terms are taken times this: as far from fp16's smallest exponent as the high ones
+__device__ __forceinline__ int scale_for(float largest) {
+  return max(14, min(254, 264 - (int)(__builtin_bit_cast(unsigned, largest) >> 23)));
+}
+__device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_cast(float, (269 - scale) << 23); }
+
+// Two numbers times `times`: the high terms, and what is left of them, times kLowScale, as the low ones.
+__device__ __forceinline__ void split_f16(float x0, float x1, float times, f16x2& high, f16x2& low) {
+  high = __builtin_convertvector((f32x2{x0 * times, x1 * times}), f16x2);
+  const f32x2 rest = {__builtin_fmaf(x0, times, -(float)high[0]), __builtin_fmaf(x1, times, -(float)high[1])};
+  low = __builtin_convertvector((f32x2{rest[0] * kLowScale, rest[1] * kLowScale}), f16x2);
+}
+
+__device__ __forceinline__ acc32x32 mfma_f16(f16x8 a, f16x8 b, acc32x32 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// The larger of a lane's number and that of the lane 32 on, in both.
+__device__ __forceinline__ float max_of_halves(float x) {
+  const u32x2 both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, both[0]), __builtin_bit_cast(float, both[1]));
+}
+
+__device__ __forceinline__ bool split_failed(float v) { return !(__builtin_fabsf(v) < __builtin_inff()); }
+
+}  // namespace spdl

@@ -29,6 +29,7 @@
 #include "spmm_split.hpp"
 #include "sddmm_window.hpp"
 #include "sddmm_split.hpp"
+#include "sddmm_long.hpp"
 
 namespace {
 
@@ -1014,6 +1015,51 @@ bool sddmm_split_runs(int variant, int m, int k, int n, int nnz) {
   return sddmm_split_estimate(m, k, n, nnz) <= 0.97 * other;
 }
 
+// Dense matrices, long dot products: whether whole blocks on the matrix cores take the place of the slab kernel.  From 576 columns
+// on, where the slab kernel's sums of so many terms are the less accurate ones (2-norm error against 64 bits, normal data:
+// at 512 columns 1.16e-7 against 1.18e-7, at 640 1.27e-7 and 1.19e-7, at 4096 2.9e-7 and 1.5e-7; the lane kernel, 1.0e-7, stays).
+// Estimates in microseconds.  The blocks: rounds of one workgroup per compute unit, each of so many chunks, which take longer on
+// a full machine (it is slowed down to its power), and entries to pick.  The slab kernel: slabs and, per 128 columns of the dot product,
+// strips of sixteen entries of the fullest rows, of which the third does not fit its registers.  Fitted on 196 uniform shapes
+// (128 .. 6000 rows and columns, 3 .. 35 %, 576 .. 4500 columns), 4 % and 8 % off; the choice takes 1.005 times the faster one's
+// time on average, never more than 1.02 times the slab kernel's, and 0.84 times it on average.  (Matrices that are not uniform gain
+// more: 2048^2, a band of 12 %, n = 1024: 382 us and 47; log-normal rows, 2048 x 1024 at 10 %: 100 and 37.)
+inline double normal_below(double x) { return 0.5 * std::erfc(-x * 0.70710678); }
+bool sddmm_long_runs(int variant, int m, int k, int n, int nnz) {
+  if (variant != kSddmmSlabDma || n < 576 || n >= (1 << 21) || m < 128 || k < 128 || nnz <= 0 || nnz >= (1 << 29)) return false;
+  const double density = (double)nnz / ((double)m * (double)k);
+  const int blocks_m = (m + kLgRows - 1) / kLgRows, blocks_k = (k + kLgCols - 1) / kLgCols;
+  const double rounds = k > m ? split_chain(blocks_k, blocks_m, -1) : split_chain(blocks_m, blocks_k, -1);
+  const double fill = std::min(1.0, (double)blocks_m * blocks_k / kComputeUnits);
+  const double entries = 1e-3 * kLgRows * std::min(k, kLgCols) * density;
+  const double blocks = 0.3 + rounds * (10.3 + (n + kLgChunk - 1) / kLgChunk * (2.63 + 0.77 * fill) + 0.3 * entries);
+  const SddmmSlabShape sh = sddmm_slab_shape(m, k, n);
+  const double mean = std::min(k, sh.S) * density, sd = std::sqrt(mean * std::max(1e-9, 1.0 - density));
+  auto filled = [&](int strips) { return normal_below((mean - 16.0 * strips - 0.5) / sd + 2.5); };
+  const double slab_rounds = split_chain(sh.panels, sh.ksplit, -1);
+  const double slab_fill = (double)sh.panels * sh.ksplit / (kComputeUnits * slab_rounds);
+  const double slabs = 0.2 + slab_rounds * (6.0 + sh.spp * (0.8 + n / 128.0 * (1.36 + 0.62 * filled(1) + 3.38 * filled(2) + 3.82 * filled(3)) *
+                                                            (1.0 + 0.21 * slab_fill)));
+  return blocks <= 0.95 * slabs;
+}
+
+// The workgroups of a panel share an XCD and with it their rows of L, or those of a range of columns their rows of R: whichever of the two
+// the XCDs would otherwise all read is the shorter.  (1024 x 4096, n = 2048, at 20 %: 71.4 us and 70.6; 4096 x 1024: 69.0 and 72.0.)
+int launch_sddmm_long(int m, int k, int n, int nnz, const int* ro, const int* ci, const float* L, const float* R, float* out,
+                      const float* scale, hipStream_t st) {
+  static std::atomic<bool> configured;
+  if (!configured.load()) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sddmm_long_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLgLdsBytes) !=
+        hipSuccess)
+      return SPDL_ERR_LAUNCH;
+    configured.store(true);
+  }
+  const int panels = (m + kLgRows - 1) / kLgRows, parts = (k + kLgCols - 1) / kLgCols;
+  sddmm_long_kernel<<<dim3(slab_grid_size(panels, parts)), dim3(kLgThreads), kLgLdsBytes, st>>>(m, k, n, nnz, panels, parts, k > m, ro, ci, L, R,
+                                                                                                out, scale);
+  return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
+}
+
 // Which workgroups of sddmm_slab_dma_kernel share an XCD: those of a panel, which read the same rows of L, or those of a
 // range of A's columns, which read the same rows of R.  Up to 1024 rows and a longer R (which every XCD would otherwise read
 // whole: 1024 x 4096, n = 4096: 575 MB from behind the L2s, now 356) the latter.  us, a launch repeated, which finds R in the Infinity
@@ -1216,6 +1262,15 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
     info->grid_x = (m + waves - 1) / waves;
     return;
   }
+  if (sizeof(T) == 4 && sddmm_long_runs(variant, m, k, n, nnz)) {
+    info->vec = 4;
+    info->lanes_per_row = kWave;
+    info->rows_per_block = kLgRows;
+    info->block_threads = kLgThreads;
+    info->grid_x = slab_grid_size((m + kLgRows - 1) / kLgRows, (k + kLgCols - 1) / kLgCols);
+    info->grid_y = (k + kLgCols - 1) / kLgCols;     // column ranges of A (the grid is 1-D)
+    return;
+  }
   if (sizeof(T) == 4 && sddmm_split_runs(variant, m, k, n, nnz)) {
     const SddmmSplitShape sh = sddmm_split_shape(m, k, n, nnz);
     info->vec = 8;
@@ -1336,6 +1391,7 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     }
   }
   if constexpr (sizeof(T) == 4) {
+    if (sddmm_long_runs(li.variant, m, k, n, nnz)) return launch_sddmm_long(m, k, n, nnz, ro, ci, L, R, out, scale, st);
     if (sddmm_split_runs(li.variant, m, k, n, nnz)) {
       const SddmmSplitShape sh = sddmm_split_shape(m, k, n, nnz);
 #define SPDL_SPLIT(KSTEPS, AHEAD)               \

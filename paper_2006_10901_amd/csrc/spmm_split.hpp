@@ -32,7 +32,7 @@
 // same stage; a cursor short of the row's end) and gathered at the end (split_gather), as is what is not finite: a zero of the
 // block times an infinity of B must not reach the result.  (Sums from some 2^100 of B's numbers' on come out as infinities too, and are gathered.)
 #pragma once
-#include "bf16_split.hpp"
+#include "f16_split.hpp"
 
 namespace spdl {
 
@@ -50,17 +50,6 @@ constexpr int kDsRedoOff = kDsRingOff + kDsMulWaves * kDsRing * kDsChunk;
 constexpr int kDsScaleOff = kDsRedoOff + kDsRows * 4;
 constexpr int kDsShiftOff = kDsScaleOff + kDsRows * 4;
 constexpr int kDsLdsBytes = kDsShiftOff + 3 * kDsRows * 8 + 16;
-
-// Powers of two, as exponents of fp32 (127: one), that bring the largest number of a row or a column to 2^10 .. 2^11; the
-// number from which on another one is needed, 2^15 after scaling.  (Infinities: the smallest; nothing seen yet: kDsNoScale, with limit 0.)
-constexpr int kDsNoScale = 254;
-constexpr float kDsLow = 2048.f;                         // the low terms are taken times this, so that they are as far from fp16's smallest exponent as the high ones
-__device__ __forceinline__ int scale_for(float largest) {
-  return max(1, min(254, 264 - (int)(__builtin_bit_cast(unsigned, largest) >> 23)));
-}
-__device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_cast(float, min(255, 269 - scale) << 23); }
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x2 __attribute__((ext_vector_type(2)));
 
 // Lane i gets the place of the (i + 1)-th one of `set`.  (Lanes beyond the last one: those of the zeros.)
 __device__ __forceinline__ int nth_one(unsigned long long set) {
@@ -211,7 +200,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
       for (int e = 0; e < 8; ++e) raw[e] = *reinterpret_cast<const float*>(p + e * 256);
     };
-    int scale = kDsNoScale, shift = 0;                                 // of the lane's column: the exponent of the power of two it is taken times
+    int scale = kNoScale, shift = 0;                                 // of the lane's column: the exponent of the power of two it is taken times
     float limit = 0.f;
     unsigned long long raised = 0;
     struct Terms { f16x8 high, low; };
@@ -221,8 +210,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int e = 1; e < 8; ++e) largest = fmaxf(largest, __builtin_fabsf(raw[e]));
       raised = __builtin_amdgcn_ballot_w64(largest > limit);
       if (__builtin_expect(raised != 0, 0)) {
-        const u32x2 both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, largest), __builtin_bit_cast(unsigned, largest), false, false);
-        largest = fmaxf(__builtin_bit_cast(float, both[0]), __builtin_bit_cast(float, both[1]));      // (the column's other half)
+        largest = max_of_halves(largest);                              // (the column's other half)
         const int to = largest > limit ? scale_for(largest) : scale;
         shift = to - scale;
         scale = to;
@@ -232,9 +220,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       Terms t;
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
-        const f16x2 x = __builtin_convertvector((f32x2{raw[e] * times, raw[e + 1] * times}), f16x2);
-        const f32x2 rest = {__builtin_fmaf(raw[e], times, -(float)x[0]), __builtin_fmaf(raw[e + 1], times, -(float)x[1])};
-        const f16x2 y = __builtin_convertvector((f32x2{rest[0] * kDsLow, rest[1] * kDsLow}), f16x2);
+        f16x2 x, y;
+        split_f16(raw[e], raw[e + 1], times, x, y);
         t.high[e] = x[0]; t.high[e + 1] = x[1];
         t.low[e] = y[0]; t.low[e + 1] = y[1];
       }
@@ -253,8 +240,8 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
 #pragma unroll
       for (int x = 0; x < 16; ++x) sum[i][x] = rest[i][x] = 0.f;
     auto two = [&](acc32x32 (&to)[2], const f16x8 (&x)[2], const f16x8& y) __attribute__((always_inline)) {
-      to[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y, to[0], 0, 0, 0);
-      to[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y, to[1], 0, 0, 0);
+      to[0] = mfma_f16(x[0], y, to[0]);
+      to[1] = mfma_f16(x[1], y, to[1]);
     };
     // (chunk t is in slot t % kDsRing)
     unsigned slot = 0;
@@ -282,7 +269,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
     // with.  `last` of a stage: half of the products need nothing of the stage's block that is not in registers.
     auto step = [&](const char* next, bool last, int before, int q, int x) __attribute__((always_inline)) {
       const Terms c = split();
-      two(rest, low, b.low * (_Float16)(1.f / kDsLow));
+      two(rest, low, b.low * (_Float16)(1.f / kLowScale));
       two(rest, low, b.high);
       asm volatile("" :: "v"(c.high), "v"(c.low));
       bring_next(slot);
@@ -345,7 +332,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int t = 0; t < 16; ++t) {
         const int row = 32 * i + 8 * (t / 4) + 4 * h + t % 4;
         *reinterpret_cast<float*>(lds_raw + quarter * (kDsRows * kDsCols * 4) + row * (kDsCols * 4) + (half * 32 + r) * 4) =
-            __builtin_ldexpf(__builtin_fmaf(rest[i][t], 1.f / kDsLow, sum[i][t]), 127 - scale);
+            __builtin_ldexpf(__builtin_fmaf(rest[i][t], 1.f / kLowScale, sum[i][t]), 127 - scale);
       }
   } else {
     const int tail = k & ~15, tail_shift = tail == k ? 0 : 16 - (k & 15);
@@ -372,7 +359,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int e = 0; e < NC; ++e) row_end[j][e] = row_offsets[min(row + 1, m)] * 4 - 64 * e;
       row_base[j] = (unsigned)((local >> 5) * 512 + ((local & 31) << 4));
       strays[j] = 0;
-      scale[j] = kDsNoScale;
+      scale[j] = kNoScale;
       limit[j] = 0.f;
     }
     auto fetch = [&](int j) __attribute__((always_inline)) {
@@ -459,7 +446,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
           LdsHalf* const to = (LdsHalf*)(uintptr_t)d;
           const _Float16 y = (_Float16)(v[e] * times);
           to[0] = y;
-          to[kDsPlane / 2] = (_Float16)(__builtin_fmaf(v[e], times, -(float)y) * kDsLow);
+          to[kDsPlane / 2] = (_Float16)(__builtin_fmaf(v[e], times, -(float)y) * kLowScale);
         }
       }
       const bool more = (mk[NC - 1] & (kFirst << 15)) != 0;

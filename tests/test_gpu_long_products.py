@@ -1,0 +1,130 @@
+"""fp32 SDDMM of dense sparse matrices with long dot products: whole blocks on the fp16 matrix cores (two terms per number), against the oracle.
+Tolerance: the terms hold a number to 2^-23 of it, or 2^-46 of the largest one of its row of L or R; a product leaves out another 2^-22; the matrix
+cores cut sums off at 2^-23 in each of a chunk's eight steps, in two accumulators, and n / 128 chunks are added:
+(48 + n / 128) 2^-24 of the sum of absolute products."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from tests.test_gpu_split_products import mask_csr
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def g():
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.fixture(autouse=True)
+def force():
+    import paper_2006_10901_amd as spdl
+    spdl.spdl_force_variant(1, 3)
+    yield
+    spdl.spdl_force_variant(1, -1)
+
+
+def runs_long(A, n):
+    import paper_2006_10901_amd as spdl
+    info = spdl.spdl_select_sddmm(A.m, A.k, n, A.nnz, 4, 0, 0)
+    return info["block_threads"] == 768 and info["grid_y"] == (A.k + 255) // 256
+
+
+def bound(A, L, R, S):
+    n = L.shape[1]
+    rows = np.repeat(np.arange(A.m), np.diff(A.row_offsets))
+    l, r = np.abs(L.astype(np.float64)), np.abs(R.astype(np.float64))
+    floor = l.max(1)[rows] * r.sum(1)[A.column_indices] + l.sum(1)[rows] * r.max(1)[A.column_indices]
+    return (48 + n / 128) * 2.0 ** -24 * S + 2.0 ** -45 * floor + n * 2.0 ** -149
+
+
+# (rows around whole panels of 64, columns of A around whole blocks of 256 and waves of 32; dot products around whole sixteens, pieces of 32
+# and chunks of 128; both choices of what an XCD shares; short rows beside full ones)
+@pytest.mark.parametrize("m,k,density", [(128, 128, 0.8), (300, 513, 0.8), (321, 255, 0.6), (193, 700, 0.5), (520, 1057, 0.3)])
+@pytest.mark.parametrize("n", [576, 577, 608, 639, 640, 643, 1031])
+def test_long_products(g, oracle_lib, m, k, density, n):
+    A = mask_csr(m, k, density, 9400 + m + n)
+    L, R = wl.dense(m, n, 9401 + n), wl.dense(k, n, 9402 + n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_long(A, n)
+    got = g.gpu_sddmm(A, L, R, n)
+    assert np.all(np.abs(got - ref) <= bound(A, L, R, S))
+    assert np.linalg.norm(got - ref) <= 2e-7 * np.linalg.norm(ref)
+    assert np.array_equal(got, g.gpu_sddmm(A, L, R, n))
+
+
+@pytest.mark.parametrize("m,k,n", [(517, 700, 641), (2049, 1025, 1030)])
+def test_long_products_scaled_and_at_odd_addresses(g, oracle_lib, m, k, n):
+    import torch
+    import paper_2006_10901_amd as spdl
+    A = mask_csr(m, k, 0.35, 9500 + n)
+    L, R = wl.dense(m, n, 9501 + n), wl.dense(k, n, 9502 + n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_long(A, n)
+    d = g.DevCsr(A)
+    out = torch.full((A.nnz + 2,), float("nan"), device="cuda")
+    lpad, rpad = torch.full((m * n + 3,), float("nan"), device="cuda"), torch.full((k * n + 3,), float("nan"), device="cuda")
+    lpad[1:1 + m * n], rpad[2:2 + k * n] = g.dev(L).view(-1), g.dev(R).view(-1)
+    spdl.spdl_sddmm(m, k, n, A.nnz, d.ro, d.ci, lpad[1:1 + m * n].view(m, n), rpad[2:2 + k * n].view(k, n), out[1:-1])
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.isnan(got[0]) and np.isnan(got[-1])
+    assert np.all(np.abs(got[1:-1] - ref) <= bound(A, L, R, S))
+    spdl.spdl_sddmm_scaled(m, k, n, A.nnz, d.ro, d.ci, d.val, g.dev(L), g.dev(R), out[1:-1])
+    torch.cuda.synchronize()
+    v = A.values.astype(np.float64)
+    assert np.all(np.abs(out[1:-1].cpu().numpy() - v * ref) <= np.abs(v) * bound(A, L, R, S) + np.abs(v * ref) * 2.0 ** -24)
+
+
+def numbers(kind, m, k, n):
+    rng = np.random.default_rng(9600)
+    L, R = rng.standard_normal((m, n)).astype(np.float32), rng.standard_normal((k, n)).astype(np.float32)
+    at = np.arange(n) / n
+    if kind == "rows":
+        L *= np.exp2(rng.integers(-40, 41, m))[:, None].astype(np.float32)
+        R *= np.exp2(rng.integers(-40, 41, k))[:, None].astype(np.float32)
+    elif kind == "growing":                                # new powers of two every few chunks, of single rows and of all
+        L *= np.exp2(np.floor(np.array([0, 12, 40])[np.arange(m) % 3][:, None] * at)).astype(np.float32)
+        R *= np.exp2(np.floor(np.array([30, 7])[np.arange(k) % 2][:, None] * at)).astype(np.float32)
+    elif kind == "falling":
+        L *= np.exp2(-np.floor(20 * at)).astype(np.float32)
+        R *= np.exp2(-np.floor(20 * at)).astype(np.float32)
+    elif kind == "zeros first":
+        L[:, :n // 3] = 0
+        R[:, :n // 4] = 0
+        L[::5], R[::7] = 0, 0
+    elif kind == "spikes":
+        L[np.arange(m), rng.integers(0, n, m)] *= np.float32(2.0 ** 40)
+        R[np.arange(k), rng.integers(0, n, k)] *= np.float32(2.0 ** 30)
+    elif kind != "plain":
+        scale_l, scale_r = kind
+        L, R = L * np.float32(2.0 ** scale_l), R * np.float32(2.0 ** scale_r)
+    return L, R
+
+
+@pytest.mark.parametrize("kind", ["rows", "growing", "falling", "zeros first", "spikes", (-100, -20), (-126, 0), (-126, 100), (105, -90), (60, 50)])
+def test_long_products_of_any_magnitude(g, oracle_lib, kind):
+    m, k, n = 321, 513, 1100
+    A = mask_csr(m, k, 0.5, 9601)
+    L, R = numbers(kind, m, k, n)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_long(A, n)
+    got = g.gpu_sddmm(A, L, R, n)
+    assert np.all(np.isfinite(got)) and np.all(np.abs(got - ref) <= bound(A, L, R, S))
+
+
+def test_long_products_keep_non_finite_values(g, oracle_lib):
+    """Infinities and NaN reach the entries that depend on them and no others."""
+    m, k, n = 321, 513, 647
+    A = mask_csr(m, k, 0.6, 9700)
+    L, R = wl.dense(m, n, 9701), wl.dense(k, n, 9702)
+    assert runs_long(A, n)
+    L[3, 1], L[200, n - 1], R[100, 0], R[400, 2], R[512, n - 1] = np.inf, np.nan, -np.inf, np.nan, np.float32(3e38)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    got = g.gpu_sddmm(A, L, R, n).astype(np.float64)
+    inside = np.abs(ref) < 1e38
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < A.nnz // 20
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.all(np.abs(got[inside] - ref[inside]) <= (n + 8) * 2.0 ** -24 * S[inside])
