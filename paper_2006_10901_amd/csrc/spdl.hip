@@ -435,15 +435,16 @@ inline int spmm_mfma_tiles(int m, int n) {
 // measured rates on shapes from 1024 x 1024 x 3136 to 8192 x 10240 x 128).  The matrix-core kernels
 // do work proportional to m*k whatever the density, in rounds of one workgroup per CU: a panel of
 // 32 rows x 512 columns costs about 5.2 us plus 13 ns per column of A, x 256 columns 8.3 ns per column, 4 ns more
-// where half of B's rows start at odd addresses (SpMM), a 64 x 64 block
-// 3.3 us plus 0.44 us per 128 columns of the dot product and 0.75 us for columns that fill no piece of eight
-// (SDDMM); filling a panel adds 0.5 ns per entry of its 32 rows, sampling the blocks 10.5 us per million
+// where half of B's rows start at odd addresses (SpMM), a block
+// 3.3 us plus what its stages take, 128 columns of the dot product for 64 x 64, 256 for smaller ones, and 0.3 us for columns that fill no piece
+// of eight (SDDMM); filling a panel adds 0.5 ns per entry of its 32 rows, sampling the blocks 13.4 us per million
 // entries.  The direct kernels run at the rate of their gathers: 21 TFLOP/s, 10 for rows at odd addresses,
 // plus 8 ns per entry of a row and 512 columns (SpMM); 14 TFLOP/s for short dot products, 12 beyond 128 columns,
 // after a latency floor of 1.5 us per 64 columns of the dot product (SDDMM).  (SpMM's rates were fitted on
 // 160 random shapes, two thirds of them 256 .. 1024 rows and columns, n = 49 .. 3584, the others up to 8192 rows
-// and columns, 1 .. 40 % density: the choice then takes 1.017 times the faster one's time on average; SDDMM's on 60,
-// 256 .. 8192 rows and columns, 1 .. 40 %, n = 24 .. 3136, half of them odd; both families forced.)
+// and columns, 1 .. 40 % density: the choice then takes 1.017 times the faster one's time on average; SDDMM's on 260,
+// three quarters of them 256 .. 1024 rows and columns, n = 48 .. 3584, the others up to 6000: 7 % off for the blocks, the choice takes 1.002 times
+// the faster one's time; both families forced.)
 inline bool spmm_mfma_pays(int m, int k, int n, int nnz) {
   const int tiles = spmm_mfma_tiles(m, n);
   const double wgs = (double)((m + 31) / 32) * (double)(((n + 255) / 256 + tiles - 1) / tiles);
@@ -475,10 +476,38 @@ int sddmm_group_short_strips(int m, int n, int nnz, int elem_bytes) {
   return nnz <= 400000 && (short_rows || (n > 64 && n <= 128)) ? 32 : 0;
 }
 
+// Blocks of the matrix-core kernel: 64 x 64, or smaller ones where those give every compute unit no more than one.  (A workgroup's time is its
+// stages': us, 64 x 64 / 64 x 32 / 32 x 32: 304 x 744, n = 2880, 60 blocks of 64 x 64 and 240 of 32 x 32, 13.0 / 11.6 / 9.8; 557 x 395, n = 1764, 10.7 / 8.8
+// / 8.0; 894 x 407, n = 2544, 98 and 364, 15.5 / 12.7 / 18.4; 860 x 590, n = 1392, 140 and 266 of 64 x 32, 8.8 / 14.3 / 17.0.)
+struct SddmmMfmaShape { int rows, cols; };
+SddmmMfmaShape sddmm_mfma_shape(int m, int k) {
+  const int64_t r32 = (m + 31) / 32, r64 = (m + 63) / 64, c32 = (k + 31) / 32;
+  if (r32 * c32 <= kComputeUnits) return {32, 32};
+  if (r64 * c32 <= kComputeUnits) return {64, 32};
+  return {64, 64};
+}
+
+template <bool ODD, int BM, int BN, int P>
+int launch_sddmm_mfma(int grid, int tiles_k, int m, int k, int n, const int* ro, const int* ci, const _Float16* L, const _Float16* R,
+                      _Float16* out, const _Float16* scale, hipStream_t st) {
+  static std::atomic<bool> configured;
+  constexpr int lds = SmBlock<BM, BN, P>::kLdsBytes;
+  auto kernel = sddmm_mfma_kernel<ODD, BM, BN, P>;
+  if (!configured.load()) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+      return SPDL_ERR_LAUNCH;
+    configured.store(true);
+  }
+  kernel<<<dim3(grid), dim3(kSmThreads), lds, st>>>(m, k, n, tiles_k, ro, ci, L, R, out, scale);
+  return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
+}
+
 inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
-  const double blocks = (double)((m + 63) / 64) * (double)((k + 63) / 64);
-  const double t_mfma = 1.0 + std::ceil(blocks / kComputeUnits) *
-                                  (3.3 + 0.44 * (double)((n + 127) / 128) + (n % 8 != 0 ? 0.75 : 0.0)) + 10.5e-6 * (double)nnz;
+  const SddmmMfmaShape sh = sddmm_mfma_shape(m, k);
+  const double rounds = std::ceil((double)((m + sh.rows - 1) / sh.rows) * (double)((k + sh.cols - 1) / sh.cols) / kComputeUnits);
+  const int columns = sh.cols == 64 ? 128 : 256;                     // per stage
+  const double stage = (sh.rows == 32 ? 0.41 : sh.cols == 32 ? 0.61 : 0.44) * (n % 2 != 0 ? 1.1 : 1.0);
+  const double t_mfma = 0.95 + rounds * (3.25 + stage * (double)((n + columns - 1) / columns) + (n % 8 != 0 ? 0.28 : 0.0)) + 13.4e-6 * (double)nnz;
   double t_direct = 5.0 + 1.5 * (double)(n / 64) + 2.0 * (double)nnz * (double)n / ((n <= 128 ? 14.0 : 12.0) * 1e6);
   // (strips of four, a round of 128 columns at a time, the fewer of the four in use the shorter the rows: fitted on 100 random shapes of up
   // to 100 thousand entries, 65 .. 2000 columns, 12 % off; the choice takes 1.001 times the faster one's time, 1.12 with the line above)
@@ -486,7 +515,7 @@ inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
     const double rounds = (double)((n + 127) / 128), row = (double)nnz / (double)std::max(m, 1);
     t_direct = 3.1 + rounds * (0.36 + 0.34 * std::max(1.0, 4.0 / std::max(row, 1e-3))) + 2.33e-7 * (double)nnz * (double)n;
   }
-  return t_mfma <= t_direct;
+  return t_mfma <= 1.05 * t_direct;
 }
 
 // The matrix-core SpMM keeps rows of B in registers whose loads are still in flight (explicit
@@ -1088,14 +1117,14 @@ void fill_sddmm_info(int m, int k, int n, int nnz, const void* L, const void* R,
   if (variant == kSddmmMfma && !mfma_ok) variant = kSddmmGroup;
   if (variant < 0 && mfma_ok && sddmm_mfma_pays(m, k, n, nnz)) variant = kSddmmMfma;
   if (variant == kSddmmMfma) {
-    const int64_t tiles = (int64_t)((m + 63) / 64) * ((k + 63) / 64);
     info->variant = kSddmmMfma;
     info->vec = 8;
     info->lanes_per_row = kWave;
-    info->rows_per_block = 64;
+    const SddmmMfmaShape sh = sddmm_mfma_shape(m, k);
+    info->rows_per_block = sh.rows;
     info->block_threads = kSmThreads;
-    info->grid_x = sddmm_mfma_grid((m + 63) / 64, (k + 63) / 64);
-    info->grid_y = (k + 63) / 64;               // 64-column blocks per panel (the grid is 1-D)
+    info->grid_x = sddmm_mfma_grid((m + sh.rows - 1) / sh.rows, (k + sh.cols - 1) / sh.cols);
+    info->grid_y = (k + sh.cols - 1) / sh.cols;     // blocks per panel (the grid is 1-D)
     return;
   }
   bool skewed_lane = false;      // (for the hint of unequal rows) lane kernel estimated faster than the nonzero-split one
@@ -1376,16 +1405,14 @@ int sddmm_impl(int m, int k, int n, int nnz, const int* ro, const int* ci, const
     if constexpr (sizeof(T) == 2) {
       // copies start at multiples of four bytes: every row's first element, or every other row's
       const bool odd = n % 2 != 0 || !aligned(L, 4) || !aligned(R, 4);
-      const auto kernel = odd ? sddmm_mfma_kernel<true> : sddmm_mfma_kernel<false>;
-      static std::atomic<bool> configured[2];
-      if (!configured[odd].load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kSddmmMfmaLdsBytes) != hipSuccess)
-          return SPDL_ERR_LAUNCH;
-        configured[odd].store(true);
-      }
-      kernel<<<dim3(li.grid_x), dim3(kSmThreads), kSddmmMfmaLdsBytes, st>>>(m, k, n, li.grid_y, ro, ci, L, R, out, scale);
-      return hipGetLastError() == hipSuccess ? SPDL_OK : SPDL_ERR_LAUNCH;
+      const SddmmMfmaShape sh = sddmm_mfma_shape(m, k);
+#define SPDL_MFMA_SDDMM(BM, BN, P)                                                                                         \
+  if (sh.rows == BM && sh.cols == BN)                                                                                      \
+    return odd ? launch_sddmm_mfma<true, BM, BN, P>(li.grid_x, li.grid_y, m, k, n, ro, ci, L, R, out, scale, st)           \
+               : launch_sddmm_mfma<false, BM, BN, P>(li.grid_x, li.grid_y, m, k, n, ro, ci, L, R, out, scale, st);
+      SPDL_MFMA_SDDMM(64, 64, 16) SPDL_MFMA_SDDMM(64, 32, 32) SPDL_MFMA_SDDMM(32, 32, 32)
+#undef SPDL_MFMA_SDDMM
+      return SPDL_ERR_UNSUPPORTED;
     } else {
       return SPDL_ERR_UNSUPPORTED;
     }
