@@ -96,10 +96,19 @@ __global__ __launch_bounds__(256) void csr_softmax_kernel(int m, const int* __re
 
 // out[t] = values[perm[t]]: moves the values of A into the order of A^T's entries (paper Sec.
 // "Discussion & Conclusion": the transpose of the values as a cached permutation).
+//
+// Neighbouring entries of A^T lie in one column of A, their values in as many lines of memory, each of which holds the row's next columns
+// as well.  Bound by how often those lines are fetched: workgroups dealt to the XCDs in turn fetch every line into all eight L2s, so
+// an XCD gets a run of the workgroups.  (us in a graph, before -> now: 330 thousand entries 3.7 -> 3.0, 420 thousand 4.8 -> 3.3, 840 thousand 8.0 -> 5.4, 3
+// million 21.5 -> 17.5, 6 million 39.7 -> 31.3; below 300 thousand the same; 8.4 million 58.7 -> 62.5, so those in turn as before.  Two, four and
+// eight entries per thread: 5.3, 6.1 and 7.3 at 420 thousand.)
+constexpr unsigned kPermuteRuns = 6000128 / 256;       // workgroups, up to which an XCD gets a run of them
 template <typename T>
 __global__ __launch_bounds__(256) void permute_values_kernel(int nnz, const int* __restrict__ perm,
                                                              const T* __restrict__ values, T* __restrict__ out) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
+  const unsigned groups = gridDim.x, id = blockIdx.x, xcd = id & 7;
+  const unsigned group = groups <= kPermuteRuns ? xcd * (groups >> 3) + min(xcd, groups & 7) + (id >> 3) : id;
+  const int t = (int)(group * 256) + threadIdx.x;
   if (t < nnz) out[t] = values[perm[t]];
 }
 
