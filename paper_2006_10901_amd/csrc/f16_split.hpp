@@ -18,6 +18,14 @@ __device__ __forceinline__ int scale_for(float largest) {
 }
 __device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_cast(float, (269 - scale) << 23); }
 
+// What a power of two of a whole row or column costs: a scaled number below 2^-13 is held to 2^-36, not to 2^-23 of itself, so that a product may be
+// off by 2^-21 (2^-36 times 2^15; half as much again where low low is left out), however small it is.  The largest number need not be one that
+// the sum has a use for: it may be multiplied by a zero.  A scaled sum of `count` products is therefore taken only if it is no smaller than
+// this: what is lost is then no more than sqrt(count) 2^-24 of the sum of absolute products (1.5 times that without low low), which is what
+// fp32 roundings of so many terms come to.  Any other sum is computed again without the matrix cores.  (Sums of normally distributed
+// numbers are some sqrt(count) 2^19: one in sixty thousand is below it.)
+__device__ __forceinline__ float scaled_floor(int count) { return 8.f * __builtin_sqrtf((float)count); }
+
 // Two numbers times `times`: the high terms, and what is left of them, times kLowScale, as the low ones.
 __device__ __forceinline__ void split_f16(float x0, float x1, float times, f16x2& high, f16x2& low) {
   high = __builtin_convertvector((f32x2{x0 * times, x1 * times}), f16x2);

@@ -5,8 +5,9 @@
 // holds, so what is left out is no more than 2^-23 of the number.  All four products of terms are taken: high high in one
 // accumulator, the three small ones in another, so that these are not rounded to the large sum's last place one by one.  The power of two
 // is chosen for each row of A and for each column of B (and quarter of A's columns), from the first numbers that are not zero, whose
-// largest comes to 2^10 .. 2^11; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers below
-// 2^-24 of the row's or column's largest lose bits of `low` to fp16's smallest exponent: 2^-46 of the largest at most.
+// largest comes to 2^10 .. 2^11; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers far below the row's or
+// column's largest lose bits of `low` to fp16's smallest exponent, so that a sum may be wrong that is small beside what these two could give:
+// such sums are gathered (scaled_floor, by the powers of two that the row and the quarters of the column have in the end, the smallest ones).
 //
 // A workgroup owns 64 sparse rows and 64 columns of C and walks A's columns in stages of 128.  Eight waves scatter: sixteen lanes to
 // a row, they find the row's entries of the stage by a cursor, take each apart into its terms and write these into a block of
@@ -50,6 +51,9 @@ constexpr int kDsRedoOff = kDsRingOff + kDsMulWaves * kDsRing * kDsChunk;
 constexpr int kDsScaleOff = kDsRedoOff + kDsRows * 4;
 constexpr int kDsShiftOff = kDsScaleOff + kDsRows * 4;
 constexpr int kDsLdsBytes = kDsShiftOff + 3 * kDsRows * 8 + 16;
+// In the shifts' place, in the end: by the quarter and the column of B what a scaled one is, 0 if all are zeros; the rows' scaled_floor, likewise.
+constexpr int kDsUnitOff = kDsShiftOff, kDsFloorOff = kDsUnitOff + 4 * kDsCols * 4;
+static_assert(kDsFloorOff + kDsRows * 4 <= kDsShiftOff + 3 * kDsRows * 8, "LDS");
 
 // Lane i gets the place of the (i + 1)-th one of `set`.  (Lanes beyond the last one: those of the zeros.)
 __device__ __forceinline__ int nth_one(unsigned long long set) {
@@ -334,6 +338,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
         *reinterpret_cast<float*>(lds_raw + quarter * (kDsRows * kDsCols * 4) + row * (kDsCols * 4) + (half * 32 + r) * 4) =
             __builtin_ldexpf(__builtin_fmaf(rest[i][t], 1.f / kLowScale, sum[i][t]), 127 - scale);
       }
+    if (h == 0) reinterpret_cast<float*>(lds_raw + kDsUnitOff)[quarter * kDsCols + half * 32 + r] = limit > 0.f ? __builtin_ldexpf(1.f, 127 - scale) : 0.f;
   } else {
     const int tail = k & ~15, tail_shift = tail == k ? 0 : 16 - (k & 15);
     const int sub = lane >> 4, l16 = lane & 15;
@@ -485,6 +490,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       if (l16 == 0) {
         redo[local] = at[j] != row_end[j][0] || (strays[j] & mine) != 0 || (entries > 0 && entries < spmm_split_entries(k));
         row_scale[local] = 127 - scale[j];
+        reinterpret_cast<float*>(lds_raw + kDsFloorOff)[local] = limit[j] > 0.f ? scaled_floor(entries) : 0.f;
       }
     }
   }
@@ -494,17 +500,23 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
   // The four sums of each result; four columns to a thread.
   static_assert(kDsThreads * 4 == kDsRows * kDsCols, "a thread for every four results");
   const int local = tid >> 4, c4 = (tid & 15) * 4, row = i0 + local, col = tile * kDsCols + c4;
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, floor[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     const f32x4 x = *reinterpret_cast<const f32x4*>(lds_raw + w * (kDsRows * kDsCols * 4) + local * (kDsCols * 4) + c4 * 4);
+    const f32x4 unit = *reinterpret_cast<const f32x4*>(lds_raw + kDsUnitOff + (w * kDsCols + c4) * 4);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) v[t] += x[t];
+    for (int t = 0; t < 4; ++t) {
+      v[t] += x[t];
+      floor[t] = fmaxf(floor[t], unit[t]);
+    }
   }
+  const float row_floor = reinterpret_cast<const float*>(lds_raw + kDsFloorOff)[local];
   const int count = row < m ? min(4, n - col) : 0;
   bool failed = redo[local] != 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
+    failed |= __builtin_fabsf(v[t]) < floor[t] * row_floor;
     v[t] = __builtin_ldexpf(v[t], row_scale[local]);
     failed |= split_failed(v[t]);
   }
