@@ -5,7 +5,7 @@
 // holds, so what is left out is no more than 2^-23 of the number.  All four products of terms are taken: high high in one
 // accumulator, the three small ones in another, so that these are not rounded to the large sum's last place one by one.  The power of two
 // is chosen for each row of A and for each column of B (and quarter of A's columns), from the first numbers that are not zero, whose
-// largest comes to 2^10 .. 2^11; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers far below the row's or
+// largest comes to 2^12 .. 2^13; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers far below the row's or
 // column's largest lose bits of `low` to fp16's smallest exponent, so that a sum may be wrong that is small beside what these two could give:
 // such sums are gathered (scaled_floor, by the powers of two that the row and the quarters of the column have in the end, the smallest ones).
 //
@@ -31,7 +31,7 @@
 //
 // Rows that are not ascending, or hold a column twice, are noticed (an entry that does not come right after a smaller column of the
 // same stage; a cursor short of the row's end) and gathered at the end (split_gather), as is what is not finite: a zero of the
-// block times an infinity of B must not reach the result.  (Sums from some 2^100 of B's numbers' on come out as infinities too, and are gathered.)
+// block times an infinity of B must not reach the result.  (Sums from some 2^98 of B's numbers' on come out as infinities too, and are gathered.)
 #pragma once
 #include "f16_split.hpp"
 
