@@ -67,9 +67,10 @@ __device__ __forceinline__ int nth_one(unsigned long long set) {
 // columns that lane i's `mask` names.  All threads of the workgroup share out the rows, and a row's among the fours of columns that any
 // row needs and parts of the row's entries, sixteen of them in flight for each thread: a single row waits for a few gathers, not for
 // as many as it has sixteens, and where all rows need four columns (an infinity in B) no lane idles.  A part whose sums are
-// all NaN already is done.  (8192 x 10240 at 30 %, n = 128, 143 us with nothing to gather; by the thread that has the result, eight entries in
-// flight -> here: one infinity in B 727 us -> 286, a row of them 2960 -> 692, B all NaN 121, one NaN in A 364 -> 149, one row
-// in 64 not ascending 342 -> 151, none 2970 -> 694.)
+// all NaN already is done.  (8192 x 10240 at 30 %, n = 128, 131 us with nothing to gather: one infinity in B 271 us, a row of them 678, B all
+// NaN 109, one NaN in A 130, one row in 64 not ascending 151, none 665.  Sums below scaled_floor: a row of B 2^10 times the others
+// 133, 2^20 times 626; A and B all +-1, where one sum in 140 is zero, 432; B with one number in a hundred that is not zero 119, in a thousand 710;
+// both log-normal, sigma 1 / 3, 154 / 393.  What is gathered is read from the L2s entry by entry, all of it at their rate.)
 __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned mask, int i0, int j0, int m, int n,
                                              const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
                                              const float* __restrict__ values, const float* __restrict__ B, float* __restrict__ C,

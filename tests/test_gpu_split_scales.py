@@ -1,7 +1,7 @@
 """fp32 SpMM of dense sparse matrices on the matrix cores (two fp16 terms per number), with numbers of every magnitude: each row of A and each column
 of B is taken times a power of two that falls when a larger number comes.  Tolerance: the bound for four products of terms, as many roundings as
-the sum has steps of sixteen columns, and 4 sqrt(k) for the bits that the common powers of two may cost a sum:
-(16 (k / 64 + 1) + 16 + 4 sqrt(k)) 2^-24 of the sum of the absolute products of A's stored entries, whatever else the row, the column or the rows of B
+the sum has steps of sixteen columns, and 8 sqrt(k) for the bits that the common powers of two may cost a sum:
+(16 (k / 64 + 1) + 16 + 8 sqrt(k)) 2^-24 of the sum of the absolute products of A's stored entries, whatever else the row, the column or the rows of B
 hold that A does not store.  That is for any signs; over all results the root of the mean square is no more than half of sqrt(k) 2^-24, what
 roundings of as many terms come to, so that no part of them may be far off."""
 import numpy as np
@@ -67,7 +67,7 @@ def check(g, oracle_lib, A, B, n):
     got = g.gpu_spmm(A, B, n)
     assert np.all(np.isfinite(got))
     off = np.abs(got - ref) - 2.0 ** -149
-    assert np.all(off <= (16 * (A.k // 64 + 1) + 16 + 4 * np.sqrt(A.k)) * 2.0 ** -24 * S)
+    assert np.all(off <= (16 * (A.k // 64 + 1) + 16 + 8 * np.sqrt(A.k)) * 2.0 ** -24 * S)
     part = np.maximum(off, 0)[S > 0] / S[S > 0]
     assert np.sqrt(np.mean(part ** 2)) <= np.sqrt(A.k) * 2.0 ** -25
 
