@@ -7,6 +7,8 @@
 // own 32 rows of R (direct-to-LDS copies of 32 columns at a time, swizzled so that neither the copies nor the reads meet in a bank,
 // asked for up to three pieces ahead), splits them in registers, one step of sixteen ahead, each row times a power of two of its own, and
 // multiplies two 32 x 32 tiles; high high in one accumulator, high low and low high in another.  (Low low is below 2^-22 of the product.)
+// A sum that is small beside what the largest numbers of its two rows could give may have lost what it consists of to the common powers of two
+// (scaled_floor): it becomes NaN, and as any result that is not finite it is computed again from L and R by the wave that stores it.
 // At a chunk's end what the two hold is added to the sums: the matrix cores cut sums off where they add, which a chain of the whole dot
 // product would feel.  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the end the sums
 // go to LDS, and all waves pick the stored entries of their rows.
@@ -36,8 +38,8 @@ constexpr int kLgPiece = 32 * 32 * 4;                    // a wave's rows of R, 
 constexpr int kLgRingOff = 2 * kLgBuf;
 constexpr int kLgShiftOff = kLgRingOff + kLgWaves * 2 * kLgPiece;   // by how much the powers of two of the rows of L rise in a chunk (three chunks'),
 constexpr int kLgRaisedOff = kLgShiftOff + 3 * kLgRows * 4;                // ... and whether they do, by the wave that splits them;
-constexpr int kLgScaleOff = kLgRaisedOff + 3 * kLgSplitWaves * 4;          // what the sums are taken times in the end
-constexpr int kLgBoundOff = kLgScaleOff + kLgRows * 4;                     // the sparse rows' first and last entry in the block
+constexpr int kLgScaleOff = kLgRaisedOff + 3 * kLgSplitWaves * 4;          // what the sums are taken times in the end, and the rows' scaled_floor
+constexpr int kLgBoundOff = kLgScaleOff + kLgRows * 8;                     // the sparse rows' first and last entry in the block
 constexpr int kLgLdsBytes = kLgBoundOff + 2 * kLgRows * 4;
 constexpr int kLgStride = (kLgCols + 8) * 4;             // bytes from row to row of the results: four rows on, the other 32 banks
 static_assert(kLgStep % 256 == 32 && kLgHalf % 256 == 16, "see above");
@@ -58,7 +60,7 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
   clocks.start();
   int* const row_shift = reinterpret_cast<int*>(lds_raw + kLgShiftOff);
   int* const row_raised = reinterpret_cast<int*>(lds_raw + kLgRaisedOff);
-  float* const row_unscale = reinterpret_cast<float*>(lds_raw + kLgScaleOff);
+  f32x2* const row_unscale = reinterpret_cast<f32x2*>(lds_raw + kLgScaleOff);
   int* const bounds = reinterpret_cast<int*>(lds_raw + kLgBoundOff);
   auto barrier = [&]() __attribute__((always_inline)) {                // (no wait for memory)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -151,8 +153,9 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
           for (int t = 0; t < 4; ++t) raw[j][4 * half + t] = x[t];
         }
     };
-    // The largest number that the power of two in use of the lane's row of R is for, and by how much that has just risen.
-    float limit = scale_limit(kNoScale);
+    // The largest number that the power of two in use of the lane's row of R is for, and by how much that has just risen.  (All zeros so far: 0, and
+    // what these are taken times does not matter.)
+    float limit = 0.f;
     int shift = 0;
     unsigned long long raised = 0;
     struct Terms { f16x8 high, low; };
@@ -268,13 +271,17 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     barrier();                                                         // nobody reads terms or rings any more
     const int column = row0 - c0 + r;
     const float unscale = __builtin_ldexpf(1.f, (int)(__builtin_bit_cast(unsigned, limit) >> 23) - 142);
+    const float floor = limit > 0.f ? __builtin_inff() : 0.f;
     if (column >= 0)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
           const int row = 32 * i + 8 * (t / 4) + 4 * h + t % 4;
-          *reinterpret_cast<float*>(lds_raw + row * kLgStride + column * 4) = total[i][t] * row_unscale[row] * unscale;
+          const f32x2 of_row = row_unscale[row];
+          const float v = total[i][t] * of_row.x * unscale;
+          *reinterpret_cast<float*>(lds_raw + row * kLgStride + column * 4) =
+              __builtin_fabsf(total[i][t]) < fminf(floor, of_row.y) ? __builtin_nanf("") : v;
         }
   } else {
     constexpr int NI = kLgRows / kLgSplitWaves / 2;                    // pairs of rows
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      if (l32 == 0) row_unscale[first + 2 * i + half] = __builtin_ldexpf(1.f, 127 - power[i]);
+      if (l32 == 0) row_unscale[first + 2 * i + half] = f32x2{__builtin_ldexpf(1.f, 127 - power[i]), limit[i] > 0.f ? scaled_floor(n) : 0.f};
     barrier();
   }
   // Every wave picks the entries of five or six rows.
@@ -380,13 +387,21 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
   }
   clocks.lap(kPhaseRest);
   barrier();                                                           // the results are there
-  // A dot product by the whole wave: what the matrix cores cannot give.
+  // A dot product by the whole wave: what the matrix cores cannot give.  (4096 x 1024 at 10 %, n = 4096, 130 us without any: a row of NaN's worth 250,
+  // all results 1360, at the L2s' rate; sums below scaled_floor: +-1 on both sides 144, log-normal, sigma 1 / 3, 152 / 177, a column of R 2^10 times
+  // the others that meets zeros 141, 2^20 times 242, 2^30 times 1360.)
   auto dot = [&](int row, int column) __attribute__((always_inline)) {
     const float* const l = L + (size_t)(i0 + row) * n;
     const float* const r = R + (size_t)column * n;
     float acc = 0.f;
+    int j = 4 * lane;
 #pragma unroll 4
-    for (int j = lane; j < n; j += kWave) acc = __builtin_fmaf(l[j], r[j], acc);
+    for (; j + 4 <= n; j += 4 * kWave) {
+      const f32x4_any x = *reinterpret_cast<const f32x4_any*>(l + j), y = *reinterpret_cast<const f32x4_any*>(r + j);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc = __builtin_fmaf(x[t], y[t], acc);
+    }
+    for (; j < n; ++j) acc = __builtin_fmaf(l[j], r[j], acc);
 #pragma unroll
     for (int d = 1; d < kWave; d *= 2) acc += __shfl_xor(acc, d, kWave);
     return acc;
