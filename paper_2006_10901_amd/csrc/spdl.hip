@@ -345,8 +345,7 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 // (us, here and in the plan's form: 8192 x 10240, n = 128, 14 % 116 and 112, 16 % 116 and 120, 20 % 127 and 143, 30 % 133 and 200; 5494 x 3943 at
 // 15 %, n = 369, 119 and 121; 2621 x 1436 at 31 %, n = 540, 41 and 55; 14741 x 1257 at 28 %, n = 748, 203 and 251); below 15.5 % of 17 shapes
 // two were faster here, by 2 and 10 %.
-// Rows of few entries are gathered there (spmm_split_entries): uniform shapes that come out have their mean 3.2 standard deviations and more
-// above that, on 200 thousand of 800 .. 1400 columns.
+// Rows of fewer than 32 entries are gathered there (kDsEntries): uniform rows have 100 and more.
 // Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
 // 1024 at 30 %, n = 4096, among others) stay with the forms that tests of them fix there.
 bool spmm_split_runs(int m, int k, int n, int nnz, const SlabPlan& plan) {

@@ -20,7 +20,7 @@
 //
 // Against 64 bits, normally distributed values, 2-norm of the error over that of the result: rows of 30 % of 10240 columns 3.2e-7, where six
 // products of three bf16 terms in one accumulator have 7.0e-7 and the slab kernel 9.9e-7.  With few entries the roundings of a sum that are no
-// entry's count: such rows are gathered (spmm_split_entries).
+// entry's count: such rows are gathered (kDsEntries).
 //
 // What bounds it: the power limit (1.5 .. 1.7 GHz) and the issue of vector instructions beside the MFMA.  A stage is 64 MFMA of 32 clocks on two of a
 // SIMD's waves, 170 vector instructions of these and 130 (10 %) to 260 (30 %) of the scattering waves, 4 clocks each or 5 where a wave is
@@ -140,9 +140,9 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
     if (col + t >= first) c[t] = v[t];
 }
 
-// Entries from which on a row's sum on the matrix cores is no less exact than a chain of multiply-adds.  (It is as exact at 100 entries of
-// 1025 columns, 155 of 2169, 290 of 5120, 460 of 10240.)
-__host__ __device__ constexpr int spmm_split_entries(int k) { return 72 + k / 24; }
+// Entries from which on a row's sum on the matrix cores is no less exact than a chain of multiply-adds: 2-norm of the error over the chain's, rows
+// of 20 / 30 / 40 / 100 / 500 entries 1.05 / 0.92 / 0.81 .. 0.86 / 0.60 / 0.31 .. 0.48, at 833 .. 10240 columns alike (of 2: 2.2).
+constexpr int kDsEntries = 32;
 
 // NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, n >= 4, 0 < nnz < 2^28.)
 template <int NC>
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       const int local = first_row + 4 * j + sub, row = min(i0 + local, m);
       const int entries = row_offsets[min(row + 1, m)] - row_offsets[row];
       if (l16 == 0) {
-        redo[local] = at[j] != row_end[j][0] || (strays[j] & mine) != 0 || (entries > 0 && entries < spmm_split_entries(k));
+        redo[local] = at[j] != row_end[j][0] || (strays[j] & mine) != 0 || (entries > 0 && entries < kDsEntries);
         row_scale[local] = 127 - scale[j];
         reinterpret_cast<float*>(lds_raw + kDsFloorOff)[local] = limit[j] > 0.f ? scaled_floor(entries) : 0.f;
       }

@@ -97,7 +97,7 @@ def test_split_spmm_is_as_exact_as_a_chain_for_rows_of_any_length(g, oracle_lib,
     """Rows of few entries between long ones, each length by itself; and rows of many zeros with one number, whose product has to come out to
     six roundings and what is left out (2^-24 each): every one of the six products of terms counts there."""
     m, n, least = 4161, 130, 72 + k // 24
-    lengths = [1, 2, 3, 16, 17, 32, 33, 49, least - 1, least, least + 20, 2 * least]
+    lengths = [1, 2, 3, 16, 17, 31, 32, 33, 49, least - 1, least, least + 20, 2 * least]
     rng = np.random.default_rng(7300 + k)
     lens = np.full(m, int(0.7 * k))
     lens[::2] = np.resize(lengths, len(lens[::2]))
