@@ -1,9 +1,9 @@
-"""fp32 SpMM of dense sparse matrices on the bf16 matrix cores (three terms per number), against the oracle.  Tolerance: a result is four
-chains, each of six products of terms for every sixteen of a quarter of A's columns, whose sixteen products are added to the sum with no
-more than four roundings; what is left out of a product is below 2^-24 of it: (24 (k / 64 + 1) + 16) 2^-24 of the sum of
-absolute products.  That bound holds for any signs and is far above what normally distributed inputs give, for which the 2-norm of the error
-has to be no larger than that of a chain of fp32 multiply-adds over the row's entries, the sums before: leaving out one of the six products of terms
-makes it several times as large."""
+"""fp32 SpMM of dense sparse matrices on the fp16 matrix cores (two terms per number), against the oracle.  Tolerance: a result is four
+chains, each of the products of high terms for every sixteen of a quarter of A's columns, added to the sum with no more than four
+roundings of 2^-23 at most, and of three smaller products in a sum of their own, 2^-11 of that; the terms hold each of two numbers to 2^-23 of it:
+(16 (k / 64 + 1) + 16) 2^-24 of the sum of absolute products, twice what this comes to.  That bound holds for any signs and is far above what normally
+distributed inputs give, for which the 2-norm of the error has to be no larger than that of a chain of fp32 multiply-adds over the row's entries, the
+sums before."""
 import ctypes
 
 import numpy as np
@@ -54,7 +54,7 @@ def spmm(g, A, n, B, order=None, bias=None):
 
 
 def tolerance(k):
-    return (24 * (k // 64 + 1) + 16) * 2.0 ** -24
+    return (16 * (k // 64 + 1) + 16) * 2.0 ** -24
 
 
 def chain(A, B, rows):
@@ -95,7 +95,7 @@ def test_split_spmm(g, oracle_lib, m, k, n, density):
 @pytest.mark.parametrize("k", [1025, 2169])
 def test_split_spmm_is_as_exact_as_a_chain_for_rows_of_any_length(g, oracle_lib, k):
     """Rows of few entries between long ones, each length by itself; and rows of many zeros with one number, whose product has to come out to
-    six roundings and what is left out (2^-24 each): every one of the six products of terms counts there."""
+    what the terms of two numbers leave out (2^-23 each) and three roundings: every one of the four products of terms counts there."""
     m, n, least = 4161, 130, 72 + k // 24
     lengths = [1, 2, 3, 16, 17, 31, 32, 33, 49, least - 1, least, least + 20, 2 * least]
     rng = np.random.default_rng(7300 + k)
@@ -167,8 +167,8 @@ def test_split_spmm_of_rows_whose_middle_lies_in_a_later_stage(g, oracle_lib, de
 
 @pytest.mark.gpu
 def test_split_spmm_keeps_non_finite_values_and_the_whole_range(g, oracle_lib):
-    """Infinities and NaN reach the results that depend on them and no others, though zeros are multiplied; numbers that no bf16 term
-    can hold (too large for a scaled first term, too small for a last one) cost time, not bits."""
+    """Infinities and NaN reach the results that depend on them and no others, though zeros are multiplied; numbers at either end of the
+    range, whose scaled sums need not be finite, cost time, not bits."""
     m, k, n = 4161, 1025, 130
     A = odd_csr(m, k, 0.35, 7700)
     B = wl.dense(k, n, 7701)
