@@ -20,12 +20,18 @@ __device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_c
 
 // What a power of two of a whole row or column costs: a scaled number below 2^-13 is held to 2^-36, not to 2^-23 of itself, so that a product may be
 // off by 2^-21 (2^-36 times 2^15; half as much again where low low is left out), however small it is.  The largest number need not be one that
-// the sum has a use for: it may be multiplied by a zero.  A scaled sum of `count` products is therefore taken only if it is no smaller than
+// the sum has a use for: it may be multiplied by a zero.  A scaled sum of `count` products, or of as many that may be off (scaled_loses), is therefore taken only if it is no smaller than
 // this.  What is lost is then no more than 8 sqrt(count) 2^-24 of the sum of absolute products, if all of it has one sign, and 5 x 2^-24 as a
 // root of the mean square (1.5 times that without low low); fp32 roundings of so many terms come to sqrt(count) 2^-24.  Any other sum is
 // computed again without the matrix cores.  (Sums of normally distributed numbers are some sqrt(count) 2^22.4: one in seven million is below it.
 // 8192 x 10240 at 30 %, n = 128, has a million sums, and one that is gathered makes it 6 us slower: 2.7 % with eight times as much, 0.4 % here.)
 __device__ __forceinline__ float scaled_floor(int count) { return __builtin_sqrtf((float)count); }
+// Whether a number of a row or a column in whose scaled numbers one is `unit` is among those, below 2^-13 and not zero, that lose bits: as many
+// products as there are such numbers in the two may be off, and where there are none, as between whole numbers, a sum may be
+// as small as it likes.
+__device__ __forceinline__ bool scaled_loses(float x, float unit) {
+  return __builtin_bit_cast(unsigned, __builtin_fabsf(x)) - 1u < __builtin_bit_cast(unsigned, unit * 0x1p-13f) - 1u;
+}
 
 // Two numbers times `times`: the high terms, and what is left of them, times kLowScale, as the low ones.
 __device__ __forceinline__ void split_f16(float x0, float x1, float times, f16x2& high, f16x2& low) {

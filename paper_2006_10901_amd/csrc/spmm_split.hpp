@@ -7,7 +7,8 @@
 // is chosen for each row of A and for each column of B (and quarter of A's columns), from the first numbers that are not zero, whose
 // largest comes to 2^12 .. 2^13; a number beyond 2^15 makes it smaller, and the sums so far with it.  Numbers far below the row's or
 // column's largest lose bits of `low` to fp16's smallest exponent, so that a sum may be wrong that is small beside what these two could give:
-// such sums are gathered (scaled_floor, by the powers of two that the row and the quarters of the column have in the end, the smallest ones).
+// such sums are gathered (scaled_floor, by the powers of two that the row and the quarters of the column have in the end, the smallest ones), unless
+// there are several and a count shows that too few numbers have lost any (kDsCount).
 //
 // A workgroup owns 64 sparse rows and 64 columns of C and walks A's columns in stages of 128.  Eight waves scatter: sixteen lanes to
 // a row, they find the row's entries of the stage by a cursor, take each apart into its terms and write these into a block of
@@ -55,38 +56,38 @@ constexpr int kDsLdsBytes = kDsShiftOff + 3 * kDsRows * 8 + 16;
 constexpr int kDsUnitOff = kDsShiftOff, kDsFloorOff = kDsUnitOff + 4 * kDsCols * 4;
 static_assert(kDsFloorOff + kDsRows * 4 <= kDsShiftOff + 3 * kDsRows * 8, "LDS");
 
-// Lane i gets the place of the (i + 1)-th one of `set`.  (Lanes beyond the last one: those of the zeros.)
-__device__ __forceinline__ int nth_one(unsigned long long set) {
-  const int lane = threadIdx.x & 63;
-  const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0u));
-  const int to = (set >> lane & 1) ? before : __builtin_popcountll(set) + lane - before;
-  return __builtin_amdgcn_ds_permute(to * 4, lane);
-}
-
-// Results that the matrix cores cannot give, from the rows of B themselves: row i of the workgroup (bit i of `rows`) in the fours of
-// columns that lane i's `mask` names.  All threads of the workgroup share out the rows, and a row's among the fours of columns that any
-// row needs and parts of the row's entries, sixteen of them in flight for each thread: a single row waits for a few gathers, not for
-// as many as it has sixteens, and where all rows need four columns (an infinity in B) no lane idles.  A part whose sums are
-// all NaN already is done.  (8192 x 10240 at 30 %, n = 128, 131 us with nothing to gather: one infinity in B 271 us, a row of them 678, B all
-// NaN 109, one NaN in A 130, one row in 64 not ascending 151, none 665.  Sums below scaled_floor: a row of B 2^10 times the others
-// 133, 2^20 times 626; A and B all +-1, where one sum in 140 is zero, 432; B with one number in a hundred that is not zero 119, in a thousand 710;
-// both log-normal, sigma 1 / 3, 154 / 393.  What is gathered is read from the L2s entry by entry, all of it at their rate.)
-__device__ __forceinline__ void split_gather(unsigned long long rows, unsigned mask, int i0, int j0, int m, int n,
+// Results that the matrix cores cannot give, from the rows of B themselves: of row i of the workgroup the fours of columns that lane i's `mask`
+// names.  The threads of the workgroup share out the list of all such fours and parts of each one's entries, sixteen of
+// them in flight for each thread: a single four waits for a few gathers, not for as many as its row has sixteens, fours here and there take as many
+// threads as they are, and where whole rows are needed sixteen lanes read 256 bytes of B in a row.  A part whose sums are
+// all NaN already is done.  (8192 x 10240 at 30 %, n = 128, inputs from a fresh generator, 149 us with nothing
+// to gather: one infinity in B 281, a row of them 671; sums below scaled_floor: a row of B 2^10 times the others 128, 2^20 times 307; A and B
+// log-normal, sigma 1 / 3, 165 / 262.  With whole rows shared out, not fours, and nothing counted (kDsCount): 2^20 634, log-normal 165 / 462; sums that
+// are small and right, A and B all +-1, where one in 140 is zero, 476, of -1, 0 and 1 688, B with one number in a thousand that is not zero 681:
+// now 158, 161, 166.  What is gathered is read from the L2s entry by entry, all of it at their rate.)
+__device__ __forceinline__ void split_gather(unsigned mask, int i0, int j0, int m, int n,
                                              const int* __restrict__ row_offsets, const int* __restrict__ column_indices,
                                              const float* __restrict__ values, const float* __restrict__ B, float* __restrict__ C,
                                              const float* __restrict__ bias, int relu, char* lds) {
-  const int tid = threadIdx.x;
-  unsigned any = mask;
+  const int tid = threadIdx.x, lane = tid & 63;
+  f32x4* const sums = reinterpret_cast<f32x4*>(lds);                   // (the products' sums before have been read)
+  unsigned short* const list = reinterpret_cast<unsigned short*>(lds + 16 * kDsThreads);
+  int through = __builtin_popcount(mask);                              // fours of the rows up to the lane's
 #pragma unroll
-  for (int d = 1; d < kWave; d *= 2) any |= (unsigned)__shfl_xor((int)any, d, kWave);
-  const int nrows = __builtin_popcountll(rows), nfours = __builtin_popcount(any);
-  const int row_bits = nrows > 1 ? 32 - __builtin_clz(nrows - 1) : 0, four_bits = nfours > 1 ? 32 - __builtin_clz(nfours - 1) : 0;
-  const int per_row = kDsThreads >> row_bits, mine = tid & (per_row - 1), index = tid / per_row;
-  const int part = mine >> four_bits, parts = min(per_row >> four_bits, 64);
-  const int local = __shfl(nth_one(rows), index, kWave), four = __shfl(nth_one(any), mine & ((1 << four_bits) - 1), kWave);
-  const unsigned wanted = (unsigned)__shfl((int)mask, local, kWave);
-  const bool on = index < nrows && (mine & ((1 << four_bits) - 1)) < nfours && (wanted >> four & 1) && part < parts;
-  const int row = i0 + local, first = j0 + 4 * four, col = min(first, n - 4);               // (the last four columns of B's row at its end)
+  for (int d = 1; d < kWave; d *= 2) {
+    const int before = __shfl_up(through, d, kWave);
+    through += lane >= d ? before : 0;
+  }
+  const int fours = __builtin_amdgcn_readlane(through, 63);
+  if (tid < kWave) {
+    int at = through - __builtin_popcount(mask);
+    for (unsigned left = mask; left != 0; left &= left - 1) list[at++] = (unsigned short)(lane * 16 + __builtin_ctz(left));
+  }
+  __syncthreads();
+  const int parts = min(kDsThreads / fours, 64), part = tid / fours;
+  const bool on = part < parts;
+  const int which = list[on ? tid - part * fours : 0];
+  const int row = i0 + which / 16, first = j0 + 4 * (which & 15), col = min(first, n - 4);  // (the last four columns of B's row at its end)
   float v[4] = {0.f, 0.f, 0.f, 0.f};
   if (on) {
     constexpr int U = 16;
@@ -123,13 +124,12 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
       if (v[0] != v[0] && v[1] != v[1] && v[2] != v[2] && v[3] != v[3]) break;
     }
   }
-  f32x4* const sums = reinterpret_cast<f32x4*>(lds);                   // (the products' sums before have been read)
   sums[tid] = f32x4{v[0], v[1], v[2], v[3]};
   __syncthreads();
   if (!on || part > 0) return;
 #pragma unroll 4
   for (int i = 1; i < parts; ++i) {
-    const f32x4 x = sums[tid + (i << four_bits)];
+    const f32x4 x = sums[tid + i * fours];
 #pragma unroll
     for (int t = 0; t < 4; ++t) v[t] += x[t];
   }
@@ -143,6 +143,13 @@ __device__ __forceinline__ void split_gather(unsigned long long rows, unsigned m
 // Entries from which on a row's sum on the matrix cores is no less exact than a chain of multiply-adds: 2-norm of the error over the chain's, rows
 // of 20 / 30 / 40 / 100 / 500 entries 1.05 / 0.92 / 0.81 .. 0.86 / 0.60 / 0.31 .. 0.48, at 833 .. 10240 columns alike (of 2: 2.2).
 constexpr int kDsEntries = 32;
+
+// Fours of columns with a sum below the floor of its entries from which on the numbers that lose bits (scaled_loses) are counted, in the tile of B and in
+// these rows of A, before what is still below the floor of as many products is gathered.  (Numbers rounded to whole ones, from more
+// to fewer sums of zero, us, counted / not: 8192 x 10240 at 30 %, 2 / 7 / 12 / 27 fours of a workgroup 137 / 141 / 141 / 142 and 133 / 164 / 189 / 245; 8192 x 3000 at
+// 20 %, 4 / 16 / 28 / 61 fours 50 / 50 / 50 / 51 and 45 / 51 / 55 / 71; 4096 x 1024 at 30 %, n = 1024, 2 / 6 / 23 fours 89 / 89 / 90 and 84 / 91 / 109.  Of normally
+// distributed numbers one workgroup in ten has one.)
+constexpr int kDsCount = 8;
 
 // NC sixteens of a row's entries fetched a stage ahead.  (k >= 16, n >= 4, 0 < nnz < 2^28.)
 template <int NC>
@@ -501,7 +508,7 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
   // The four sums of each result; four columns to a thread.
   static_assert(kDsThreads * 4 == kDsRows * kDsCols, "a thread for every four results");
   const int local = tid >> 4, c4 = (tid & 15) * 4, row = i0 + local, col = tile * kDsCols + c4;
-  float v[4] = {0.f, 0.f, 0.f, 0.f}, floor[4] = {0.f, 0.f, 0.f, 0.f};
+  float v[4] = {0.f, 0.f, 0.f, 0.f}, floor[4] = {0.f, 0.f, 0.f, 0.f}, scaled[4];
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     const f32x4 x = *reinterpret_cast<const f32x4*>(lds_raw + w * (kDsRows * kDsCols * 4) + local * (kDsCols * 4) + c4 * 4);
@@ -513,18 +520,18 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
     }
   }
   const float row_floor = reinterpret_cast<const float*>(lds_raw + kDsFloorOff)[local];
-  const int count = row < m ? min(4, n - col) : 0;
-  bool failed = redo[local] != 0;
+  const int cols = min(4, n - col), count = row < m ? cols : 0;
+  bool failed = redo[local] != 0, small = false;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    failed |= __builtin_fabsf(v[t]) < floor[t] * row_floor;
+    scaled[t] = v[t];
+    small |= __builtin_fabsf(v[t]) < floor[t] * row_floor;
     v[t] = __builtin_ldexpf(v[t], row_scale[local]);
     failed |= split_failed(v[t]);
   }
   failed &= count > 0;
-  const unsigned long long fails = __builtin_amdgcn_ballot_w64(failed);
-  if ((tid & 15) == 0) redo[local] = (int)((unsigned)(fails >> (lane & 48)) & 0xffffu);      // (fours of columns to be gathered)
-  if (!failed) {
+  small &= count > 0 && !failed;
+  auto store = [&]() __attribute__((always_inline)) {
     if (count > 0) spmm_epilogue<float, 4>(v, bias, row, relu);
     float* c = C + (size_t)row * n + col;
     if (count >= 4) {
@@ -534,12 +541,70 @@ __global__ __launch_bounds__(kDsThreads) void spmm_split_kernel(
       for (int t = 0; t < 3; ++t)
         if (t < count) c[t] = v[t];
     }
-  }
+  };
+  // The row's fours of columns to be gathered, those that are only small beside the floor sixteen bits up.
+  auto note = [&]() __attribute__((always_inline)) {
+    const unsigned long long fails = __builtin_amdgcn_ballot_w64(failed), smalls = __builtin_amdgcn_ballot_w64(small);
+    if ((tid & 15) == 0) redo[local] = (int)((unsigned)(fails >> (lane & 48)) & 0xffffu | (unsigned)(smalls >> (lane & 48)) << 16);
+  };
+  note();
+  if (!failed && !small) store();
   barrier();
-  const unsigned mask = (unsigned)redo[lane];
-  const unsigned long long rows = __builtin_amdgcn_ballot_w64(mask != 0);
-  if (rows == 0) return;
-  split_gather(rows, mask, i0, tile * kDsCols, m, n, row_offsets, column_indices, values, B, C, bias, relu, lds_raw);
+  unsigned mask = (unsigned)redo[lane];
+  if (__builtin_amdgcn_ballot_w64(mask != 0) == 0) return;
+  int smalls = __builtin_popcount(mask >> 16);
+#pragma unroll
+  for (int d = 1; d < kWave; d *= 2) smalls += __shfl_xor(smalls, d, kWave);
+  if (smalls >= kDsCount) {
+    int* const lost = reinterpret_cast<int*>(lds_raw);                 // of the tile's columns.  (The products' sums have been read.)
+    if (tid < kDsCols) lost[tid] = 0;
+    barrier();
+    int mine[4] = {0, 0, 0, 0};
+    if (cols >= 4) {
+#pragma unroll 16
+      for (int p = local; p < k; p += kDsRows) {
+        float b[4];
+        Pack<float, 4>::load(B + (size_t)p * n + col, b);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mine[t] += scaled_loses(b[t], floor[t]);
+      }
+    } else {
+      for (int p = local; p < k; p += kDsRows)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          if (t < cols) mine[t] += scaled_loses(B[(size_t)p * n + col + t], floor[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      mine[t] += __shfl_xor(mine[t], 16, kWave);
+      mine[t] += __shfl_xor(mine[t], 32, kWave);
+      if (lane < 16 && mine[t] != 0) atomicAdd(&lost[c4 + t], mine[t]);
+    }
+    int of_row = 0;
+    if (((unsigned)redo[local] >> 16) != 0) {
+      const float unit = __builtin_ldexpf(1.f, row_scale[local]);
+      const int end = row_offsets[row + 1];
+#pragma unroll 8
+      for (int p = row_offsets[row] + (tid & 15); p < end; p += 16) of_row += scaled_loses(values[p], unit);
+    }
+#pragma unroll
+    for (int d = 1; d < 16; d *= 2) of_row += __shfl_xor(of_row, d, kWave);
+    barrier();
+    const bool was = small;
+    small = false;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      small |= __builtin_fabsf(scaled[t]) <                            // (a column of tiny numbers: a part of the sum may have been a denormal one)
+               floor[t] * (floor[t] < 0x1p-76f ? row_floor : fminf(row_floor, scaled_floor(of_row + lost[c4 + t])));
+    small &= was;
+    note();
+    if (was && !small) store();
+    barrier();
+    mask = (unsigned)redo[lane];
+  }
+  mask = (mask | mask >> 16) & 0xffffu;
+  if (__builtin_amdgcn_ballot_w64(mask != 0) == 0) return;
+  split_gather(mask, i0, tile * kDsCols, m, n, row_offsets, column_indices, values, B, C, bias, relu, lds_raw);
 }
 
 }  // namespace spdl
