@@ -8,7 +8,8 @@
 // asked for up to three pieces ahead), splits them in registers, one step of sixteen ahead, each row times a power of two of its own, and
 // multiplies two 32 x 32 tiles; high high in one accumulator, high low and low high in another.  (Low low is below 2^-22 of the product.)
 // A sum that is small beside what the largest numbers of its two rows could give may have lost what it consists of to the common powers of two
-// (scaled_floor): it becomes NaN, and as any result that is not finite it is computed again from L and R by the wave that stores it.
+// (scaled_floor): as any result that is not finite it is computed again from L and R by the wave that stores it, unless there are many and
+// a count shows that too few numbers have lost any (kLgCount).
 // At a chunk's end what the two hold is added to the sums: the matrix cores cut sums off where they add, which a chain of the whole dot
 // product would feel.  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the end the sums
 // go to LDS, and all waves pick the stored entries of their rows.
@@ -38,12 +39,23 @@ constexpr int kLgPiece = 32 * 32 * 4;                    // a wave's rows of R, 
 constexpr int kLgRingOff = 2 * kLgBuf;
 constexpr int kLgShiftOff = kLgRingOff + kLgWaves * 2 * kLgPiece;   // by how much the powers of two of the rows of L rise in a chunk (three chunks'),
 constexpr int kLgRaisedOff = kLgShiftOff + 3 * kLgRows * 4;                // ... and whether they do, by the wave that splits them;
-constexpr int kLgScaleOff = kLgRaisedOff + 3 * kLgSplitWaves * 4;          // what the sums are taken times in the end, and the rows' scaled_floor
+constexpr int kLgScaleOff = kLgRaisedOff + 3 * kLgSplitWaves * 4;          // RowScale of the rows of L
 constexpr int kLgBoundOff = kLgScaleOff + kLgRows * 8;                     // the sparse rows' first and last entry in the block
 constexpr int kLgLdsBytes = kLgBoundOff + 2 * kLgRows * 4;
 constexpr int kLgStride = (kLgCols + 8) * 4;             // bytes from row to row of the results: four rows on, the other 32 banks
 static_assert(kLgStep % 256 == 32 && kLgHalf % 256 == 16, "see above");
-static_assert(kLgRows * kLgStride <= kLgShiftOff, "the results lie where the terms and the rings were");
+// Where the terms and the rings were, in the end: the scaled sums, RowScale of the rows of R, and how many of a wave's sums are small.
+constexpr int kLgColOff = kLgRows * kLgStride, kLgSmallOff = kLgColOff + kLgCols * 8;
+static_assert(kLgSmallOff + kLgWaves * 4 <= kLgShiftOff, "LDS");
+// Stored sums that are small beside the floor of n products, by their share of the block's, from which on the numbers that lose bits (scaled_loses) are
+// counted in the block's rows before what is still small beside the floor of as many products is computed again: as many rows are
+// read as for this many sums.  (4096 x 1024 at 10 %, n = 4096, few numbers that are not zero, 110 us, 206 / 299 / 434 stored sums of a block zero:
+// counted 260, not 328 / 400 / 511; at 20 %, n = 2048, 60 us, 589 / 1064: 150, 276 / 422.)
+constexpr int kLgCount = 160;
+
+// The exponent of what a scaled one of a row of L or R is, and in how many of its numbers bits may have been lost to the common power of two: all
+// n until they are counted; -infinity where all are zeros, whose sums are right whatever the other row holds.
+struct RowScale { int unit; float lost; };
 
 // (n > 32, k >= 32, 0 < nnz < 2^29, n < 2^21.)
 __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
@@ -60,7 +72,9 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
   clocks.start();
   int* const row_shift = reinterpret_cast<int*>(lds_raw + kLgShiftOff);
   int* const row_raised = reinterpret_cast<int*>(lds_raw + kLgRaisedOff);
-  f32x2* const row_unscale = reinterpret_cast<f32x2*>(lds_raw + kLgScaleOff);
+  RowScale* const of_row = reinterpret_cast<RowScale*>(lds_raw + kLgScaleOff);
+  RowScale* const of_col = reinterpret_cast<RowScale*>(lds_raw + kLgColOff);
+  int* const small_sums = reinterpret_cast<int*>(lds_raw + kLgSmallOff);
   int* const bounds = reinterpret_cast<int*>(lds_raw + kLgBoundOff);
   auto barrier = [&]() __attribute__((always_inline)) {                // (no wait for memory)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -270,19 +284,30 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // (what was asked for past the end)
     barrier();                                                         // nobody reads terms or rings any more
     const int column = row0 - c0 + r;
-    const float unscale = __builtin_ldexpf(1.f, (int)(__builtin_bit_cast(unsigned, limit) >> 23) - 142);
-    const float floor = limit > 0.f ? __builtin_inff() : 0.f;
-    if (column >= 0)
+    const RowScale mine = {(int)(__builtin_bit_cast(unsigned, limit) >> 23) - 142, limit > 0.f ? (float)n : -__builtin_inff()};
+    const float floor = limit > 0.f ? scaled_floor(n) : 0.f;
+    unsigned long long small = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < 16; ++t) small |= __builtin_amdgcn_ballot_w64(__builtin_fabsf(total[i][t]) < floor);
+    int smalls = 0;
+    if (small != 0) {                                                  // (rows of zeros need no look)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-          const int row = 32 * i + 8 * (t / 4) + 4 * h + t % 4;
-          const f32x2 of_row = row_unscale[row];
-          const float v = total[i][t] * of_row.x * unscale;
-          *reinterpret_cast<float*>(lds_raw + row * kLgStride + column * 4) =
-              __builtin_fabsf(total[i][t]) < fminf(floor, of_row.y) ? __builtin_nanf("") : v;
-        }
+        for (int t = 0; t < 16; ++t)
+          smalls += __builtin_popcountll(__builtin_amdgcn_ballot_w64(__builtin_fabsf(total[i][t]) < floor && of_row[32 * i + 8 * (t / 4) + 4 * h + t % 4].lost > 0.f));
+    }
+    if (lane == 0) small_sums[wave] = smalls;
+    if (column >= 0) {
+      if (h == 0) of_col[column] = mine;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+          *reinterpret_cast<float*>(lds_raw + (32 * i + 8 * (t / 4) + 4 * h + t % 4) * kLgStride + column * 4) = total[i][t];
+    }
   } else {
     constexpr int NI = kLgRows / kLgSplitWaves / 2;                    // pairs of rows
     const int first = (kLgRows / kLgSplitWaves) * (wave - kLgWaves), half = lane >> 5, l32 = lane & 31;
@@ -373,7 +398,7 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      if (l32 == 0) row_unscale[first + 2 * i + half] = f32x2{__builtin_ldexpf(1.f, 127 - power[i]), limit[i] > 0.f ? scaled_floor(n) : 0.f};
+      if (l32 == 0) of_row[first + 2 * i + half] = {127 - power[i], limit[i] > 0.f ? (float)n : -__builtin_inff()};
     barrier();
   }
   // Every wave picks the entries of five or six rows.
@@ -386,10 +411,42 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     index[i] = columns_at(cursor[i]);
   }
   clocks.lap(kPhaseRest);
-  barrier();                                                           // the results are there
+  barrier();                                                           // the sums are there
+  int smalls = 0;
+#pragma unroll
+  for (int i = 0; i < kLgWaves; ++i) smalls += small_sums[i];
+  if (uniform(smalls) > 0) {
+    int entries = max(0, bounds[2 * lane + 1] - bounds[2 * lane]);
+#pragma unroll
+    for (int d = 1; d < kWave; d *= 2) entries += __shfl_xor(entries, d, kWave);
+    // (of the block's sums, as many as are stored if these are as small as the others)
+    if (uniform((int)((float)smalls * (float)entries * (1.f / (kLgRows * kLgCols)))) >= kLgCount) {
+      for (int x = wave; x < kLgRows + kLgCols; x += NW) {
+        const bool left = x < kLgRows;
+        const int row = left ? i0 + x : c0 + x - kLgRows;
+        if (row >= (left ? m : k)) continue;
+        RowScale* const of = left ? of_row + x : of_col + x - kLgRows;
+        if (uniform((int)(of->lost > 0.f)) == 0) continue;
+        const float unit = __builtin_ldexpf(1.f, of->unit);
+        const float* const from = (left ? L : R) + (size_t)row * n;
+        int lost = 0, j = 4 * lane;
+#pragma unroll 8
+        for (; j + 4 <= n; j += 4 * kWave) {
+          const f32x4 v = *reinterpret_cast<const f32x4_any*>(from + j);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) lost += scaled_loses(v[t], unit);
+        }
+        for (; j < n; ++j) lost += scaled_loses(from[j], unit);
+#pragma unroll
+        for (int d = 1; d < kWave; d *= 2) lost += __shfl_xor(lost, d, kWave);
+        if (lane == 0) of->lost = (float)lost;
+      }
+      barrier();
+    }
+  }
   // A dot product by the whole wave: what the matrix cores cannot give.  (4096 x 1024 at 10 %, n = 4096, 130 us without any: a row of NaN's worth 250,
-  // all results 1360, at the L2s' rate; sums below scaled_floor: +-1 on both sides 144, log-normal, sigma 1 / 3, 152 / 177, a column of R 2^10 times
-  // the others that meets zeros 141, 2^20 times 242, 2^30 times 1360.)
+  // all results 1360, at the L2s' rate; sums below scaled_floor, 149 us from the same generator: +-1 on both sides 152, log-normal, sigma 1 / 3, 150 / 181,
+  // columns 2^20 times the others and zeros 390; one number in a hundred on both sides not zero 272, one in a row 293: 977 and 1372 with nothing counted.)
   auto dot = [&](int row, int column) __attribute__((always_inline)) {
     const float* const l = L + (size_t)(i0 + row) * n;
     const float* const r = R + (size_t)column * n;
@@ -415,13 +472,19 @@ __global__ __launch_bounds__(kLgThreads) void sddmm_long_kernel(
     const int end = uniform(bounds[2 * row + 1]);
     int at = cursor[i];
     int column = index[i];
+    const RowScale left = of_row[row];
     while (at < end) {
       const unsigned rel = (unsigned)(column - c0);
       const unsigned long long in = __builtin_amdgcn_ballot_w64(rel < (unsigned)kLgCols) & __builtin_amdgcn_ballot_w64(lane < end - at);
       const int count = in == ~0ull ? 64 : __builtin_ctzll(~in);       // from the first one on without a gap
-      const float v = *reinterpret_cast<const float*>(lds_raw + row * kLgStride + min(rel, (unsigned)kLgCols - 1) * 4);
-      if (lane < count) sddmm_store<float>(out, scale, at + lane, v);
-      unsigned long long fails = __builtin_amdgcn_ballot_w64(lane < count && split_failed(v));
+      const int inside = min(rel, (unsigned)kLgCols - 1);
+      const float sum = *reinterpret_cast<const float*>(lds_raw + row * kLgStride + inside * 4);
+      const RowScale right = of_col[inside];
+      const float v = __builtin_ldexpf(sum, left.unit + right.unit);
+      // (sum below scaled_floor of as many products as may be off)
+      const bool again = sum * sum < fminf((float)n, left.lost + right.lost) || split_failed(v);
+      if (lane < count && !again) sddmm_store<float>(out, scale, at + lane, v);
+      unsigned long long fails = __builtin_amdgcn_ballot_w64(lane < count && again);
       for (; fails != 0; fails &= fails - 1) {
         const int e = __builtin_ctzll(fails);
         const float result = dot(row, __builtin_amdgcn_readlane(column, e));

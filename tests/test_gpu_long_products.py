@@ -163,3 +163,52 @@ def test_long_products_keep_non_finite_values(g, oracle_lib):
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and 0 < np.count_nonzero(~inside) < A.nnz // 20
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     assert np.all(np.abs(got[inside] - ref[inside]) <= (n + 8) * 2.0 ** -24 * S[inside])
+
+
+@pytest.mark.parametrize("tiny", [0, 1, 40])
+def test_small_sums_of_numbers_that_lose_nothing_and_of_some_that_do(g, oracle_lib, tiny):
+    """Numbers of -1, 0 and 1, few enough that most products are zeros: exact.  Then with a few numbers, in L and in R, that are far below the
+    others: what they are all of a sum is as good as any other."""
+    m, k, n = 321, 513, 1101
+    A = mask_csr(m, k, 0.5, 9701)
+    rng = np.random.default_rng(9702)
+    L, R = (rng.integers(-1, 2, (rows, n)) * (rng.random((rows, n)) < 0.05) for rows in (m, k))
+    L, R = L.astype(np.float32), R.astype(np.float32)
+    L[::5], R[::7] = 0, 0
+    L[3] *= np.float32(2.0 ** -130)
+    R[5] *= np.float32(2.0 ** 110)
+    for i in range(tiny):
+        L[rng.integers(0, m, 8), rng.integers(0, n, 8)] = np.float32(2.0 ** -30) * rng.standard_normal(8)
+        R[rng.integers(0, k, 8), rng.integers(0, n, 8)] = np.float32(2.0 ** -30) * rng.standard_normal(8)
+    ref, S = oracle_lib.sddmm(m, k, n, A.row_offsets, A.column_indices, L, R)
+    assert runs_long(A, n)
+    got = g.gpu_sddmm(A, L, R, n)
+    if tiny:
+        assert_close_at_any_magnitude(got, ref, S, n)
+    else:
+        assert np.array_equal(got, ref.astype(np.float32))
+
+
+def test_sums_that_are_small_and_right_cost_little(g):
+    """One number in a hundred of L and R is not zero, and two sums in three are sums of nothing.  Measured: 2.1 times the time of normally distributed numbers; 7.2 times it
+    where all of them are computed again."""
+    import torch
+    import paper_2006_10901_amd as spdl
+    m, k, n = 4096, 1024, 4096
+    A = wl.uniform_mask_csr(m, k, 0.1, 9703)
+    assert runs_long(A, n)
+    d, out, times = g.DevCsr(A), torch.empty(A.nnz, device="cuda"), []
+    for share in (1.0, 0.01):
+        L, R = (x * (torch.rand(x.shape, device="cuda") < share) for x in (torch.randn(m, n, device="cuda"), torch.randn(k, n, device="cuda")))
+        runs = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(5):
+                spdl.spdl_sddmm(m, k, n, A.nnz, d.ro, d.ci, L, R, out)
+            end.record()
+            end.synchronize()
+            runs.append(start.elapsed_time(end))
+        times.append(min(runs))
+    print(f"{times[1] / times[0]:.2f} times {times[0] / 5:.4f} ms")
+    assert times[1] < 3 * times[0], times
