@@ -99,15 +99,15 @@ __global__ __launch_bounds__(256) void csr_softmax_kernel(int m, const int* __re
 //
 // Neighbouring entries of A^T lie in one column of A, their values in as many lines of memory, each of which holds the row's next columns
 // as well.  Bound by how often those lines are fetched: workgroups dealt to the XCDs in turn fetch every line into all eight L2s, so
-// an XCD gets a run of the workgroups.  (us in a graph, before -> now: 330 thousand entries 3.7 -> 3.0, 420 thousand 4.8 -> 3.3, 840 thousand 8.0 -> 5.4, 3
-// million 21.5 -> 17.5, 6 million 39.7 -> 31.3; below 300 thousand the same; 8.4 million 58.7 -> 62.5, so those in turn as before.  Two, four and
-// eight entries per thread: 5.3, 6.1 and 7.3 at 420 thousand.)
-constexpr unsigned kPermuteRuns = 6000128 / 256;       // workgroups, up to which an XCD gets a run of them
+// an XCD gets a run of the workgroups.  (us in a graph, in turn -> in runs: 330 thousand entries 3.7 -> 3.0, 420 thousand 4.8 -> 3.3, 840 thousand
+// 8.0 -> 5.4, 3 million 21.5 -> 17.5; below 300 thousand the same.  2048 x 4096, 6.0 / 6.7 / 7.5 million 38.5 -> 29.6 / 39.6 -> 32.5 /
+// 46.9 -> 36.4; 8192 x 10240, 5.9 / 8.4 / 16.8 million 38.6 -> 31.0 / 53.2 -> 42.4 / 103.6 -> 80.9; 32768 x 512, 6.7 / 10 million 55.0 -> 44.3 /
+// 83.2 -> 66.6; 8.4 million of 4096 x 4096 and of 8192 x 2048 the same, 41 and 42.  Two, four and eight entries per thread: 5.3, 6.1 and 7.3 at 420 thousand.)
 template <typename T>
 __global__ __launch_bounds__(256) void permute_values_kernel(int nnz, const int* __restrict__ perm,
                                                              const T* __restrict__ values, T* __restrict__ out) {
   const unsigned groups = gridDim.x, id = blockIdx.x, xcd = id & 7;
-  const unsigned group = groups <= kPermuteRuns ? xcd * (groups >> 3) + min(xcd, groups & 7) + (id >> 3) : id;
+  const unsigned group = xcd * (groups >> 3) + min(xcd, groups & 7) + (id >> 3);
   const int t = (int)(group * 256) + threadIdx.x;
   if (t < nnz) out[t] = values[perm[t]];
 }
