@@ -64,13 +64,18 @@ typedef enum {
  *   stored order, that are added up at the end: where rows are too few to fill the machine (fp32 rows of a few dozen entries among
  *   them), rows much longer than the mean, and in the window kernel (attention-shaped problems among others: it keeps a window of
  *   B around a band of A in on-chip memory and takes rows in their natural order).
- *   Dense A (about one position in five and more, from 33 columns of B on, where the output fills the machine): products from
- *   three bf16 terms per number, which hold all of its 24 bits, of whose nine products the six largest (the others: less than
- *   2^-24 of the whole) are added up in fp32 on the matrix cores, zeros of A included.  Rows of fewer than 72 + k / 24 entries,
- *   rows that are not ascending and what comes out as Inf or NaN are gathered.  For normally distributed inputs, where it was
- *   measured, no row's result is less exact than the other kernels' (2-norm of the error, 8192 x 10240 at 20 %: 6.4e-7 of the
- *   result's, 8.2e-7 there).  Gathering costs time: 8192 x 10240 at 30 %, n = 128: 140 us, with one Inf in B 285, with a row of
- *   them, or where no row is ascending, 690; B full of NaN 121.
+ *   Dense A (about one position in six and more, from 800 columns of A and 33 of B on, where the output fills the machine):
+ *   products on the fp16 matrix cores, zeros of A included.  A number, taken times a power of two of its row of A or of its column of
+ *   B, is two fp16 terms, which hold it to 2^-23 of itself, or to 2^-48 of the largest number of that row or column if that is
+ *   more; all four products of terms are added up in fp32.  A sum that is small beside what the largest numbers of its row and
+ *   column could give is gathered, that is, formed by fp32 multiply-adds of A's stored entries alone, unless a count shows that too few numbers
+ *   lose bits there for it to matter.  So are rows of fewer than 32 entries, rows that are not ascending and what comes out as
+ *   Inf or NaN.  A result of a row of c entries is then no further from the definition's, whatever numbers stand in rows of B
+ *   that the row does not store, than (k / 4 + 32 + 8 sqrt(c)) 2^-24 of its sum of absolute products, and for normally distributed
+ *   inputs, where it was measured, no row's is less exact than the other kernels' (2-norm of the error, 8192 x 10240 at 30 %:
+ *   3.2e-7 of the result's, 9.9e-7 there).  Gathering costs time.  8192 x 10240 at 30 %, n = 128, 149 us with nothing to gather:
+ *   with one Inf in B 281, with a row of them, or where no row is ascending, 670; whole numbers, whose sums are often zero, or B
+ *   with one number in a thousand that is not zero, 155 .. 166; numbers spread over thirty powers of two and more 260 .. 310.
  *   Either way the result is deterministic and does not depend on row_order. */
 int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
               const float* values, const int* row_order, const float* B, float* C, void* stream);
@@ -85,6 +90,15 @@ int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* c
  *   bf16 terms per number, which hold all of its 24 bits, of whose nine products the six largest (the others: less than
  *   2^-24 of the whole) are added up in fp32 on the matrix cores.  For normally distributed inputs, where it was measured,
  *   that is no less exact than the other kernels (2-norm of the error at n = 64: 5.0e-8 of the result's, 6.8e-8 there).
+ *   Dense A (some 10 % and more) with dot products of 576 columns and more, from 128 rows and columns of A on: products from two
+ *   fp16 terms per number, taken times a power of two of its row of L or R, which hold it to 2^-23 of itself, or to 2^-48 of the row's
+ *   largest number if that is more; of the four products of terms the smallest, below 2^-22 of the whole, is left out, the others
+ *   are added up in fp32.  Sums that are small beside what the largest numbers of their two rows could give are formed again by fp32
+ *   multiply-adds, as in spdl_spmm, and so is what comes out as Inf or NaN.  A result is then no further from the
+ *   definition's than (48 + n / 128 + 12 sqrt(n)) 2^-24 of its sum of absolute products, and for normally distributed inputs, where it was
+ *   measured, no less exact than the other kernel's (2-norm of the error at n = 640 / 4096: 1.19e-7 / 1.5e-7 of the result's,
+ *   1.27e-7 / 2.9e-7 there).  4096 x 1024 at 10 %, n = 4096, 150 us: where only one number in a hundred of L and R is not zero, and most
+ *   sums are therefore, 272 us; rows in which one number is 2^20 times the others, and zeros, 390; all results NaN 1360.
  *   The result is deterministic, rows in no order included. */
 int spdl_sddmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
                const float* L, const float* R, float* out_values, void* stream);

@@ -343,8 +343,9 @@ bool slab_tiles_first(int groups, int m) { return groups >= 8 && m <= 2048; }
 // walk over A's columns.  Fitted on 80 uniform shapes of 129 tiles of 64 x 64 and more (1024 .. 16000 rows, 836 .. 10800 columns, n = 33 ..
 // 2048, 11 .. 35 %: 4 % off for the matrix cores; on 200 for the forms that walk and with one row per group, 4 % and 6 %).  The two meet at 15 .. 18 %
 // (us, here and in the plan's form: 8192 x 10240, n = 128, 14 % 116 and 112, 16 % 116 and 120, 20 % 127 and 143, 30 % 133 and 200; 5494 x 3943 at
-// 15 %, n = 369, 119 and 121; 2621 x 1436 at 31 %, n = 540, 41 and 55; 14741 x 1257 at 28 %, n = 748, 203 and 251); below 15.5 % of 17 shapes
-// two were faster here, by 2 and 10 %.
+// 15 %, n = 369, 119 and 121; 2621 x 1436 at 31 %, n = 540, 41 and 55; 14741 x 1257 at 28 %, n = 748, 203 and 251).  Below 15.5 % the estimate is
+// not exact enough to tell: of 11 shapes of 11.7 .. 15.4 % that it would bring here 7 were slower, by 1 .. 11 % (13813 x 9316 at 13.3 %, n = 140,
+// 301 and 272; 7251 x 5835 at 15 %, n = 151, 127 and 120), 3 faster, by 2, 3 and 9 % (8928 x 7261 at 15.4 %, n = 36, 72 and 79).
 // Rows of fewer than 32 entries are gathered there (kDsEntries): uniform rows have 100 and more.
 // Fewer tiles, whose rows the slab form shares out: level at 40 %, not taken.  Fewer than 800 columns and more than 2048 columns of C (4096 x
 // 1024 at 30 %, n = 4096, among others) stay with the forms that tests of them fix there.
@@ -514,6 +515,8 @@ inline bool sddmm_mfma_pays(int m, int k, int n, int nnz) {
     const double rounds = (double)((n + 127) / 128), row = (double)nnz / (double)std::max(m, 1);
     t_direct = 3.1 + rounds * (0.36 + 0.34 * std::max(1.0, 4.0 / std::max(row, 1e-3))) + 2.33e-7 * (double)nnz * (double)n;
   }
+  // (where the two meet: 90 random shapes, both forced, whose estimate for the blocks is 0.85 .. 0.95 / .. 1.0 / .. 1.05 / .. 1.1 / .. 1.2 times the
+  // direct kernels': the blocks take 0.84 / 0.88 / 0.95 / 1.00 / 1.06 times their time)
   return t_mfma <= 1.05 * t_direct;
 }
 

@@ -25,8 +25,9 @@
 //
 // What bounds it: the power limit (1.5 .. 1.7 GHz) and the issue of vector instructions beside the MFMA.  A stage is 64 MFMA of 32 clocks on two of a
 // SIMD's waves, 170 vector instructions of these and 130 (10 %) to 260 (30 %) of the scattering waves, 4 clocks each or 5 where a wave is
-// alone; it takes 2900 clocks.  8192 x 10240 at 10 %, n = 128, 141 us: without MFMA 105, without scattering 108, without copies of B 131, without the
-// three small products' smallest 131.  A step's operands all read a step ahead, one accumulator and registers for
+// alone; it takes 2700 to 3100 clocks.  8192 x 10240 at 10 / 30 %, n = 128, launches back to back, 136 / 161 us: without MFMA 101 / 123, without storing what is
+// scattered 123 / 141, without copies of B 116 / 147, without the three small products' smallest 125 / 152.  (A launch among others finds the chip
+// cooler: 113 / 133.)  A step's operands all read a step ahead, one accumulator and registers for
 // two blocks instead: 7 % slower.  8192 x 10240, n = 128, three bf16 terms and six products -> here, inputs in turn: 20 % 136.8 us -> 126.5, 30 %
 // 149.8 -> 132.9; 5923 x 6704 at 20 % 77.6 -> 69.6; 4368 x 5000 at 20 % 56.4 -> 53.6 (slab kernel at these: 143, 200, 86.6, 65.1).
 //
