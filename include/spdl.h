@@ -97,8 +97,9 @@ int spdl_spmm(int m, int k, int n, int nnz, const int* row_offsets, const int* c
  *   multiply-adds, as in spdl_spmm, and so is what comes out as Inf or NaN.  A result is then no further from the
  *   definition's than (48 + n / 128 + 12 sqrt(n)) 2^-24 of its sum of absolute products, and for normally distributed inputs, where it was
  *   measured, no less exact than the other kernel's (2-norm of the error at n = 640 / 4096: 1.19e-7 / 1.5e-7 of the result's,
- *   1.27e-7 / 2.9e-7 there).  4096 x 1024 at 10 %, n = 4096, 150 us: where only one number in a hundred of L and R is not zero, and most
- *   sums are therefore, 272 us; rows in which one number is 2^20 times the others, and zeros, 390; all results NaN 1360.
+ *   1.27e-7 / 2.9e-7 there; n = 700 / 4096 where no product is negative 5.1e-8 / 9.0e-8, 3.9e-8 / 5.2e-8 there).  4096 x 1024 at 10 %,
+ *   n = 4096, 150 us: where only one number in a hundred of L and R is not zero, and most sums are therefore zero, 272 us; rows in
+ *   which one number is 2^20 times the others, and zeros, 390; all results NaN 1360.
  *   The result is deterministic, rows in no order included. */
 int spdl_sddmm(int m, int k, int n, int nnz, const int* row_offsets, const int* column_indices,
                const float* L, const float* R, float* out_values, void* stream);

@@ -11,7 +11,8 @@
 // (scaled_floor): as any result that is not finite it is computed again from L and R by the wave that stores it, unless there are many and
 // a count shows that too few numbers have lost any (kLgCount).
 // At a chunk's end what the two hold is added to the sums: the matrix cores cut sums off where they add, which a chain of the whole dot
-// product would feel.  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the end the sums
+// product would feel.  (2-norm of the error, n = 4096, normal numbers 1.5e-7, slab kernel 2.9e-7; both cut at zero, so that all products have one sign,
+// 9.0e-8 and 5.2e-8: most of it from adding up the chunks.  Chunks of 64 columns in the sums: 1.8 and 1.25e-7, and 4 % slower.)  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the end the sums
 // go to LDS, and all waves pick the stored entries of their rows.
 //
 // What bounds it: a SIMD has 12 MFMA of 32 clocks and 140 vector instructions for a step of sixteen columns, which take about
