@@ -11,9 +11,10 @@
 // (scaled_floor): as any result that is not finite it is computed again from L and R by the wave that stores it, unless there are many and
 // a count shows that too few numbers have lost any (kLgCount).
 // At a chunk's end what the two hold is added to the sums: the matrix cores cut sums off where they add, which a chain of the whole dot
-// product would feel.  (2-norm of the error, n = 4096, normal numbers 1.5e-7, slab kernel 2.9e-7; both cut at zero, so that all products have one sign,
-// 9.0e-8 and 5.2e-8: most of it from adding up the chunks.  Chunks of 64 columns in the sums: 1.8 and 1.25e-7, and 4 % slower.)  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the end the sums
-// go to LDS, and all waves pick the stored entries of their rows.
+// product would feel.  (2-norm of the error in 1e-8, n = 700 / 4096: normal numbers 12.1 / 15.3, slab kernel 13.2 / 29.3; both operands cut at zero, so that
+// all products have one sign, 5.1 / 9.0, slab kernel 3.9 / 5.2.  Added every 64 columns 11.7 / 17.7 and 5.4 / 12.5, 4 % slower; every 256 13.4 / 15.2 and 6.1 /
+// 6.9; every 512 15.7 / 17.5 and 9.4 / 6.5.)  The waves meet once a chunk, when its terms of L have been read and the next one's are there.  In the
+// end the sums go to LDS, and all waves pick the stored entries of their rows.
 //
 // What bounds it: a SIMD has 12 MFMA of 32 clocks and 140 vector instructions for a step of sixteen columns, which take about
 // their sum, 820 clocks at 1.6 GHz (the clock of a machine at its power limit): 4096 x 1024, n = 4096: 129 us whatever the density, without
