@@ -20,8 +20,8 @@ __device__ __forceinline__ float scale_limit(int scale) { return __builtin_bit_c
 
 // What a power of two of a whole row or column costs: a scaled number below 2^-13 is held to 2^-36, not to 2^-23 of itself, so that a product may be
 // off by 2^-21 (2^-36 times 2^15; half as much again where low low is left out), however small it is.  The largest number need not be one that
-// the sum has a use for: it may be multiplied by a zero.  A scaled sum of `count` products, or of as many that may be off (scaled_loses), is therefore taken only if it is no smaller than
-// this.  What is lost is then no more than 8 sqrt(count) 2^-24 of the sum of absolute products, if all of it has one sign, and 5 x 2^-24 as a
+// the sum has a use for: it may be multiplied by a zero.  A scaled sum of `count` products, or with as many among them that may be off
+// (scaled_loses), is therefore taken only if it is no smaller than this.  What is lost is then no more than 8 sqrt(count) 2^-24 of the sum of absolute products, if all of it has one sign, and 5 x 2^-24 as a
 // root of the mean square (1.5 times that without low low); fp32 roundings of so many terms come to sqrt(count) 2^-24.  Any other sum is
 // computed again without the matrix cores.  (Sums of normally distributed numbers are some sqrt(count) 2^22.4: one in seven million is below it.
 // 8192 x 10240 at 30 %, n = 128, has a million sums, and one that is gathered makes it 6 us slower: 2.7 % with eight times as much, 0.4 % here.)
